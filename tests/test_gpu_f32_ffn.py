@@ -1,0 +1,77 @@
+"""The fp32 grouped FFN on the fp32 matrix cores against the oracle, at the sizes where its tiles can go wrong: both tile
+sizes (32 x 32 with a shared contraction, 64 x 64), widths that are no multiple of a tile, a slice or four floats, ragged
+and empty groups, more groups than lanes, and operands that are not 16-byte aligned.  Checks and tolerance (1e-5, row by
+row) are those of test_gpu_parity.py."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2411_10003_amd import workload as wl
+import test_gpu_parity as P
+
+pytestmark = pytest.mark.gpu
+
+G = P.G          # module-scoped fixtures of the parity tests
+orc = P.orc
+
+
+def _cfg(**kw):
+    kw = dict(dict(dtype="f32", act="gelu", k=2, E=8, P=4, alpha=1.2, n_replicas=1, backward=True), **kw)
+    return wl.scaled(wl.CONFIGS[0], **kw)
+
+
+CASES = [
+    _cfg(T=70, d=64, h=32),                                     # one tile across, contractions of one slice and less
+    _cfg(T=97, d=68, h=33, act="swiglu"),                       # widths one past a tile; h odd: 4-byte loads
+    _cfg(T=200, d=60, h=127),
+    _cfg(T=333, d=132, h=260, act="swiglu", alpha=2.5),         # h a multiple of four only, very uneven groups
+    _cfg(T=640, d=256, h=64, k=1, E=80, P=1, n_replicas=0),     # 80 hosted groups, some of them empty
+    _cfg(T=2500, d=516, h=1092),                                # 64 x 64 tiles in every contraction, remainders in all
+    _cfg(T=2500, d=516, h=1090, act="swiglu", alpha=2.0),       # the same with 4-byte loads
+]
+_ids = lambda c: f"{c.act}-T{c.T}-d{c.d}-h{c.h}-E{c.E}-k{c.k}"   # noqa: E731
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=_ids)
+def test_forward(G, orc, cfg):
+    P.test_ffn_forward_and_combine(G, orc, cfg)
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=_ids)
+def test_backward(G, orc, cfg):
+    P.test_backward_calls(G, orc, cfg)
+
+
+def _shifted(t):
+    """The same tensor four bytes past a 16-byte boundary."""
+    if t is None:
+        return None
+    flat = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)[1:]
+    flat.copy_(t.reshape(-1))
+    return flat.view(t.shape)
+
+
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+def test_unaligned_operands_give_the_same_bits(G, act):
+    """4-byte loads feed the same order of multiply-adds as 16-byte loads."""
+    cfg = _cfg(T=300, d=128, h=192, act=act)
+    case = G.Case(cfg)
+    hd = G.make_handle(cfg)
+    res = []
+    for f in (lambda t: t, _shifted):
+        b = G.binding.LayerBuffers(hd, True)
+        G.gpu_route(hd, case, b)
+        hd.dispatch(case.ddest, case.dX, b.idx, b.counts, b.layout, b.Xp)
+        b.Yp.zero_(); b.dXp.zero_()
+        W1, W2, W3 = f(case.dW1), f(case.dW2), f(case.dW3)
+        dYp = f(torch.randn(cfg.A, cfg.d, device=G.DEV, generator=torch.Generator(device=G.DEV).manual_seed(3)))
+        Z, U, Yp, dXp = f(b.Z.zero_()), f(b.U.zero_()) if act == "swiglu" else None, f(b.Yp), f(b.dXp)
+        hd.expert_ffn_fwd(f(b.Xp), b.layout, W1, W2, W3, Yp, Z, U)
+        dW = [f(torch.zeros_like(b.dW1)), f(torch.zeros_like(b.dW2)), f(torch.zeros_like(b.dW1)) if act == "swiglu" else None]
+        hd.expert_ffn_bwd(dYp, f(b.Xp), Z, U, b.layout, W1, W2, W3, dXp, *dW)
+        torch.cuda.synchronize()
+        res.append([Yp, Z, U, dXp, *dW])
+    for a, c in zip(*res):
+        assert (a is None) == (c is None)
+        if a is not None:
+            assert np.array_equal(G.host(a).view(np.uint32), G.host(c).view(np.uint32))
