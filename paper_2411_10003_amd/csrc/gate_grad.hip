@@ -3,17 +3,14 @@
 //   dWg[c,e] = sum_t X[t,c] dlogits[t,e]      dbg[e] = sum_t dlogits[t,e]
 //   dX[t,c]  = sum_j dXp[pos[t*k+j],c]  +  sum_e dlogits[t,e] Wg[c,e]
 // The first sum of dX is the backward of the send (the fourth all-to-all of the performance model,
-// Section 4.2); fusing the gate path into it saves a pass over dX.  Both kernels are bound by HBM
-// (they stream X or dXp once) with E fp32 multiply-adds per element beside it (on the fp32 MFMA for the
-// parameter gradients, where they form a dense contraction over the tokens); fp32 throughout.  More than 64
-// experts are taken in passes (parameter gradients) or chunks (input gradient) of 64.
+// Section 4.2); fusing the gate path into it saves a pass over dX.  Both kernels stream X or dXp once, with E fp32
+// multiply-adds per element beside it on the fp32 MFMA; fp32 throughout.  Where the experts no longer fit (64 of them in
+// the accumulators of the parameter gradients, 128 in the LDS of the input gradient) they are taken in passes or chunks.
 #include "internal.h"
 
 #include <type_traits>
 
 namespace {
-
-constexpr int MAXK_IG = 8;      // the handle allows k <= 8
 
 __device__ __forceinline__ void unpack_bf16x8(const uint4& v, float* f)
 {
@@ -24,196 +21,158 @@ __device__ __forceinline__ void unpack_bf16x8(const uint4& v, float* f)
 }
 
 // ---- dX = backward of the send + dlogits Wg^T ---------------------------------------------------
-// A block owns a strip of 64*VN columns and TOK_PER_BLOCK tokens.  The strip of Wg is staged once per
-// block in LDS, transposed to [e][column] so that a lane reads the VN weights of its columns with
-// 16-byte LDS loads; the E logit gradients of a token are the same for every lane (scalar loads).
-template <typename ET, int VN, int EC>
-__global__ __launch_bounds__(256) void input_grad_kernel(
-    const ET* __restrict__ dXp, const int32_t* __restrict__ pos, const float* __restrict__ dlogits,
-    const float* __restrict__ Wg, ET* __restrict__ dX, int T, int d, int E, int k, int tok_per_block)
-{
-    extern __shared__ __attribute__((aligned(16))) float wt[];      // [E][64*VN + 4]
-    constexpr int CW = 64 * VN, WP = CW + 4;                       // strip width, padded row of wt
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = blockDim.x >> 6;
-    const int c0 = blockIdx.x * CW;                                // first column of the strip
-    // Wg[c0 + c][e] -> wt[e][c], read in memory order; the rows of wt are 4 floats longer than the strip so
-    // that the 16..64 experts of a column and the columns next to it fall into different banks
-#pragma unroll 4
-    for (int i = tid; i < CW * E; i += blockDim.x) {
-        const int c = i / E, e = i - c * E;
-        wt[e * WP + c] = (c0 + c < d) ? Wg[(size_t)(c0 + c) * E + e] : 0.0f;
-    }
-    __syncthreads();
-    const int col = c0 + lane * VN;
-    const int t_begin = blockIdx.y * tok_per_block, t_end = min(T, t_begin + tok_per_block);
-    // several tokens per trip, all of their loads issued before the first use.  The U x E logit gradients
-    // of a trip are fetched by the lanes as one flat array and handed out with readlane, so a token costs
-    // no dependent memory round trip of its own.
-    constexpr int U = EC <= 16 ? 4 : 2;
-    constexpr int NDL = (U * EC + 63) / 64;
-    for (int t0 = t_begin + wave; t0 < t_end; t0 += n_waves * U) {
-        float acc[U][VN];
-        uint4 raw[U][MAXK_IG];
-        float dlv[NDL];
-#pragma unroll
-        for (int q = 0; q < NDL; ++q) {
-            const int f = q * 64 + lane, u = f / EC, e = f % EC;
-            const int t = t0 + n_waves * u;
-            dlv[q] = (u < U && t < t_end && e < E) ? dlogits[(size_t)t * E + e] : 0.0f;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int t = t0 + n_waves * u;
-#pragma unroll
-            for (int j = 0; j < MAXK_IG; ++j)
-                if (j < k && t < t_end && col < d)       // pos comes through the scalar cache (16 tokens per line)
-                    raw[u][j] = *reinterpret_cast<const uint4*>(dXp + (size_t)pos[(size_t)t * k + j] * d + col);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int t = t0 + n_waves * u;
-            if (t >= t_end || col >= d) continue;
-#pragma unroll
-            for (int i = 0; i < VN; ++i) acc[u][i] = 0.0f;
-#pragma unroll
-            for (int j = 0; j < MAXK_IG; ++j) {                    // expert path, ascending j
-                if (j < k) {
-                    float f[VN];
-                    if (VN == 8) unpack_bf16x8(raw[u][j], f);
-                    else { f[0] = __uint_as_float(raw[u][j].x); f[1] = __uint_as_float(raw[u][j].y); f[2 % VN] = __uint_as_float(raw[u][j].z); f[3 % VN] = __uint_as_float(raw[u][j].w); }
-#pragma unroll
-                    for (int i = 0; i < VN; ++i) acc[u][i] += f[i];
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < EC; ++e) {
-                const int f = u * EC + e;                          // position in the flat [U][EC] array
-                const float g = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, dlv[f / 64]), f % 64));
-                if (g == 0.0f) continue;                           // renormalised top-k: only k of the E are non-zero
-                const float* wrow = wt + e * WP + lane * VN;
-#pragma unroll
-                for (int i = 0; i < VN; i += 4) {
-                    const float4 wv = *reinterpret_cast<const float4*>(wrow + i);
-                    acc[u][i + 0] = fmaf(g, wv.x, acc[u][i + 0]); acc[u][i + 1] = fmaf(g, wv.y, acc[u][i + 1]);
-                    acc[u][i + 2] = fmaf(g, wv.z, acc[u][i + 2]); acc[u][i + 3] = fmaf(g, wv.w, acc[u][i + 3]);
-                }
-            }
-            if (VN == 8) {
-                *reinterpret_cast<uint4*>(dX + (size_t)t * d + col) =
-                    make_uint4(pack_bf16x2(acc[u][0], acc[u][1]), pack_bf16x2(acc[u][2], acc[u][3]),
-                               pack_bf16x2(acc[u][4 % VN], acc[u][5 % VN]), pack_bf16x2(acc[u][6 % VN], acc[u][7 % VN]));
-            } else {
-                *reinterpret_cast<float4*>(dX + (size_t)t * d + col) = make_float4(acc[u][0], acc[u][1], acc[u][2], acc[u][3]);
-            }
-        }
-    }
-}
-
-// ---- the same on the matrix cores (E <= 32) ---------------------------------------------------------
-// dlogits Wg^T is a dense product with the experts as its short contraction: on the fp32 16x16x4 MFMA, four
-// instructions (E = 16) give a 16-token x 16-column tile.  Tile j of a strip holds the columns
-// strip0 + n * VN + j (n = 0..15), so that lane l ends up with VN consecutive columns (n = l % 16) of the
-// tokens 4 (l / 16) + r, r = 0..3: exactly one 16-byte piece per token, which is what the gather of the dXp
-// rows and the store of dX move.  The B operands (a lane's VN columns of Wg against 4 experts per instruction)
-// stay in registers for the whole block; the A operand is dlogits[token l % 16][expert 4 m + l / 16].
+// dlogits Wg^T is a dense product with the experts as its short contraction, on the fp32 16x16x4 MFMA.  A wave owns a
+// strip of 16 VN columns and takes 16 tokens at a time.  Tile j of the strip holds the columns strip0 + n * VN + j
+// (n = 0..15), so that lane l ends up with VN consecutive columns (n = l % 16) of the tokens 4 (l / 16) + r, r = 0..3:
+// exactly one 16-byte piece per token, which is what the gather of the dXp rows and the store of dX move.  The A
+// operand is dlogits[token l % 16][expert], the B operand the strip of Wg: instruction (i, jj) contracts the experts
+// 16 i + 4 q + jj, q = l / 16, so that a lane reads its logit gradients 16 bytes at a time.
+// What bounds it: HBM for E <= 32 (dXp and dX), the matrix rate beyond.  The strip of Wg lies in LDS in the order in
+// which the instructions read it (two 16-byte reads per eight instructions), staged once per block for up to 128
+// experts, in chunks of 128 per 64 tokens beyond.  In registers (what E <= 32 did before) it took 64 and 128 of them per
+// lane and left two waves per SIMD; on the vector ALUs with a readlane per expert (what E > 32 did) the LDS reads bound
+// it.  All row pieces of a group are requested before its matrix instructions, unconditionally (rows and columns past
+// the end read the last valid ones and are not stored): a load under a condition makes the compiler drain them early.
+// Measured, us before -> after (bf16): T = 16384, d = 2048, k = 2, E = 32: 81 -> 52 (2.1 GFLOP beside 201 MB); k = 1, E = 64:
+// 377 -> 61; T = 8001, k = 4, E = 128: 524 -> 94; T = 1000, d = 512, E = 16: 43 -> 10 (16 blocks before); T = 32768,
+// d = 4096, E = 16: 172 -> 172 (807 MB, 4.7 TB/s).
 typedef __attribute__((ext_vector_type(4))) float ig_f32x4_t;
 
-template <typename ET, int VN, int NE, int CS, int KMAX>
-__global__ __launch_bounds__(256) void input_grad_mfma_kernel(
+// waves per SIMD the compiler is held to: 4, or 2 where the row pieces (16 KMAX registers) or the LDS leave no room for that
+template <typename ET, int NE, int KMAX>
+__global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? 4 : 2) void input_grad_kernel(
     const ET* __restrict__ dXp, const int32_t* __restrict__ pos, const float* __restrict__ dlogits,
-    const float* __restrict__ Wg, ET* __restrict__ dX, int T, int d, int E, int k, int tok_per_block)
+    const float* __restrict__ Wg, ET* __restrict__ dX, int T, int d, int E, int k, int groups_per_wave, int vec)
 {
-    constexpr int SW = 16 * VN, NM = NE * 4;                       // columns of a strip, MFMA steps over the experts
+    constexpr int VN = 16 / sizeof(ET), SW = 16 * VN, VH = VN / 4, EC = 16 * NE;
+    constexpr bool MANY = NE > 2, CHUNKS = NE == 8;                // more than 32 experts; perhaps more than fit LDS at once
     typedef typename std::conditional<sizeof(ET) == 2, uint4, float4>::type raw_t;
-    static_assert(sizeof(ET) * VN == 16, "a lane moves 16 bytes of a row");
-    const int tid = threadIdx.x, lane = tid & 63;
+    extern __shared__ __attribute__((aligned(16))) float wl[];      // [4 NE steps][VH][64 lanes][4]
+    const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, lq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ln = lane & 15, lq = lane >> 4;
-    const int c0 = (blockIdx.x * 4 + wave) * (CS * SW);            // the four waves take neighbouring strips of the same tokens
-    const int t_begin = blockIdx.y * tok_per_block, t_end = min(T, t_begin + tok_per_block);
+    const int c0 = blockIdx.x * SW;
+    const int c = c0 + ln * VN, cc = c < d ? c : 0;
 
-    float wreg[CS][VN][NM];                                        // Wg[column of the lane][expert 4 m + lq]
-#pragma unroll
-    for (int s = 0; s < CS; ++s)
-#pragma unroll
-        for (int j = 0; j < VN; ++j)
-#pragma unroll
-            for (int m = 0; m < NM; ++m) {
-                const int c = c0 + s * SW + ln * VN + j, e = 4 * m + lq;
-                wreg[s][j][m] = (c < d && e < E) ? Wg[(size_t)c * E + e] : 0.0f;
-            }
-
-    for (int tg = t_begin; tg < t_end; tg += 16) {
-        // everything that does not depend on another load first: logit gradients, positions
-        float a[NM];
-        const int ta = tg + ln;
-#pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            const int e = 4 * m + lq;
-            a[m] = (ta < t_end && e < E) ? dlogits[(size_t)ta * E + e] : 0.0f;
-        }
-        int rows[4][KMAX];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int t = tg + 4 * lq + r;
-#pragma unroll
-            for (int j = 0; j < KMAX; ++j) rows[r][j] = (j < k && t < t_end) ? pos[(size_t)t * k + j] : -1;
-        }
-        // all row pieces of the 4 tokens are requested before the first one is used
-        raw_t raw[4][CS][KMAX];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int s = 0; s < CS; ++s) {
-                const int c = c0 + s * SW + ln * VN;
-#pragma unroll
-                for (int j = 0; j < KMAX; ++j) {
-                    if (j < k && rows[r][j] >= 0 && c < d) raw[r][s][j] = *reinterpret_cast<const raw_t*>(dXp + (size_t)rows[r][j] * d + c);
-                    else raw[r][s][j] = raw_t{};
+    // the strip's weights for the experts ec0 .. ec0 + EC - 1 (zeros past E and d); whether any of them is not finite
+    auto stage = [&](int ec0) -> bool {
+        bool odd = false;
+        for (int i = tid; i < SW * EC / 4; i += 256) {
+            const int cl = i % SW, e4 = i / SW, e = ec0 + 4 * e4, col = c0 + cl;
+            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (col < d) {
+                const float* src = Wg + (size_t)col * E + e;
+                if (vec) { if (e < E) v = *reinterpret_cast<const float4*>(src); }
+                else {
+                    if (e + 0 < E) v.x = src[0];
+                    if (e + 1 < E) v.y = src[1];
+                    if (e + 2 < E) v.z = src[2];
+                    if (e + 3 < E) v.w = src[3];
                 }
             }
-        ig_f32x4_t acc[CS][VN];
+            float* dst = wl + ((4 * (e4 >> 2)) * VH + (cl % VN) / 4) * 256 + ((e4 & 3) * 16 + cl / VN) * 4 + cl % 4;
+            dst[0] = v.x; dst[VH * 256] = v.y; dst[2 * VH * 256] = v.z; dst[3 * VH * 256] = v.w;
+            odd |= !(fabsf(v.x) < INFINITY && fabsf(v.y) < INFINITY && fabsf(v.z) < INFINITY && fabsf(v.w) < INFINITY);
+        }
+        return odd;
+    };
+    bool skip_zeros = false;
+    if (!CHUNKS || E <= EC) skip_zeros = __syncthreads_or(stage(0));
+
+    for (int gi = 0; gi < groups_per_wave; ++gi) {
+        const int tg = (blockIdx.y * groups_per_wave + gi) * 64 + wave * 16;
+        raw_t raw[4][KMAX];
 #pragma unroll
-        for (int s = 0; s < CS; ++s)
+        for (int r = 0; r < 4; ++r) {
+            const int t = min(tg + 4 * lq + r, T - 1);
 #pragma unroll
-            for (int j = 0; j < VN; ++j) {
-                acc[s][j] = ig_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int j = 0; j < KMAX; ++j)
+                raw[r][j] = *reinterpret_cast<const raw_t*>(dXp + (size_t)pos[(size_t)t * k + (j < k ? j : 0)] * d + cc);
+        }
+        ig_f32x4_t acc[VN];
 #pragma unroll
-                for (int m = 0; m < NM; ++m) acc[s][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m], wreg[s][j][m], acc[s][j], 0, 0, 0);
+        for (int j = 0; j < VN; ++j) acc[j] = ig_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        const float* dl = dlogits + (size_t)min(tg + ln, T - 1) * E;
+        for (int ec0 = 0; ec0 < (CHUNKS ? E : 1); ec0 += EC) {
+            if (CHUNKS && E > EC) {
+                __syncthreads();                                   // everyone is done with the chunk before
+                skip_zeros = __syncthreads_or(stage(ec0));
             }
+            float a[4 * NE];
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const int e = ec0 + 16 * i + 4 * lq;
+                if (vec) {                                         // E is a multiple of 4
+                    const float4 v = *reinterpret_cast<const float4*>(dl + (e < E ? e : 0));
+                    a[4 * i] = e < E ? v.x : 0.0f; a[4 * i + 1] = e < E ? v.y : 0.0f;
+                    a[4 * i + 2] = e < E ? v.z : 0.0f; a[4 * i + 3] = e < E ? v.w : 0.0f;
+                } else {
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) {
+                        const float v = dl[e + jj < E ? e + jj : 0];
+                        a[4 * i + jj] = e + jj < E ? v : 0.0f;
+                    }
+                }
+            }
+            // the weights are read from LDS again for every group: hoisted out of the loop over the groups they would spill
+            if (NE > 1) asm volatile("" ::: "memory");
+            if (!MANY || !skip_zeros) {
+#pragma unroll
+                for (int m = 0; m < 4 * NE; ++m) {
+                    float w[VN];
+#pragma unroll
+                    for (int v = 0; v < VH; ++v) {
+                        const float4 f = *reinterpret_cast<const float4*>(wl + (m * VH + v) * 256 + lane * 4);
+                        w[4 * v] = f.x; w[4 * v + 1] = f.y; w[4 * v + 2] = f.z; w[4 * v + 3] = f.w;
+                    }
+#pragma unroll
+                    for (int j = 0; j < VN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m], w[j], acc[j], 0, 0, 0);
+                }
+            } else {
+                // A weight that is not finite and more than 32 experts: an expert without a gradient is left out instead
+                // of contributing 0 * inf (the routing of a token may well exclude that expert).
+#pragma unroll
+                for (int m = 0; m < 4 * NE; ++m)
+#pragma unroll 1
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float g = __shfl(a[m], q * 16 + 4 * lq + r, 64);
+#pragma unroll
+                            for (int j = 0; j < VN; ++j) {
+                                const float w = wl[(m * VH + j / 4) * 256 + (q * 16 + ln) * 4 + j % 4];
+                                if (g != 0.0f) acc[j][r] = fmaf(g, w, acc[j][r]);
+                            }
+                        }
+            }
+        }
         // add the k rows of every token (j ascending, as the plain send backward adds them) and store
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int t = tg + 4 * lq + r;
+            float sum[VN];
 #pragma unroll
-            for (int s = 0; s < CS; ++s) {
-                const int c = c0 + s * SW + ln * VN;
-                if (t >= t_end || c >= d) continue;
-                float sum[VN];
+            for (int i = 0; i < VN; ++i) sum[i] = 0.0f;
 #pragma unroll
-                for (int j = 0; j < VN; ++j) sum[j] = 0.0f;
-#pragma unroll
-                for (int j = 0; j < KMAX; ++j) {
-                    if (j >= k) break;
-                    float x[VN];
-                    if constexpr (sizeof(ET) == 2) {
-                        unpack_bf16x8(raw[r][s][j], x);
-                    } else {
-                        x[0] = raw[r][s][j].x; x[1] = raw[r][s][j].y; x[2] = raw[r][s][j].z; x[3] = raw[r][s][j].w;
-                    }
-#pragma unroll
-                    for (int i = 0; i < VN; ++i) sum[i] += x[i];
-                }
-#pragma unroll
-                for (int i = 0; i < VN; ++i) sum[i] += acc[s][i][r];
+            for (int j = 0; j < KMAX; ++j) {
+                if (j >= k) break;
+                float x[VN];
                 if constexpr (sizeof(ET) == 2) {
-                    *reinterpret_cast<uint4*>(dX + (size_t)t * d + c) =
-                        make_uint4(pack_bf16x2(sum[0], sum[1]), pack_bf16x2(sum[2], sum[3]),
-                                   pack_bf16x2(sum[4 % VN], sum[5 % VN]), pack_bf16x2(sum[6 % VN], sum[7 % VN]));
+                    unpack_bf16x8(raw[r][j], x);
                 } else {
-                    *reinterpret_cast<float4*>(dX + (size_t)t * d + c) = make_float4(sum[0], sum[1], sum[2], sum[3]);
+                    x[0] = raw[r][j].x; x[1] = raw[r][j].y; x[2] = raw[r][j].z; x[3] = raw[r][j].w;
                 }
+#pragma unroll
+                for (int i = 0; i < VN; ++i) sum[i] += x[i];
+            }
+#pragma unroll
+            for (int i = 0; i < VN; ++i) sum[i] += acc[i][r];
+            if (t >= T || c >= d) continue;
+            if constexpr (sizeof(ET) == 2) {
+                *reinterpret_cast<uint4*>(dX + (size_t)t * d + c) =
+                    make_uint4(pack_bf16x2(sum[0], sum[1]), pack_bf16x2(sum[2], sum[3]),
+                               pack_bf16x2(sum[4 % VN], sum[5 % VN]), pack_bf16x2(sum[6 % VN], sum[7 % VN]));
+            } else {
+                *reinterpret_cast<float4*>(dX + (size_t)t * d + c) = make_float4(sum[0], sum[1], sum[2], sum[3]);
             }
         }
     }
@@ -404,144 +363,53 @@ __global__ void gate_wgrad_reduce_kernel(const float* __restrict__ partial, cons
     }
 }
 
-// ---- the same for more than 64 experts ---------------------------------------------------------------
-// The strip of Wg no longer fits LDS at once, so it is staged in chunks of 64 experts and the accumulators
-// must outlive the chunks: a wave keeps U tokens (U x VN sums per lane) for the whole block, the block stages
-// each chunk once and its 4 U tokens use it.  Expert path first (j ascending), then the gate path in
-// ascending e, one rounding at the end.
-template <typename ET, int VN>
-__global__ __launch_bounds__(256) void input_grad_wide_kernel(
-    const ET* __restrict__ dXp, const int32_t* __restrict__ pos, const float* __restrict__ dlogits,
-    const float* __restrict__ Wg, ET* __restrict__ dX, int T, int d, int E, int k)
-{
-    constexpr int CW = 64 * VN, WP = CW + 4, U = 8, EC = 64;
-    __shared__ __attribute__((aligned(16))) float wt[EC * WP];     // [expert of the chunk][column of the strip]
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c0 = blockIdx.x * CW, col = c0 + lane * VN;
-    const int t0 = (blockIdx.y * 4 + wave) * U;
-    float acc[U][VN];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int i = 0; i < VN; ++i) acc[u][i] = 0.0f;
-        const int t = t0 + u;
-        if (t >= T || col >= d) continue;
-        for (int j = 0; j < k; ++j) {
-            const ET* src = dXp + (size_t)pos[(size_t)t * k + j] * d + col;
-            float f[VN];
-            if constexpr (sizeof(ET) == 2) {
-                unpack_bf16x8(*reinterpret_cast<const uint4*>(src), f);
-            } else {
-                const float4 v = *reinterpret_cast<const float4*>(src);
-                f[0] = v.x; f[1] = v.y; f[2 % VN] = v.z; f[3 % VN] = v.w;
-            }
-#pragma unroll
-            for (int i = 0; i < VN; ++i) acc[u][i] += f[i];
-        }
-    }
-    for (int ec0 = 0; ec0 < E; ec0 += EC) {
-        __syncthreads();                                           // everyone is done with the previous chunk
-        for (int i = tid; i < CW * EC; i += 256) {
-            const int c = i / EC, e = i - c * EC;
-            wt[e * WP + c] = (c0 + c < d && ec0 + e < E) ? Wg[(size_t)(c0 + c) * E + ec0 + e] : 0.0f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int t = t0 + u;
-            if (t >= T) continue;                                  // uniform per wave
-            const float gl = (ec0 + lane < E) ? dlogits[(size_t)t * E + ec0 + lane] : 0.0f;
-            for (int e = 0; e < EC; ++e) {
-                const float g = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, gl), e));
-                if (g == 0.0f) continue;
-                const float* wrow = wt + e * WP + lane * VN;
-#pragma unroll
-                for (int i = 0; i < VN; i += 4) {
-                    const float4 wv = *reinterpret_cast<const float4*>(wrow + i);
-                    acc[u][i + 0] = fmaf(g, wv.x, acc[u][i + 0]); acc[u][i + 1] = fmaf(g, wv.y, acc[u][i + 1]);
-                    acc[u][i + 2] = fmaf(g, wv.z, acc[u][i + 2]); acc[u][i + 3] = fmaf(g, wv.w, acc[u][i + 3]);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int t = t0 + u;
-        if (t >= T || col >= d) continue;
-        if constexpr (sizeof(ET) == 2) {
-            *reinterpret_cast<uint4*>(dX + (size_t)t * d + col) =
-                make_uint4(pack_bf16x2(acc[u][0], acc[u][1]), pack_bf16x2(acc[u][2], acc[u][3]),
-                           pack_bf16x2(acc[u][4 % VN], acc[u][5 % VN]), pack_bf16x2(acc[u][6 % VN], acc[u][7 % VN]));
-        } else {
-            *reinterpret_cast<float4*>(dX + (size_t)t * d + col) = make_float4(acc[u][0], acc[u][1], acc[u][2], acc[u][3]);
-        }
-    }
-}
-
-template <typename ET, int VN>
-hipError_t launch_input_grad_wide_t(const moe_shape_t& s, const void* dXp, const int32_t* pos, const float* dlogits,
-                                    const float* Wg, void* dX, hipStream_t st)
-{
-    constexpr int CW = 64 * VN, TOK = 4 * 8;
-    const dim3 grid((s.d + CW - 1) / CW, (s.T + TOK - 1) / TOK);
-    hipLaunchKernelGGL((input_grad_wide_kernel<ET, VN>), grid, dim3(256), 0, st, (const ET*)dXp, pos, dlogits, Wg, (ET*)dX,
-                       s.T, s.d, s.E, s.k);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 int gate_grad_partitions(const moe_shape_t& s) { return s.T < 32 * 256 ? (s.T + 255) / 256 : 32; }
 
-template <typename ET, int VN, int EC>
+template <typename ET, int NE, int KMAX>
 hipError_t launch_input_grad_t(const moe_shape_t& s, const void* dXp, const int32_t* pos, const float* dlogits,
                                const float* Wg, void* dX, hipStream_t st)
 {
-    constexpr int CW = 64 * VN, TOK = 128;
-    const dim3 grid((s.d + CW - 1) / CW, (s.T + TOK - 1) / TOK);
-    const size_t lds = (size_t)s.E * (CW + 4) * sizeof(float);
-    auto kern = input_grad_kernel<ET, VN, EC>;
-    static PerDeviceOnce once;           // per instantiation
-    const int dev = current_device();
-    if (!once.is_done(dev)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 64 * (CW + 4) * 4);
-        if (e != hipSuccess) return e;
-        once.mark(dev);
-    }
-    hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, (const ET*)dXp, pos, dlogits, Wg, (ET*)dX, s.T, s.d, s.E, s.k, TOK);
+    constexpr int VN = 16 / sizeof(ET), SW = 16 * VN;
+    constexpr size_t lds = (size_t)4 * NE * 64 * VN * sizeof(float);               // 64 KB for 128 experts and bf16
+    const int strips = (s.d + SW - 1) / SW, t64 = (s.T + 63) / 64;
+    // groups of tokens per wave: as many as leave four blocks per CU, up to 8 (the staging of Wg is 1/8 of a group's
+    // traffic by then)
+    long gpw = (long)strips * t64 / 1024;
+    gpw = gpw < 1 ? 1 : (gpw > 8 ? 8 : gpw);
+    const dim3 grid(strips, (unsigned)((t64 + gpw - 1) / gpw));
+    const int vec = s.E % 4 == 0 && ((reinterpret_cast<uintptr_t>(Wg) | reinterpret_cast<uintptr_t>(dlogits)) & 15) == 0;
+    hipLaunchKernelGGL((input_grad_kernel<ET, NE, KMAX>), grid, dim3(256), lds, st, (const ET*)dXp, pos, dlogits, Wg,
+                       (ET*)dX, s.T, s.d, s.E, s.k, (int)gpw, vec);
     return hipGetLastError();
 }
 
-template <typename ET, int VN, int NE, int CS>
-hipError_t launch_input_grad_mfma_t(const moe_shape_t& s, const void* dXp, const int32_t* pos, const float* dlogits,
-                                    const float* Wg, void* dX, hipStream_t st)
+template <typename ET, int NE>
+hipError_t launch_input_grad_k(const moe_shape_t& s, const void* dXp, const int32_t* pos, const float* dlogits,
+                               const float* Wg, void* dX, hipStream_t st)
 {
-    constexpr int CW = 4 * CS * 16 * VN, TOK = 256;                // a block: 4 waves x CS strips, 256 tokens
-    const dim3 grid((s.d + CW - 1) / CW, (s.T + TOK - 1) / TOK);
-    if (s.k <= 2)
-        hipLaunchKernelGGL((input_grad_mfma_kernel<ET, VN, NE, CS, 2>), grid, dim3(256), 0, st, (const ET*)dXp, pos, dlogits, Wg,
-                           (ET*)dX, s.T, s.d, s.E, s.k, TOK);
-    else
-        hipLaunchKernelGGL((input_grad_mfma_kernel<ET, VN, NE, CS, MAXK_IG>), grid, dim3(256), 0, st, (const ET*)dXp, pos, dlogits, Wg,
-                           (ET*)dX, s.T, s.d, s.E, s.k, TOK);
-    return hipGetLastError();
+    if (s.k == 1) return launch_input_grad_t<ET, NE, 1>(s, dXp, pos, dlogits, Wg, dX, st);
+    if (s.k == 2) return launch_input_grad_t<ET, NE, 2>(s, dXp, pos, dlogits, Wg, dX, st);
+    if (s.k <= 4) return launch_input_grad_t<ET, NE, 4>(s, dXp, pos, dlogits, Wg, dX, st);
+    return launch_input_grad_t<ET, NE, 8>(s, dXp, pos, dlogits, Wg, dX, st);
+}
+
+template <typename ET>
+hipError_t launch_input_grad_e(const moe_shape_t& s, const void* dXp, const int32_t* pos, const float* dlogits,
+                               const float* Wg, void* dX, hipStream_t st)
+{
+    if (s.E <= 16) return launch_input_grad_k<ET, 1>(s, dXp, pos, dlogits, Wg, dX, st);
+    if (s.E <= 32) return launch_input_grad_k<ET, 2>(s, dXp, pos, dlogits, Wg, dX, st);
+    if (s.E <= 64) return launch_input_grad_k<ET, 4>(s, dXp, pos, dlogits, Wg, dX, st);
+    return launch_input_grad_k<ET, 8>(s, dXp, pos, dlogits, Wg, dX, st);
 }
 
 hipError_t launch_input_grad(const moe_shape_t& s, const void* dXp, const int32_t* pos, const float* dlogits,
                              const float* Wg, void* dX, hipStream_t st)
 {
-    const bool bf = s.dtype == MOE_BF16;
-    if (s.E > 64) return bf ? launch_input_grad_wide_t<bf16_t, 8>(s, dXp, pos, dlogits, Wg, dX, st)
-                            : launch_input_grad_wide_t<float, 4>(s, dXp, pos, dlogits, Wg, dX, st);
-#ifndef IG_VALU
-    if (s.E <= 16) return bf ? launch_input_grad_mfma_t<bf16_t, 8, 1, 1>(s, dXp, pos, dlogits, Wg, dX, st) : launch_input_grad_mfma_t<float, 4, 1, 2>(s, dXp, pos, dlogits, Wg, dX, st);
-    if (s.E <= 32) return bf ? launch_input_grad_mfma_t<bf16_t, 8, 2, 1>(s, dXp, pos, dlogits, Wg, dX, st) : launch_input_grad_mfma_t<float, 4, 2, 2>(s, dXp, pos, dlogits, Wg, dX, st);
-#endif
-    if (s.E <= 8)  return bf ? launch_input_grad_t<bf16_t, 8, 8>(s, dXp, pos, dlogits, Wg, dX, st) : launch_input_grad_t<float, 4, 8>(s, dXp, pos, dlogits, Wg, dX, st);
-    if (s.E <= 16) return bf ? launch_input_grad_t<bf16_t, 8, 16>(s, dXp, pos, dlogits, Wg, dX, st) : launch_input_grad_t<float, 4, 16>(s, dXp, pos, dlogits, Wg, dX, st);
-    if (s.E <= 32) return bf ? launch_input_grad_t<bf16_t, 8, 32>(s, dXp, pos, dlogits, Wg, dX, st) : launch_input_grad_t<float, 4, 32>(s, dXp, pos, dlogits, Wg, dX, st);
-    return bf ? launch_input_grad_t<bf16_t, 8, 64>(s, dXp, pos, dlogits, Wg, dX, st) : launch_input_grad_t<float, 4, 64>(s, dXp, pos, dlogits, Wg, dX, st);
+    return s.dtype == MOE_BF16 ? launch_input_grad_e<bf16_t>(s, dXp, pos, dlogits, Wg, dX, st)
+                               : launch_input_grad_e<float>(s, dXp, pos, dlogits, Wg, dX, st);
 }
 
 hipError_t launch_gate_wgrad(const moe_shape_t& s, const void* X, const float* dlogits, float* partial, float* partial_b,

@@ -87,3 +87,55 @@ def test_argument_errors():
         hd.gate_bwd_params(None, z, z, z)
     with pytest.raises((binding.MoeError, ValueError)):
         hd.input_grad(z, None, z, z, z)
+
+
+def _ig_cfg(**kw):
+    return wl.scaled(wl.CONFIGS[1], **dict(dict(T=200, d=128, h=64, E=16, k=2, P=4, n_replicas=0), **kw))
+
+
+@pytest.mark.parametrize("cfg", [
+    _ig_cfg(T=63, d=64, E=17, k=1, P=1),                       # half a strip, E one past a block of experts: 4-byte loads
+    _ig_cfg(T=65, d=192, E=48, k=3),                           # k between two of the unrolled counts
+    _ig_cfg(T=130, d=128, E=64, k=5),
+    _ig_cfg(T=16, d=320, E=128, k=8),                          # the most experts staged at once, one group of tokens
+    _ig_cfg(T=129, d=128, E=132, k=2),                         # a second chunk of four experts
+    _ig_cfg(T=70, d=128, E=257, k=2, P=1),                     # a third chunk of one expert
+    _ig_cfg(T=8200, d=2048, E=32, k=2),                        # several groups of tokens per wave
+    _ig_cfg(T=77, d=36, E=33, k=2, P=3, dtype="f32"),          # fp32: half a strip, 4-byte loads
+], ids=lambda c: f"{c.dtype}-T{c.T}-d{c.d}-E{c.E}-k{c.k}")
+def test_input_grad_edges(cfg):
+    """Input gradient against a product in double: every count of experts and of rows per token the kernel is unrolled
+    for, with logit gradients for all experts."""
+    T, d, E, k, A = cfg.T, cfg.d, cfg.E, cfg.k, cfg.A
+    rng = np.random.default_rng(T + E)
+    dl = rng.standard_normal((T, E)).astype(np.float32)
+    Wg = (rng.standard_normal((d, E)) * E ** -0.5).astype(np.float32)
+    dXp = rng.standard_normal((A, d)).astype(np.float32)
+    if cfg.dtype == "bf16":
+        wl.round_to_bf16(dXp)
+    pos = rng.permutation(A).astype(np.int32)
+    hd = G.make_handle(cfg, G=4)
+    dX = torch.zeros(T, d, dtype=hd.elt, device=G.DEV)
+    hd.input_grad(G.dev(dXp, cfg.dtype), G.dev(pos), G.dev(dl), G.dev(Wg), dX)
+    want = dXp[pos].reshape(T, k, d).astype(np.float64).sum(1) + dl.astype(np.float64) @ Wg.astype(np.float64).T
+    G.assert_rows_close(G.host(dX), want, G.TOL[cfg.dtype], "dX")
+
+
+@pytest.mark.parametrize("E", [40, 96, 200])
+def test_input_grad_leaves_out_experts_without_a_gradient(E):
+    """More than 32 experts: an expert without a logit gradient adds nothing, also where its gate weights are not finite."""
+    cfg = _ig_cfg(T=70, d=128, E=E, k=2, P=1)
+    rng = np.random.default_rng(E)
+    dl = np.zeros((cfg.T, E), np.float32)
+    idx = np.stack([rng.permutation(E - 1)[:2] for _ in range(cfg.T)])
+    np.put_along_axis(dl, idx, rng.standard_normal((cfg.T, 2)).astype(np.float32), axis=1)
+    Wg = (rng.standard_normal((cfg.d, E)) * 0.2).astype(np.float32)
+    dXp = wl.round_to_bf16(rng.standard_normal((cfg.A, cfg.d)).astype(np.float32))
+    pos = rng.permutation(cfg.A).astype(np.int32)
+    want = dXp[pos].reshape(cfg.T, 2, cfg.d).astype(np.float64).sum(1) + dl.astype(np.float64) @ Wg.astype(np.float64).T
+    Wg[:, E - 1] = np.inf
+    Wg[5, E - 1] = np.nan
+    hd = G.make_handle(cfg, G=4)
+    dX = torch.zeros(cfg.T, cfg.d, dtype=hd.elt, device=G.DEV)
+    hd.input_grad(G.dev(dXp, cfg.dtype), G.dev(pos), G.dev(dl), G.dev(Wg), dX)
+    G.assert_rows_close(G.host(dX), want, G.TOL["bf16"], "dX")
