@@ -4,8 +4,9 @@
 //   dX[t,c]  = sum_j dXp[pos[t*k+j],c]  +  sum_e dlogits[t,e] Wg[c,e]
 // The first sum of dX is the backward of the send (the fourth all-to-all of the performance model,
 // Section 4.2); fusing the gate path into it saves a pass over dX.  Both kernels stream X or dXp once, with E fp32
-// multiply-adds per element beside it on the fp32 MFMA; fp32 throughout.  Where the experts no longer fit (64 of them in
-// the accumulators of the parameter gradients, 128 in the LDS of the input gradient) they are taken in passes or chunks.
+// multiply-adds per element beside it on the fp32 MFMA; fp32 throughout.  Where the experts no longer fit (32 of them in
+// the accumulators of the parameter gradients, 128 in the LDS of the input gradient) they are taken by further blocks or
+// in chunks.
 #include "internal.h"
 
 #include <type_traits>
@@ -188,14 +189,21 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? 4 : 2) void input_grad_k
 // lane l, register r is column index i = 4 (l / 16) + r, expert l % 16.
 // A block's four waves take every fourth group of 4 tokens of the partition; their sums are folded through
 // LDS in a fixed order and written as one partial per token partition (the reduce kernel adds those).
+// What bounds it: HBM (X once) beside the matrix rate from E = 32 on, and before either the latency of a wave's loads:
+// with the accumulators of 32 experts there are two waves per SIMD, so a wave requests its next 16 tokens before it
+// multiplies the current ones (held to 256 registers; without the bound the compiler takes a whole SIMD for one wave,
+// 52 us).  More than 32 experts are further blocks of the same launch: X comes from cache for them, and twice the blocks
+// with half the accumulators (64 experts in one wave) fill the chip.  Both kernels, us, before -> after: T = 16384,
+// d = 2048, E = 32: 45 -> 40, E = 64: 85 -> 65; T = 32768, d = 4096, E = 16: 79 -> 68; T = 8001, d = 2048, E = 128:
+// 109 -> 72; T = 4000, d = 1024, E = 100: 52 -> 24.
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 template <typename ET, int VN, int NE, int CS>
-__global__ __launch_bounds__(256) void gate_wgrad_mfma_kernel(
+__global__ __launch_bounds__(256, 2) void gate_wgrad_mfma_kernel(
     const ET* __restrict__ X, const float* __restrict__ dlogits, float* __restrict__ partial,
-    float* __restrict__ partial_b, int T, int d, int E, int tok_per_part, int e0)
+    float* __restrict__ partial_b, int T, int d, int E, int tok_per_part)
 {
-    // e0: first expert of this pass (more than 64 experts are taken in passes of 16 NE)
+    const int e0 = blockIdx.z * 16 * NE;                           // first expert of the block
     constexpr int SW = 16 * VN;                                    // columns of one strip
     constexpr int NACC = CS * VN * NE;                             // 16 x 16 accumulators of a wave
     typedef typename std::conditional<sizeof(ET) == 2, uint4, float4>::type raw_t;
@@ -221,52 +229,63 @@ __global__ __launch_bounds__(256) void gate_wgrad_mfma_kernel(
     for (int n = 0; n < NE; ++n) accb[n] = 0.0f;
 
     constexpr int U = 4;                                           // groups of 4 tokens requested together: one trip
+    // unconditional loads (tokens past the partition and columns past d read valid ones, replaced by zeros when used)
     auto load_trip = [&](int tg, raw_t (&raw)[U][CS], float (&dl)[U][NE]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int t = tg + 16 * u + lk;
-            const bool tv = t < t_end;
+            const int t = min(tg + 16 * u + lk, T - 1);
 #pragma unroll
             for (int n = 0; n < NE; ++n) {
                 const int e = e0 + n * 16 + li;
-                dl[u][n] = (tv && e < E) ? dlogits[(size_t)t * E + e] : 0.0f;
+                dl[u][n] = dlogits[(size_t)t * E + (e < E ? e : 0)];
             }
 #pragma unroll
             for (int s = 0; s < CS; ++s) {
                 const int c = c0 + s * SW + li * VN;
-                if (tv && c < d) raw[u][s] = *reinterpret_cast<const raw_t*>(X + (size_t)t * d + c);
-                else raw[u][s] = raw_t{};
+                raw[u][s] = *reinterpret_cast<const raw_t*>(X + (size_t)t * d + (c < d ? c : 0));
             }
         }
     };
-    auto use_trip = [&](const raw_t (&raw)[U][CS], const float (&dl)[U][NE]) {      // rows past the end were loaded as zeros
+    auto use_trip = [&](int tg, const raw_t (&raw)[U][CS], const float (&dl)[U][NE]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            const bool tv = tg + 16 * u + lk < t_end;
+            float g[NE];
+#pragma unroll
+            for (int n = 0; n < NE; ++n) g[n] = (tv && e0 + n * 16 + li < E) ? dl[u][n] : 0.0f;
 #pragma unroll
             for (int s = 0; s < CS; ++s) {
+                const raw_t w = (tv && c0 + s * SW + li * VN < d) ? raw[u][s] : raw_t{};
                 float x[VN];
                 if constexpr (sizeof(ET) == 2) {
-                    unpack_bf16x8(raw[u][s], x);
+                    unpack_bf16x8(w, x);
                 } else {
-                    x[0] = raw[u][s].x; x[1] = raw[u][s].y; x[2] = raw[u][s].z; x[3] = raw[u][s].w;
+                    x[0] = w.x; x[1] = w.y; x[2] = w.z; x[3] = w.w;
                 }
 #pragma unroll
                 for (int j = 0; j < VN; ++j)
 #pragma unroll
                     for (int n = 0; n < NE; ++n)
-                        acc[s][j][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], dl[u][n], acc[s][j][n], 0, 0, 0);
+                        acc[s][j][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], g[n], acc[s][j][n], 0, 0, 0);
             }
 #pragma unroll
-            for (int n = 0; n < NE; ++n) accb[n] += dl[u][n];
+            for (int n = 0; n < NE; ++n) accb[n] += g[n];
         }
     };
-    // one trip at a time per wave; the other waves of the CU cover its latency
+    // the next trip of a wave is on its way while the current one is multiplied (two register sets)
     constexpr int TRIP = 16 * U;
-    for (int tg = t_begin + 4 * wave; tg < t_end; tg += TRIP) {
-        raw_t raw[U][CS];
-        float dl[U][NE];
-        load_trip(tg, raw, dl);
-        use_trip(raw, dl);
+    raw_t raw0[U][CS], raw1[U][CS];
+    float dl0[U][NE], dl1[U][NE];
+    int tg = t_begin + 4 * wave;
+    load_trip(tg, raw0, dl0);
+    while (tg < t_end) {
+        load_trip(tg + TRIP, raw1, dl1);
+        use_trip(tg, raw0, dl0);
+        tg += TRIP;
+        if (tg >= t_end) break;
+        load_trip(tg + TRIP, raw0, dl0);
+        use_trip(tg, raw1, dl1);
+        tg += TRIP;
     }
     // lanes with the same l % 16 hold pieces of the same bias gradient
 #pragma unroll
@@ -329,14 +348,10 @@ hipError_t launch_wgrad_mfma_t(const moe_shape_t& s, const void* X, const float*
                                int n_part, int tok_per_part, hipStream_t st)
 {
     const int cw = CS * 16 * VN;
-    const dim3 grid((s.d + cw - 1) / cw, n_part);
-    for (int e0 = 0; e0 < s.E; e0 += 16 * NE) {                    // one pass unless E > 64
-        hipLaunchKernelGGL((gate_wgrad_mfma_kernel<ET, VN, NE, CS>), grid, dim3(256), 0, st, (const ET*)X, dlogits, partial,
-                           partial_b, s.T, s.d, s.E, tok_per_part, e0);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    const dim3 grid((s.d + cw - 1) / cw, n_part, (s.E + 16 * NE - 1) / (16 * NE));
+    hipLaunchKernelGGL((gate_wgrad_mfma_kernel<ET, VN, NE, CS>), grid, dim3(256), 0, st, (const ET*)X, dlogits, partial,
+                       partial_b, s.T, s.d, s.E, tok_per_part);
+    return hipGetLastError();
 }
 
 __global__ void gate_wgrad_reduce_kernel(const float* __restrict__ partial, const float* __restrict__ partial_b,
@@ -346,12 +361,12 @@ __global__ void gate_wgrad_reduce_kernel(const float* __restrict__ partial, cons
     if (i < dE) {
         float s = 0.0f;
         int p = 0;
-        for (; p + 8 <= n_part; p += 8) {                          // eight loads in flight, added in partition order
-            float v[8];
+        for (; p + 16 <= n_part; p += 16) {                        // sixteen loads in flight, added in partition order
+            float v[16];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = partial[(size_t)(p + q) * dE + i];
+            for (int q = 0; q < 16; ++q) v[q] = partial[(size_t)(p + q) * dE + i];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) s += v[q];
+            for (int q = 0; q < 16; ++q) s += v[q];
         }
         for (; p < n_part; ++p) s += partial[(size_t)p * dE + i];
         dWg[i] = s;
@@ -421,10 +436,8 @@ hipError_t launch_gate_wgrad(const moe_shape_t& s, const void* X, const float* d
     const bool bf = s.dtype == MOE_BF16;
     if (s.E <= 16)      e = bf ? launch_wgrad_mfma_t<bf16_t, 8, 1, 2>(s, X, dlogits, partial, partial_b, n_part, tok_per_part, st)
                                : launch_wgrad_mfma_t<float, 4, 1, 2>(s, X, dlogits, partial, partial_b, n_part, tok_per_part, st);
-    else if (s.E <= 32) e = bf ? launch_wgrad_mfma_t<bf16_t, 8, 2, 1>(s, X, dlogits, partial, partial_b, n_part, tok_per_part, st)
+    else                e = bf ? launch_wgrad_mfma_t<bf16_t, 8, 2, 1>(s, X, dlogits, partial, partial_b, n_part, tok_per_part, st)
                                : launch_wgrad_mfma_t<float, 4, 2, 2>(s, X, dlogits, partial, partial_b, n_part, tok_per_part, st);
-    else                e = bf ? launch_wgrad_mfma_t<bf16_t, 8, 4, 1>(s, X, dlogits, partial, partial_b, n_part, tok_per_part, st)
-                               : launch_wgrad_mfma_t<float, 4, 4, 1>(s, X, dlogits, partial, partial_b, n_part, tok_per_part, st);
     if (e != hipSuccess) return e;
     const int dE = s.d * s.E;
     hipLaunchKernelGGL(gate_wgrad_reduce_kernel, dim3((dE + 255) / 256), dim3(256), 0, st, partial, partial_b, dWg, dbg, n_part, dE, s.E);

@@ -139,3 +139,14 @@ def test_input_grad_leaves_out_experts_without_a_gradient(E):
     dX = torch.zeros(cfg.T, cfg.d, dtype=hd.elt, device=G.DEV)
     hd.input_grad(G.dev(dXp, cfg.dtype), G.dev(pos), G.dev(dl), G.dev(Wg), dX)
     G.assert_rows_close(G.host(dX), want, G.TOL["bf16"], "dX")
+
+
+@pytest.mark.parametrize("kw", [
+    dict(T=31, d=64, E=12, k=2, P=4),                          # a wave without tokens, half a strip
+    dict(T=257, d=192, E=36, k=2, P=4),                        # a second pass of four experts, two partitions
+    dict(T=1100, d=128, E=48, k=2, P=8),                       # one pass and a half
+    dict(T=300, d=100, E=40, k=1, P=4, dtype="f32"),           # fp32 tokens, strips that are not full
+], ids=lambda kw: f"T{kw['T']}-d{kw['d']}-E{kw['E']}")
+def test_gate_gradients_pass_edges(kw):
+    cfg, case = _case(1, h=64, n_replicas=0, **kw)
+    _check(cfg, case, seed=kw["E"])
