@@ -70,85 +70,66 @@ template <int J> __device__ __forceinline__ float piece_get(const XPiece<float>&
     return (J % 4 == 0) ? h.x : (J % 4 == 1) ? h.y : (J % 4 == 2) ? h.z : h.w;
 }
 
-// Top-k, softmax and gate weights of one token from its E logits.
-__device__ __forceinline__ void route_one(const float* lg, int t, int E, int k, int renorm,
-                                          int32_t* __restrict__ idx, float* __restrict__ wout)
+// Top-k, softmax and gate weights of a token by L lanes (lane = L * token + part; part holds the logits of the experts
+// part, part + L, ... in registers): every lane proposes its best remaining logit, log2(L) exchange steps pick the winner
+// by (value descending, index ascending), which is the order of a serial scan with NaN ranked as -inf; the softmax sum
+// is folded the same way.  All 64 lanes take part in the exchanges; `store` says whether the token exists.
+template <int L, int EPL>
+__device__ __forceinline__ void route_lanes(const float* lg, int part, int t, bool store, int E, int k, int renorm,
+                                            int32_t* __restrict__ idx, float* __restrict__ wout)
 {
-    int sel[8];
-    float selv[8];
-    for (int j = 0; j < k; ++j) {
-        int best = -1;
-        float bv = 0.0f;
-        for (int e = 0; e < E; ++e) {
-            bool taken = false;
-            for (int q = 0; q < j; ++q) taken |= (sel[q] == e);
-            if (taken) continue;
-            float v = lg[e];
-            v = (v != v) ? -INFINITY : v;
-            if (best < 0 || v > bv) { best = e; bv = v; }
-        }
-        sel[j] = best;
-        selv[j] = bv;
-    }
-    const float m = selv[0];
-    float sum = 0.0f;
-    for (int e = 0; e < E; ++e) {
-        float v = lg[e];
-        v = (v != v) ? -INFINITY : v;
-        sum += expf(v - m);
-    }
-    float ps[8], psum = 0.0f;
-    for (int j = 0; j < k; ++j) { ps[j] = expf(selv[j] - m) / sum; psum += ps[j]; }
-    for (int j = 0; j < k; ++j) {
-        idx[(size_t)t * k + j] = sel[j];
-        wout[(size_t)t * k + j] = renorm ? ps[j] / psum : ps[j];
-    }
-}
-
-// The same routing by four lanes per token (lane = 4 * token + part; part takes the experts e = part, part + 4, ...):
-// every lane proposes its best remaining logit, two exchange steps pick the winner by (value descending, index
-// ascending), which is the order of the serial scan; the softmax sum is folded the same way.  All 64 lanes take part
-// in the exchanges; `store` says whether the token exists.
-__device__ __forceinline__ void route_four(const float* lg, int part, int t, bool store, int E, int k, int renorm,
-                                           int32_t* __restrict__ idx, float* __restrict__ wout)
-{
-    int sel[8];
-    float selv[8];
-    for (int j = 0; j < k; ++j) {
-        int best = 0x7fffffff;
-        float bv = -INFINITY;
-        for (int e = part; e < E; e += 4) {
-            bool taken = false;
-            for (int q = 0; q < j; ++q) taken |= (sel[q] == e);
-            if (taken) continue;
-            float v = lg[e];
-            v = (v != v) ? -INFINITY : v;
-            if (best == 0x7fffffff || v > bv) { best = e; bv = v; }
-        }
+    constexpr int MAXK = 8;
+    float v[EPL];
+    unsigned long long left = 0ull;                        // logits of this lane not chosen yet
 #pragma unroll
-        for (int off = 1; off <= 2; off <<= 1) {
+    for (int i = 0; i < EPL; ++i) {
+        const int e = part + L * i;
+        const float x = lg[e < E ? e : 0];
+        v[i] = (x != x) ? -INFINITY : x;
+        if (e < E) left |= 1ull << i;
+    }
+    const unsigned long long all = left;
+    int sel[MAXK];
+    float selv[MAXK];
+#pragma unroll
+    for (int j = 0; j < MAXK; ++j) {
+        if (j >= k) break;
+        int bi = -1;
+        float bv = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i)
+            if (((left >> i) & 1ull) && (bi < 0 || v[i] > bv)) { bi = i; bv = v[i]; }
+        int best = bi < 0 ? 0x7fffffff : part + L * bi;
+#pragma unroll
+        for (int off = 1; off < L; off <<= 1) {
             const float ov = __shfl_xor(bv, off, 64);
             const int oi = __shfl_xor(best, off, 64);
             if (oi != 0x7fffffff && (best == 0x7fffffff || ov > bv || (ov == bv && oi < best))) { bv = ov; best = oi; }
         }
+        if (best % L == part) left &= ~(1ull << (best / L));
         sel[j] = best;
         selv[j] = bv;
     }
     const float m = selv[0];
     float sum = 0.0f;
-    for (int e = part; e < E; e += 4) {
-        float v = lg[e];
-        v = (v != v) ? -INFINITY : v;
-        sum += expf(v - m);
+#pragma unroll
+    for (int i = 0; i < EPL; ++i)
+        if ((all >> i) & 1ull) sum += expf(v[i] - m);
+#pragma unroll
+    for (int off = 1; off < L; off <<= 1) sum += __shfl_xor(sum, off, 64);
+    float psum = 0.0f;
+#pragma unroll
+    for (int j = 0; j < MAXK; ++j) {
+        if (j >= k) break;
+        selv[j] = expf(selv[j] - m) / sum;
+        psum += selv[j];
     }
-    sum += __shfl_xor(sum, 1, 64);
-    sum += __shfl_xor(sum, 2, 64);
-    float ps[8], psum = 0.0f;
-    for (int j = 0; j < k; ++j) { ps[j] = expf(selv[j] - m) / sum; psum += ps[j]; }
     if (store && part == 0)
-        for (int j = 0; j < k; ++j) {
+#pragma unroll
+        for (int j = 0; j < MAXK; ++j) {
+            if (j >= k) break;
             idx[(size_t)t * k + j] = sel[j];
-            wout[(size_t)t * k + j] = renorm ? ps[j] / psum : ps[j];
+            wout[(size_t)t * k + j] = renorm ? selv[j] / psum : selv[j];
         }
 }
 
@@ -295,7 +276,7 @@ __global__ __launch_bounds__(GATE_THREADS) void gate_mfma_kernel(
             const int tk = i / E, e = i - tk * E;
             if (tok0w + tk < T) logits[(size_t)tok0w * E + i] = logit_lds[(wave * 16 + tk) * e_pitch + e];
         }
-        route_four(logit_lds + (wave * 16 + (lane >> 2)) * e_pitch, lane & 3, tok0w + (lane >> 2), tok0w + (lane >> 2) < T, E, k, renorm, idx, wout);
+        route_lanes<4, 4 * NT>(logit_lds + (wave * 16 + (lane >> 2)) * e_pitch, lane & 3, tok0w + (lane >> 2), tok0w + (lane >> 2) < T, E, k, renorm, idx, wout);
     }
 }
 
@@ -444,16 +425,30 @@ __global__ __launch_bounds__(GATE_THREADS) void gate_mfma_dma_kernel(
             const int tk = i / E, e = i - tk * E;
             if (tok0w + tk < T) logits[(size_t)tok0w * E + i] = logit_lds[(wave * 16 + tk) * e_pitch + e];
         }
-        route_four(logit_lds + (wave * 16 + (lane >> 2)) * e_pitch, lane & 3, tok0w + (lane >> 2), tok0w + (lane >> 2) < T, E, k, renorm, idx, wout);
+        route_lanes<4, 4 * NT>(logit_lds + (wave * 16 + (lane >> 2)) * e_pitch, lane & 3, tok0w + (lane >> 2), tok0w + (lane >> 2) < T, E, k, renorm, idx, wout);
     }
 }
 
-// Routing from logits in global memory (E > 64: the logits were written in passes).
-__global__ void gate_route_kernel(const float* __restrict__ logits, int32_t* __restrict__ idx, float* __restrict__ wout,
-                                  int T, int E, int k, int renorm)
+// Routing from logits in global memory (E > 64: the logits were written in passes), 16 lanes per token: a wave reads four
+// tokens' rows in whole 64-byte pieces, once.  One lane per token read them k + 1 times an element at a time: 149 us at
+// T = 8001, E = 128, k = 4; the whole call 250 -> 95 us, at T = 20000, k = 8 513 -> 107.
+constexpr int ROUTE_THREADS = 256, ROUTE_TOK = ROUTE_THREADS / 16;
+template <int EPL>
+__global__ __launch_bounds__(ROUTE_THREADS) void gate_route_kernel(const float* __restrict__ logits, int32_t* __restrict__ idx,
+                                                                   float* __restrict__ wout, int T, int E, int k, int renorm)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < T) route_one(logits + (size_t)t * E, t, E, k, renorm, idx, wout);
+    const int t = blockIdx.x * ROUTE_TOK + threadIdx.x / 16;
+    const bool on = t < T;
+    route_lanes<16, EPL>(logits + (size_t)(on ? t : T - 1) * E, threadIdx.x & 15, t, on, E, k, renorm, idx, wout);
+}
+
+hipError_t run_gate_route(const moe_shape_t& s, const float* logits, int32_t* idx, float* w, hipStream_t st)
+{
+    const dim3 grid((s.T + ROUTE_TOK - 1) / ROUTE_TOK), block(ROUTE_THREADS);
+    if (s.E <= 128) hipLaunchKernelGGL(gate_route_kernel<8>, grid, block, 0, st, logits, idx, w, s.T, s.E, s.k, s.renorm);
+    else if (s.E <= 256) hipLaunchKernelGGL(gate_route_kernel<16>, grid, block, 0, st, logits, idx, w, s.T, s.E, s.k, s.renorm);
+    else hipLaunchKernelGGL(gate_route_kernel<64>, grid, block, 0, st, logits, idx, w, s.T, s.E, s.k, s.renorm);
+    return hipGetLastError();
 }
 
 // Gradient of the gate weights: 16 lanes per token, each with every 16th logit, so that a wave reads and writes whole
@@ -537,8 +532,7 @@ hipError_t run_gate(const moe_shape_t& s, const void* X, const float* Wg, const 
                        (const XT*)X, Wg, bg, logits, idx, w, s.T, s.d, s.E, s.k, s.renorm, 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(gate_route_kernel, dim3((s.T + 255) / 256), dim3(256), 0, st, logits, idx, w, s.T, s.E, s.k, s.renorm);
-    return hipGetLastError();
+    return run_gate_route(s, logits, idx, w, st);
 }
 
 template <int NT>
@@ -569,8 +563,7 @@ hipError_t run_gate_dma(const moe_shape_t& s, const void* X, const float* Wg, co
                        s.T, s.d, s.E, s.k, s.renorm, 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(gate_route_kernel, dim3((s.T + 255) / 256), dim3(256), 0, st, logits, idx, w, s.T, s.E, s.k, s.renorm);
-    return hipGetLastError();
+    return run_gate_route(s, logits, idx, w, st);
 }
 
 template <typename XT, int NT, int NXP>
