@@ -143,10 +143,7 @@ int moe_expert_counts(moe_handle_t h, const int32_t* idx, int32_t* counts, void*
     if (!h || !idx || !counts) return MOE_ERR_NULL;
     if (!ws || misaligned(ws)) return MOE_ERR_WORKSPACE;
     const Carve c{(char*)ws, h};
-    hipStream_t st = (hipStream_t)stream;
-    hipError_t e = launch_chunk_hist(h->s, idx, c.chunk_hist(), h->n_chunks, st);
-    if (e == hipSuccess) e = launch_counts_from_hist(h->s, c.chunk_hist(), h->n_chunks, counts, st);
-    return hip_status(e);
+    return hip_status(launch_counts(h->s, idx, c.chunk_hist(), h->n_chunks, counts, (hipStream_t)stream));
 }
 
 // fresh_hist: the per-chunk histograms of this idx are already in the workspace (the caller says so)

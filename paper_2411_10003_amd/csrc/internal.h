@@ -49,7 +49,7 @@ hipError_t launch_gate_bwd(const moe_shape_t& s, const float* dw, const float* l
                            float* dlogits, hipStream_t st);
 
 hipError_t launch_chunk_hist(const moe_shape_t& s, const int32_t* idx, int32_t* chunk_hist, int n_chunks, hipStream_t st);
-hipError_t launch_counts_from_hist(const moe_shape_t& s, const int32_t* chunk_hist, int n_chunks, int32_t* counts, hipStream_t st);
+hipError_t launch_counts(const moe_shape_t& s, const int32_t* idx, int32_t* chunk_hist, int n_chunks, int32_t* counts, hipStream_t st);
 hipError_t launch_layout_scan(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* counts,
                               const int32_t* chunk_hist, int32_t* chunk_base, int n_chunks,
                               const moe_layout_t& L, int32_t* status, hipStream_t st);

@@ -43,8 +43,7 @@ extern "C" int moe_expert_counts_static(moe_handle_t h, const int32_t* idx, int3
     int32_t* hist = nullptr;
     hipError_t e = scratch_for_current_device(&hist);
     hipStream_t st = (hipStream_t)stream;
-    // every word counts_from_hist reads ([chunk < n_chunks][e < E]) is written by chunk_hist first
-    if (e == hipSuccess) e = launch_chunk_hist(h->s, idx, hist, h->n_chunks, st);
-    if (e == hipSuccess) e = launch_counts_from_hist(h->s, hist, h->n_chunks, counts, st);
+    // every word of the array that the kernels read ([chunk < n_chunks][e < E]) they have written first
+    if (e == hipSuccess) e = launch_counts(h->s, idx, hist, h->n_chunks, counts, st);
     return moe_hip_status(e);
 }

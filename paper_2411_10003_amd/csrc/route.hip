@@ -1,19 +1,52 @@
 // Input distribution (Section 3 of the paper: inputs per expert), the send layout of a placement
-// (Section 4.1) and the stable positions of the assignments inside it.  Integer work only; the
-// per-wave histograms and ranks come from wavefront ballots, the offsets from prefix scans.
+// (Section 4.1) and the stable positions of the assignments inside it.  Integer work only.
 //
 // Assignments are cut into chunks of ROUTE_CHUNK consecutive ids, one wavefront per chunk.
-//   chunk_hist[c][e]  assignments of expert e in chunk c
+//   chunk_hist[c][e]  assignments of expert e in chunk c (LDS counters; sums of ones, the same in any order)
 //   chunk_base[c][e]  the same summed over all earlier chunks
 //   pos[a] = slot_offsets[slot(e)] + chunk_base[c][e] + (rank of a among the chunk's earlier e's)
+// What bounds all of it is latency: a few hundred KB at most, so launches, dependent loads and serial loops are what
+// counts.  The lanes of a wave that hold the same expert find each other with one ballot per bit of the expert id.
 #include "internal.h"
 
 namespace {
 
 constexpr int ROUTE_WAVES = 4;
+constexpr int ROUNDS = ROUTE_CHUNK / 64;
 
 __device__ __forceinline__ unsigned long long lanemask_lt(int lane) {
     return (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+}
+
+// The expert of assignment a, -1 past the end and for a corrupt index (not counted, gets no row).
+__device__ __forceinline__ int expert_of(const int32_t* __restrict__ idx, int a, int A, int E)
+{
+    const int e = a < A ? idx[a] : -1;
+    return (e < 0 || e >= E) ? -1 : e;
+}
+
+// Lanes of the wave that hold the same expert as this one (nothing for -1).  bits: of the largest expert id.
+__device__ __forceinline__ unsigned long long same_expert(int e, int bits)
+{
+    unsigned long long m = __ballot(e >= 0);
+    for (int b = 0; b < bits; ++b) {
+        const bool one = (e >> b) & 1;
+        const unsigned long long v = __ballot(one);
+        m &= one ? v : ~v;
+    }
+    return e >= 0 ? m : 0ull;
+}
+__device__ __forceinline__ int id_bits(int E) { return 32 - __clz(E - 1 > 0 ? E - 1 : 1); }
+
+// One wave: histogram of a chunk in its LDS row.
+__device__ __forceinline__ void chunk_histogram(int32_t* hist, const int (&e_of)[ROUNDS], int E, int lane)
+{
+    for (int e = lane; e < E; e += 64) hist[e] = 0;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+        if (e_of[r] >= 0) atomicAdd(&hist[e_of[r]], 1);
+    __builtin_amdgcn_wave_barrier();
 }
 
 __global__ __launch_bounds__(ROUTE_WAVES * 64) void chunk_hist_kernel(
@@ -22,27 +55,47 @@ __global__ __launch_bounds__(ROUTE_WAVES * 64) void chunk_hist_kernel(
     extern __shared__ int32_t hist_lds[];          // [ROUTE_WAVES][E]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int chunk = blockIdx.x * ROUTE_WAVES + wave;
-    volatile int32_t* hist = hist_lds + wave * E;
-    for (int e = lane; e < E; e += 64) hist[e] = 0;
-    if (chunk < n_chunks) {
-        for (int r = 0; r < ROUTE_CHUNK / 64; ++r) {
-            const int a = chunk * ROUTE_CHUNK + r * 64 + lane;
-            int e = -1;
-            if (a < A) {
-                e = idx[a];
-                if (e < 0 || e >= E) e = -1;            // a corrupt index is not counted
-            }
-            unsigned long long active = __ballot(e >= 0);
-            while (active) {
-                const int leader = __ffsll((long long)active) - 1;
-                const int e0 = __shfl(e, leader, 64);
-                const unsigned long long m = __ballot(e == e0);
-                if (lane == leader) hist[e0] = hist[e0] + __popcll(m);
-                active &= ~m;
-            }
+    if (chunk >= n_chunks) return;
+    int32_t* hist = hist_lds + wave * E;
+    int e_of[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) e_of[r] = expert_of(idx, chunk * ROUTE_CHUNK + r * 64 + lane, A, E);
+    chunk_histogram(hist, e_of, E, lane);
+    for (int e = lane; e < E; e += 64) chunk_hist[(size_t)chunk * E + e] = hist[e];
+}
+
+// Histograms and counts of up to COUNT_CHUNKS chunks in one block: one launch instead of two where the second would
+// wait for a handful of waves.
+constexpr int COUNT_WAVES = 16, COUNT_CHUNKS = 64;
+__global__ __launch_bounds__(COUNT_WAVES * 64) void small_counts_kernel(
+    const int32_t* __restrict__ idx, int32_t* __restrict__ chunk_hist, int32_t* __restrict__ counts, int A, int E, int n_chunks)
+{
+    extern __shared__ int32_t hist_lds[];          // [COUNT_WAVES][E] and [E]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t* hist = hist_lds + wave * E;
+    int32_t* total = hist_lds + COUNT_WAVES * E;
+    for (int e = threadIdx.x; e < E; e += COUNT_WAVES * 64) total[e] = 0;
+    int e_of[COUNT_CHUNKS / COUNT_WAVES][ROUNDS];
+#pragma unroll
+    for (int i = 0; i < COUNT_CHUNKS / COUNT_WAVES; ++i)
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+            e_of[i][r] = expert_of(idx, (i * COUNT_WAVES + wave) * ROUTE_CHUNK + r * 64 + lane, A, E);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < COUNT_CHUNKS / COUNT_WAVES; ++i) {
+        const int chunk = i * COUNT_WAVES + wave;
+        if (chunk >= n_chunks) break;
+        chunk_histogram(hist, e_of[i], E, lane);
+        for (int e = lane; e < E; e += 64) {
+            const int n = hist[e];
+            chunk_hist[(size_t)chunk * E + e] = n;
+            if (n) atomicAdd(&total[e], n);
         }
-        for (int e = lane; e < E; e += 64) chunk_hist[(size_t)chunk * E + e] = hist[e];
+        __builtin_amdgcn_wave_barrier();
     }
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += COUNT_WAVES * 64) counts[e] = total[e];
 }
 
 __global__ void counts_from_hist_kernel(const int32_t* __restrict__ chunk_hist, int n_chunks, int E,
@@ -58,69 +111,26 @@ __global__ void counts_from_hist_kernel(const int32_t* __restrict__ chunk_hist, 
     if (lane == 0) counts[e] = s;
 }
 
-// One block.  Builds the layout from the counts and the placement, and the per-chunk bases.
-__global__ __launch_bounds__(256) void layout_scan_kernel(
-    const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ counts,
-    const int32_t* __restrict__ chunk_hist, int32_t* __restrict__ chunk_base, int n_chunks,
-    int32_t* __restrict__ slot_of_expert, int32_t* __restrict__ slot_offsets,
-    int32_t* __restrict__ dest_offsets, int32_t* __restrict__ dest_slots,
-    int32_t* __restrict__ status, int E, int P, int self, int Gcap)
+// One wave: the rows of a chunk's assignments.  next: the wave's LDS row with the next free row of every expert.
+template <typename PUT>
+__device__ __forceinline__ void chunk_positions(int32_t* next, const int (&e_of)[ROUNDS], int E, int lane, PUT put)
 {
-    extern __shared__ int32_t sm[];                // dest[E], slot_cnt[E], slot_off[E+1], flag
-    int32_t* dest = sm;
-    int32_t* slot_cnt = sm + E;
-    int32_t* slot_off = sm + 2 * E;
-    int32_t* flag = sm + 3 * E + 1;
-    const int tid = threadIdx.x;
-    if (tid == 0) *flag = 0;
-    __syncthreads();
-    for (int e = tid; e < E; e += blockDim.x) {
-        int p = expert_dest[e];
-        if (p < 0 || p >= P) { atomicOr(flag, 1); p = p < 0 ? 0 : P - 1; }
-        dest[e] = p;
-    }
-    __syncthreads();
-    // slot of expert e = number of experts ordered before it by (destination, id)
-    for (int e = tid; e < E; e += blockDim.x) {
-        const int p = dest[e];
-        int s = 0;
-        for (int f = 0; f < E; ++f) s += (dest[f] < p) || (dest[f] == p && f < e);
-        slot_of_expert[e] = s;
-        slot_cnt[s] = counts[e];
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int row = 0;
-        for (int s = 0; s < E; ++s) { slot_off[s] = row; row += slot_cnt[s]; }
-        slot_off[E] = row;
-        int hosted = 0;
-        for (int e = 0; e < E; ++e) hosted += (dest[e] == self);
-        if (hosted > Gcap) *flag = 1;
-        *status = *flag ? (int32_t)MOE_ERR_PLAN : (int32_t)MOE_OK;
-    }
-    __syncthreads();
-    for (int s = tid; s <= E; s += blockDim.x) slot_offsets[s] = slot_off[s];
-    for (int p = tid; p <= P; p += blockDim.x) {
-        int first = 0;                              // slots of destinations below p
-        for (int f = 0; f < E; ++f) first += (dest[f] < p);
-        dest_slots[p] = first;
-        dest_offsets[p] = slot_off[first];
-    }
-    // exclusive prefix of chunk_hist over chunks, one wavefront per expert at a time
-    const int lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
-    for (int e = wave; e < E; e += n_waves) {
-        int carry = 0;
-        for (int c0 = 0; c0 < n_chunks; c0 += 64) {
-            const int c = c0 + lane;
-            const int v = (c < n_chunks) ? chunk_hist[(size_t)c * E + e] : 0;
-            int incl = v;
-            for (int off = 1; off < 64; off <<= 1) {
-                const int up = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += up;
-            }
-            if (c < n_chunks) chunk_base[(size_t)c * E + e] = carry + incl - v;
-            carry += __shfl(incl, 63, 64);
+    const int bits = id_bits(E);
+    volatile int32_t* nx = next;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int e = e_of[r];
+        const unsigned long long peers = same_expert(e, bits);
+        const int rank = __popcll(peers & lanemask_lt(lane));
+        int base = 0;
+        if (e >= 0) base = nx[e];
+        __builtin_amdgcn_wave_barrier();
+        if (e >= 0) {
+            put(r, base + rank);
+            if (rank == 0) nx[e] = base + __popcll(peers);
         }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -133,156 +143,162 @@ __global__ __launch_bounds__(ROUTE_WAVES * 64) void positions_kernel(
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int chunk = blockIdx.x * ROUTE_WAVES + wave;
     if (chunk >= n_chunks) return;
-    volatile int32_t* next = next_lds + wave * E;
+    int32_t* next = next_lds + wave * E;
     for (int e = lane; e < E; e += 64)
         next[e] = slot_offsets[slot_of_expert[e]] + chunk_base[(size_t)chunk * E + e];
-    for (int r = 0; r < ROUTE_CHUNK / 64; ++r) {
+    int e_of[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) e_of[r] = expert_of(idx, chunk * ROUTE_CHUNK + r * 64 + lane, A, E);
+    chunk_positions(next, e_of, E, lane, [&](int r, int row) {
         const int a = chunk * ROUTE_CHUNK + r * 64 + lane;
-        int e = -1;
-        if (a < A) {
-            e = idx[a];
-            if (e < 0 || e >= E) e = -1;
-        }
-        unsigned long long active = __ballot(e >= 0);
-        while (active) {
-            const int leader = __ffsll((long long)active) - 1;
-            const int e0 = __shfl(e, leader, 64);
-            const unsigned long long m = __ballot(e == e0);
-            const int base = next[e0];
-            if (e == e0) {
-                const int row = base + __popcll(m & lanemask_lt(lane));
-                pos[a] = row;
-                perm[row] = a;
+        pos[a] = row;
+        perm[row] = a;
+    });
+}
+
+// The layout from the counts and the placement, rebuilt by a whole block in LDS.  lds: 4 E + 2 words: dest, slot of
+// each expert, count and first row of each slot (E + 1), a flag.
+struct BlockLayout { int32_t *dest, *slot_of, *slot_cnt, *slot_off, *flag; };
+__device__ __forceinline__ BlockLayout block_layout_lds(int32_t* lds, int E)
+{
+    return BlockLayout{lds, lds + E, lds + 2 * E, lds + 3 * E, lds + 4 * E + 1};
+}
+__host__ __device__ __forceinline__ constexpr int block_layout_words(int E) { return 4 * E + 2; }
+
+__device__ __forceinline__ void build_layout(const BlockLayout& L, const int32_t* __restrict__ expert_dest,
+                                             const int32_t* __restrict__ counts, int E, int P)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid == 0) *L.flag = 0;
+    __syncthreads();
+    for (int e = tid; e < E; e += blockDim.x) {
+        int p = expert_dest[e];
+        if (p < 0 || p >= P) { atomicOr(L.flag, 1); p = p < 0 ? 0 : P - 1; }
+        L.dest[e] = p;
+    }
+    __syncthreads();
+    for (int e = tid; e < E; e += blockDim.x) {             // slot = rank by (destination, id)
+        const int p = L.dest[e], n = counts[e];
+        int sl = 0;
+#pragma unroll 4
+        for (int f = 0; f < E; ++f) sl += (L.dest[f] < p) || (L.dest[f] == p && f < e);
+        L.slot_of[e] = sl;
+        L.slot_cnt[sl] = n;
+    }
+    __syncthreads();
+    if (tid < 64) {                                         // exclusive scan of the slot counts, one wave
+        int carry = 0;
+        for (int s0 = 0; s0 < E; s0 += 64) {
+            const int v = s0 + lane < E ? L.slot_cnt[s0 + lane] : 0;
+            int incl = v;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int up = __shfl_up(incl, off, 64);
+                if (lane >= off) incl += up;
             }
-            if (lane == leader) next[e0] = base + __popcll(m);
-            active &= ~m;
+            if (s0 + lane < E) L.slot_off[s0 + lane] = carry + incl - v;
+            carry += __shfl(incl, 63, 64);
         }
+        if (lane == 0) L.slot_off[E] = carry;
+    }
+    __syncthreads();
+}
+
+// One block publishes the layout.
+__device__ __forceinline__ void publish_layout(const BlockLayout& L, const moe_layout_t& out, int32_t* __restrict__ status,
+                                               int E, int P, int self, int Gcap)
+{
+    const int tid = threadIdx.x;
+    for (int e = tid; e < E; e += blockDim.x) out.slot_of_expert[e] = L.slot_of[e];
+    for (int s = tid; s <= E; s += blockDim.x) out.slot_offsets[s] = L.slot_off[s];
+    for (int p = tid; p <= P; p += blockDim.x) {
+        int first = 0, mine = 0;                            // slots of destinations below p, of p
+        for (int f = 0; f < E; ++f) { first += (L.dest[f] < p); mine += (L.dest[f] == p); }
+        out.dest_slots[p] = first;
+        out.dest_offsets[p] = L.slot_off[first];
+        if (p == self) *status = (*L.flag || mine > Gcap) ? (int32_t)MOE_ERR_PLAN : (int32_t)MOE_OK;
     }
 }
 
-// Layout and positions in one launch, for the common case of few chunks: every block rebuilds the
-// (small) layout from the counts and the placement in LDS, block 0 publishes it, and every wave gets
-// the base of its chunk by summing the histograms of the chunks before it instead of reading a
-// prefix table that a separate single-block launch would have to write first.
-constexpr int FUSED_MAX_E = 64, FUSED_MAX_CHUNKS = 1024;
+// The layout and the per-chunk bases, for more chunks than layout_positions_kernel adds up: one block per 64 experts scans
+// their histograms over the chunks, block 0 publishes the layout.
+constexpr int SCAN_WAVES = 16;
+__global__ __launch_bounds__(SCAN_WAVES * 64) void layout_scan_kernel(
+    const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ counts,
+    const int32_t* __restrict__ chunk_hist, int32_t* __restrict__ chunk_base, int n_chunks,
+    const moe_layout_t out, int32_t* __restrict__ status, int E, int P, int self, int Gcap)
+{
+    extern __shared__ int32_t lds[];
+    __shared__ int32_t part[SCAN_WAVES][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, e = blockIdx.x * 64 + lane;
+    if (blockIdx.x == 0) {
+        const BlockLayout L = block_layout_lds(lds, E);
+        build_layout(L, expert_dest, counts, E, P);
+        publish_layout(L, out, status, E, P, self, Gcap);
+    }
+    // wave w owns a run of chunks: their sum, the sums of the runs before, then the bases of its chunks
+    const int per = (n_chunks + SCAN_WAVES - 1) / SCAN_WAVES, c0 = min(wave * per, n_chunks), c1 = min(c0 + per, n_chunks);
+    int sum = 0;
+#pragma unroll 8
+    for (int c = c0; c < c1; ++c) sum += e < E ? chunk_hist[(size_t)c * E + e] : 0;
+    part[wave][lane] = sum;
+    __syncthreads();
+    int base = 0;
+    for (int w = 0; w < wave; ++w) base += part[w][lane];
+#pragma unroll 8
+    for (int c = c0; c < c1; ++c) {
+        const int v = e < E ? chunk_hist[(size_t)c * E + e] : 0;
+        if (e < E) chunk_base[(size_t)c * E + e] = base;
+        base += v;
+    }
+}
 
+// Layout and positions in one launch: every block rebuilds the (small) layout in LDS, block 0 publishes it, and the
+// base of a block's first chunk is summed from the histograms of all chunks before it (its waves share them; whole rows,
+// all loads independent) instead of being read from a prefix table that a launch of a single block would have to write
+// first.
 __global__ __launch_bounds__(ROUTE_WAVES * 64) void layout_positions_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ counts,
-    const int32_t* __restrict__ chunk_hist,
-    int32_t* __restrict__ slot_of_expert, int32_t* __restrict__ slot_offsets,
-    int32_t* __restrict__ dest_offsets, int32_t* __restrict__ dest_slots, int32_t* __restrict__ status,
-    int32_t* __restrict__ pos, int32_t* __restrict__ perm, int A, int E, int P, int self, int Gcap, int n_chunks)
+    const int32_t* __restrict__ chunk_hist, const moe_layout_t out, int32_t* __restrict__ status,
+    int A, int E, int P, int self, int Gcap, int n_chunks)
 {
-    __shared__ int32_t dest[FUSED_MAX_E], slot_of[FUSED_MAX_E], slot_cnt[FUSED_MAX_E], slot_off[FUSED_MAX_E + 1];
-    __shared__ int32_t next_all[ROUTE_WAVES][FUSED_MAX_E];
-    __shared__ int32_t flag;
+    extern __shared__ int32_t lds[];               // layout, [ROUTE_WAVES][E] next free rows
+    const BlockLayout L = block_layout_lds(lds, E);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int chunk = blockIdx.x * ROUTE_WAVES + wave;
-    // every load that does not depend on the layout is issued first, so that the kernel pays one memory
-    // round trip and not one per stage: placement and counts, this wave's assignments, and the histograms of
-    // the chunks before it
-    int my_dest = 0, my_count = 0;
-    if (tid < E) { my_dest = expert_dest[tid]; my_count = counts[tid]; }
-    int e_of[ROUTE_CHUNK / 64];
+    const int chunk0 = blockIdx.x * ROUTE_WAVES, chunk = chunk0 + wave;
+    int32_t* next = lds + block_layout_words(E);
+    int e_of[ROUNDS];
 #pragma unroll
-    for (int r = 0; r < ROUTE_CHUNK / 64; ++r) {
-        const int a = chunk * ROUTE_CHUNK + r * 64 + lane;
-        int e = -1;
-        if (chunk < n_chunks && a < A) {
-            e = idx[a];
-            if (e < 0 || e >= E) e = -1;
+    for (int r = 0; r < ROUNDS; ++r) e_of[r] = expert_of(idx, chunk * ROUTE_CHUNK + r * 64 + lane, A, E);
+    for (int i = tid; i < ROUTE_WAVES * E; i += blockDim.x) next[i] = 0;
+    build_layout(L, expert_dest, counts, E, P);
+    // wave w adds up every ROUTE_WAVES-th chunk before this block, for everybody, and the block's chunks w .. 2 for the
+    // waves behind them; lane l takes the experts l, l + 64, ...
+    for (int s0 = 0; s0 < E; s0 += 64) {
+        const int e = s0 + lane;
+        const bool on = e < E;
+        const int32_t* col = chunk_hist + (on ? e : 0);     // unconditional loads
+        int sum = 0;
+#pragma unroll 8
+        for (int c = wave; c < chunk0; c += ROUTE_WAVES) sum += col[(size_t)c * E];
+        const int mine = chunk < n_chunks ? col[(size_t)chunk * E] : 0;
+        if (on) {
+            if (wave == 0) sum += L.slot_off[L.slot_of[e]];
+#pragma unroll
+            for (int w = 0; w < ROUTE_WAVES; ++w) {
+                const int add = sum + (w > wave ? mine : 0);
+                if (add) atomicAdd(&next[w * E + e], add);
+            }
         }
-        e_of[r] = e;
-    }
-    // rows of every expert in the chunks before this one.  The histograms of those chunks are one flat array
-    // of 16-byte pieces, q = E/4 per chunk; q divides 64, so a lane striding by 64 always meets the same four
-    // experts and all of its loads are independent.
-    const int q = E >> 2;
-    int4 acc = make_int4(0, 0, 0, 0);
-    if (chunk < n_chunks) {
-        const int4* hp = reinterpret_cast<const int4*>(chunk_hist);
-        const int n4 = chunk * q;
-#pragma unroll 4
-        for (int i = lane; i < n4; i += 64) {
-            const int4 v = hp[i];
-            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-        }
-    }
-
-    if (tid == 0) flag = 0;
-    __syncthreads();
-    if (tid < E) {
-        int p = my_dest;
-        if (p < 0 || p >= P) { atomicOr(&flag, 1); p = p < 0 ? 0 : P - 1; }
-        dest[tid] = p;
     }
     __syncthreads();
-    if (tid < E) {                                          // slot = rank by (destination, id)
-        const int p = dest[tid];
-        int sl = 0;
-        for (int f = 0; f < E; ++f) sl += (dest[f] < p) || (dest[f] == p && f < tid);
-        slot_of[tid] = sl;
-        slot_cnt[sl] = my_count;
-    }
-    __syncthreads();
-    if (wave == 0) {                                        // exclusive scan of the slot counts (E <= 64: one wave)
-        const int v = lane < E ? slot_cnt[lane] : 0;
-        int incl = v;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int up = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += up;
-        }
-        if (lane < E) slot_off[lane] = incl - v;
-        if (lane == 63) slot_off[E] = incl;
-    }
-    __syncthreads();
-    if (blockIdx.x == 0) {                                  // one block publishes the layout
-        if (tid < E) slot_of_expert[tid] = slot_of[tid];
-        if (tid <= E) slot_offsets[tid] = slot_off[tid];
-        if (tid <= P) {
-            int first = 0;
-            for (int f = 0; f < E; ++f) first += (dest[f] < tid);
-            dest_slots[tid] = first;
-            dest_offsets[tid] = slot_off[first];
-        }
-        if (tid == 0) {
-            int hosted = 0;
-            for (int e = 0; e < E; ++e) hosted += (dest[e] == self);
-            *status = (flag || hosted > Gcap) ? (int32_t)MOE_ERR_PLAN : (int32_t)MOE_OK;
-        }
-    }
+    if (blockIdx.x == 0) publish_layout(L, out, status, E, P, self, Gcap);
     if (chunk >= n_chunks) return;
-    for (int off = q; off < 64; off <<= 1) {
-        acc.x += __shfl_xor(acc.x, off, 64); acc.y += __shfl_xor(acc.y, off, 64);
-        acc.z += __shfl_xor(acc.z, off, 64); acc.w += __shfl_xor(acc.w, off, 64);
-    }
-    // lane e keeps the next free row of expert e (E <= 64); lanes 0..q-1 hold the sums of experts 4l..4l+3
-    int32_t* nx = next_all[wave];
-    if (lane < q) { nx[4 * lane + 0] = acc.x; nx[4 * lane + 1] = acc.y; nx[4 * lane + 2] = acc.z; nx[4 * lane + 3] = acc.w; }
-    __builtin_amdgcn_wave_barrier();
-    int next_row = 0;
-    if (lane < E) next_row = slot_off[slot_of[lane]] + reinterpret_cast<volatile int32_t*>(nx)[lane];
-    // One ballot per expert instead of one per distinct expert met: no data-dependent loop and nothing that
-    // waits on LDS inside it.
-#pragma unroll
-    for (int r = 0; r < ROUTE_CHUNK / 64; ++r) {
+    chunk_positions(next + wave * E, e_of, E, lane, [&](int r, int row) {
         const int a = chunk * ROUTE_CHUNK + r * 64 + lane;
-        const int e = e_of[r];
-        unsigned long long mine = 0ull;
-        int add = 0;
-        for (int e0 = 0; e0 < E; ++e0) {
-            const unsigned long long m = __ballot(e == e0);
-            if (e == e0) mine = m;
-            if (lane == e0) add = __popcll(m);
-        }
-        const int base = __shfl(next_row, e < 0 ? 0 : e, 64);
-        if (e >= 0) {
-            const int row = base + __popcll(mine & lanemask_lt(lane));
-            pos[a] = row;
-            perm[row] = a;
-        }
-        next_row += add;
-    }
+        out.pos[a] = row;
+        out.perm[row] = a;
+    });
 }
 
 // Layout of the rows a device receives for the experts it hosts: the same slots as the local layout, the row
@@ -311,8 +327,17 @@ hipError_t launch_chunk_hist(const moe_shape_t& s, const int32_t* idx, int32_t* 
     return hipGetLastError();
 }
 
-hipError_t launch_counts_from_hist(const moe_shape_t& s, const int32_t* chunk_hist, int n_chunks, int32_t* counts, hipStream_t st)
+// Histograms into chunk_hist and the counts.  Up to COUNT_CHUNKS chunks (and 256 experts: 17 LDS rows) in one launch: expert_counts alone 12 -> 8 us, of which
+// the host takes most, the two launches took 6 + 5 us of the GPU in a row.
+hipError_t launch_counts(const moe_shape_t& s, const int32_t* idx, int32_t* chunk_hist, int n_chunks, int32_t* counts, hipStream_t st)
 {
+    if (n_chunks <= COUNT_CHUNKS && s.E <= 256) {
+        hipLaunchKernelGGL(small_counts_kernel, dim3(1), dim3(COUNT_WAVES * 64), (size_t)(COUNT_WAVES + 1) * s.E * sizeof(int32_t), st,
+                           idx, chunk_hist, counts, s.T * s.k, s.E, n_chunks);
+        return hipGetLastError();
+    }
+    const hipError_t e = launch_chunk_hist(s, idx, chunk_hist, n_chunks, st);
+    if (e != hipSuccess) return e;
     const int waves = 4;
     hipLaunchKernelGGL(counts_from_hist_kernel, dim3((s.E + waves - 1) / waves), dim3(waves * 64), 0, st,
                        chunk_hist, n_chunks, s.E, counts);
@@ -323,10 +348,8 @@ hipError_t launch_layout_scan(const moe_shape_t& s, const int32_t* expert_dest, 
                               const int32_t* chunk_hist, int32_t* chunk_base, int n_chunks,
                               const moe_layout_t& L, int32_t* status, hipStream_t st)
 {
-    const size_t lds = (size_t)(3 * s.E + 2) * sizeof(int32_t);
-    hipLaunchKernelGGL(layout_scan_kernel, dim3(1), dim3(256), lds, st, expert_dest, counts, chunk_hist, chunk_base,
-                       n_chunks, L.slot_of_expert, L.slot_offsets, L.dest_offsets, L.dest_slots, status,
-                       s.E, s.P, s.self, s.G);
+    hipLaunchKernelGGL(layout_scan_kernel, dim3((s.E + 63) / 64), dim3(SCAN_WAVES * 64), (size_t)block_layout_words(s.E) * sizeof(int32_t), st,
+                       expert_dest, counts, chunk_hist, chunk_base, n_chunks, L, status, s.E, s.P, s.self, s.G);
     return hipGetLastError();
 }
 
@@ -340,19 +363,20 @@ hipError_t launch_positions(const moe_shape_t& s, const int32_t* idx, const int3
     return hipGetLastError();
 }
 
+// The fused launch reads n_chunks^2 E / (2 ROUTE_WAVES) histogram words through L2 in all: up to 2^26 / 8 of them (33 MB,
+// 1024 chunks of 64 experts) that is less than the launch of a scan costs.
 bool layout_positions_fusable(const moe_shape_t& s, int n_chunks)
 {
-    const bool e_ok = s.E >= 4 && s.E <= FUSED_MAX_E && (s.E & (s.E - 1)) == 0;      // a power of two: E/4 divides 64
-    return e_ok && s.P <= ROUTE_WAVES * 64 - 1 && n_chunks >= 1 && n_chunks <= FUSED_MAX_CHUNKS;
+    return n_chunks >= 1 && (long long)n_chunks * n_chunks * s.E <= (1ll << 26);
 }
 
 hipError_t launch_layout_positions(const moe_shape_t& s, const int32_t* idx, const int32_t* expert_dest, const int32_t* counts,
                                    const int32_t* chunk_hist, int n_chunks, const moe_layout_t& L, int32_t* status, hipStream_t st)
 {
     const int grid = (n_chunks + ROUTE_WAVES - 1) / ROUTE_WAVES;
-    hipLaunchKernelGGL(layout_positions_kernel, dim3(grid), dim3(ROUTE_WAVES * 64), 0, st, idx, expert_dest, counts, chunk_hist,
-                       L.slot_of_expert, L.slot_offsets, L.dest_offsets, L.dest_slots, status, L.pos, L.perm,
-                       s.T * s.k, s.E, s.P, s.self, s.G, n_chunks);
+    const size_t lds = (size_t)(block_layout_words(s.E) + ROUTE_WAVES * s.E) * sizeof(int32_t);
+    hipLaunchKernelGGL(layout_positions_kernel, dim3(grid), dim3(ROUTE_WAVES * 64), lds, st, idx, expert_dest, counts, chunk_hist,
+                       L, status, s.T * s.k, s.E, s.P, s.self, s.G, n_chunks);
     return hipGetLastError();
 }
 

@@ -1,0 +1,82 @@
+"""Gate selection, counts, layout and positions where the number of experts or chunks changes the path: expert counts that
+are no power of two, up to the largest; every number of chunks at which a launch is fused or split; several experts per
+token; ties, NaN and infinities.  All of it exact against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as G
+from oracle import moe_oracle as orc
+from paper_2411_10003_amd import workload as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(**kw):
+    return wl.scaled(wl.CONFIGS[1], **dict(dict(d=64, h=64, k=2, n_replicas=0, self_dest=0), **kw))
+
+
+CASES = [
+    _cfg(T=1, E=1, k=1, P=1),
+    _cfg(T=127, E=5, P=5, k=3),                       # one chunk, not full
+    _cfg(T=128, E=16, P=4),                           # exactly one chunk
+    _cfg(T=129, E=63, P=7, k=1),
+    _cfg(T=513, E=64, P=64),                          # P as many as experts
+    _cfg(T=700, E=65, P=13, k=8),                     # a second row of lanes with one expert
+    _cfg(T=8192, E=24, P=4),                          # the last number of chunks counted in one block
+    _cfg(T=8193, E=24, P=4),                          # the first past it
+    _cfg(T=300, E=257, P=257, k=8),                   # past the experts of the one-block counts
+    _cfg(T=4000, E=1024, P=512, k=8),                 # the most experts, 125 chunks
+    _cfg(T=40000, E=1000, P=10, k=2),                 # more chunks than are added up: the scan
+    _cfg(T=140000, E=64, P=8, k=2),
+]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: f"T{c.T}-E{c.E}-k{c.k}-P{c.P}")
+def test_counts_layout_positions(cfg):
+    rng = np.random.default_rng(cfg.T + cfg.E)
+    p = rng.gamma(0.3, size=cfg.E) + 1e-4             # uneven, with experts that get next to nothing
+    noise = rng.gumbel(size=(cfg.T, cfg.E)).astype(np.float32) + np.log(p).astype(np.float32)
+    idx = np.argpartition(-noise, min(cfg.k, cfg.E) - 1, axis=1)[:, :cfg.k].astype(np.int32)
+    dest = rng.integers(0, cfg.P, size=cfg.E).astype(np.int32)
+    cnt = orc.counts(idx, cfg.E)
+    lay = orc.place(idx, cnt, dest, cfg.P)
+    X = wl.round_to_bf16(rng.standard_normal((cfg.T, cfg.d)).astype(np.float32))
+    hd = G.make_handle(cfg, G=min(cfg.E, 64))
+    for after in (False, True):
+        b = G.binding.LayerBuffers(hd, False)
+        d_idx = G.dev(idx)
+        b.counts.fill_(-1)
+        hd.expert_counts(d_idx, b.counts)
+        assert np.array_equal(G.host(b.counts), cnt)
+        hd.dispatch(G.dev(dest), G.dev(X, "bf16"), d_idx, b.counts, b.layout, b.Xp, after_counts=after)
+        torch.cuda.synchronize()
+        G.assert_layout_equal(b, lay)
+        assert np.array_equal(G.host(b.Xp), orc.dispatch(X, lay["perm"], cfg.k))
+        hosted = int((dest == cfg.self_dest).sum())
+        assert hd.read_status() == (0 if hosted <= min(cfg.E, 64) else -3)
+
+
+@pytest.mark.parametrize("E,k", [(72, 1), (128, 8), (129, 3), (300, 8), (1024, 8)])
+def test_routing_of_many_experts(E, k):
+    """Selection and weights for more than 64 experts, with ties, NaN and infinities among the biases."""
+    cfg = _cfg(T=203, E=E, k=k, P=1, renorm=1)
+    rng = np.random.default_rng(E + k)
+    X = wl.round_to_bf16(rng.standard_normal((cfg.T, cfg.d)).astype(np.float32))
+    Wg = (rng.standard_normal((cfg.d, E)) * 0.1).astype(np.float32)
+    Wg[:, 40:60] = Wg[:, 40:41]                       # twenty experts that always tie
+    bg = rng.standard_normal(E).astype(np.float32)
+    bg[40:60] = 2.0
+    bg[3] = -np.inf
+    bg[7] = np.nan
+    ref = orc.route(X, Wg, bg, k, 1)
+    hd = G.make_handle(cfg, G=1)
+    b = G.binding.LayerBuffers(hd, False)
+    hd.gate_topk(G.dev(X, "bf16"), G.dev(Wg), G.dev(bg), b.logits, b.idx, b.w)
+    torch.cuda.synchronize()
+    got = G.host(b.logits)
+    assert np.array_equal(np.isnan(got), np.isnan(ref["logits"]))
+    ok = ~np.isnan(got)
+    assert np.array_equal(got.view(np.uint32)[ok], ref["logits"].view(np.uint32)[ok])
+    assert np.array_equal(G.host(b.idx), ref["idx"])
+    assert np.allclose(G.host(b.w), ref["w"], rtol=1e-5, atol=1e-7)
