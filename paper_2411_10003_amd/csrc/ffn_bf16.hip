@@ -9,10 +9,10 @@
 //   wgrad dW1 = Xp^T dZ, dW3 = Xp^T dU, dW2 = Act^T dYp over the rows of each group
 // Groups are ragged and may be empty; row tiles start at the group's first row and the last one
 // is masked, so nothing is padded to the largest load.  The kernel is persistent: one block per
-// CU walks its share of the tiles, which it derives on the device from the group offsets (the
-// host never reads the counts).
+// CU (two of the small geometry) walks its share of the tiles, which it derives on the device from
+// the group offsets (the host never reads the counts).
 //
-// Tiling: 256 x 256 output tile per block, 32-deep contraction slices moved from HBM/L2 straight
+// Tiling: 256 x 256 output tile per block (128 x 128 where those leave the chip idle, see GeometryCost), 32-deep contraction slices moved from HBM/L2 straight
 // into a 5-deep ring of LDS buffers by buffer loads (no register staging; rows outside a ragged
 // group arrive as zeros because they lie past the end of the buffer resource), 32x32x16 bf16 MFMA
 // with the accumulators in AGPRs.  An operand whose contraction index is contiguous in memory is
@@ -28,6 +28,8 @@
 // multiplying, half an iteration apart.
 #include "internal.h"
 #include <type_traits>
+#include <algorithm>
+#include <cmath>
 
 // Where the main loop starts relative to a 256-byte boundary of the code, in 4-byte steps.  The loop is one basic
 // block that every wave runs tens of thousands of times; how its two phases fall into the instruction fetch
@@ -78,6 +80,7 @@ struct GemmParams {
     int write_act;               // BWD1: recompute the activation into O2 (0: the forward pass's copy is still there)
     float* split_ws;             // NN/NT: partial tiles of the K-split last round, [unit][wave][128 registers][64 lanes]
     int split_cap;               // units that fit there
+    int split_max, split_slices; // parts of a tile at most, slices of a part at least
 };
 
 // GELU (Eq. 2 with the Gaussian CDF) and its derivative from one exponential and one reciprocal: erf by the
@@ -106,9 +109,28 @@ __device__ __forceinline__ float gelu_grad_f(float z) { const gelu_parts g = gel
 // epilogue whose vector instructions are what the matrix cores wait for between two tiles
 __device__ __forceinline__ float sigmoid_f(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 
-// Tile geometry: 256 x 256 outputs per block, 8 waves of 128 x 64, contraction slices of 32
-// staged through a 5-deep ring of LDS buffers (16 KB per operand and buffer): all 160 KB of LDS.
-constexpr int BM = 256, BN = 256, BK = 32, STAGES = 5;
+// Tile geometries.  Contraction slices of 32 are staged through a ring of LDS buffers.
+//   Large: 256 x 256 outputs per block of 8 waves of 128 x 64, one block per CU (a 5-deep ring of 32 KB: all of LDS).
+//   Small: 128 x 128 outputs per block of 4 waves of 64 x 64, two blocks per CU (5-deep rings of 16 KB).
+constexpr int BK = 32;
+template <int WGM_, int WGN_, int TM_, int TN_, int STAGES_, int BLOCKS_> struct Geometry {
+    static constexpr int WGM = WGM_, WGN = WGN_, TM = TM_, TN = TN_, STAGES = STAGES_, BLOCKS = BLOCKS_;
+    static constexpr int NWAVES = WGM * WGN, THREADS = NWAVES * 64;
+    static constexpr int WM = 32 * TM, WN = 32 * TN, BM = WM * WGM, BN = WN * WGN;
+    static constexpr uint32_t A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
+    static constexpr int PA = A_BYTES / 1024 / NWAVES, PB = B_BYTES / 1024 / NWAVES;   // 1-KB DMA pieces per wave and slice
+    static constexpr int EP_PITCH = WN * 4 + 16;           // epilogue patch: bytes per staged row of WN floats (padded against bank conflicts)
+    static constexpr int EP_ROWS = 32;                     // rows a wave stages at a time: one row of fragments
+    static constexpr int EP_WAVE = EP_ROWS * EP_PITCH;
+    static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE_BYTES;
+    static constexpr bool TWO_PHASE = BLOCKS == 1;         // the rows of waves of a block alternate; else the blocks of a CU do
+    static constexpr int UNIT_BYTES = BM * BN * 4;         // a partial tile of a K-split round
+    static_assert(LDS_BYTES >= (size_t)NWAVES * EP_WAVE && BLOCKS * LDS_BYTES <= 160 * 1024, "patches inside the ring, rings inside LDS");
+    static_assert(WGM == 2 && WGN % 2 == 0, "the two halves of a K-contiguous operand's rows belong to one row of waves or half the columns");
+};
+typedef Geometry<2, 4, 4, 2, 5, 1> Large;
+typedef Geometry<2, 2, 2, 2, 5, 2> Small;
+
 // Row tiles per band of the tile walk, per contraction (measured at d = 4096, h = 14336, SwiGLU; see launch()).
 #ifndef BAND_FWD1
 #define BAND_FWD1 16
@@ -125,25 +147,26 @@ constexpr int BM = 256, BN = 256, BK = 32, STAGES = 5;
 #ifndef BAND_WGRAD
 #define BAND_WGRAD 8
 #endif
-constexpr int WGM = 2, WGN = 4, NWAVES = WGM * WGN, NT = NWAVES * 64;
-constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
-constexpr int PIECES = 16 / NWAVES;         // 1-KB DMA pieces per wave per 16-KB operand slice
-constexpr uint32_t OPER_BYTES = 16384, STAGE_BYTES = 2 * OPER_BYTES;
-constexpr int EP_PITCH = WN * 4 + 16;       // epilogue patch: bytes per staged row of WN floats (padded against bank conflicts)
-constexpr int EP_ROWS = 32;               // rows a wave stages at a time: one row of fragments
-constexpr int EP_WAVE = EP_ROWS * EP_PITCH;
-constexpr size_t RING_BYTES = (size_t)STAGES * STAGE_BYTES;
-constexpr size_t LDS_BYTES = RING_BYTES > (size_t)NWAVES * EP_WAVE ? RING_BYTES : (size_t)NWAVES * EP_WAVE;
-
 // ---- LDS layouts (byte offsets inside one operand buffer) --------------------------------------
 // K-contiguous operand (NN and NT fetch it in whole 128-byte lines): a buffer holds 128 rows x 64 steps (two
 // slices of 32), 128 bytes per row, its eight 16-byte pieces XOR-swizzled by the row so that 16 consecutive rows of
 // one piece cover all banks.
 __device__ __forceinline__ uint32_t halfpair_off(int row, int piece8) { return row * 128 + ((piece8 ^ ((row >> 1) & 7)) << 4); }
 // K-major operand: [32 steps][COLS columns]; 64-byte granules of a row XOR-swizzled by the step so
-// that the four steps a transposing load touches fall into different banks.
+// that the four steps a transposing load touches fall into different banks (rows of 64 columns are 128 bytes: steps two
+// apart share their banks and are kept apart by the one bit there is).
+template <int COLS> __device__ __forceinline__ int kmajor_swizzle(int krow) { return COLS >= 128 ? (krow & 3) : ((krow >> 1) & 1); }
 template <int COLS>
-__device__ __forceinline__ uint32_t kmajor_off(int krow, int col) { return krow * (COLS * 2) + ((((col >> 5) ^ (krow & 3))) << 6) + (col & 31) * 2; }
+__device__ __forceinline__ uint32_t kmajor_off(int krow, int col) { return krow * (COLS * 2) + ((((col >> 5) ^ kmajor_swizzle<COLS>(krow))) << 6) + (col & 31) * 2; }
+// The inverse for the DMA: byte offset in memory of the 16-byte piece that belongs at slot L of such a buffer.
+template <int COLS>
+__device__ __forceinline__ uint32_t kmajor_source(int L, long ld)
+{
+    constexpr int PER_ROW = COLS / 8;
+    const int krow = L / PER_ROW, pp = L % PER_ROW;
+    const int col = (((pp >> 2) ^ kmajor_swizzle<COLS>(krow)) << 5) + (pp & 3) * 8;
+    return (uint32_t)((krow * ld + col) * 2);
+}
 
 // Fragment = 32 rows (or columns) x 16 contraction steps; lane l holds row l%32, steps 8*(l/32)..+7.
 // Fragment reads are issued as assembly and waited for by hand (WAIT_FRAGS below): the compiler's
@@ -199,9 +222,13 @@ __device__ __forceinline__ void dma16(rsrc_t r, uint32_t lds_base, uint32_t voff
 
 
 // ---- the kernel ---------------------------------------------------------------------------------
-template <int KIND, int EPI, bool FIN>
-__global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
+template <int KIND, int EPI, bool FIN, class GEO>
+__global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void grouped_gemm_kernel(const GemmParams p)
 {
+    constexpr int WGN = GEO::WGN, NWAVES = GEO::NWAVES, WM = GEO::WM, WN = GEO::WN, BM = GEO::BM, BN = GEO::BN, TM = GEO::TM, TN = GEO::TN;
+    constexpr int STAGES = GEO::STAGES, PA = GEO::PA, PB = GEO::PB, EP_PITCH = GEO::EP_PITCH, EP_ROWS = GEO::EP_ROWS, EP_WAVE = GEO::EP_WAVE;
+    constexpr uint32_t A_BYTES = GEO::A_BYTES, STAGE_BYTES = GEO::STAGE_BYTES;
+    constexpr size_t LDS_BYTES = GEO::LDS_BYTES;
     constexpr bool A_KMAJOR = (KIND == KIND_TN);
     constexpr bool B_KMAJOR = (KIND != KIND_NT);
     constexpr bool DUAL = (EPI == EPI_FWD1_SWIGLU);
@@ -253,8 +280,8 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
     const int n_full = (KIND == KIND_TN) ? 0 : (n_act / nblk) * nblk, rem = n_act - n_full;
     int S = 1;
     if (KIND != KIND_TN && rem > 0 && p.split_ws != nullptr) {
-        S = min(4, nblk / rem);
-        S = min(S, max(1, p.n_seg * (p.Kseg / BK) / 64));   // a part is worth its 256-KB round trip from 64 slices on
+        S = min(p.split_max, nblk / rem);
+        S = min(S, max(1, p.n_seg * (p.Kseg / BK) / p.split_slices));   // a part has to be worth its round trip
         if (rem * S > p.split_cap) S = 1;
     }
     if (FIN && S == 1) return;
@@ -262,7 +289,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
     const int n_rounds = (KIND == KIND_TN) ? p.Gcap * rpg : (n_items + q_stride - 1) / q_stride;
     const int q_first = FIN ? (int)blockIdx.x : q0;
     const int q_step = FIN ? nblk : q_stride;
-    const int q_end = FIN ? rem : ((n_rounds + 7) >> 3) * q_stride;
+    const int q_end = FIN ? rem * TM : ((n_rounds + 7) >> 3) * q_stride;   // FIN: a row of fragments of a tile is an item
 
   for (int q = q_first; q < q_end; q += q_step) {
     int g, rt, ct;
@@ -291,7 +318,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
     } else {
         int t;
         if (FIN) {
-            t = n_full + q; parts = S; unit = q * S;
+            t = n_full + q / TM; parts = S; unit = (q / TM) * S;
         } else {
             const int item = (((q - q0) / q_stride) * 8 + xcd) * q_stride + q0;
             if (item >= n_items) break;
@@ -322,8 +349,8 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
     // ---- buffer resources: everything outside the valid rows of an operand reads as zero --------
     // Each wave moves two 1-KB pieces of the A slice and two of the B slice per contraction slice.
     rsrc_t rA[2], rB[2];                   // per segment (A), per segment or per dual half (B)
-    uint32_t voffA[2], voffB[2];                           // per-lane byte offsets of this wave's two pieces
-    uint32_t ldsA[2], ldsB[2];                             // LDS byte offsets of the pieces inside a stage
+    uint32_t voffA[PA], voffB[PB];                         // per-lane byte offsets of this wave's pieces
+    uint32_t ldsA[PA], ldsB[PB];                           // LDS byte offsets of the pieces inside a stage
     uint32_t stepA, stepB;                                 // byte advance of the source per slice
     const bf16_t *tn_baseA = nullptr, *tn_baseB = nullptr; // TN: where the current resources start, and how many
     long tn_bytesA = 0, tn_bytesB = 0;                     // bytes of the group's rows lie behind that point
@@ -355,35 +382,29 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
                 stepB = BK * 2;
             }
         }
+        // a 1-KB piece of a K-contiguous operand is 8 rows x 128 bytes of half the tile's rows: lane l reads piece l%8 of
+        // row l/8, where the swizzle of the buffer puts it
+        auto line_source = [&](int blk, long ld) {
+            const int row = blk * 8 + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
+            return (uint32_t)((row * ld + piece * 8) * 2);
+        };
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) {
-            const int blk = wave + NWAVES * i;             // piece index inside a 16-KB operand buffer
-            const int L = blk * 64 + lane;                 // 16-byte slot inside the buffer
+        for (int i = 0; i < PA; ++i) {
+            const int blk = wave + NWAVES * i;             // piece index inside an operand buffer
             ldsA[i] = blk * 1024;
-            if (A_KMAJOR) {
-                const int krow = L >> 5, pp = L & 31, col = (((pp >> 2) ^ (krow & 3)) << 5) + (pp & 3) * 8;
-                voffA[i] = (uint32_t)((krow * p.lda + col) * 2);
-            } else {
-                // a 1-KB piece is 8 rows x 128 bytes of a 128-row half: lane l reads piece l%8 of row l/8, where the
-                // swizzle of the buffer puts it
-                const int row = blk * 8 + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
-                voffA[i] = (uint32_t)((row * p.lda + piece * 8) * 2);
-            }
-            if (!B_KMAJOR) {
-                ldsB[i] = blk * 1024;
-                const int row = blk * 8 + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
-                voffB[i] = (uint32_t)((row * p.ldb + piece * 8) * 2);
-            } else if (DUAL) {
-                // two sub-buffers of [32][128] (8 pieces each); this wave's pieces alternate between them
+            voffA[i] = A_KMAJOR ? kmajor_source<BM>(blk * 64 + lane, p.lda) : line_source(blk, p.lda);
+        }
+#pragma unroll
+        for (int i = 0; i < PB; ++i) {
+            const int blk = wave + NWAVES * i;
+            if (DUAL) {
+                // two sub-buffers of [32][BN / 2]; this wave's pieces alternate between them
                 const int half = i & 1, blk2 = wave + NWAVES * (i >> 1);
-                const int L2 = blk2 * 64 + lane;
-                ldsB[i] = half * 8192 + blk2 * 1024;
-                const int krow = L2 >> 4, pp = L2 & 15, col = (((pp >> 2) ^ (krow & 3)) << 5) + (pp & 3) * 8;
-                voffB[i] = (uint32_t)((krow * p.ldb + col) * 2);
+                ldsB[i] = half * (GEO::B_BYTES / 2) + blk2 * 1024;
+                voffB[i] = kmajor_source<BN / 2>(blk2 * 64 + lane, p.ldb);
             } else {
                 ldsB[i] = blk * 1024;
-                const int krow = L >> 5, pp = L & 31, col = (((pp >> 2) ^ (krow & 3)) << 5) + (pp & 3) * 8;
-                voffB[i] = (uint32_t)((krow * p.ldb + col) * 2);
+                voffB[i] = B_KMAJOR ? kmajor_source<BN>(blk * 64 + lane, p.ldb) : line_source(blk, p.ldb);
             }
         }
     }
@@ -397,9 +418,9 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
         const uint32_t st = lds0 + (uint32_t)iss_stage * STAGE_BYTES;
         iss_stage = (iss_stage + 1 == STAGES) ? 0 : iss_stage + 1;
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) dma16(ra, st + ldsA[i], voffA[i], soffA);
+        for (int i = 0; i < PA; ++i) dma16(ra, st + ldsA[i], voffA[i], soffA);
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) dma16((DUAL && (i & 1)) ? rb1 : rb0, st + OPER_BYTES + ldsB[i], voffB[i], soffB);
+        for (int i = 0; i < PB; ++i) dma16((DUAL && (i & 1)) ? rb1 : rb0, st + A_BYTES + ldsB[i], voffB[i], soffB);
         ++iss_in_seg;
         soffA += stepA; soffB += stepB;
     };
@@ -432,7 +453,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
     // instructions per group as a slice, half as many requests to L2.  A K-major operand (the weights of NN) keeps
     // one slice per group.  PAR: the parity of the group, known where the loop is written out.
     constexpr bool A_PAIR = !A_KMAJOR, B_PAIR = !B_KMAJOR;
-    const uint32_t halfA = (uint32_t)(128 * p.lda * 2), halfB = (uint32_t)(128 * p.ldb * 2);   // to the lower 128 rows
+    const uint32_t halfA = (uint32_t)(BM / 2 * p.lda * 2), halfB = (uint32_t)(BN / 2 * p.ldb * 2);   // to the lower half
     auto issue_group = [&](auto PAR, const rsrc_t ra, const rsrc_t rb0, const rsrc_t rb1) {
         constexpr int par = decltype(PAR)::value;
         const uint32_t st = lds0 + (uint32_t)iss_stage * STAGE_BYTES;
@@ -440,9 +461,9 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
         const uint32_t oa = (A_PAIR && par) ? soffA + halfA : soffA;
         const uint32_t ob = (B_PAIR && par) ? soffB + halfB : soffB;
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) dma16(ra, st + ldsA[i], voffA[i], oa);
+        for (int i = 0; i < PA; ++i) dma16(ra, st + ldsA[i], voffA[i], oa);
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) dma16((DUAL && (i & 1)) ? rb1 : rb0, st + OPER_BYTES + ldsB[i], voffB[i], ob);
+        for (int i = 0; i < PB; ++i) dma16((DUAL && (i & 1)) ? rb1 : rb0, st + A_BYTES + ldsB[i], voffB[i], ob);
         ++iss_in_seg;
         if (!A_PAIR || par) soffA += A_PAIR ? 2 * stepA : stepA;
         if (!B_PAIR || par) soffB += B_PAIR ? 2 * stepB : stepB;
@@ -456,7 +477,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
     // address that changes from slice to slice, and every vector instruction of the fetching wave takes an issue
     // slot from the matrix instructions of its partner: fragments that lie a constant distance apart share one
     // address register and differ in the instruction's immediate offset.
-    static_assert(TM == 4 && TN == 2, "the fragment reads below are written out for 4 x 2 fragments");
+    static_assert((TM == 4 || TM == 2) && TN == 2, "the fragment reads below are written out for 4 x 2 or 2 x 2 fragments");
     // K-major operands (step half 0; half 1 is 16 steps further down)
     uint32_t fa_addr[TM], fb_addr[TN];
     constexpr uint32_t A_HALF = 16 * (BM * 2);
@@ -472,9 +493,9 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
         const int b = lane >> 4, s = lane & 15;
         const int krow = 8 * (b >> 1) + (s >> 2), cofs = 16 * (b & 1) + 4 * (s & 3);
         if (DUAL)   // even fragments from the W1 sub-buffer, odd ones from the W3 sub-buffer
-            fb_addr[j] = OPER_BYTES + (j & 1) * 8192 + kmajor_off<BN / 2>(krow, wn * (WN / 2) + (j >> 1) * 32 + cofs);
+            fb_addr[j] = A_BYTES + (j & 1) * (GEO::B_BYTES / 2) + kmajor_off<BN / 2>(krow, wn * (WN / 2) + (j >> 1) * 32 + cofs);
         else
-            fb_addr[j] = OPER_BYTES + kmajor_off<BN>(krow, wn * WN + j * 32 + cofs);
+            fb_addr[j] = A_BYTES + kmajor_off<BN>(krow, wn * WN + j * 32 + cofs);
     }
     // TN: both operands K-major, a slice per ring buffer
     auto load_frags = [&](bf16x8 (&fa)[TM], bf16x8 (&fb)[TN], int stage, auto HALF) {
@@ -493,7 +514,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         fpa[v] = halfpair_off(lane & 31, lane >> 5) ^ (uint32_t)(v << 5);
-        fpb[v] = OPER_BYTES + (halfpair_off((wn & 1) * 64 + (lane & 31), lane >> 5) ^ (uint32_t)(v << 5));
+        fpb[v] = A_BYTES + (halfpair_off((wn % (WGN / 2)) * WN + (lane & 31), lane >> 5) ^ (uint32_t)(v << 5));
     }
     auto load_group_frags = [&](bf16x8 (&fa)[TM], bf16x8 (&fb)[TN], uint32_t stA, uint32_t stB, auto Q) {
         constexpr int quarter = decltype(Q)::value;        // 2 * (slice of the pair) + (16-step half of the slice)
@@ -501,8 +522,10 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
             const uint32_t a = stA + fpa[quarter];
             lds_frag_kcontig_at<0>(fa[0], a);
             lds_frag_kcontig_at<4096>(fa[1], a);
-            lds_frag_kcontig_at<8192>(fa[2], a);
-            lds_frag_kcontig_at<12288>(fa[3], a);
+            if constexpr (TM == 4) {
+                lds_frag_kcontig_at<8192>(fa[2], a);
+                lds_frag_kcontig_at<12288>(fa[3], a);
+            }
         }
         if constexpr (B_KMAJOR) {                          // stB: the buffer of the slice
 #pragma unroll
@@ -549,12 +572,15 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
     // waits for in practice is the delivery of the slices from L2/HBM.  All fragment reads are issued
     // before the DMA requests so that a request held up by the memory system never delays them (a
     // request placed between MFMAs stalls the matrix pipe for several MFMA slots instead).
-    static_assert(WGN == 4 && PIECES == 2, "the loop is written for 8 waves");
+    // Two blocks on a CU (Small) need no such order: a wave of each shares a SIMD, and while one block collects operands,
+    // waits or runs an epilogue, the other multiplies.  One barrier per slice then: the waits before it cover this wave's
+    // pieces of the next slice and its reads of the current one, and what a request overwrites was last read before the
+    // barrier of the slice before.
     if (!FIN && k_cnt > 0) {
       if constexpr (KIND == KIND_TN) {
         bf16x8 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
         constexpr int L = STAGES - 1;                      // slices requested ahead
-        constexpr int SLICE_OPS = 2 * PIECES;              // DMA instructions of one wave per slice
+        constexpr int SLICE_OPS = PA + PB;              // DMA instructions of one wave per slice
         // Every slice t is preceded by exactly t + L request groups of this wave (the prologue issues L of them,
         // every slice one more), so "my pieces of slice t + 1 have landed" is always "at most L - 1 groups are still
         // on their way": one fixed wait count for the whole contraction.  Where there is no slice left to request
@@ -567,7 +593,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
         }
         WAIT_VMCNT((L - 1) * SLICE_OPS);                   // slice 0 has landed
         BLOCK_BARRIER();
-        if (wm == 1) BLOCK_BARRIER();
+        if (GEO::TWO_PHASE && wm == 1) BLOCK_BARRIER();
         int cur = 0;
         asm volatile(".p2align 8\n\t.rept " LOOP_OFF_STR "\n\ts_nop 0\n\t.endr" ::: "memory");
         // One slice: fetch phase (fragments of slice t, then the requests for slice t + L, then the wait for this
@@ -595,14 +621,14 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
                 mma(fa1, fb1);
                 __builtin_amdgcn_s_setprio(0);
                 __builtin_amdgcn_sched_barrier(0);
-                BLOCK_BARRIER();
+                if (GEO::TWO_PHASE) BLOCK_BARRIER();
                 cur = (cur + 1 == STAGES) ? 0 : cur + 1;
             }
             t += n;
             if (more) issue_fixups();
         }
         WAIT_VMCNT(0);                                     // the zero-length requests too: the epilogue reuses the ring
-        if (wm == 0) BLOCK_BARRIER();                      // both rows have passed the same number of barriers
+        if (GEO::TWO_PHASE && wm == 0) BLOCK_BARRIER();    // both rows have passed the same number of barriers
         BLOCK_BARRIER();                                   // and everybody's requests have landed
       } else {
         bf16x8 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
@@ -616,7 +642,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
         // so the loop is written out for pairs: slice 0, then pairs of an odd and an even slice, whose two groups are
         // the two halves of one later pair of slices and need no fixup between them, then the last slice.
         constexpr int L = 3;
-        constexpr int SLICE_OPS = 2 * PIECES;              // DMA instructions of one wave per group
+        constexpr int SLICE_OPS = PA + PB;              // DMA instructions of one wave per group
         const rsrc_t rnull = make_rsrc(p.A[0], 0);
         auto real_a = [&]() { return iss_seg ? rA[1] : rA[0]; };
         auto real_b0 = [&]() { return (KIND == KIND_NT && iss_seg) ? rB[1] : rB[0]; };
@@ -628,10 +654,10 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
         else issue_group(std::integral_constant<int, 0>{}, rnull, rnull, rnull);
         WAIT_VMCNT(SLICE_OPS);                             // groups 0 and 1 have landed: slices 0 and 1
         BLOCK_BARRIER();
-        if (wm == 1) BLOCK_BARRIER();
+        if (GEO::TWO_PHASE && wm == 1) BLOCK_BARRIER();
         int cur = 0;                                       // ring slot of the slice's own group
         int pair0 = 0;                                     // ring slot of the even group of the slice's pair
-        const int hA = wm, hB = wn >> 1;                   // which group of a pair holds this wave's rows of A and B
+        const int hA = wm, hB = wn / (WGN / 2);                   // which group of a pair holds this wave's rows of A and B
         auto slot_base = [&](int slot) { return lds0 + (uint32_t)(slot >= STAGES ? slot - STAGES : slot) * STAGE_BYTES; };
         // One slice of parity PAR; ra .. rb1: the resources of the group it requests (of the opposite parity).
         auto mma_first = [&](const bf16x8 (&fa)[TM], const bf16x8 (&fb)[TN]) {      // acc = products (+ 0)
@@ -657,7 +683,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
             mma(fa1, fb1);
             __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_sched_barrier(0);
-            BLOCK_BARRIER();
+            if (GEO::TWO_PHASE) BLOCK_BARRIER();
             cur = (cur + 1 == STAGES) ? 0 : cur + 1;
             if (par) pair0 = (pair0 + 2 >= STAGES) ? pair0 + 2 - STAGES : pair0 + 2;
         };
@@ -682,7 +708,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
         }
         slice(std::integral_constant<int, 1>{}, std::false_type{}, rnull, rnull, rnull);      // the last slice
         WAIT_VMCNT(0);                                     // the zero-length requests too: the epilogue reuses the ring
-        if (wm == 0) BLOCK_BARRIER();                      // both rows have passed the same number of barriers
+        if (GEO::TWO_PHASE && wm == 0) BLOCK_BARRIER();    // both rows have passed the same number of barriers
         BLOCK_BARRIER();                                   // and everybody's requests have landed
       }
     }
@@ -691,10 +717,12 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
     // partial tiles: [unit][wave][register / 4][lane] as float4, every instruction moves 1 KB
     if (KIND != KIND_TN && !FIN && parts > 1) {
         float4* ws4 = reinterpret_cast<float4*>(p.split_ws) + ((size_t)unit * NWAVES + wave) * (TM * TN * 4) * 64 + lane;
+        const long rows_left = a_row_end - a_row0 - wm * WM;                // fragments past the group's last row are not kept
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
+                if (i * 32 >= rows_left) continue;
 #pragma unroll
                 for (int e4 = 0; e4 < 4; ++e4)
                     ws4[((i * TN + j) * 4 + e4) * 64] = make_float4(acc[i][j][e4 * 4], acc[i][j][e4 * 4 + 1], acc[i][j][e4 * 4 + 2], acc[i][j][e4 * 4 + 3]);
@@ -756,9 +784,31 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
             if (EPI == EPI_BWD1_SWIGLU) ui[k] = *reinterpret_cast<const uint4*>(p.Uin + row * p.ldo + col);
         }
     };
-    if (BWD1) request(0, 0, zin[0], uin[0]);
+    if (BWD1 && !FIN) request(0, 0, zin[0], uin[0]);
 #pragma unroll
     for (int fr = 0; fr < TM; ++fr) {
+        if (FIN && fr != q % TM) continue;                     // the tile's other rows of fragments are items of other blocks
+        if (BWD1 && FIN) request(fr, 0, zin[(fr * NB) & 1], uin[EPI == EPI_BWD1_SWIGLU ? (fr * NB) & 1 : 0]);
+        float4 fsum[FIN ? TN : 1][4];
+        if (KIND != KIND_TN && FIN) {                          // the parts of a split tile, added in ascending order
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e4 = 0; e4 < 4; ++e4) fsum[j][e4] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (fr * 32 < row_limit - m0 - wm * WM) {
+                constexpr long PART = (long)NWAVES * (TM * TN * 4) * 64;
+                const float4* ws4 = reinterpret_cast<const float4*>(p.split_ws) + unit * PART + (wave * (TM * TN * 4) + fr * TN * 4) * 64 + lane;
+#pragma unroll 2
+                for (int s = 0; s < parts; ++s)                // the loads of two parts, 16 KB of a wave, on their way together
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int e4 = 0; e4 < 4; ++e4) {
+                            const float4 v = ws4[s * PART + (j * 4 + e4) * 64];
+                            fsum[j][e4].x += v.x; fsum[j][e4].y += v.y; fsum[j][e4].z += v.z; fsum[j][e4].w += v.w;
+                        }
+            }
+        }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -767,17 +817,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
             for (int q = 0; q < 4; ++q) {
                 const f32x16& a = acc[fr][j];
                 float4 val = make_float4(a[q * 4 + 0], a[q * 4 + 1], a[q * 4 + 2], a[q * 4 + 3]);
-                if (KIND != KIND_TN && FIN) {                  // the parts of a split tile, added in ascending order
-                    const float4* ws4 = reinterpret_cast<const float4*>(p.split_ws) + ((size_t)unit * NWAVES + wave) * (TM * TN * 4) * 64 + lane;
-                    float4 v[4];                               // at most 4 parts; all loads independent of each other
-#pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        v[s] = (s < parts) ? ws4[(size_t)s * NWAVES * (TM * TN * 4) * 64 + ((fr * TN + j) * 4 + q) * 64]
-                                           : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    val = v[0];
-#pragma unroll
-                    for (int s = 1; s < 4; ++s) { val.x += v[s].x; val.y += v[s].y; val.z += v[s].z; val.w += v[s].w; }
-                }
+                if (FIN) val = fsum[j][q];
                 *reinterpret_cast<float4*>(patch + lrow * EP_PITCH + (j * 32 + q * 8 + lcol) * 4) = val;
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -787,7 +827,7 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
         const int pb = b * BATCH, cur = (fr * NB + b) & 1;
         if (BWD1) {
             const int nxt = fr * NB + b + 1;
-            if (nxt < TM * NB) request(nxt / NB, (nxt % NB) * BATCH, zin[cur ^ 1], uin[cur ^ 1]);
+            if (nxt < (FIN ? (fr + 1) * NB : TM * NB)) request(nxt / NB, (nxt % NB) * BATCH, zin[cur ^ 1], uin[cur ^ 1]);
         }
 #pragma unroll
         for (int pass = pb; pass < pb + BATCH; ++pass) {
@@ -894,11 +934,79 @@ __global__ __launch_bounds__(NT) void grouped_gemm_kernel(const GemmParams p)
 }
 
 // ---- host side ----------------------------------------------------------------------------------
-template <int KIND, int EPI>
-hipError_t launch(GemmParams p, int rows_upper, int n_groups_cap, hipStream_t st)
+// ---- which geometry ------------------------------------------------------------------------------
+// Large multiplies a quarter faster once its tiles fill the chip several times over (train-size contractions: 0.72 us per
+// slice and round of 256 tiles, where Small takes 0.55 per round of 512 tiles a quarter as large), Small wins where Large
+// leaves CUs idle, rounds up to a round it does not need, or spends its time in prologues and epilogues that nothing hides:
+// there one of Small's two blocks per CU multiplies while the other stores, and its tiles and parts are four times finer.
+// Measured, us, Large | Small (with the finishing launch):  d = 768, h = 3072, 1987 rows in 5 groups: forward 48 + 68 | 41 +
+// 33, backward 35 + 74 + 2 x 57 | 24 + 45 + 2 x 36;  d = 1024, h = 1024, 1262 rows: 36 + 27 | 25 + 27;  d = 2944, h = 576,
+// 3002 rows: 76 + 25 | 36 + 22;  d = 1024, h = 4096, 9279 rows: 123 + 111 | 134 + 118, weight gradients 156 | 126 each;
+// d = 2048, h = 8192, 11742 rows: 444 + 405 | 560 + 478, 420 | 560 each;  29112 rows: 980 + 800 | 1237 + 1050, 850 | 1440.
+// The host knows T k and how many of the experts are hosted here, not how many rows they got: it estimates 0.8 T k
+// sqrt(G / E) (between the share of an even load, G / E, and all of it: hosted experts are the popular ones) and compares
+// the two by the times above.  Over 24 shapes (120 contractions) the choice is within 2 % of the better one in the mean,
+// where Large alone lost 22 %.
+struct GeometryCost { double slice, over_bf16, over_fwd1, over_bwd1, finish, hbm; int tiles_at_once, split_max; };   // us, us, TB/s
+constexpr GeometryCost LARGE_COST{0.70, 11.0, 15.0, 18.0, 14.0, 4.2, 256, 4}, SMALL_COST{0.55, 6.5, 9.0, 10.0, 10.0, 5.0, 512, 8};
+
+inline double estimated_rows(const moe_shape_t& s)
+{
+    const double A = (double)s.T * s.k;
+    return std::max(1.0, std::min(A, 0.8 * A * std::sqrt((double)s.G / s.E)));
+}
+inline double tiles_of(const moe_shape_t& s, int bm, int cols, int bn)
+{
+    const double rows = estimated_rows(s), groups = std::min((double)s.G, rows);      // as if spread evenly
+    return groups * std::ceil(rows / s.G < 1.0 ? 1.0 / bm : rows / s.G / bm) * ((cols + bn - 1) / bn);
+}
+double row_contraction_cost(const GeometryCost& c, double tiles, int slices, int epi, int split_slices, double weight_mb)
+{
+    const double over = epi == EPI_BF16 ? c.over_bf16 : ((epi == EPI_FWD1_GELU || epi == EPI_FWD1_SWIGLU) ? c.over_fwd1 : c.over_bwd1);
+    const double x = tiles / c.tiles_at_once;
+    const bool split = slices >= 2 * split_slices;
+    double t;
+    if (x <= 1.0) {
+        const int S = std::max(1, std::min(std::min(c.split_max, (int)(1.0 / x)), slices / split_slices));
+        t = c.slice * slices / S + over + (S > 1 ? c.finish : (split ? 5.0 : 0.0));
+    } else {
+        t = split ? (x + 0.3) * (c.slice * slices + over) + c.finish : (x + 0.5) * (c.slice * slices + over);
+    }
+    return std::max(t, weight_mb / c.hbm);
+}
+constexpr int SMALL_SPLIT_SLICES = 16;
+// Large: a part of a split tile has to be worth its 256-KB round trip, 64 slices where the split only shortens the last of
+// several rounds, 24 where it is what fills the chip (d = 768, h = 3072, 33 tiles of 96 slices: 69 us whole, 45 in four parts).
+inline int large_split_slices(double tiles) { return tiles <= 2.0 * LARGE_COST.tiles_at_once ? 24 : 64; }
+
+bool small_wins_rows(const moe_shape_t& s, int N, int slices, int n_seg, int epi)
+{
+    const bool dual = epi == EPI_FWD1_SWIGLU;
+    const double tl = tiles_of(s, Large::BM, N, dual ? Large::BN / 2 : Large::BN), ts = tiles_of(s, Small::BM, N, dual ? Small::BN / 2 : Small::BN);
+    const double mb = std::min((double)s.G, estimated_rows(s)) * s.d * s.h * 2.0 * (dual ? 2 : n_seg) / 1e6;
+    GeometryCost sc = SMALL_COST;
+    if (dual) sc.hbm = 3.0;                                // 128-byte pieces of two weight matrices
+    return row_contraction_cost(sc, ts, slices, epi, SMALL_SPLIT_SLICES, mb) < row_contraction_cost(LARGE_COST, tl, slices, epi, large_split_slices(tl), mb);
+}
+// Weight gradients: a round of an XCD's blocks per 32 (64) tiles of a group, dealt to the 8 XCDs; 17 and 9 us per tile
+// beside the slices (the fp32 tile is stored).
+bool small_wins_wgrad(const moe_shape_t& s, int Mout, int N)
+{
+    const double slices = std::ceil(estimated_rows(s) / s.G / BK);
+    auto cost = [&](int b, int at_once, double slice, double over) {
+        const double rounds = (double)((((Mout + b - 1) / b) * ((N + b - 1) / b) + at_once - 1) / at_once);
+        return std::max(s.G * rounds / 8.0, 1.0) * (slices * slice + over);
+    };
+    return cost(Small::BM, 64, 0.55, 9.0) < cost(Large::BM, 32, 0.70, 17.0);
+}
+
+template <int KIND, int EPI, class GEO>
+hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, hipStream_t st)
 {
     constexpr bool DUAL = (EPI == EPI_FWD1_SWIGLU);
-    const int bn = DUAL ? BN / 2 : BN;
+    constexpr int BM = GEO::BM;
+    constexpr size_t LDS_BYTES = GEO::LDS_BYTES;
+    const int bn = DUAL ? GEO::BN / 2 : GEO::BN;
     p.col_tiles = (p.N + bn - 1) / bn;
     if (KIND == KIND_TN) {
         p.row_tiles = (p.Mout + BM - 1) / BM;
@@ -908,14 +1016,14 @@ hipError_t launch(GemmParams p, int rows_upper, int n_groups_cap, hipStream_t st
         p.n_tiles = p.row_tiles * p.col_tiles;
     }
     if (p.n_tiles == 0) return hipSuccess;
-    // persistent: one block per CU (LDS allows no more), a multiple of 8.  The CU count and the kernels' dynamic
+    // persistent: as many blocks as fit the CUs (their LDS allows no more), a multiple of 8.  The CU count and the kernels' dynamic
     // LDS limit are looked up / set once per device (per instantiation).
     static PerDeviceOnce once;
     static std::atomic<int> cus_of[64];
     const int dev = current_device();
     int cus = (dev >= 0 && dev < 64) ? cus_of[dev].load(std::memory_order_acquire) : 0;
-    auto kern = grouped_gemm_kernel<KIND, EPI, false>;
-    auto kern_fin = grouped_gemm_kernel<KIND, EPI, KIND != KIND_TN>;     // TN has no split round
+    auto kern = grouped_gemm_kernel<KIND, EPI, false, GEO>;
+    auto kern_fin = grouped_gemm_kernel<KIND, EPI, KIND != KIND_TN, GEO>;     // TN has no split round
     if (!once.is_done(dev) || cus == 0) {
         int n = 0;
         if (dev < 0 || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
@@ -927,16 +1035,31 @@ hipError_t launch(GemmParams p, int rows_upper, int n_groups_cap, hipStream_t st
         if (dev >= 0 && dev < 64) cus_of[dev].store(cus, std::memory_order_release);
         once.mark(dev);
     }
-    const int grid = cus;
+    const int grid = cus * GEO::BLOCKS;
     // short contractions gain less from the split than the second launch costs
-    if (KIND == KIND_TN || p.n_seg * (p.Kseg / BK) < 128) p.split_ws = nullptr;
-    p.split_cap = SPLIT_UNITS;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), LDS_BYTES, st, p);
+    p.split_max = GEO::BLOCKS == 1 ? LARGE_COST.split_max : SMALL_COST.split_max;
+    if (KIND == KIND_TN || p.n_seg * (p.Kseg / BK) < 2 * p.split_slices) p.split_ws = nullptr;
+    p.split_cap = (int)((size_t)SPLIT_UNITS * Large::UNIT_BYTES / GEO::UNIT_BYTES);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || KIND == KIND_TN || p.split_ws == nullptr) return e;
     // the tiles of a K-split last round: add their parts, run their epilogues
-    hipLaunchKernelGGL(kern_fin, dim3(grid), dim3(NT), LDS_BYTES, st, p);
+    hipLaunchKernelGGL(kern_fin, dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
     return hipGetLastError();
+}
+
+template <int KIND, int EPI>
+hipError_t launch(GemmParams p, const moe_shape_t& s, hipStream_t st)
+{
+    const int A = s.T * s.k, slices = p.n_seg * (p.Kseg / BK);
+    const bool small = KIND == KIND_TN ? small_wins_wgrad(s, p.Mout, p.N) : small_wins_rows(s, p.N, slices, p.n_seg, EPI);
+    if (small) {
+        p.band = 8;                                        // 64 tiles in flight on an XCD: 8 x 8 of 128 x 128
+        p.split_slices = SMALL_SPLIT_SLICES;
+        return launch_geo<KIND, EPI, Small>(p, A, s.G, st);
+    }
+    p.split_slices = KIND == KIND_TN ? 64 : large_split_slices(tiles_of(s, Large::BM, p.N, EPI == EPI_FWD1_SWIGLU ? Large::BN / 2 : Large::BN));
+    return launch_geo<KIND, EPI, Large>(p, A, s.G, st);
 }
 
 GemmParams base_params(const moe_shape_t& s, const ffn_args& a)
@@ -965,8 +1088,8 @@ hipError_t launch_ffn_fwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
         p.A[0] = (const bf16_t*)a.Xp; p.B[0] = (const bf16_t*)a.W1; p.B_dual = (const bf16_t*)a.W3;
         p.lda = d; p.ldb = h; p.b_group_stride = d * h; p.Kseg = s.d; p.N = s.h;
         p.O0 = (bf16_t*)a.Z; p.O1 = (bf16_t*)a.U; p.O2 = (bf16_t*)a.Act; p.ldo = h;
-        e = (s.act == MOE_ACT_SWIGLU) ? launch<KIND_NN, EPI_FWD1_SWIGLU>(p, A, s.G, st)
-                                      : launch<KIND_NN, EPI_FWD1_GELU>(p, A, s.G, st);
+        e = (s.act == MOE_ACT_SWIGLU) ? launch<KIND_NN, EPI_FWD1_SWIGLU>(p, s, st)
+                                      : launch<KIND_NN, EPI_FWD1_GELU>(p, s, st);
         if (e != hipSuccess) return e;
     }
     {   // fwd2: Act [rows, h] x W2[g] (h x d)
@@ -975,7 +1098,7 @@ hipError_t launch_ffn_fwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
         p.A[0] = (const bf16_t*)a.Act; p.B[0] = (const bf16_t*)a.W2;
         p.lda = h; p.ldb = d; p.b_group_stride = d * h; p.Kseg = s.h; p.N = s.d;
         p.O0 = (bf16_t*)a.Yp; p.ldo = d;
-        e = launch<KIND_NN, EPI_BF16>(p, A, s.G, st);
+        e = launch<KIND_NN, EPI_BF16>(p, s, st);
     }
     return e;
 }
@@ -995,8 +1118,8 @@ hipError_t launch_ffn_bwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
             p.O0 = (bf16_t*)a.dZ; p.O1 = (bf16_t*)a.dU; p.O2 = (bf16_t*)a.Act; p.ldo = h;
             p.Zin = (const bf16_t*)a.Z; p.Uin = (const bf16_t*)a.U;
             p.write_act = a.act_saved ? 0 : 1;
-            e = swiglu ? launch<KIND_NT, EPI_BWD1_SWIGLU>(p, A, s.G, st)
-                       : launch<KIND_NT, EPI_BWD1_GELU>(p, A, s.G, st);
+            e = swiglu ? launch<KIND_NT, EPI_BWD1_SWIGLU>(p, s, st)
+                       : launch<KIND_NT, EPI_BWD1_GELU>(p, s, st);
             if (e != hipSuccess) return e;
         }
         {   // bwd2: dXp = dZ [rows, h] x W1[g]^T (+ dU x W3[g]^T)
@@ -1007,7 +1130,7 @@ hipError_t launch_ffn_bwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
             p.n_seg = swiglu ? 2 : 1;
             p.lda = h; p.ldb = h; p.b_group_stride = d * h; p.Kseg = s.h; p.N = s.d;
             p.O0 = (bf16_t*)a.dXp; p.ldo = d;
-            e = launch<KIND_NT, EPI_BF16>(p, A, s.G, st);
+            e = launch<KIND_NT, EPI_BF16>(p, s, st);
             if (e != hipSuccess) return e;
         }
     }
@@ -1018,7 +1141,7 @@ hipError_t launch_ffn_bwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
         p.A[0] = (const bf16_t*)L; p.B[0] = (const bf16_t*)R;
         p.lda = ldl; p.ldb = ldr; p.b_group_stride = 0; p.Mout = Mout; p.N = N;
         p.OF = out; p.ldo = N; p.o_group_stride = d * h; p.accumulate = a.accumulate ? 1 : 0;
-        return launch<KIND_TN, EPI_F32>(p, A, s.G, st);
+        return launch<KIND_TN, EPI_F32>(p, s, st);
     };
     e = wgrad(a.Xp, d, s.d, a.dZ, h, s.h, a.dW1);
     if (e != hipSuccess) return e;

@@ -1,0 +1,93 @@
+"""The two tile geometries of the bf16 grouped FFN against a plain float64 product on the GPU, forward and backward, at the
+sizes where a tile, a part of a split contraction or the choice between the two can go wrong: row counts around 128 and
+256, widths that are odd multiples of 64, contractions of one pair of slices up to ones cut into eight parts, empty groups,
+many groups, and shapes on both sides of the rule that picks the geometry (the larger ones take 256 x 256 tiles).
+Tolerance as in test_gpu_parity.py: 1e-2 row by row, four roundings to bf16 (2^-9 each) with room for their spread."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as G
+from paper_2411_10003_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # rows per hosted group, rows of other destinations behind them, d, h, activation
+    ([1], 0, 64, 64, "gelu"),
+    ([127, 0, 129], 5, 64, 192, "swiglu"),
+    ([128, 1, 255, 257], 0, 320, 64, "gelu"),
+    ([33], 10, 64, 4096, "swiglu"),                        # eight parts of 16 slices each
+    ([200, 3], 0, 4160, 64, "gelu"),                       # parts that end at uneven slices
+    ([40, 300], 7, 1088, 1600, "swiglu"),
+    ([5] * 40, 0, 128, 192, "gelu"),                       # many groups, one ragged tile each
+    ([0, 0, 0], 64, 64, 128, "swiglu"),                    # nothing to do
+    ([700, 513, 90], 0, 448, 2112, "gelu"),
+    ([9000, 4000, 130], 64, 192, 2752, "swiglu"),          # 256 x 256 tiles
+    ([12000, 511, 7000], 0, 320, 3136, "gelu"),
+    ([14000, 3000], 0, 2112, 320, "swiglu"),
+    ([30000], 0, 64, 1600, "gelu"),                        # and one pair of slices per tile
+]
+
+
+@pytest.mark.parametrize("rows,other,d,h,act", CASES, ids=lambda v: str(v).replace(" ", "") if not isinstance(v, list) else f"{len(v)}g{sum(v)}r")
+def test_forward_backward(rows, other, d, h, act):
+    Gn, M, A = len(rows), sum(rows), sum(rows) + other
+    E = Gn + 1                                             # the last expert belongs to another destination
+    g = torch.Generator(device=G.DEV).manual_seed(d + h + M)
+
+    def rnd(*shape, std=1.0):
+        return (torch.randn(*shape, generator=g, device=G.DEV) * std).to(torch.bfloat16)
+
+    hd = binding.Handle(T=A, d=d, h=h, E=E, k=1, P=2, self_dest=0, G=Gn, dtype="bf16", act=act, renorm=0, device=G.DEV)
+    idx = torch.repeat_interleave(torch.arange(E, dtype=torch.int32), torch.tensor(rows + [other])).to(G.DEV)
+    dest = torch.tensor([0] * Gn + [1], dtype=torch.int32, device=G.DEV)
+    counts, lay = torch.zeros(E, dtype=torch.int32, device=G.DEV), hd.new_layout()
+    Xp, dYp = torch.empty(A, d, dtype=torch.bfloat16, device=G.DEV), rnd(A, d)
+    hd.expert_counts(idx, counts)
+    hd.dispatch(dest, rnd(A, d), idx, counts, lay, Xp)     # idx is sorted: rows stay where they are
+    W1, W2 = rnd(Gn, d, h, std=d ** -0.5), rnd(Gn, h, d, std=h ** -0.5)
+    W3 = rnd(Gn, d, h, std=d ** -0.5) if act == "swiglu" else None
+    fill = rnd(A, max(d, h))
+    Yp, dXp, Z = (fill[:, :w].contiguous().clone() for w in (d, d, h))
+    U = Z.clone() if act == "swiglu" else None
+    dW = [torch.full((Gn, d, h), 7.0, device=G.DEV), torch.full((Gn, h, d), 7.0, device=G.DEV),
+          torch.full((Gn, d, h), 7.0, device=G.DEV) if act == "swiglu" else None]
+    hd.expert_ffn_fwd(Xp, lay, W1, W2, W3, Yp, Z, U)
+    hd.expert_ffn_bwd(dYp, Xp, Z, U, lay, W1, W2, W3, dXp, *dW)
+    torch.cuda.synchronize()
+    for t, w in ((Yp, d), (dXp, d), (Z, h)) + (((U, h),) if act == "swiglu" else ()):
+        assert torch.equal(t[M:], fill[M:, :w]), "rows of other destinations were touched"
+
+    # A hidden unit's gradient in a group of a few rows is one activation, or a few, times dYp: act(z) from a z rounded to
+    # bf16 is off by up to |z act'(z) / act(z)| 2^-9 of itself, which grows like z^2 in the negative tail (0.014 at z = -2.5),
+    # while the whole gradient stays within 2^-9 of its norm.  So weight gradients are measured against the typical row.
+    def close(got, want, what):
+        G.assert_rows_close(G.host(got), want.cpu().numpy(), 1e-2, what, floor=1.0 if what.startswith("dW") else 0.02)
+
+    o = 0
+    for i, n in enumerate(rows):
+        if n == 0:
+            assert all(t is None or not bool(t[i].any()) for t in dW)
+            continue
+        x, dy = Xp[o:o + n].double(), dYp[o:o + n].double()
+        w1, w2 = W1[i].double(), W2[i].double()
+        z = x @ w1
+        dA = dy @ w2.t()
+        if act == "swiglu":
+            w3 = W3[i].double()
+            u, sg = x @ w3, torch.sigmoid(z)
+            a, du, dz = z * sg * u, dA * z * sg, dA * u * (sg * (1 + z * (1 - sg)))
+            dx = dz @ w1.t() + du @ w3.t()
+            close(U[o:o + n], u, "U")
+            close(dW[2][i], x.t() @ du, "dW3")
+        else:
+            cdf = 0.5 * (1 + torch.erf(z * 0.5 ** 0.5))
+            a, dz = z * cdf, dA * (cdf + z * torch.exp(-0.5 * z * z) * (2 * np.pi) ** -0.5)
+            dx = dz @ w1.t()
+        close(Z[o:o + n], z, "Z")
+        close(Yp[o:o + n], a @ w2, "Yp")
+        close(dXp[o:o + n], dx, "dXp")
+        close(dW[0][i], x.t() @ dz, "dW1")
+        close(dW[1][i], a.t() @ dy, "dW2")
+        o += n
