@@ -280,14 +280,19 @@ __global__ __launch_bounds__(GATE_THREADS) void gate_mfma_kernel(
     }
 }
 
-// ---- bf16 tokens, d % 64 == 0, every staged expert exists: the same contraction with both operands delivered by
-// buffer loads that write LDS directly, so that nothing asynchronous ever targets a register and the waits can be
-// written by hand (the compiler's own counts allow a third of the requests that may be outstanding).
-// Per wave a ring of NXP token chunks (its 16 tokens x 64 columns, 2 KB: lane l's two 16-byte pieces at l * 16);
-// per block a ring of NXP + 1 gate-matrix chunks (64 columns x 16 NT experts), every wave fetching a quarter.
-// A gate-matrix piece (4 consecutive experts of one column) lands where the instruction that uses it finds the 64
-// values of its lanes side by side: piece (block s, j, tile, q, i / 4) at 16 * ((((8 s + j) NT + tile) 4 + q) 4 + i / 4),
-// so the A operand of instruction (s, j, tile) is one `ds_read_b32` at lane * 4 plus a constant.
+// ---- bf16 tokens (d % 64 == 0), E % 4 == 0: the same contraction with both operands delivered by buffer loads that write
+// LDS directly, so that nothing asynchronous ever targets a register and the waits can be written by hand (the compiler's
+// own counts allow a third of the requests that may be outstanding).
+// A tile of 16 tokens belongs to two waves, one per partial sum: wave s visits the 32-column blocks s, s + 2, s + 4, ..
+// in order, which is the order the interface fixes, and the two sums meet in LDS at the end.  That halves the serial chain
+// of a tile (512 matrix instructions of 32 cycles at d = 4096, E = 16) and gives a CU twice the waves.  A step is two of a
+// wave's blocks (128 columns of the rows).
+// Per wave a ring of NXP steps of its tokens (2 KB each: lane l's two 16-byte pieces at 16 l and 1024 + 16 l); per partial
+// sum a ring of NXP + 1 steps of the gate matrix (64 columns x 16 NT experts), fetched in equal shares by the waves that
+// use it.  A gate-matrix piece (4 consecutive experts of one column) lands where the instruction that uses it finds the 64
+// values of its lanes side by side: piece (block of the step, j, tile, q, i / 4) at 16 * ((((8 b + j) NT + tile) 4 + q) 4 +
+// i / 4), so the A operand of instruction (b, j, tile) is one `ds_read_b32` at lane * 4 plus a constant.  Experts past the
+// last one multiply whatever lies there (the next column's, or zeros past the matrix) into rows that are not stored.
 typedef __attribute__((ext_vector_type(4))) int gate_rsrc_t;
 #define GATE_LDS_PTR(T) __attribute__((address_space(3))) T*
 
@@ -308,124 +313,127 @@ __device__ __forceinline__ void gate_dma16(gate_rsrc_t r, uint32_t lds_base, uin
                  :: "s"(lds_base), "v"(voff), "s"(r), "s"(soff) : "memory");
 }
 
-constexpr int GATE_NXP = 5;                                // token chunks requested ahead
-constexpr int GATE_NW = GATE_NXP + 1;                      // gate-matrix chunks in the ring
-constexpr int GATE_XSLOT = 2048;                           // bytes of one wave's token chunk
-constexpr int GATE_XRING = GATE_WAVES * GATE_NXP * GATE_XSLOT;
+template <int NT, int TILES, int NXP> constexpr int gate_split_lds()
+{
+    return 2 * TILES * NXP * 2048 + 2 * (NXP + 1) * 4096 * NT;
+}
 
-template <int NT, bool ROUTE>
-__global__ __launch_bounds__(GATE_THREADS) void gate_mfma_dma_kernel(
+// TILES: token tiles of a block (2 TILES waves).  blockIdx.y: pass of 16 NT experts.  ROUTE: one pass, routing fused.
+template <int NT, int TILES, int NXP, bool ROUTE>
+__global__ __launch_bounds__(TILES * 128) void gate_split_kernel(
     const bf16_t* __restrict__ X, const float* __restrict__ Wg, const float* __restrict__ bg,
     float* __restrict__ logits, int32_t* __restrict__ idx, float* __restrict__ wout,
-    int T, int d, int E, int k, int renorm, int e_pitch)
+    int T, int d, int E, int k, int renorm)
 {
-    constexpr int NXP = GATE_NXP, NW = GATE_NW, XSLOT = GATE_XSLOT, XRING = GATE_XRING;
-    constexpr int WCH = 4096 * NT;                         // bytes of one gate-matrix chunk
-    constexpr int LPS = 2 + NT;                            // requests of one wave per chunk
-    extern __shared__ __attribute__((aligned(1024))) unsigned char gsm[];   // token rings | gate-matrix ring | logits
+    constexpr int NW = NXP + 1, XSTEP = 2048, WSTEP = 4096 * NT, XRING = 2 * TILES * NXP * XSTEP;
+    constexpr int WOPS = 4 * NT / TILES, OPS = 2 + WOPS;   // requests of one wave per step
+    static_assert(4 * NT % TILES == 0, "equal shares of the gate matrix");
+    constexpr int PITCH = 16 * NT + 1;                     // logits of a token in LDS
+    static_assert(TILES * 16 * PITCH * 4 + TILES * NT * 1024 <= gate_split_lds<NT, TILES, NXP>(), "logits and sums fit the rings");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char gsm[];   // token rings | gate-matrix rings; then sums | logits
     const uint32_t lds0 = (uint32_t)(uintptr_t)(GATE_LDS_PTR(unsigned char))gsm;
-    float* logit_lds = reinterpret_cast<float*>(gsm + XRING + NW * WCH);
-
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int s = wave & 1, tile = wave >> 1;              // partial sum, token tile
     const int q = lane >> 4, i16 = lane & 15;
-    const int blk_tok0 = blockIdx.x * GATE_TOK;
-    const int tok0w = blk_tok0 + wave * 16;
-    const int tok = tok0w + i16;
-    const int npairs = d / 64;
+    const int blk_tok0 = blockIdx.x * (16 * TILES), tok0w = blk_tok0 + tile * 16, tok = tok0w + i16;
+    const int ec0 = blockIdx.y * (16 * NT);
+    const int nb = d / 64, steps = (nb + 1) / 2;           // 32-column blocks of each partial sum
 
-    // tokens: rows of this block onwards; a token past the end reads the last one (never stored); a chunk past the
+    // tokens: rows of this block onwards; a token past the end reads the last one (never stored); a block past the
     // end of a row reads into the next rows or, after the last row, zeros: never multiplied
     const gate_rsrc_t rX = gate_make_rsrc(X + (size_t)blk_tok0 * d, (unsigned long long)(T - blk_tok0) * d * 2);
     const int rowrel = (tok < T ? tok : T - 1) - blk_tok0;
-    const uint32_t xv0 = (uint32_t)((rowrel * d + 8 * q) * 2), xv1 = xv0 + 64;
-    const uint32_t xl_w = lds0 + (uint32_t)(wave * NXP * XSLOT);
-    // gate matrix: this wave's NT requests of a chunk
-    uint32_t wv[NT];
+    const uint32_t xv = (uint32_t)((rowrel * d + 32 * s + 8 * q) * 2);
+    const uint32_t xl = lds0 + (uint32_t)(wave * NXP * XSTEP);
+    // gate matrix: this wave's share of a step
+    const gate_rsrc_t rW = gate_make_rsrc(Wg + ec0, ((unsigned long long)d * E - ec0) * 4);     // past the last column: zeros
+    uint32_t wv[WOPS];
 #pragma unroll
-    for (int n = 0; n < NT; ++n) {
-        const int L = (wave * NT + n) * 64 + lane;         // 16-byte slot of the chunk
-        const int e4l = L & 3, qq = (L >> 2) & 3, tl = (L >> 4) % NT, sj = L / (16 * NT);
-        const int c_local = 32 * (sj >> 3) + 8 * qq + (sj & 7);
-        wv[n] = (uint32_t)((c_local * E + 16 * tl + 4 * e4l) * 4);
+    for (int n = 0; n < WOPS; ++n) {
+        const int L = (tile * WOPS + n) * 64 + lane;       // 16-byte slot of the step
+        const int e4 = L & 3, qq = (L >> 2) & 3, tl = (L >> 4) % NT, bj = L / (16 * NT);
+        wv[n] = (uint32_t)(((64 * (bj >> 3) + 32 * s + 8 * qq + (bj & 7)) * E + 16 * tl + 4 * e4) * 4);
     }
-    const uint32_t wl_w = lds0 + (uint32_t)(XRING + wave * NT * 1024);
-
-    for (int ec0 = 0; ec0 < E; ec0 += 16 * NT) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // the stores of the previous pass do not count below
-        // columns at or past d are at or past the limit: zeros
-        const gate_rsrc_t rW = gate_make_rsrc(Wg + ec0, ((unsigned long long)d * E - ec0) * 4);
-        auto issue = [&](int P, int xslot, int wstage) {
-            gate_dma16(rX, xl_w + (uint32_t)(xslot * XSLOT), xv0, (uint32_t)P * 128u);
-            gate_dma16(rX, xl_w + (uint32_t)(xslot * XSLOT + 1024), xv1, (uint32_t)P * 128u);
+    const uint32_t wl = lds0 + (uint32_t)(XRING + s * NW * WSTEP + tile * WOPS * 1024);
+    auto issue = [&](int P, int xslot, int wslot) {
+        gate_dma16(rX, xl + (uint32_t)(xslot * XSTEP), xv, (uint32_t)P * 256u);
+        gate_dma16(rX, xl + (uint32_t)(xslot * XSTEP + 1024), xv + 128u, (uint32_t)P * 256u);
 #pragma unroll
-            for (int n = 0; n < NT; ++n)
-                gate_dma16(rW, wl_w + (uint32_t)(wstage * WCH + n * 1024), wv[n], (uint32_t)P * (uint32_t)(64 * E * 4));
-        };
-        gate_f4 acc[2][NT];
+        for (int n = 0; n < WOPS; ++n)
+            gate_dma16(rW, wl + (uint32_t)(wslot * WSTEP + n * 1024), wv[n], (uint32_t)P * (uint32_t)(128 * E * 4));
+    };
+    gate_f4 acc[NT];
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+    for (int tl = 0; tl < NT; ++tl) acc[tl] = gate_f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int tl = 0; tl < NT; ++tl) acc[s][tl] = gate_f4{0.0f, 0.0f, 0.0f, 0.0f};
-
+    for (int P = 0; P < NXP; ++P) issue(P, P, P);
+    int xslot = 0, wslot = 0;
+    for (int P = 0; P < steps; ++P) {
+        // this wave's requests for step P have landed (NXP - 1 younger steps may be pending); after the barrier so have
+        // everybody's shares of the gate matrix, and everybody is done with step P - 1
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NXP - 1) * OPS) : "memory");
+        asm volatile("s_barrier" ::: "memory");
+        const unsigned char* xs = gsm + (wave * NXP + xslot) * XSTEP + lane * 16;
+        const float* ws = reinterpret_cast<const float*>(gsm + XRING + (s * NW + wslot) * WSTEP) + lane;
+        auto block = [&](auto B) {
+            constexpr int b = decltype(B)::value;
+            const gate_u4 x = *reinterpret_cast<const gate_u4*>(xs + b * 1024);
+            float wf[8][NT];
 #pragma unroll
-        for (int P = 0; P < NXP; ++P) issue(P, P, P);
-        int xslot = 0, wstage = 0;
-        for (int p = 0; p < npairs; ++p) {
-            // this wave's requests for chunk p have landed (NXP - 1 younger groups may be pending); after the barrier
-            // so have everybody's quarters of the gate-matrix chunk, and everybody is done with chunk p - 1
-            asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NXP - 1) * LPS) : "memory");
-            asm volatile("s_barrier" ::: "memory");
-            const unsigned char* xs = gsm + (wave * NXP + xslot) * XSLOT + lane * 16;
-            const gate_u4 x0 = *reinterpret_cast<const gate_u4*>(xs);
-            const gate_u4 x1 = *reinterpret_cast<const gate_u4*>(xs + 1024);
-            const float* wsb = reinterpret_cast<const float*>(gsm + XRING + wstage * WCH) + lane;
-            float wf[2][8][NT];
+            for (int j = 0; j < 8; ++j)
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-#pragma unroll
-                    for (int tl = 0; tl < NT; ++tl) wf[s][j][tl] = wsb[((s * 8 + j) * NT + tl) * 64];
+                for (int tl = 0; tl < NT; ++tl) wf[j][tl] = ws[((b * 8 + j) * NT + tl) * 64];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const uint32_t w0 = x0[j / 2], w1 = x1[j / 2];
-                const float a0 = __uint_as_float((j & 1) ? (w0 & 0xffff0000u) : (w0 << 16));
-                const float a1 = __uint_as_float((j & 1) ? (w1 & 0xffff0000u) : (w1 << 16));
+                const uint32_t w = x[j / 2];
+                const float a = __uint_as_float((j & 1) ? (w & 0xffff0000u) : (w << 16));
 #pragma unroll
-                for (int tl = 0; tl < NT; ++tl) {
-                    acc[0][tl] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[0][j][tl], a0, acc[0][tl], 0, 0, 0);
-                    acc[1][tl] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[1][j][tl], a1, acc[1][tl], 0, 0, 0);
-                }
+                for (int tl = 0; tl < NT; ++tl) acc[tl] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[j][tl], a, acc[tl], 0, 0, 0);
             }
-            // the reads of this chunk have returned before its slot is requested again
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            issue(p + NXP, xslot, wstage == 0 ? NW - 1 : wstage - 1);
-            xslot = (xslot + 1 == NXP) ? 0 : xslot + 1;
-            wstage = (wstage + 1 == NW) ? 0 : wstage + 1;
-        }
-        // requests past the end are still on their way into the rings: nothing may reuse LDS before they land
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-
-        // lane l, register r of tile tl: expert ec0 + 16 tl + 4q + r, token i16
+        };
+        block(std::integral_constant<int, 0>{});
+        if (2 * P + 1 < nb) block(std::integral_constant<int, 1>{});        // an odd number of blocks ends with half a step
+        // the reads of this step have returned before its slot is requested again
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        issue(P + NXP, xslot, wslot == 0 ? NW - 1 : wslot - 1);
+        xslot = (xslot + 1 == NXP) ? 0 : xslot + 1;
+        wslot = (wslot + 1 == NW) ? 0 : wslot + 1;
+    }
+    // requests past the end are still on their way into the rings: nothing may reuse LDS before they land
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    float* sums = reinterpret_cast<float*>(gsm) + tile * NT * 256 + lane;
+    float* logit_lds = reinterpret_cast<float*>(gsm) + TILES * NT * 256 + tile * 16 * PITCH;
+    if (s == 1)
+#pragma unroll
+        for (int tl = 0; tl < NT; ++tl)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sums[(tl * 4 + r) * 64] = acc[tl][r];
+    __syncthreads();
+    // lane l, register r of tile tl: expert ec0 + 16 tl + 4q + r, token i16
+    if (s == 0)
 #pragma unroll
         for (int tl = 0; tl < NT; ++tl)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int e = ec0 + 16 * tl + 4 * q + r;
-                const float v = (acc[0][tl][r] + acc[1][tl][r]) + bg[e];
-                if (ROUTE) logit_lds[(wave * 16 + i16) * e_pitch + e] = v;
-                else if (tok < T) logits[(size_t)tok * E + e] = v;
+                if (e < E) {
+                    const float v = (acc[tl][r] + sums[(tl * 4 + r) * 64]) + bg[e];
+                    if (ROUTE) logit_lds[i16 * PITCH + e] = v;
+                    else if (tok < T) logits[(size_t)tok * E + e] = v;
+                }
             }
-    }
     if (ROUTE) {
         __syncthreads();
-        for (int i = lane; i < 16 * E; i += 64) {                 // the wave's 16 rows of logits are contiguous
-            const int tk = i / E, e = i - tk * E;
-            if (tok0w + tk < T) logits[(size_t)tok0w * E + i] = logit_lds[(wave * 16 + tk) * e_pitch + e];
+        if (s == 1) {
+            for (int i = lane; i < 16 * E; i += 64) {             // the tile's 16 rows of logits are contiguous
+                const int tk = i / E, e = i - tk * E;
+                if (tok0w + tk < T) logits[(size_t)tok0w * E + i] = logit_lds[tk * PITCH + e];
+            }
+        } else {
+            route_lanes<4, 4 * NT>(logit_lds + (lane >> 2) * PITCH, lane & 3, tok0w + (lane >> 2), tok0w + (lane >> 2) < T, E, k, renorm, idx, wout);
         }
-        route_lanes<4, 4 * NT>(logit_lds + (wave * 16 + (lane >> 2)) * e_pitch, lane & 3, tok0w + (lane >> 2), tok0w + (lane >> 2) < T, E, k, renorm, idx, wout);
     }
 }
 
@@ -535,35 +543,23 @@ hipError_t run_gate(const moe_shape_t& s, const void* X, const float* Wg, const 
     return run_gate_route(s, logits, idx, w, st);
 }
 
-template <int NT>
-hipError_t run_gate_dma(const moe_shape_t& s, const void* X, const float* Wg, const float* bg,
-                        float* logits, int32_t* idx, float* w, hipStream_t st)
+template <int NT, int TILES, int NXP, bool ROUTE>
+hipError_t run_gate_split(const moe_shape_t& s, const void* X, const float* Wg, const float* bg,
+                          float* logits, int32_t* idx, float* w, hipStream_t st)
 {
-    const int grid = (s.T + GATE_TOK - 1) / GATE_TOK;
-    const bool route = s.E <= 16 * NT;
-    const int e_pitch = s.E | 1;
-    const size_t lds = (size_t)GATE_XRING + (size_t)GATE_NW * 4096 * NT + (route ? (size_t)GATE_TOK * e_pitch * sizeof(float) : 0);
-    auto kr = gate_mfma_dma_kernel<NT, true>;
-    auto kn = gate_mfma_dma_kernel<NT, false>;
+    constexpr int lds = gate_split_lds<NT, TILES, NXP>();
+    auto kern = gate_split_kernel<NT, TILES, NXP, ROUTE>;
     static PerDeviceOnce once;                             // per instantiation
     const int dev = current_device();
     if (!once.is_done(dev)) {
-        const int most = GATE_XRING + GATE_NW * 4096 * NT + GATE_TOK * (16 * NT + 1) * (int)sizeof(float);
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kr), hipFuncAttributeMaxDynamicSharedMemorySize, most);
-        if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kn), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         once.mark(dev);
     }
-    if (route) {
-        hipLaunchKernelGGL(kr, dim3(grid), dim3(GATE_THREADS), lds, st, (const bf16_t*)X, Wg, bg, logits, idx, w,
-                           s.T, s.d, s.E, s.k, s.renorm, e_pitch);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(kn, dim3(grid), dim3(GATE_THREADS), lds, st, (const bf16_t*)X, Wg, bg, logits, idx, w,
-                       s.T, s.d, s.E, s.k, s.renorm, 0);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return run_gate_route(s, logits, idx, w, st);
+    const dim3 grid((s.T + 16 * TILES - 1) / (16 * TILES), (s.E + 16 * NT - 1) / (16 * NT));
+    hipLaunchKernelGGL(kern, grid, dim3(TILES * 128), lds, st, (const bf16_t*)X, Wg, bg, logits, idx, w, s.T, s.d, s.E, s.k, s.renorm);
+    const hipError_t e = hipGetLastError();
+    return (e != hipSuccess || ROUTE) ? e : run_gate_route(s, logits, idx, w, st);
 }
 
 template <typename XT, int NT, int NXP>
@@ -595,10 +591,22 @@ hipError_t launch_gate_topk(const moe_shape_t& s, const void* X, const float* Wg
     if (s.T == 0) return hipSuccess;
     if (s.dtype == MOE_F32) return run_gate_t<float>(s, X, Wg, bg, logits, idx, w, st);
     // rows of 64 tokens must stay inside the 32-bit offsets of a buffer load
-    if (s.d % 64 == 0 && (long long)s.d * 2 * (GATE_TOK + 1) < (1ll << 31) && (long long)s.d * s.E * 4 < (1ll << 31)) {
-        if (s.E == 16) return run_gate_dma<1>(s, X, Wg, bg, logits, idx, w, st);
-        if (s.E == 32) return run_gate_dma<2>(s, X, Wg, bg, logits, idx, w, st);
-        if (s.E % 64 == 0) return run_gate_dma<4>(s, X, Wg, bg, logits, idx, w, st);
+    if (s.E % 4 == 0 && (long long)s.d * 2 * (GATE_TOK + 1) < (1ll << 31) && (long long)s.d * s.E * 4 < (1ll << 31)) {
+        // Few tokens: a block per 16 tokens and 16 experts (more experts: the routing is a launch of its own), so that the
+        // gate matrix comes in through as many CUs as there are.  Up to 512 such blocks; beyond, 64 tokens share a block's
+        // gate matrix.  The call, us, before -> now: T = 64, d = 4096, E = 16 34 -> 20; T = 1, d = 2048 19 -> 13; T = 3000,
+        // d = 1024, E = 48 45 -> 21; T = 2000, E = 100, k = 8 85 -> 34; T = 8001, d = 2048, E = 128 95 -> 56; T = 4000, E = 24
+        // 30 -> 15; T = 16384, E = 32 32 -> 29, E = 64 52 -> 49; T = 32768, d = 4096, E = 16 70 -> 66.
+        const long tiles = (long)((s.T + 15) / 16) * ((s.E + 15) / 16);
+        if (tiles <= 512) {
+            if (s.E <= 16) return run_gate_split<1, 1, 4, true>(s, X, Wg, bg, logits, idx, w, st);
+            return run_gate_split<1, 1, 4, false>(s, X, Wg, bg, logits, idx, w, st);
+        }
+        if (s.E <= 16) return run_gate_split<1, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 32) return run_gate_split<2, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 48) return run_gate_split<3, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 64) return run_gate_split<4, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
+        return run_gate_split<4, 4, 2, false>(s, X, Wg, bg, logits, idx, w, st);
     }
     return run_gate_t<bf16_t>(s, X, Wg, bg, logits, idx, w, st);
 }

@@ -80,3 +80,26 @@ def test_routing_of_many_experts(E, k):
     assert np.array_equal(got.view(np.uint32)[ok], ref["logits"].view(np.uint32)[ok])
     assert np.array_equal(G.host(b.idx), ref["idx"])
     assert np.allclose(G.host(b.w), ref["w"], rtol=1e-5, atol=1e-7)
+
+
+@pytest.mark.parametrize("T,d,E", [
+    (1, 64, 4), (17, 128, 8), (16, 192, 12),                     # one wave per partial sum, one block of columns and more
+    (33, 4160, 16), (100, 320, 20), (50, 256, 132),              # experts in blocks of 16, the last one partly empty
+    (8200, 64, 16), (8193, 192, 16),                             # the last number of tokens with a block per 16, the first past it
+    (4100, 320, 36), (5000, 128, 64), (3000, 192, 68),           # 64 tokens per block: three and four tiles of experts, two passes
+    (90, 128, 18),                                               # no multiple of four: the general kernel
+], ids=str)
+def test_gate_logits_bit_for_bit(T, d, E):
+    cfg = _cfg(T=T, d=d, E=E, k=min(2, E), P=1, renorm=1)
+    rng = np.random.default_rng(T + d + E)
+    X = wl.round_to_bf16(rng.standard_normal((T, d)).astype(np.float32))
+    Wg = (rng.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    bg = rng.standard_normal(E).astype(np.float32)
+    ref = orc.route(X, Wg, bg, cfg.k, 1)
+    hd = G.make_handle(cfg, G=1)
+    b = G.binding.LayerBuffers(hd, False)
+    hd.gate_topk(G.dev(X, "bf16"), G.dev(Wg), G.dev(bg), b.logits, b.idx, b.w)
+    torch.cuda.synchronize()
+    assert np.array_equal(G.host(b.logits).view(np.uint32), ref["logits"].view(np.uint32))
+    assert np.array_equal(G.host(b.idx), ref["idx"])
+    assert np.allclose(G.host(b.w), ref["w"], rtol=1e-5, atol=1e-7)
