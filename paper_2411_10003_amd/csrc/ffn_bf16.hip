@@ -78,8 +78,9 @@ struct GemmParams {
     long ldo, o_group_stride;
     const bf16_t *Zin, *Uin;     // BWD1: saved pre-activations
     int write_act;               // BWD1: recompute the activation into O2 (0: the forward pass's copy is still there)
-    float* split_ws;             // NN/NT: partial tiles of the K-split last round, [unit][wave][128 registers][64 lanes]
+    float* split_ws;             // partial tiles of split contractions, [unit][wave][registers][64 lanes]; null: none is split
     int split_cap;               // units that fit there
+    int tn_over;                 // TN: what a tile costs beside its slices, in slices
     int split_max, split_slices; // parts of a tile at most, slices of a part at least
 };
 
@@ -284,12 +285,103 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         S = min(S, max(1, p.n_seg * (p.Kseg / BK) / p.split_slices));   // a part has to be worth its round trip
         if (rem * S > p.split_cap) S = 1;
     }
-    if (FIN && S == 1) return;
+    if (KIND != KIND_TN && FIN && S == 1) return;
     const int n_items = n_full + rem * S;
-    const int n_rounds = (KIND == KIND_TN) ? p.Gcap * rpg : (n_items + q_stride - 1) / q_stride;
+    const int n_rounds = (n_items + q_stride - 1) / q_stride;
+
+    // TN: the contraction of a group is as long as its rows are many, and a group may have fewer tiles than there are
+    // blocks.  A group whose contraction is longer than a block's share of all the work is cut along it into parts of about
+    // that share; lane v holds part v (of some group; a whole group is its only part).  The parts' tiles go through the
+    // workspace and the finishing launch like those of a split last round.
+    // Parts differ in length, so their rounds are dealt to the XCDs by load: the longest first, a part's rounds spread
+    // evenly, the odd ones to the XCDs with the least to do so far (every block keeps the loads of all eight, lane x that
+    // of XCD x, and so comes to the same dealing).  Measured, us
+    // per product, whole groups dealt in turn (256 x 256 tiles, 128 x 128) -> now, with the finishing launch: d = 3136,
+    // h = 576, 20623 rows in 8 uneven groups 310, 266 -> 142; d = 3968, h = 704, 12532 rows in 2 216, 179 -> 112 to 144;
+    // d = 2944, h = 576, one group of 3002 71, 47 -> 35; d = 1024, h = 4096, 9279 rows in 4 150, 126 -> 118.  Where nothing is
+    // cut: d = 512, h = 14272, 2522 rows 93 -> 80; the largest configuration the same (4.12 ms).
+    int n_parts = 0, v_group = 0, v_row0 = 0, v_rows = 0, v_of = 1, v_unit = 0;     // unit of the part's tile 0
+    int tn_split = 1, tn_unit = 0;                         // lane g: parts of group g, unit of its first part's tile 0
+    unsigned long long tn_split_mask = 0ull;
+    if (KIND == KIND_TN) {
+        n_parts = p.Gcap; v_group = lane; v_row0 = g_row0; v_rows = g_rows;
+    }
+    if (KIND == KIND_TN && p.split_ws != nullptr) {
+        const int k = lane < p.Gcap ? (g_rows + BK - 1) / BK : 0;
+        int all = k;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) all += __shfl_xor(all, off, 64);
+        const int share = (int)((long)tiles_g * (all + p.Gcap * p.tn_over) / nblk);
+        if (k + p.tn_over > share + share / 4) {
+            const int len = max(share - p.tn_over, p.split_slices);
+            tn_split = min(p.split_max, (k + len - 1) / len);
+        }
+        tn_split_mask = __ballot(tn_split > 1);
+        if (tn_split_mask) {
+            tn_split = max(1, min(tn_split, p.split_cap / (tiles_g * __popcll(tn_split_mask))));    // what the workspace holds
+            tn_split_mask = __ballot(tn_split > 1);
+        }
+        int incl = lane < p.Gcap ? tn_split : 0, units = tn_split > 1 ? tn_split : 0;
+        const int own_units = units;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int up = __shfl_up(incl, off, 64), uu = __shfl_up(units, off, 64);
+            if (lane >= off) { incl += up; units += uu; }
+        }
+        tn_unit = (units - own_units) * tiles_g;
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        if (total > 64) tn_split_mask = 0ull;              // more parts than lanes: whole groups
+        if (tn_split_mask != 0ull) {
+            n_parts = total;
+            const int first = incl - tn_split;
+            for (int i = 0; i < p.Gcap; ++i) {
+                const int f = __builtin_amdgcn_readlane(first, i), n = __builtin_amdgcn_readlane(tn_split, i);
+                const int part = lane - f, kk = __builtin_amdgcn_readlane(k, i), rows = __builtin_amdgcn_readlane(g_rows, i);
+                const int r0 = __builtin_amdgcn_readlane(g_row0, i), u = __builtin_amdgcn_readlane(tn_unit, i);
+                if (part >= 0 && part < n) {
+                    const int lo = (int)((long)part * kk / n) * BK, hi = part + 1 == n ? rows : (int)((long)(part + 1) * kk / n) * BK;
+                    v_group = i; v_row0 = r0 + lo; v_rows = hi - lo; v_of = n; v_unit = u + part;
+                }
+            }
+        }
+    }
+    if (KIND == KIND_TN && FIN && tn_split_mask == 0ull) return;
+    int tn_left = n_parts;                                 // parts not taken yet
+    unsigned long long tn_taken = 0ull;
+    int tn_v = 0, tn_n = 0, tn_i = 0, tn_extra = 0;        // current part, its rounds for this XCD, the next one, its odd round
+    int tn_load = 0;                                       // lane x: slices and tile boundaries dealt to XCD x
+    auto tn_next_part = [&]() {
+        const bool mine = lane < n_parts && !((tn_taken >> lane) & 1ull);
+        int best = mine ? v_rows : -1;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) best = max(best, __shfl_xor(best, off, 64));
+        tn_v = __ffsll((unsigned long long)__ballot(mine && v_rows == best)) - 1;
+        tn_taken |= 1ull << tn_v;
+        --tn_left;
+        const int cost = (best + BK - 1) / BK + p.tn_over, even = rpg >> 3, odd = rpg & 7;
+        int rank = 0;                                      // of XCD `lane` by load, then number
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            const int o = __builtin_amdgcn_readlane(tn_load, x);
+            rank += (o < tn_load || (o == tn_load && x < (lane & 7))) ? 1 : 0;
+        }
+        tn_load += (even + (rank < odd ? 1 : 0)) * cost;   // lanes past 7 hold nothing that is read
+        const int my_rank = __builtin_amdgcn_readlane(rank, xcd);
+        tn_n = even + (my_rank < odd ? 1 : 0);
+        tn_extra = 8 * even + my_rank;
+        tn_i = 0;
+    };
+    // few rounds: one each, in turn
+    const bool tn_simple = n_parts * rpg <= 8;
+    if (KIND == KIND_TN && tn_simple) {
+        tn_left = 0;
+        tn_v = xcd / rpg;
+        tn_n = tn_v < n_parts ? 1 : 0;
+    }
     const int q_first = FIN ? (int)blockIdx.x : q0;
     const int q_step = FIN ? nblk : q_stride;
-    const int q_end = FIN ? rem * TM : ((n_rounds + 7) >> 3) * q_stride;   // FIN: a row of fragments of a tile is an item
+    const int q_end = FIN ? (KIND == KIND_TN ? __popcll(tn_split_mask) * tiles_g : rem) * TM       // FIN: a row of fragments of a tile is an item
+                          : (KIND == KIND_TN ? 0x7fffffff : ((n_rounds + 7) >> 3) * q_stride);
 
   for (int q = q_first; q < q_end; q += q_step) {
     int g, rt, ct;
@@ -300,19 +392,36 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     if (KIND == KIND_TN) {
         // every group has the same tile grid but its own contraction length: a round never mixes
         // groups, so the blocks of an XCD stay on the same contraction slices of shared operands
-        const int R = ((q - q0) / q_stride) * 8 + xcd;
-        g = R / rpg;
-        if (g >= p.Gcap) break;
-        const int t = (R - g * rpg) * q_stride + q0;
-        if (t >= tiles_g) continue;
+        int t;
+        long row0 = 0;
+        int rows = 0;
+        if (FIN) {
+            const int i = q / TM;
+            unsigned long long m = tn_split_mask;
+            for (int n = i / tiles_g; n > 0; --n) m &= m - 1;              // the n-th group that was split
+            g = __ffsll(m) - 1;
+            t = i % tiles_g;
+            parts = __builtin_amdgcn_readlane(tn_split, g);
+            unit = __builtin_amdgcn_readlane(tn_unit, g) + t * parts;
+        } else {
+            while (tn_i == tn_n && tn_left > 0) tn_next_part();
+            if (tn_i == tn_n) break;
+            const int in_part = tn_simple ? xcd % rpg : ((tn_i + 1 == tn_n && tn_n > (rpg >> 3)) ? tn_extra : tn_i * 8 + xcd);
+            ++tn_i;
+            t = in_part * q_stride + q0;
+            if (t >= tiles_g) continue;
+            g = __builtin_amdgcn_readlane(v_group, tn_v);
+            row0 = __builtin_amdgcn_readlane(v_row0, tn_v);
+            rows = __builtin_amdgcn_readlane(v_rows, tn_v);
+            parts = __builtin_amdgcn_readlane(v_of, tn_v);
+            unit = __builtin_amdgcn_readlane(v_unit, tn_v) + t * parts;
+        }
         const int band = t / (BAND * p.col_tiles);
         const int in_band = t - band * BAND * p.col_tiles;
         const int band_rows = min(BAND, p.row_tiles - band * BAND);
         rt = band * BAND + in_band % band_rows;
         ct = in_band / band_rows;
-        const int row0 = __builtin_amdgcn_readlane(g_row0, g & 63);       // empty for unused groups
-        const int rows = __builtin_amdgcn_readlane(g_rows, g & 63);
-        a_row0 = row0; a_row_end = row0 + rows;
+        a_row0 = row0; a_row_end = row0 + rows;                            // none for unused groups
         k_tiles = (rows + BK - 1) / BK;
         m0 = rt * BM;
     } else {
@@ -342,8 +451,9 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     const int k_per_seg = (KIND == KIND_TN) ? k_tiles : p.Kseg / BK;
     // slices of this item: all of them, or one part of a split tile; none in the finishing launch
     // (a K-contiguous operand is fetched two slices at a time: parts begin at even slices)
-    const int k_lo = (int)((long)part * k_tiles / parts) & ~1;
-    const int k_hi = (part + 1 == parts) ? k_tiles : ((int)((long)(part + 1) * k_tiles / parts) & ~1);
+    // (TN: the rows are those of the part)
+    const int k_lo = (KIND == KIND_TN) ? 0 : ((int)((long)part * k_tiles / parts) & ~1);
+    const int k_hi = (KIND == KIND_TN || part + 1 == parts) ? k_tiles : ((int)((long)(part + 1) * k_tiles / parts) & ~1);
     const int k_cnt = FIN ? 0 : k_hi - k_lo;
 
     // ---- buffer resources: everything outside the valid rows of an operand reads as zero --------
@@ -715,9 +825,10 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
 
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");     // the last MFMAs have written back before the accumulators are read
     // partial tiles: [unit][wave][register / 4][lane] as float4, every instruction moves 1 KB
-    if (KIND != KIND_TN && !FIN && parts > 1) {
+    if (!FIN && parts > 1) {
         float4* ws4 = reinterpret_cast<float4*>(p.split_ws) + ((size_t)unit * NWAVES + wave) * (TM * TN * 4) * 64 + lane;
-        const long rows_left = a_row_end - a_row0 - wm * WM;                // fragments past the group's last row are not kept
+        // fragments past the group's last row (TN: the last row of the gradient) are not kept
+        const long rows_left = (KIND == KIND_TN ? p.Mout - m0 : a_row_end - a_row0) - wm * WM;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -790,7 +901,7 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         if (FIN && fr != q % TM) continue;                     // the tile's other rows of fragments are items of other blocks
         if (BWD1 && FIN) request(fr, 0, zin[(fr * NB) & 1], uin[EPI == EPI_BWD1_SWIGLU ? (fr * NB) & 1 : 0]);
         float4 fsum[FIN ? TN : 1][4];
-        if (KIND != KIND_TN && FIN) {                          // the parts of a split tile, added in ascending order
+        if (FIN) {                                             // the parts of a split tile, added in ascending order
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -975,6 +1086,9 @@ double row_contraction_cost(const GeometryCost& c, double tiles, int slices, int
     return std::max(t, weight_mb / c.hbm);
 }
 constexpr int SMALL_SPLIT_SLICES = 16;
+// weight gradients: what a tile costs beside its slices, in slices, and the least slices of a part
+template <class GEO> constexpr int TN_OVER = GEO::BLOCKS == 1 ? 24 : 16;
+template <class GEO> constexpr int TN_SPLIT_SLICES = GEO::BLOCKS == 1 ? 48 : 32;
 // Large: a part of a split tile has to be worth its 256-KB round trip, 64 slices where the split only shortens the last of
 // several rounds, 24 where it is what fills the chip (d = 768, h = 3072, 33 tiles of 96 slices: 69 us whole, 45 in four parts).
 inline int large_split_slices(double tiles) { return tiles <= 2.0 * LARGE_COST.tiles_at_once ? 24 : 64; }
@@ -988,16 +1102,26 @@ bool small_wins_rows(const moe_shape_t& s, int N, int slices, int n_seg, int epi
     if (dual) sc.hbm = 3.0;                                // 128-byte pieces of two weight matrices
     return row_contraction_cost(sc, ts, slices, epi, SMALL_SPLIT_SLICES, mb) < row_contraction_cost(LARGE_COST, tl, slices, epi, large_split_slices(tl), mb);
 }
-// Weight gradients: a round of an XCD's blocks per 32 (64) tiles of a group, dealt to the 8 XCDs; 17 and 9 us per tile
-// beside the slices (the fp32 tile is stored).
-bool small_wins_wgrad(const moe_shape_t& s, int Mout, int N)
+// Weight gradients.  Whole groups: a round of an XCD's blocks per 32 (64) tiles of a group, dealt to the 8 XCDs, 17 (9) us
+// per tile beside the slices (the fp32 tile is stored), and no less than the chain of a group with twice its even share of
+// the rows.  Cut groups: every block its share, and a finishing launch of about 20 (12) us.  A cut pays where a group has
+// fewer tiles than there are blocks, and the kernel only makes one where it finds a group that is too long; it is offered
+// where four times a group's even share would be.
+struct WgradPlan { double us; bool cut; };
+template <class GEO>
+WgradPlan wgrad_plan(const moe_shape_t& s, int Mout, int N)
 {
-    const double slices = std::ceil(estimated_rows(s) / s.G / BK);
-    auto cost = [&](int b, int at_once, double slice, double over) {
-        const double rounds = (double)((((Mout + b - 1) / b) * ((N + b - 1) / b) + at_once - 1) / at_once);
-        return std::max(s.G * rounds / 8.0, 1.0) * (slices * slice + over);
-    };
-    return cost(Small::BM, 64, 0.55, 9.0) < cost(Large::BM, 32, 0.70, 17.0);
+    constexpr bool large = GEO::BLOCKS == 1;
+    constexpr double slice = large ? 0.70 : 0.55, over = large ? 17.0 : 9.0, finish = large ? 20.0 : 12.0;
+    constexpr int blocks = large ? 256 : 512, over_slices = TN_OVER<GEO>, least = TN_SPLIT_SLICES<GEO>;
+    const double tiles = (double)((Mout + GEO::BM - 1) / GEO::BM) * ((N + GEO::BN - 1) / GEO::BN);
+    const double even = std::ceil(estimated_rows(s) / s.G / BK), all = std::ceil(estimated_rows(s) / BK);
+    const double whole = std::max(std::max(s.G * std::ceil(tiles / (blocks / 8)) / 8.0, 1.0) * (even * slice + over),
+                                  std::min(2.0 * even, all) * slice + over);
+    const double share = tiles * s.G * (even + over_slices) / blocks, longest = std::min(4.0 * even, all);
+    if (tiles >= blocks || longest < 2 * least || longest + over_slices < 1.25 * share) return WgradPlan{whole, false};
+    const double cut = std::max(share, (double)least) * slice + over + finish;
+    return cut < whole ? WgradPlan{cut, true} : WgradPlan{whole, false};
 }
 
 template <int KIND, int EPI, class GEO>
@@ -1023,27 +1147,27 @@ hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, hipStream_
     const int dev = current_device();
     int cus = (dev >= 0 && dev < 64) ? cus_of[dev].load(std::memory_order_acquire) : 0;
     auto kern = grouped_gemm_kernel<KIND, EPI, false, GEO>;
-    auto kern_fin = grouped_gemm_kernel<KIND, EPI, KIND != KIND_TN, GEO>;     // TN has no split round
+    auto kern_fin = grouped_gemm_kernel<KIND, EPI, true, GEO>;
     if (!once.is_done(dev) || cus == 0) {
         int n = 0;
         if (dev < 0 || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
         cus = n / 8 * 8;
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-        if (e == hipSuccess && KIND != KIND_TN)
+        if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern_fin), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
         if (e != hipSuccess) return e;
         if (dev >= 0 && dev < 64) cus_of[dev].store(cus, std::memory_order_release);
         once.mark(dev);
     }
     const int grid = cus * GEO::BLOCKS;
-    // short contractions gain less from the split than the second launch costs
+    p.tn_over = TN_OVER<GEO>;
     p.split_max = GEO::BLOCKS == 1 ? LARGE_COST.split_max : SMALL_COST.split_max;
-    if (KIND == KIND_TN || p.n_seg * (p.Kseg / BK) < 2 * p.split_slices) p.split_ws = nullptr;
+    if (KIND != KIND_TN && p.n_seg * (p.Kseg / BK) < 2 * p.split_slices) p.split_ws = nullptr;     // too short to be split
     p.split_cap = (int)((size_t)SPLIT_UNITS * Large::UNIT_BYTES / GEO::UNIT_BYTES);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || KIND == KIND_TN || p.split_ws == nullptr) return e;
-    // the tiles of a K-split last round: add their parts, run their epilogues
+    if (e != hipSuccess || p.split_ws == nullptr) return e;
+    // the tiles of split contractions: add their parts, run their epilogues
     hipLaunchKernelGGL(kern_fin, dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
     return hipGetLastError();
 }
@@ -1051,15 +1175,22 @@ hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, hipStream_
 template <int KIND, int EPI>
 hipError_t launch(GemmParams p, const moe_shape_t& s, hipStream_t st)
 {
-    const int A = s.T * s.k, slices = p.n_seg * (p.Kseg / BK);
-    const bool small = KIND == KIND_TN ? small_wins_wgrad(s, p.Mout, p.N) : small_wins_rows(s, p.N, slices, p.n_seg, EPI);
-    if (small) {
-        p.band = 8;                                        // 64 tiles in flight on an XCD: 8 x 8 of 128 x 128
-        p.split_slices = SMALL_SPLIT_SLICES;
-        return launch_geo<KIND, EPI, Small>(p, A, s.G, st);
+    const int A = s.T * s.k;
+    if constexpr (KIND == KIND_TN) {
+        const WgradPlan l = wgrad_plan<Large>(s, p.Mout, p.N), m = wgrad_plan<Small>(s, p.Mout, p.N);
+        const bool small = m.us < l.us;
+        if (!(small ? m.cut : l.cut)) p.split_ws = nullptr;
+        p.split_slices = small ? TN_SPLIT_SLICES<Small> : TN_SPLIT_SLICES<Large>;
+        return small ? launch_geo<KIND, EPI, Small>(p, A, s.G, st) : launch_geo<KIND, EPI, Large>(p, A, s.G, st);
+    } else {
+        if (small_wins_rows(s, p.N, p.n_seg * (p.Kseg / BK), p.n_seg, EPI)) {
+            p.band = 8;                                    // 64 tiles in flight on an XCD: 8 x 8 of 128 x 128
+            p.split_slices = SMALL_SPLIT_SLICES;
+            return launch_geo<KIND, EPI, Small>(p, A, s.G, st);
+        }
+        p.split_slices = large_split_slices(tiles_of(s, Large::BM, p.N, EPI == EPI_FWD1_SWIGLU ? Large::BN / 2 : Large::BN));
+        return launch_geo<KIND, EPI, Large>(p, A, s.G, st);
     }
-    p.split_slices = KIND == KIND_TN ? 64 : large_split_slices(tiles_of(s, Large::BM, p.N, EPI == EPI_FWD1_SWIGLU ? Large::BN / 2 : Large::BN));
-    return launch_geo<KIND, EPI, Large>(p, A, s.G, st);
 }
 
 GemmParams base_params(const moe_shape_t& s, const ffn_args& a)

@@ -27,6 +27,11 @@ CASES = [
     ([12000, 511, 7000], 0, 320, 3136, "gelu"),
     ([14000, 3000], 0, 2112, 320, "swiglu"),
     ([30000], 0, 64, 1600, "gelu"),                        # and one pair of slices per tile
+    # few tiles of long contractions in the weight gradients: cut into parts, beside groups that are not
+    ([9000, 200, 0, 33], 0, 320, 192, "swiglu"),
+    ([4000], 100, 2944, 128, "gelu"),
+    ([7000, 6500, 100, 6000, 31], 0, 1088, 448, "gelu"),
+    ([300] * 20 + [8000], 0, 64, 320, "swiglu"),
 ]
 
 
@@ -55,7 +60,11 @@ def test_forward_backward(rows, other, d, h, act):
           torch.full((Gn, d, h), 7.0, device=G.DEV) if act == "swiglu" else None]
     hd.expert_ffn_fwd(Xp, lay, W1, W2, W3, Yp, Z, U)
     hd.expert_ffn_bwd(dYp, Xp, Z, U, lay, W1, W2, W3, dXp, *dW)
+    # added to what the buffers hold: doubling is exact in fp32
+    acc = [t.clone() if t is not None else None for t in dW]
+    hd.expert_ffn_bwd_acc(dYp, Xp, Z, U, lay, W1, W2, W3, dXp, *acc)
     torch.cuda.synchronize()
+    assert all(t is None or torch.equal(a, 2 * t) for t, a in zip(dW, acc))
     for t, w in ((Yp, d), (dXp, d), (Z, h)) + (((U, h),) if act == "swiglu" else ()):
         assert torch.equal(t[M:], fill[M:, :w]), "rows of other destinations were touched"
 
