@@ -41,6 +41,21 @@ int check_shape(const moe_shape_t& s)
     return MOE_OK;
 }
 
+// Whether tensors of one call touch what another of them writes: written[i] (written_bytes[i]) against every other array.
+// Such tensors are taken one after the other, as the call's order says; all others share a launch.
+bool tensors_overlap(int n, const void* const* read, const void* const* written, const size_t* unit_bytes, size_t read_units, size_t written_units)
+{
+    auto meet = [](const void* a, size_t na, const void* b, size_t nb) {
+        const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+        return x < y + nb && y < x + na;
+    };
+    for (int i = 0; i < n; ++i)
+        for (int j = 0; j < n; ++j)
+            if (i != j && (meet(written[i], unit_bytes[i] * written_units, written[j], unit_bytes[j] * written_units) ||
+                           meet(written[i], unit_bytes[i] * written_units, read[j], unit_bytes[j] * read_units))) return true;
+    return false;
+}
+
 inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255) != 0; }
 
 struct Carve {
@@ -300,10 +315,10 @@ int moe_trans(moe_handle_t h, const int32_t* expert_dest, const int32_t* pool_ve
         if ((reinterpret_cast<uintptr_t>(pools[i]) | reinterpret_cast<uintptr_t>(groups[i])) & 15) return MOE_ERR_SHAPE;
     }
     hipStream_t st = (hipStream_t)stream;
+    const bool apart = tensors_overlap(n_tensors, pools, groups, bytes_per_expert, h->s.E, h->s.G);
     hipError_t e = hipSuccess;
-    for (int i = 0; i < n_tensors && e == hipSuccess; ++i)
-        e = launch_trans_gather(h->s, expert_dest, pool_version, slot_expert, slot_version, pools[i], groups[i],
-                                (long)bytes_per_expert[i], st);
+    for (int i = 0, n = apart ? 1 : n_tensors; i < n_tensors && e == hipSuccess; i += n)
+        e = launch_trans_gather(h->s, expert_dest, pool_version, slot_expert, slot_version, n, pools + i, groups + i, bytes_per_expert + i, st);
     if (e == hipSuccess) e = launch_trans_commit(h->s, expert_dest, pool_version, slot_expert, slot_version, st);
     return hip_status(e);
 }
@@ -318,9 +333,13 @@ int moe_agg(moe_handle_t h, const int32_t* expert_dest, int n_tensors, const flo
         if (floats_per_expert[i] == 0 || floats_per_expert[i] % 4 != 0) return MOE_ERR_SHAPE;
         if ((reinterpret_cast<uintptr_t>(group_grads[i]) | reinterpret_cast<uintptr_t>(pool_grads[i])) & 15) return MOE_ERR_SHAPE;
     }
+    size_t bytes[8];
+    const void *read[8], *written[8];
+    for (int i = 0; i < n_tensors; ++i) { bytes[i] = floats_per_expert[i] * sizeof(float); read[i] = group_grads[i]; written[i] = pool_grads[i]; }
+    const bool apart = tensors_overlap(n_tensors, read, written, bytes, h->s.G, h->s.E);
     hipError_t e = hipSuccess;
-    for (int i = 0; i < n_tensors && e == hipSuccess; ++i)
-        e = launch_agg_add(h->s, expert_dest, group_grads[i], pool_grads[i], (long)floats_per_expert[i], (hipStream_t)stream);
+    for (int i = 0, n = apart ? 1 : n_tensors; i < n_tensors && e == hipSuccess; i += n)
+        e = launch_agg_add(h->s, expert_dest, n, group_grads + i, pool_grads + i, floats_per_expert + i, (hipStream_t)stream);
     return hip_status(e);
 }
 

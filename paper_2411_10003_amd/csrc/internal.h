@@ -70,11 +70,11 @@ hipError_t launch_gate_wgrad(const moe_shape_t& s, const void* X, const float* d
                              float* dWg, float* dbg, hipStream_t st);
 hipError_t launch_trans_gather(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* pool_version,
                                const int32_t* slot_expert, const int32_t* slot_version,
-                               const void* pool, void* groups, long bytes_per_expert, hipStream_t st);
+                               int n, const void* const* pools, void* const* groups, const size_t* bytes_per_expert, hipStream_t st);
 hipError_t launch_trans_commit(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* pool_version,
                                int32_t* slot_expert, int32_t* slot_version, hipStream_t st);
-hipError_t launch_agg_add(const moe_shape_t& s, const int32_t* expert_dest, const float* groups, float* pool,
-                          long floats_per_expert, hipStream_t st);
+hipError_t launch_agg_add(const moe_shape_t& s, const int32_t* expert_dest, int n, const float* const* groups, float* const* pools,
+                          const size_t* floats_per_expert, hipStream_t st);
 hipError_t launch_recv_layout(const moe_shape_t& s, const int32_t* local_dest_slots, const int32_t* recv_offsets,
                               int32_t* slot_offsets, int32_t* dest_slots, hipStream_t st);
 hipError_t launch_plan(const moe_planner_t& cfg, const int32_t* gating, const moe_plan_out_t& out, hipStream_t st);

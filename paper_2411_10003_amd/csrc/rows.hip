@@ -322,54 +322,61 @@ hipError_t launch_dispatch_bwd(const moe_shape_t& s, const void* dXp, const int3
 // expert that the caller bumps with every update, and a replica of an older version is copied again.
 namespace {
 
+// The g-th expert (ascending) that is hosted here, -1 if there are fewer.  All 64 lanes of the wave take part: one load and
+// one ballot per 64 experts (a scalar walk over the experts waited for one load per expert, 5 us for 16 of them).
 __device__ __forceinline__ int hosted_expert_of_group(const int32_t* __restrict__ expert_dest, int E, int self, int g)
 {
-    // wave-uniform scan; E <= 1024
-    int seen = 0;
-    for (int e = 0; e < E; ++e) {
-        if (expert_dest[e] == self) {
-            if (seen == g) return e;
-            ++seen;
+    const int lane = threadIdx.x & 63;
+    for (int e0 = 0; e0 < E; e0 += 64) {
+        const unsigned long long m = __ballot(e0 + lane < E && expert_dest[min(e0 + lane, E - 1)] == self);
+        const int n = __popcll(m);
+        if (g < n) {
+            const bool mine = ((m >> lane) & 1ull) && __popcll(m & ((1ull << lane) - 1ull)) == g;
+            return e0 + __ffsll((unsigned long long)__ballot(mine)) - 1;
         }
+        g -= n;
     }
     return -1;
 }
 
+// All tensors of a call in one launch: grid z is the tensor.
+constexpr int MAX_TENSORS = 8, MOVE_UNROLL = 4;
+struct MoveArgs { const uint4* src[MAX_TENSORS]; uint4* dst[MAX_TENSORS]; long vec[MAX_TENSORS]; };
+
 __global__ __launch_bounds__(256) void trans_gather_kernel(
     const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ pool_version,
-    const int32_t* __restrict__ slot_expert, const int32_t* __restrict__ slot_version,
-    const uint4* __restrict__ pool, uint4* __restrict__ groups, long vec_per_expert, int E, int self)
+    const int32_t* __restrict__ slot_expert, const int32_t* __restrict__ slot_version, const MoveArgs a, int E, int self)
 {
     const int g = blockIdx.y;
     const int e = hosted_expert_of_group(expert_dest, E, self, g);
     if (e < 0) return;                                     // unused slot
     // the expert is already there, in the version the pool holds now (no versions given: always copied)
     if (pool_version != nullptr && e == slot_expert[g] && slot_version[g] == pool_version[e]) return;
-    const uint4* src = pool + (long)e * vec_per_expert;
-    uint4* dst = groups + (long)g * vec_per_expert;
-    const long stride = (long)gridDim.x * blockDim.x * 4;
-    for (long v = ((long)blockIdx.x * blockDim.x + threadIdx.x); v < vec_per_expert; v += stride) {
-        uint4 r[4];
+    const long vec_per_expert = a.vec[blockIdx.z], lanes = (long)gridDim.x * blockDim.x;
+    const uint4* __restrict__ src = a.src[blockIdx.z] + (long)e * vec_per_expert;
+    uint4* __restrict__ dst = a.dst[blockIdx.z] + (long)g * vec_per_expert;
+    for (long v = (long)blockIdx.x * blockDim.x + threadIdx.x; v < vec_per_expert; v += lanes * MOVE_UNROLL) {
+        uint4 r[MOVE_UNROLL];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const long i = v + (long)u * gridDim.x * blockDim.x;
+        for (int u = 0; u < MOVE_UNROLL; ++u) {
+            const long i = v + u * lanes;
             if (i < vec_per_expert) r[u] = src[i];
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const long i = v + (long)u * gridDim.x * blockDim.x;
+        for (int u = 0; u < MOVE_UNROLL; ++u) {
+            const long i = v + u * lanes;
             if (i < vec_per_expert) dst[i] = r[u];
         }
     }
 }
 
-__global__ void trans_commit_kernel(const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ pool_version,
-                                    int32_t* __restrict__ slot_expert, int32_t* __restrict__ slot_version, int E, int self, int G)
+// one wave per slot
+__global__ __launch_bounds__(64) void trans_commit_kernel(const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ pool_version,
+                                    int32_t* __restrict__ slot_expert, int32_t* __restrict__ slot_version, int E, int self)
 {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= G) return;
+    const int g = blockIdx.x;
     const int e = hosted_expert_of_group(expert_dest, E, self, g);
-    if (e >= 0) {                                          // an unused slot keeps what it holds
+    if (e >= 0 && threadIdx.x == 0) {                      // an unused slot keeps what it holds
         slot_expert[g] = e;
         if (pool_version != nullptr) slot_version[g] = pool_version[e];
     }
@@ -378,52 +385,64 @@ __global__ void trans_commit_kernel(const int32_t* __restrict__ expert_dest, con
 // Agg on one GPU (Section 4.1: the gradients a replica computed are added to the expert's gradient where its
 // parameters live).  The inverse walk of the gather above: the fp32 gradient of hosted group g is added to the
 // pool entry of the expert the plan puts there.  Every element is touched by one thread: same bits every run.
-__global__ __launch_bounds__(256) void agg_add_kernel(
-    const int32_t* __restrict__ expert_dest, const float4* __restrict__ groups, float4* __restrict__ pool,
-    long vec_per_expert, int E, int self)
+__global__ __launch_bounds__(256) void agg_add_kernel(const int32_t* __restrict__ expert_dest, const MoveArgs a, int E, int self)
 {
     const int g = blockIdx.y;
     const int e = hosted_expert_of_group(expert_dest, E, self, g);
     if (e < 0) return;
-    const float4* src = groups + (long)g * vec_per_expert;
-    float4* dst = pool + (long)e * vec_per_expert;
-    const long stride = (long)gridDim.x * blockDim.x;
-    for (long v = (long)blockIdx.x * blockDim.x + threadIdx.x; v < vec_per_expert; v += stride) {
-        const float4 a = src[v];
-        float4 b = dst[v];
-        b.x += a.x; b.y += a.y; b.z += a.z; b.w += a.w;
-        dst[v] = b;
+    const long vec_per_expert = a.vec[blockIdx.z], lanes = (long)gridDim.x * blockDim.x;
+    const float4* __restrict__ src = reinterpret_cast<const float4*>(a.src[blockIdx.z]) + (long)g * vec_per_expert;
+    float4* __restrict__ dst = reinterpret_cast<float4*>(a.dst[blockIdx.z]) + (long)e * vec_per_expert;
+    for (long v = (long)blockIdx.x * blockDim.x + threadIdx.x; v < vec_per_expert; v += lanes * MOVE_UNROLL) {
+        float4 x[MOVE_UNROLL], y[MOVE_UNROLL];
+#pragma unroll
+        for (int u = 0; u < MOVE_UNROLL; ++u) {
+            const long i = v + u * lanes;
+            if (i < vec_per_expert) { x[u] = src[i]; y[u] = dst[i]; }
+        }
+#pragma unroll
+        for (int u = 0; u < MOVE_UNROLL; ++u) {
+            const long i = v + u * lanes;
+            if (i < vec_per_expert) dst[i] = make_float4(y[u].x + x[u].x, y[u].y + x[u].y, y[u].z + x[u].z, y[u].w + x[u].w);
+        }
     }
+}
+
+// Blocks per slot and tensor: one trip of four pieces per lane up to 512 blocks (8 MB), then a longer walk.
+inline unsigned move_blocks(const MoveArgs& a, int n)
+{
+    long most = 1;
+    for (int i = 0; i < n; ++i) most = a.vec[i] > most ? a.vec[i] : most;
+    const long bx = (most + 256 * MOVE_UNROLL - 1) / (256 * MOVE_UNROLL);
+    return (unsigned)(bx > 512 ? 512 : bx);
 }
 
 }  // namespace
 
-hipError_t launch_agg_add(const moe_shape_t& s, const int32_t* expert_dest, const float* groups, float* pool,
-                          long floats_per_expert, hipStream_t st)
+hipError_t launch_agg_add(const moe_shape_t& s, const int32_t* expert_dest, int n, const float* const* groups, float* const* pools,
+                          const size_t* floats_per_expert, hipStream_t st)
 {
-    const long vec = floats_per_expert / 4;
-    long bx = (vec + 256 * 4 - 1) / (256 * 4);
-    bx = bx < 1 ? 1 : (bx > 1024 ? 1024 : bx);
-    hipLaunchKernelGGL(agg_add_kernel, dim3((unsigned)bx, s.G), dim3(256), 0, st, expert_dest,
-                       (const float4*)groups, (float4*)pool, vec, s.E, s.self);
+    MoveArgs a{};
+    for (int i = 0; i < n; ++i) { a.src[i] = (const uint4*)groups[i]; a.dst[i] = (uint4*)pools[i]; a.vec[i] = (long)(floats_per_expert[i] / 4); }
+    hipLaunchKernelGGL(agg_add_kernel, dim3(move_blocks(a, n), s.G, n), dim3(256), 0, st, expert_dest, a, s.E, s.self);
     return hipGetLastError();
 }
 
 hipError_t launch_trans_gather(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* pool_version,
                                const int32_t* slot_expert, const int32_t* slot_version,
-                               const void* pool, void* groups, long bytes_per_expert, hipStream_t st)
+                               int n, const void* const* pools, void* const* groups, const size_t* bytes_per_expert, hipStream_t st)
 {
-    const long vec = bytes_per_expert / 16;
-    const int bx = (int)((vec + 256 * 4 - 1) / (256 * 4) < 512 ? (vec + 256 * 4 - 1) / (256 * 4) : 512);
-    hipLaunchKernelGGL(trans_gather_kernel, dim3(bx > 0 ? bx : 1, s.G), dim3(256), 0, st, expert_dest, pool_version, slot_expert, slot_version,
-                       (const uint4*)pool, (uint4*)groups, vec, s.E, s.self);
+    MoveArgs a{};
+    for (int i = 0; i < n; ++i) { a.src[i] = (const uint4*)pools[i]; a.dst[i] = (uint4*)groups[i]; a.vec[i] = (long)(bytes_per_expert[i] / 16); }
+    hipLaunchKernelGGL(trans_gather_kernel, dim3(move_blocks(a, n), s.G, n), dim3(256), 0, st, expert_dest, pool_version, slot_expert,
+                       slot_version, a, s.E, s.self);
     return hipGetLastError();
 }
 
 hipError_t launch_trans_commit(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* pool_version,
                                int32_t* slot_expert, int32_t* slot_version, hipStream_t st)
 {
-    hipLaunchKernelGGL(trans_commit_kernel, dim3((s.G + 63) / 64), dim3(64), 0, st, expert_dest, pool_version, slot_expert,
-                       slot_version, s.E, s.self, s.G);
+    hipLaunchKernelGGL(trans_commit_kernel, dim3(s.G), dim3(64), 0, st, expert_dest, pool_version, slot_expert,
+                       slot_version, s.E, s.self);
     return hipGetLastError();
 }
