@@ -54,6 +54,7 @@ class _PlanOut(ctypes.Structure):
     _fields_ = [(n, ctypes.c_void_p) for n in ("expert_dest", "selected", "skipped", "H", "R", "times", "info")]
 
 
+_raw_stream, _current_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
 _lib = None
 
 
@@ -110,7 +111,11 @@ def _ptr(t: Optional[torch.Tensor], dtype: torch.dtype, numel: int, name: str) -
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # The raw handle of the current stream.  torch.cuda.current_stream() builds a Stream object around it first: 2.9 us, a
+    # third of the host time of a call; this takes 0.2 (the five calls of the tiny forward layer 43 -> 30 us).
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 class PlanBuffers:
