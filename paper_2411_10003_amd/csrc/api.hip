@@ -171,6 +171,8 @@ static int dispatch_impl(moe_handle_t h, const int32_t* expert_dest, const void*
     if (!ws || misaligned(ws)) return MOE_ERR_WORKSPACE;
     const Carve c{(char*)ws, h};
     hipStream_t st = (hipStream_t)stream;
+    if (small_dispatch_fits(h->s, h->n_chunks))
+        return hip_status(launch_small_dispatch(h->s, idx, expert_dest, counts, X, Xp, h->n_chunks, *L, c.status(), st));
     hipError_t e = hipSuccess;
     if (!fresh_hist) e = launch_chunk_hist(h->s, idx, c.chunk_hist(), h->n_chunks, st);
     if (e == hipSuccess && layout_positions_fusable(h->s, h->n_chunks)) {

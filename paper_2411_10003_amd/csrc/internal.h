@@ -60,6 +60,9 @@ hipError_t launch_scatter_rows(const moe_shape_t& s, const void* X, const int32_
 hipError_t launch_combine(const moe_shape_t& s, const void* Yp, const int32_t* pos, const float* w, void* out, hipStream_t st);
 hipError_t launch_combine_bwd(const moe_shape_t& s, const void* dOut, const void* Yp, const int32_t* pos,
                               const float* w, void* dYp, float* dw, hipStream_t st);
+bool small_dispatch_fits(const moe_shape_t& s, int n_chunks);
+hipError_t launch_small_dispatch(const moe_shape_t& s, const int32_t* idx, const int32_t* expert_dest, const int32_t* counts,
+                                 const void* X, void* Xp, int n_chunks, const moe_layout_t& L, int32_t* status, hipStream_t st);
 bool layout_positions_fusable(const moe_shape_t& s, int n_chunks);
 hipError_t launch_layout_positions(const moe_shape_t& s, const int32_t* idx, const int32_t* expert_dest, const int32_t* counts,
                                    const int32_t* chunk_hist, int n_chunks, const moe_layout_t& L, int32_t* status, hipStream_t st);

@@ -23,6 +23,10 @@ CASES = [
     _cfg(T=129, E=63, P=7, k=1),
     _cfg(T=513, E=64, P=64),                          # P as many as experts
     _cfg(T=700, E=65, P=13, k=8),                     # a second row of lanes with one expert
+    _cfg(T=4096, E=256, P=16, k=1),                   # the most chunks and experts dispatched in one launch
+    _cfg(T=4097, E=256, P=16, k=1),                   # a chunk past that
+    _cfg(T=60, d=4160, E=12, P=3, k=3),               # rows of three pieces, the last one short
+    _cfg(T=50, d=36, E=7, P=7, dtype="f32"),          # fp32 rows of nine 16-byte vectors
     _cfg(T=8192, E=24, P=4),                          # the last number of chunks counted in one block
     _cfg(T=8193, E=24, P=4),                          # the first past it
     _cfg(T=300, E=257, P=257, k=8),                   # past the experts of the one-block counts
@@ -32,7 +36,7 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("cfg", CASES, ids=lambda c: f"T{c.T}-E{c.E}-k{c.k}-P{c.P}")
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: f"{c.dtype}-T{c.T}-d{c.d}-E{c.E}-k{c.k}-P{c.P}")
 def test_counts_layout_positions(cfg):
     rng = np.random.default_rng(cfg.T + cfg.E)
     p = rng.gamma(0.3, size=cfg.E) + 1e-4             # uneven, with experts that get next to nothing
@@ -41,7 +45,9 @@ def test_counts_layout_positions(cfg):
     dest = rng.integers(0, cfg.P, size=cfg.E).astype(np.int32)
     cnt = orc.counts(idx, cfg.E)
     lay = orc.place(idx, cnt, dest, cfg.P)
-    X = wl.round_to_bf16(rng.standard_normal((cfg.T, cfg.d)).astype(np.float32))
+    X = rng.standard_normal((cfg.T, cfg.d)).astype(np.float32)
+    if cfg.dtype == "bf16":
+        wl.round_to_bf16(X)
     hd = G.make_handle(cfg, G=min(cfg.E, 64))
     for after in (False, True):
         b = G.binding.LayerBuffers(hd, False)
@@ -49,7 +55,7 @@ def test_counts_layout_positions(cfg):
         b.counts.fill_(-1)
         hd.expert_counts(d_idx, b.counts)
         assert np.array_equal(G.host(b.counts), cnt)
-        hd.dispatch(G.dev(dest), G.dev(X, "bf16"), d_idx, b.counts, b.layout, b.Xp, after_counts=after)
+        hd.dispatch(G.dev(dest), G.dev(X, cfg.dtype), d_idx, b.counts, b.layout, b.Xp, after_counts=after)
         torch.cuda.synchronize()
         G.assert_layout_equal(b, lay)
         assert np.array_equal(G.host(b.Xp), orc.dispatch(X, lay["perm"], cfg.k))
