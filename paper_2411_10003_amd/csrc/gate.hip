@@ -287,8 +287,9 @@ __global__ __launch_bounds__(GATE_THREADS) void gate_mfma_kernel(
 // in order, which is the order the interface fixes, and the two sums meet in LDS at the end.  That halves the serial chain
 // of a tile (512 matrix instructions of 32 cycles at d = 4096, E = 16) and gives a CU twice the waves.  A step is two of a
 // wave's blocks (128 columns of the rows).
-// Per wave a ring of NXP steps of its tokens (2 KB each: lane l's two 16-byte pieces at 16 l and 1024 + 16 l); per partial
-// sum a ring of NXP + 1 steps of the gate matrix (64 columns x 16 NT experts), fetched in equal shares by the waves that
+// A ring of RING steps of a tile's tokens (4 KB each, shared by its two waves: each requests 8 of the 16 rows, so that a
+// request is whole 128-byte lines; 64-byte halves, a wave its own columns, asked L2 for every line twice); per partial
+// sum a ring of RING steps of the gate matrix (64 columns x 16 NT experts), fetched in equal shares by the waves that
 // use it.  A gate-matrix piece (4 consecutive experts of one column) lands where the instruction that uses it finds the 64
 // values of its lanes side by side: piece (block of the step, j, tile, q, i / 4) at 16 * ((((8 b + j) NT + tile) 4 + q) 4 +
 // i / 4), so the A operand of instruction (b, j, tile) is one `ds_read_b32` at lane * 4 plus a constant.  Experts past the
@@ -313,23 +314,27 @@ __device__ __forceinline__ void gate_dma16(gate_rsrc_t r, uint32_t lds_base, uin
                  :: "s"(lds_base), "v"(voff), "s"(r), "s"(soff) : "memory");
 }
 
-template <int NT, int TILES, int NXP> constexpr int gate_split_lds()
-{
-    return 2 * TILES * NXP * 2048 + 2 * (NXP + 1) * 4096 * NT;
-}
+template <int NT, int TILES, int RING> constexpr int gate_split_lds() { return RING * (4096 * TILES + 2 * 4096 * NT); }
 
 // TILES: token tiles of a block (2 TILES waves).  blockIdx.y: pass of 16 NT experts.  ROUTE: one pass, routing fused.
-template <int NT, int TILES, int NXP, bool ROUTE>
+// What bounds it: few tokens, the chain of dependent matrix instructions of a partial sum, whose order is fixed (0.45 us per
+// step; rings of 3, 5 and 10 steps take the same); many, the rows from HBM.  So the chain is kept going: the LDS reads of a
+// block go out between the products of the block before it, the requests between those of the odd block.  The call, us,
+// back to back and with the caches swept before it, separate reads, products and requests and half lines -> now: T = 64,
+// d = 4096, E = 16 20.4, 23 -> 18.6, 21.4; T = 8192, d = 1024 10.8, 15.3 -> 10.3, 14.1; T = 8001, d = 2048, E = 128 55, 62 ->
+// 52, 55; T = 16384, E = 64 48, 58 -> 45, 50; T = 32768, d = 4096, E = 16 64, 113 -> 60, 112.
+template <int NT, int TILES, int RING, bool ROUTE>
 __global__ __launch_bounds__(TILES * 128) void gate_split_kernel(
     const bf16_t* __restrict__ X, const float* __restrict__ Wg, const float* __restrict__ bg,
     float* __restrict__ logits, int32_t* __restrict__ idx, float* __restrict__ wout,
     int T, int d, int E, int k, int renorm)
 {
-    constexpr int NW = NXP + 1, XSTEP = 2048, WSTEP = 4096 * NT, XRING = 2 * TILES * NXP * XSTEP;
+    constexpr int XSTEP = 4096, WSTEP = 4096 * NT, XRING = TILES * RING * XSTEP;
     constexpr int WOPS = 4 * NT / TILES, OPS = 2 + WOPS;   // requests of one wave per step
-    static_assert(4 * NT % TILES == 0, "equal shares of the gate matrix");
+    static_assert(4 * NT % TILES == 0 && OPS <= 8, "equal shares of the gate matrix, a request per column of a block");
+    static_assert(RING >= 2, "a step is requested while the one before it is multiplied");
     constexpr int PITCH = 16 * NT + 1;                     // logits of a token in LDS
-    static_assert(TILES * 16 * PITCH * 4 + TILES * NT * 1024 <= gate_split_lds<NT, TILES, NXP>(), "logits and sums fit the rings");
+    static_assert(TILES * 16 * PITCH * 4 + TILES * NT * 1024 <= gate_split_lds<NT, TILES, RING>(), "logits and sums fit the rings");
     extern __shared__ __attribute__((aligned(1024))) unsigned char gsm[];   // token rings | gate-matrix rings; then sums | logits
     const uint32_t lds0 = (uint32_t)(uintptr_t)(GATE_LDS_PTR(unsigned char))gsm;
     const int lane = threadIdx.x & 63;
@@ -341,11 +346,14 @@ __global__ __launch_bounds__(TILES * 128) void gate_split_kernel(
     const int nb = d / 64, steps = (nb + 1) / 2;           // 32-column blocks of each partial sum
 
     // tokens: rows of this block onwards; a token past the end reads the last one (never stored); a block past the
-    // end of a row reads into the next rows or, after the last row, zeros: never multiplied
+    // end of a row reads into the next rows or, after the last row, zeros: never multiplied.  The two waves of a tile
+    // share its ring: a wave requests 8 of the 16 rows, whole 128-byte lines (64 columns, 32 of either sum); in LDS a
+    // row's eight 16-byte pieces are XOR-swizzled by the row, so that the 16 rows of a piece cover all banks.
     const gate_rsrc_t rX = gate_make_rsrc(X + (size_t)blk_tok0 * d, (unsigned long long)(T - blk_tok0) * d * 2);
-    const int rowrel = (tok < T ? tok : T - 1) - blk_tok0;
-    const uint32_t xv = (uint32_t)((rowrel * d + 32 * s + 8 * q) * 2);
-    const uint32_t xl = lds0 + (uint32_t)(wave * NXP * XSTEP);
+    const int xrow = 8 * s + (lane >> 3);                  // row of the tile this lane requests a piece of
+    const int rowrel = (tok0w + xrow < T ? tok0w + xrow : T - 1) - blk_tok0;
+    const uint32_t xv = (uint32_t)(rowrel * d * 2 + (((lane & 7) ^ ((xrow >> 1) & 7)) << 4));
+    const uint32_t xl = lds0 + (uint32_t)(tile * RING * XSTEP + s * 1024);
     // gate matrix: this wave's share of a step
     const gate_rsrc_t rW = gate_make_rsrc(Wg + ec0, ((unsigned long long)d * E - ec0) * 4);     // past the last column: zeros
     uint32_t wv[WOPS];
@@ -355,50 +363,65 @@ __global__ __launch_bounds__(TILES * 128) void gate_split_kernel(
         const int e4 = L & 3, qq = (L >> 2) & 3, tl = (L >> 4) % NT, bj = L / (16 * NT);
         wv[n] = (uint32_t)(((64 * (bj >> 3) + 32 * s + 8 * qq + (bj & 7)) * E + 16 * tl + 4 * e4) * 4);
     }
-    const uint32_t wl = lds0 + (uint32_t)(XRING + s * NW * WSTEP + tile * WOPS * 1024);
-    auto issue = [&](int P, int xslot, int wslot) {
-        gate_dma16(rX, xl + (uint32_t)(xslot * XSTEP), xv, (uint32_t)P * 256u);
-        gate_dma16(rX, xl + (uint32_t)(xslot * XSTEP + 1024), xv + 128u, (uint32_t)P * 256u);
-#pragma unroll
-        for (int n = 0; n < WOPS; ++n)
-            gate_dma16(rW, wl + (uint32_t)(wslot * WSTEP + n * 1024), wv[n], (uint32_t)P * (uint32_t)(128 * E * 4));
+    const uint32_t wl = lds0 + (uint32_t)(XRING + s * RING * WSTEP + tile * WOPS * 1024);
+    auto request = [&](int n, int P, int slot) {           // request n of this wave for step P
+        if (n < 2) gate_dma16(rX, xl + (uint32_t)(slot * XSTEP + n * 2048), xv + 128u * n, (uint32_t)P * 256u);
+        else gate_dma16(rW, wl + (uint32_t)(slot * WSTEP + (n - 2) * 1024), wv[n - 2], (uint32_t)P * (uint32_t)(128 * E * 4));
     };
     gate_f4 acc[NT];
 #pragma unroll
     for (int tl = 0; tl < NT; ++tl) acc[tl] = gate_f4{0.0f, 0.0f, 0.0f, 0.0f};
+    // operands of a block: 8 columns of a token per lane (bf16 pairs), 8 x NT elements of the gate matrix
+    struct Block { gate_u4 x; float w[8][NT]; };
+    const uint32_t xr = (uint32_t)(tile * RING * XSTEP + i16 * 128 + (((4 * s + q) ^ ((i16 >> 1) & 7)) << 4));
+    const uint32_t wr = (uint32_t)(XRING + s * RING * WSTEP + lane * 4);
+    auto read_x = [&](Block& o, int slot, int b) { o.x = *reinterpret_cast<const gate_u4*>(gsm + xr + slot * XSTEP + b * 2048); };
+    auto read_w = [&](Block& o, int slot, int b, int j) {
 #pragma unroll
-    for (int P = 0; P < NXP; ++P) issue(P, P, P);
-    int xslot = 0, wslot = 0;
+        for (int tl = 0; tl < NT; ++tl) o.w[j][tl] = *reinterpret_cast<const float*>(gsm + wr + slot * WSTEP + ((b * 8 + j) * NT + tl) * 256);
+    };
+    auto multiply = [&](const Block& o, int j) {
+        const uint32_t w = o.x[j / 2];
+        const float a = __uint_as_float((j & 1) ? (w & 0xffff0000u) : (w << 16));
+#pragma unroll
+        for (int tl = 0; tl < NT; ++tl) acc[tl] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.w[j][tl], a, acc[tl], 0, 0, 0);
+    };
+    Block b0, b1;                                          // the even and the odd block of a step
+#pragma unroll
+    for (int P = 0; P < RING; ++P)
+#pragma unroll
+        for (int n = 0; n < OPS; ++n) request(n, P, P);
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((RING - 1) * OPS) : "memory");
+    asm volatile("s_barrier" ::: "memory");
+    read_x(b0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) read_w(b0, 0, 0, j);
+    int slot = 0;
     for (int P = 0; P < steps; ++P) {
-        // this wave's requests for step P have landed (NXP - 1 younger steps may be pending); after the barrier so have
-        // everybody's shares of the gate matrix, and everybody is done with step P - 1
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NXP - 1) * OPS) : "memory");
+        const int next = (slot + 1 == RING) ? 0 : slot + 1;
+        // the odd block's operands come in under the even block's products
+        read_x(b1, slot, 1);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            read_w(b1, slot, 1, j);
+            multiply(b0, j);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // this wave has read all of step P and its requests for step P + 1 have landed (RING - 2 younger steps may be
+        // pending); after the barrier that is true of every wave: step P's slot is free, step P + 1 can be read
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((RING - 2) * OPS) : "memory");
         asm volatile("s_barrier" ::: "memory");
-        const unsigned char* xs = gsm + (wave * NXP + xslot) * XSTEP + lane * 16;
-        const float* ws = reinterpret_cast<const float*>(gsm + XRING + (s * NW + wslot) * WSTEP) + lane;
-        auto block = [&](auto B) {
-            constexpr int b = decltype(B)::value;
-            const gate_u4 x = *reinterpret_cast<const gate_u4*>(xs + b * 1024);
-            float wf[8][NT];
+        // under the odd block's products: the requests for step P + RING, the operands of the next even block
+        const bool odd = 2 * P + 1 < nb;                   // an odd number of blocks ends with half a step
+        read_x(b0, next, 0);
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-#pragma unroll
-                for (int tl = 0; tl < NT; ++tl) wf[j][tl] = ws[((b * 8 + j) * NT + tl) * 64];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const uint32_t w = x[j / 2];
-                const float a = __uint_as_float((j & 1) ? (w & 0xffff0000u) : (w << 16));
-#pragma unroll
-                for (int tl = 0; tl < NT; ++tl) acc[tl] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[j][tl], a, acc[tl], 0, 0, 0);
-            }
-        };
-        block(std::integral_constant<int, 0>{});
-        if (2 * P + 1 < nb) block(std::integral_constant<int, 1>{});        // an odd number of blocks ends with half a step
-        // the reads of this step have returned before its slot is requested again
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        issue(P + NXP, xslot, wslot == 0 ? NW - 1 : wslot - 1);
-        xslot = (xslot + 1 == NXP) ? 0 : xslot + 1;
-        wslot = (wslot + 1 == NW) ? 0 : wslot + 1;
+        for (int j = 0; j < 8; ++j) {
+            if (j < OPS) request(j, P + RING, slot);
+            read_w(b0, next, 0, j);
+            if (odd) multiply(b1, j);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        slot = next;
     }
     // requests past the end are still on their way into the rings: nothing may reuse LDS before they land
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -543,12 +566,12 @@ hipError_t run_gate(const moe_shape_t& s, const void* X, const float* Wg, const 
     return run_gate_route(s, logits, idx, w, st);
 }
 
-template <int NT, int TILES, int NXP, bool ROUTE>
+template <int NT, int TILES, int RING, bool ROUTE>
 hipError_t run_gate_split(const moe_shape_t& s, const void* X, const float* Wg, const float* bg,
                           float* logits, int32_t* idx, float* w, hipStream_t st)
 {
-    constexpr int lds = gate_split_lds<NT, TILES, NXP>();
-    auto kern = gate_split_kernel<NT, TILES, NXP, ROUTE>;
+    constexpr int lds = gate_split_lds<NT, TILES, RING>();
+    auto kern = gate_split_kernel<NT, TILES, RING, ROUTE>;
     static PerDeviceOnce once;                             // per instantiation
     const int dev = current_device();
     if (!once.is_done(dev)) {
@@ -596,17 +619,21 @@ hipError_t launch_gate_topk(const moe_shape_t& s, const void* X, const float* Wg
         // gate matrix comes in through as many CUs as there are.  Up to 512 such blocks; beyond, 64 tokens share a block's
         // gate matrix.  The call, us, before -> now: T = 64, d = 4096, E = 16 34 -> 20; T = 1, d = 2048 19 -> 13; T = 3000,
         // d = 1024, E = 48 45 -> 21; T = 2000, E = 100, k = 8 85 -> 34; T = 8001, d = 2048, E = 128 95 -> 56; T = 4000, E = 24
-        // 30 -> 15; T = 16384, E = 32 32 -> 29, E = 64 52 -> 49; T = 32768, d = 4096, E = 16 70 -> 66.
+        // 30 -> 15; T = 16384, E = 32 32 -> 29, E = 64 52 -> 49; T = 32768, d = 4096, E = 16 70 -> 66 (the kernel has gained a
+        // few percent more since, see there).
+        // Rings: three steps, or two where that puts a second block on a CU that has one to run: T = 30000, d = 1984, E = 48
+        // 68 -> 61 us; T = 40000, d = 2048, E = 32 76 -> 67 (but T = 16384, one block per CU anyway, caches swept, 37 -> 39).
         const long tiles = (long)((s.T + 15) / 16) * ((s.E + 15) / 16);
         if (tiles <= 512) {
-            if (s.E <= 16) return run_gate_split<1, 1, 4, true>(s, X, Wg, bg, logits, idx, w, st);
-            return run_gate_split<1, 1, 4, false>(s, X, Wg, bg, logits, idx, w, st);
+            if (s.E <= 16) return run_gate_split<1, 1, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+            return run_gate_split<1, 1, 3, false>(s, X, Wg, bg, logits, idx, w, st);
         }
-        if (s.E <= 16) return run_gate_split<1, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 16) return run_gate_split<1, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 32 && s.T <= 64 * 256) return run_gate_split<2, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
         if (s.E <= 32) return run_gate_split<2, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
         if (s.E <= 48) return run_gate_split<3, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
-        if (s.E <= 64) return run_gate_split<4, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
-        return run_gate_split<4, 4, 2, false>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 64) return run_gate_split<4, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+        return run_gate_split<4, 4, 3, false>(s, X, Wg, bg, logits, idx, w, st);
     }
     return run_gate_t<bf16_t>(s, X, Wg, bg, logits, idx, w, st);
 }

@@ -93,6 +93,7 @@ def test_routing_of_many_experts(E, k):
     (33, 4160, 16), (100, 320, 20), (50, 256, 132),              # experts in blocks of 16, the last one partly empty
     (8200, 64, 16), (8193, 192, 16),                             # the last number of tokens with a block per 16, the first past it
     (4100, 320, 36), (5000, 128, 64), (3000, 192, 68),           # 64 tokens per block: three and four tiles of experts, two passes
+    (5000, 320, 20), (16384, 192, 24), (16385, 448, 32),         # two tiles of experts: rings of three steps, the last T with them, of two
     (90, 128, 18),                                               # no multiple of four: the general kernel
 ], ids=str)
 def test_gate_logits_bit_for_bit(T, d, E):
