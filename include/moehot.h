@@ -139,8 +139,8 @@ int moe_expert_counts_static(moe_handle_t h, const int32_t* idx, int32_t* counts
  *        moe_expert_counts for the same idx
  *   out: every array of *layout (host struct of device pointers); Xp[A,d] elt with
  *        Xp[r,:] = X[perm[r] / k, :] (bit copies)
- * Uses the workspace (it rebuilds the per-chunk histograms of idx there; nothing is carried over from
- * earlier calls). */
+ * Uses the workspace (it rebuilds the per-chunk histograms of idx there, unless the batch is small enough to
+ * do without; nothing is carried over from earlier calls). */
 int moe_dispatch(moe_handle_t h, const int32_t* expert_dest, const void* X, const int32_t* idx,
                  const int32_t* counts, const moe_layout_t* layout, void* Xp, void* ws, void* stream);
 

@@ -12,9 +12,9 @@
 // CU (two of the small geometry) walks its share of the tiles, which it derives on the device from
 // the group offsets (the host never reads the counts).
 //
-// Tiling: 256 x 256 output tile per block (128 x 128 where those leave the chip idle, see GeometryCost), 32-deep contraction slices moved from HBM/L2 straight
-// into a 5-deep ring of LDS buffers by buffer loads (no register staging; rows outside a ragged
-// group arrive as zeros because they lie past the end of the buffer resource), 32x32x16 bf16 MFMA
+// Tiling: 256 x 256 output tile per block (128 x 128 where those leave the chip idle, see GeometryCost), 32-deep
+// contraction slices moved from HBM/L2 straight into a 5-deep ring of LDS buffers by buffer loads (no
+// register staging; rows outside a ragged group arrive as zeros because they lie past the end of the buffer resource), 32x32x16 bf16 MFMA
 // with the accumulators in AGPRs.  An operand whose contraction index is contiguous in memory is
 // kept row-major in LDS and read with 16-byte loads; one whose contraction index is the slow one
 // is kept as it is and read with the transposing LDS load, so no operand is ever transposed in
@@ -856,9 +856,8 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     constexpr bool BWD1 = (EPI == EPI_BWD1_GELU || EPI == EPI_BWD1_SWIGLU);
     constexpr int N_PASS = EP_ROWS / ROWS_PER_PASS;        // passes per staged row of fragments
     // NN/NT: every store of the epilogue is issued whatever the tile looks like, as a buffer store whose resource
-    // ends with the tile's last valid row (or has no length at all, for an output that is not written): the number
-    // of memory instructions of an epilogue is then a constant of the instantiation, which the waits for the next
-    // tile's first slices count on (see the main loop).  TN keeps ordinary predicated stores.
+    // ends with the tile's last valid row (or has no length at all, for an output that is not written): no predicate
+    // per row.  TN keeps ordinary predicated stores.
     constexpr bool UNCOND = (KIND != KIND_TN);
     const int wcol0 = n0 + (DUAL ? wn * (WN / 2) : wn * WN);           // first column of this wave: all of its columns exist or none
     buf_rsrc_t rO0 = buf_rsrc_t(), rO1 = buf_rsrc_t(), rO2 = buf_rsrc_t();

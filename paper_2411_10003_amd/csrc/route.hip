@@ -302,8 +302,10 @@ __global__ __launch_bounds__(ROUTE_WAVES * 64) void layout_positions_kernel(
 }
 
 // The whole dispatch of a small batch (up to SMALL_CHUNKS chunks) in one launch: every block finds all positions for itself
-// (a chunk per wave, in LDS) and copies its share of the rows; block 0 publishes layout and positions.  No histogram is read.  The two launches this replaces took 8 + 5 us of the GPU in a row at T = 64 and 3 us each of
-// the host.  Gate, counts and dispatch in a row: T = 1999, d = 768, E = 16, k = 2 30 -> 20 us; T = 512, d = 64, E = 8 29 -> 18.
+// (a chunk per wave, in LDS) and copies its share of the rows; block 0 publishes layout and positions.  No histogram is
+// read.  What bounds it is latency: the two launches this replaces took 8 + 5 us of the GPU in a row at T = 64 and 3 us each
+// of the host.  Gate, counts and dispatch in a row: T = 1999, d = 768, E = 16, k = 2 30 -> 20 us; T = 512, d = 64, E = 8
+// 29 -> 18.
 constexpr int SMALL_CHUNKS = 16, SMALL_EXPERTS = 256, PIECE_VECS = 256;
 __global__ __launch_bounds__(SMALL_CHUNKS * 64) void small_dispatch_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ counts,
@@ -385,8 +387,8 @@ hipError_t launch_chunk_hist(const moe_shape_t& s, const int32_t* idx, int32_t* 
     return hipGetLastError();
 }
 
-// Histograms into chunk_hist and the counts.  Up to COUNT_CHUNKS chunks (and 256 experts: 17 LDS rows) in one launch: expert_counts alone 12 -> 8 us, of which
-// the host takes most, the two launches took 6 + 5 us of the GPU in a row.
+// Histograms into chunk_hist and the counts.  Up to COUNT_CHUNKS chunks (and 256 experts: 17 LDS rows) in one launch:
+// expert_counts alone 12 -> 8 us, of which the host takes most, the two launches took 6 + 5 us of the GPU in a row.
 hipError_t launch_counts(const moe_shape_t& s, const int32_t* idx, int32_t* chunk_hist, int n_chunks, int32_t* counts, hipStream_t st)
 {
     if (n_chunks <= COUNT_CHUNKS && s.E <= 256) {
