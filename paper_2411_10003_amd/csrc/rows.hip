@@ -82,6 +82,9 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void scatter_rows_k_kernel(
 }
 
 // out[t,:] = sum_j w[t,j] * Yp[pos[t*k+j],:]   (fp32, ascending j, one rounding)
+// Bound by HBM: what counts is how many pieces of a token's rows are on their way.  KT is k where it is 1, 2 or 4 (bf16);
+// with any k in one loop every row is a branch and one piece of each row is out at a time: k = 4, T = 8000, d = 4096 83 -> 62 us
+// (caches swept 125 -> 110), T = 8001, d = 2048 27 -> 25 (71 -> 61).  The scatter gains nothing from more registers: k = 8 97 -> 100.
 template <typename ET, int KT>
 __global__ __launch_bounds__(ROW_WAVES * 64) void combine_kernel(
     const ET* __restrict__ Yp, const int32_t* __restrict__ pos, const float* __restrict__ w,
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void combine_kernel(
     }
     uint4* dst = reinterpret_cast<uint4*>(out + (size_t)t * d);
     const int nv = d / VN;
-    constexpr int U = (KT == 1 || KT == 2) ? 4 : 1;      // 16-byte pieces per lane requested before any is used
+    constexpr int U = (KT == 1 || KT == 2) ? 4 : (KT == 4 ? 2 : 1);      // 16-byte pieces per row and lane requested before any is used
     for (int v0 = lane; v0 < nv; v0 += 64 * U) {
         uint4 raw[U][KMAX];
 #pragma unroll
@@ -159,7 +162,7 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void combine_bwd_kernel(
     }
     const uint4* gsrc = reinterpret_cast<const uint4*>(dOut + (size_t)t * d);
     const int nv = d / VN;
-    constexpr int U = (KT == 1 || KT == 2) ? 2 : 1;
+    constexpr int U = KT ? 2 : 1;
     for (int v0 = lane; v0 < nv; v0 += 64 * U) {
         uint4 graw[U], yraw[U][KMAX];
 #pragma unroll
@@ -272,6 +275,8 @@ hipError_t launch_combine(const moe_shape_t& s, const void* Yp, const int32_t* p
         hipLaunchKernelGGL((combine_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
     else if (s.k == 2)
         hipLaunchKernelGGL((combine_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
+    else if (s.k == 4)
+        hipLaunchKernelGGL((combine_kernel<bf16_t, 4>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
     else
         hipLaunchKernelGGL((combine_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
     return hipGetLastError();
@@ -290,6 +295,9 @@ hipError_t launch_combine_bwd(const moe_shape_t& s, const void* dOut, const void
                            (bf16_t*)dYp, dw, s.T, s.d, s.k);
     else if (s.k == 2)
         hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
+                           (bf16_t*)dYp, dw, s.T, s.d, s.k);
+    else if (s.k == 4)
+        hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 4>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
                            (bf16_t*)dYp, dw, s.T, s.d, s.k);
     else
         hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
