@@ -33,7 +33,9 @@ __device__ __forceinline__ void unpack_bf16x8(const uint4& v, float* f)
 // experts, in chunks of 128 per 64 tokens beyond.  In registers (what E <= 32 did before) it took 64 and 128 of them per
 // lane and left two waves per SIMD; on the vector ALUs with a readlane per expert (what E > 32 did) the LDS reads bound
 // it.  All row pieces of a group are requested before its matrix instructions, unconditionally (rows and columns past
-// the end read the last valid ones and are not stored): a load under a condition makes the compiler drain them early.
+// the end read the last valid ones and are not stored): a load under a condition makes the compiler drain them early.  An
+// assignment without a row (a negative position, what an expert id out of range leaves where the caller put it) reads row 0
+// and adds zeros.
 // Measured, us before -> after (bf16): T = 16384, d = 2048, k = 2, E = 32: 81 -> 52 (2.1 GFLOP beside 201 MB); k = 1, E = 64:
 // 377 -> 61; T = 8001, k = 4, E = 128: 524 -> 94; T = 1000, d = 512, E = 16: 43 -> 10 (16 blocks before); T = 32768,
 // d = 4096, E = 16: 172 -> 172 (807 MB, 4.7 TB/s).
@@ -82,13 +84,23 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? 4 : 2) void input_grad_k
     for (int gi = 0; gi < groups_per_wave; ++gi) {
         const int tg = (blockIdx.y * groups_per_wave + gi) * 64 + wave * 16;
         raw_t raw[4][KMAX];
+        int lowest = 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int t = min(tg + 4 * lq + r, T - 1);
 #pragma unroll
-            for (int j = 0; j < KMAX; ++j)
-                raw[r][j] = *reinterpret_cast<const raw_t*>(dXp + (size_t)pos[(size_t)t * k + (j < k ? j : 0)] * d + cc);
+            for (int j = 0; j < KMAX; ++j) {
+                const int row = pos[(size_t)t * k + (j < k ? j : 0)];
+                lowest = min(lowest, row);
+                raw[r][j] = *reinterpret_cast<const raw_t*>(dXp + (size_t)max(row, 0) * d + cc);
+            }
         }
+        if (__any(lowest < 0))
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < KMAX; ++j)
+                    if (j < k && pos[(size_t)min(tg + 4 * lq + r, T - 1) * k + j] < 0) raw[r][j] = raw_t{};
         ig_f32x4_t acc[VN];
 #pragma unroll
         for (int j = 0; j < VN; ++j) acc[j] = ig_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};

@@ -150,3 +150,27 @@ def test_input_grad_leaves_out_experts_without_a_gradient(E):
 def test_gate_gradients_pass_edges(kw):
     cfg, case = _case(1, h=64, n_replicas=0, **kw)
     _check(cfg, case, seed=kw["E"])
+
+
+@pytest.mark.parametrize("E,k,dtype", [(16, 2, "bf16"), (32, 8, "bf16"), (64, 3, "bf16"), (132, 1, "bf16"), (8, 4, "f32")])
+def test_input_grad_of_assignments_without_a_row(E, k, dtype):
+    """A negative position (an assignment that got no row) adds nothing, also where row 0 is not finite."""
+    cfg = _ig_cfg(T=70, d=192, E=E, k=k, P=1, dtype=dtype)
+    T, d, A = cfg.T, cfg.d, cfg.A
+    rng = np.random.default_rng(E + k)
+    dl = rng.standard_normal((T, E)).astype(np.float32)
+    Wg = (rng.standard_normal((d, E)) * E ** -0.5).astype(np.float32)
+    dXp = rng.standard_normal((A, d)).astype(np.float32)
+    if dtype == "bf16":
+        wl.round_to_bf16(dXp)
+    pos = rng.permutation(A).astype(np.int32)
+    pos[pos == 0] = -1                                         # nobody's row: what lies there is not to be seen
+    pos[rng.permutation(A)[: A // 5]] = -1
+    pos[k * 17: k * 18] = -7                                   # a token without any row
+    rows = np.where(pos[:, None] >= 0, dXp[np.maximum(pos, 0)], 0.0).reshape(T, k, d).astype(np.float64).sum(1)
+    want = rows + dl.astype(np.float64) @ Wg.astype(np.float64).T
+    dXp[0] = np.nan
+    hd = G.make_handle(cfg, G=4)
+    dX = torch.zeros(T, d, dtype=hd.elt, device=G.DEV)
+    hd.input_grad(G.dev(dXp, dtype), G.dev(pos), G.dev(dl), G.dev(Wg), dX)
+    G.assert_rows_close(G.host(dX), want, G.TOL[dtype], "dX")
