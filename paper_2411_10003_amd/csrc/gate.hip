@@ -613,8 +613,9 @@ hipError_t launch_gate_topk(const moe_shape_t& s, const void* X, const float* Wg
 {
     if (s.T == 0) return hipSuccess;
     if (s.dtype == MOE_F32) return run_gate_t<float>(s, X, Wg, bg, logits, idx, w, st);
-    // rows of 64 tokens must stay inside the 32-bit offsets of a buffer load
-    if (s.E % 4 == 0 && (long long)s.d * 2 * (GATE_TOK + 1) < (1ll << 31) && (long long)s.d * s.E * 4 < (1ll << 31)) {
+    // rows of 64 tokens must stay inside the 32-bit offsets of a buffer load; a load that writes LDS moves whole aligned
+    // words, so tokens that begin at an odd bf16 take the general kernel (ordinary loads need no alignment)
+    if (s.E % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 3) == 0 && (long long)s.d * 2 * (GATE_TOK + 1) < (1ll << 31) && (long long)s.d * s.E * 4 < (1ll << 31)) {
         // Few tokens: a block per 16 tokens and 16 experts (more experts: the routing is a launch of its own), so that the
         // gate matrix comes in through as many CUs as there are.  Up to 512 such blocks; beyond, 64 tokens share a block's
         // gate matrix.  The call, us, before -> now: T = 64, d = 4096, E = 16 34 -> 20; T = 1, d = 2048 19 -> 13; T = 3000,

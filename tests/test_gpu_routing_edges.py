@@ -110,3 +110,30 @@ def test_gate_logits_bit_for_bit(T, d, E):
     assert np.array_equal(G.host(b.logits).view(np.uint32), ref["logits"].view(np.uint32))
     assert np.array_equal(G.host(b.idx), ref["idx"])
     assert np.allclose(G.host(b.w), ref["w"], rtol=1e-5, atol=1e-7)
+
+
+@pytest.mark.parametrize("x_off,w_off", [(1, 0), (2, 0), (6, 0), (0, 1), (3, 3)], ids=str)
+@pytest.mark.parametrize("T,d,E", [(40, 128, 8), (8200, 64, 16), (700, 192, 48), (50, 256, 132)], ids=str)
+def test_gate_of_operands_at_any_address(T, d, E, x_off, w_off):
+    """Tokens that begin at any bf16, a gate matrix that begins at any float: the same bits."""
+    cfg = _cfg(T=T, d=d, E=E, k=2, P=1, renorm=1)
+    rng = np.random.default_rng(T + E)
+    X = wl.round_to_bf16(rng.standard_normal((T, d)).astype(np.float32))
+    Wg = (rng.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    bg = rng.standard_normal(E).astype(np.float32)
+    ref = orc.route(X, Wg, bg, cfg.k, 1)
+
+    def at(a, off, dtype):                            # the same values, `off` elements past a 16-byte boundary
+        t = G.dev(a, dtype)
+        flat = torch.zeros(t.numel() + off, dtype=t.dtype, device=G.DEV)[off:]
+        assert flat.data_ptr() % 16 == off * t.element_size() % 16
+        flat.copy_(t.reshape(-1))
+        return flat.view(t.shape)
+
+    hd = G.make_handle(cfg, G=1)
+    b = G.binding.LayerBuffers(hd, False)
+    hd.gate_topk(at(X, x_off, "bf16"), at(Wg, w_off, "f32"), G.dev(bg), b.logits, b.idx, b.w)
+    torch.cuda.synchronize()
+    assert np.array_equal(G.host(b.logits).view(np.uint32), ref["logits"].view(np.uint32))
+    assert np.array_equal(G.host(b.idx), ref["idx"])
+    assert np.allclose(G.host(b.w), ref["w"], rtol=1e-5, atol=1e-7)
