@@ -608,10 +608,14 @@ hipError_t run_gate_t(const moe_shape_t& s, const void* X, const float* Wg, cons
 
 }  // namespace
 
-hipError_t launch_gate_topk(const moe_shape_t& s, const void* X, const float* Wg, const float* bg,
-                            float* logits, int32_t* idx, float* w, hipStream_t st)
+// A launch has fewer than 2^32 threads along x.  The gate spends up to 16 threads on a token (routing of more than 64
+// experts), T may be just short of 2^30: tokens are taken 2^26 at a time.
+constexpr int GATE_LAUNCH_TOK = 1 << 26;
+static_assert(GATE_LAUNCH_TOK % GATE_TOK == 0 && GATE_LAUNCH_TOK <= (1ll << 32) / 32, "whole blocks, within a launch");
+
+static hipError_t launch_gate_part(const moe_shape_t& s, const void* X, const float* Wg, const float* bg,
+                                   float* logits, int32_t* idx, float* w, hipStream_t st)
 {
-    if (s.T == 0) return hipSuccess;
     if (s.dtype == MOE_F32) return run_gate_t<float>(s, X, Wg, bg, logits, idx, w, st);
     // rows of 64 tokens must stay inside the 32-bit offsets of a buffer load; a load that writes LDS moves whole aligned
     // words, so tokens that begin at an odd bf16 take the general kernel (ordinary loads need no alignment)
@@ -639,12 +643,30 @@ hipError_t launch_gate_topk(const moe_shape_t& s, const void* X, const float* Wg
     return run_gate_t<bf16_t>(s, X, Wg, bg, logits, idx, w, st);
 }
 
+hipError_t launch_gate_topk(const moe_shape_t& s, const void* X, const float* Wg, const float* bg,
+                            float* logits, int32_t* idx, float* w, hipStream_t st)
+{
+    const size_t row = (size_t)s.d * (s.dtype == MOE_BF16 ? 2 : 4);
+    moe_shape_t part = s;
+    hipError_t e = hipSuccess;
+    for (int t0 = 0; t0 < s.T && e == hipSuccess; t0 += part.T) {
+        part.T = s.T - t0 < GATE_LAUNCH_TOK ? s.T - t0 : GATE_LAUNCH_TOK;
+        e = launch_gate_part(part, (const char*)X + t0 * row, Wg, bg, logits + (size_t)t0 * s.E, idx + (size_t)t0 * s.k, w + (size_t)t0 * s.k, st);
+    }
+    return e;
+}
+
 hipError_t launch_gate_bwd(const moe_shape_t& s, const float* dw, const float* logits, const int32_t* idx,
                            float* dlogits, hipStream_t st)
 {
-    if (s.T == 0) return hipSuccess;
     const int tokens = GBW_THREADS / GBW_LANES;
-    hipLaunchKernelGGL(gate_bwd_kernel, dim3((s.T + tokens - 1) / tokens), dim3(GBW_THREADS), 0, st,
-                       dw, logits, idx, dlogits, s.T, s.E, s.k, s.renorm);
-    return hipGetLastError();
+    hipError_t e = hipSuccess;
+    for (int t0 = 0; t0 < s.T && e == hipSuccess; t0 += GATE_LAUNCH_TOK) {
+        const int n = s.T - t0 < GATE_LAUNCH_TOK ? s.T - t0 : GATE_LAUNCH_TOK;
+        const size_t a = (size_t)t0 * s.k, l = (size_t)t0 * s.E;
+        hipLaunchKernelGGL(gate_bwd_kernel, dim3((n + tokens - 1) / tokens), dim3(GBW_THREADS), 0, st,
+                           dw + a, logits + l, idx + a, dlogits + l, n, s.E, s.k, s.renorm);
+        e = hipGetLastError();
+    }
+    return e;
 }

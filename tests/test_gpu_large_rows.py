@@ -68,3 +68,58 @@ def test_rows_beyond_32_bit_offsets():
             assert G.rel_l2(G.host(g2[g, j, :]), r2) <= tol, (g, j)
             assert G.rel_l2(G.host(g1[g, :, j]), c1) <= tol, (g, j)
             assert G.rel_l2(G.host(g3[g, :, j]), c3) <= tol, (g, j)
+
+
+def _check_ranges(T):
+    """Tokens at the start, around the boundaries between launches and at the end."""
+    step = 1 << 26
+    return [(0, 40)] + [(t - 24, t + 40) for t in (step, 3 * step, T // step * step) if t + 40 <= T] + [(T - 33, T)]
+
+
+def test_gate_gradient_of_more_tokens_than_a_launch_takes():
+    """16 threads per token: 2^28 tokens are more threads than a launch may have."""
+    T, E = (1 << 28) + 101, 2
+    assert 16 * T > 1 << 32
+    big = binding.Handle(T=T, d=64, h=64, E=E, k=1, P=1, self_dest=0, G=1, dtype="bf16", act="gelu", renorm=0, device=G.DEV, alloc_workspace=False)
+    g = torch.Generator(device=G.DEV).manual_seed(1)
+    logits = torch.randn(T, E, device=G.DEV, generator=g)
+    dw = torch.randn(T, 1, device=G.DEV, generator=g)
+    idx = (logits[:, 1:] > logits[:, :1]).to(torch.int32)
+    dl = torch.full((T, E), 7.0, device=G.DEV)
+    big.gate_bwd(dw, logits, idx, dl)
+    torch.cuda.synchronize()
+    for a, b in _check_ranges(T):
+        want = G.orc.gate_bwd(G.host(dw[a:b]), G.host(logits[a:b]), G.host(idx[a:b]), 0)
+        G.assert_rows_close(G.host(dl[a:b]), want, 1e-5, f"dlogits {a}", floor=1.0)
+    assert not bool((dl[:, 0] == 7.0).any())
+    del logits, dw, idx, dl
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.timeout(300)
+def test_gate_of_more_tokens_than_a_launch_takes():
+    """Eight threads per token: 2^29 tokens are more threads than a launch may have (69 GB of them at d = 64)."""
+    T, d, E = (1 << 29) + 101, 64, 4
+    assert 8 * T > 1 << 32
+    big = binding.Handle(T=T, d=d, h=64, E=E, k=1, P=1, self_dest=0, G=1, dtype="bf16", act="gelu", renorm=0, device=G.DEV, alloc_workspace=False)
+    rng = np.random.default_rng(5)
+    X = torch.zeros(T, d, dtype=torch.bfloat16, device=G.DEV)
+    Wg = (rng.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    bg = rng.standard_normal(E).astype(np.float32)
+    rows = {}
+    for a, b in _check_ranges(T):
+        rows[a, b] = wl.round_to_bf16(rng.standard_normal((b - a, d)).astype(np.float32))
+        X[a:b] = G.dev(rows[a, b], "bf16")
+    logits = torch.full((T, E), 7.0, device=G.DEV)
+    idx = torch.full((T, 1), -1, dtype=torch.int32, device=G.DEV)
+    w = torch.zeros(T, 1, device=G.DEV)
+    big.gate_topk(X, G.dev(Wg), G.dev(bg), logits, idx, w)
+    torch.cuda.synchronize()
+    for (a, b), x in rows.items():
+        ref = G.orc.route(x, Wg, bg, 1, 0)
+        assert np.array_equal(G.host(logits[a:b]).view(np.uint32), ref["logits"].view(np.uint32))
+        assert np.array_equal(G.host(idx[a:b]), ref["idx"])
+        assert np.allclose(G.host(w[a:b]), ref["w"], rtol=1e-5, atol=1e-7)
+    assert not bool((idx < 0).any())
+    del X, logits, idx, w
+    torch.cuda.empty_cache()
