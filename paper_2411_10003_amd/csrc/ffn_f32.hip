@@ -232,16 +232,16 @@ __device__ __forceinline__ bool find_row_tile(const F32Args& a, int rt, int bm, 
     return false;
 }
 
-// grid: row tiles (an upper bound) x column tiles, the columns of a row tile next to each other
+// grid: column tiles x row tiles (an upper bound), so that the columns of a row tile run next to each other.  (Two axes: a
+// grid has fewer than 2^32 threads along each, and wide layers of many groups need more in all.)
 template <int MODE, class TL, bool DUAL, bool VEC>
-__global__ __launch_bounds__(F32_THREADS) void ffn_f32_kernel(F32Args a, int col_tiles)
+__global__ __launch_bounds__(F32_THREADS) void ffn_f32_kernel(F32Args a)
 {
     constexpr bool BKC = (MODE == BWD1 || MODE == BWD2);
     __shared__ __attribute__((aligned(16))) float lds[lds_floats<TL, true, BKC, DUAL>()];
-    const int ct = blockIdx.x % col_tiles;
     int g, first_row, row0, rows;
-    if (!find_row_tile(a, blockIdx.x / col_tiles, TL::BM, g, first_row, row0, rows)) return;
-    const int d = a.d, h = a.h, n0 = ct * TL::BN, nr = rows - first_row;
+    if (!find_row_tile(a, blockIdx.y, TL::BM, g, first_row, row0, rows)) return;
+    const int d = a.d, h = a.h, n0 = blockIdx.x * TL::BN, nr = rows - first_row;
     const bool swiglu = a.act == MOE_ACT_SWIGLU;
     const long r0 = (long)row0 + first_row, wdh = (long)g * d * h;
     f32x16 acc, acc2;
@@ -289,13 +289,12 @@ __global__ __launch_bounds__(F32_THREADS) void ffn_f32_kernel(F32Args a, int col
 }
 
 // Weight gradients, all products of all groups in one launch: out[m, n] = sum over the group's rows r of L[r, m] R[r, n]
-// (dW1 = Xp^T dZ, dW2 = Act^T dYp, dW3 = Xp^T dU).  grid: groups x (tiles of dW1, dW2, dW3).
+// (dW1 = Xp^T dZ, dW2 = Act^T dYp, dW3 = Xp^T dU).  grid: tiles of a product x (products of group 0, of group 1, ...).
 template <class TL, bool VEC>
-__global__ __launch_bounds__(F32_THREADS) void ffn_f32_wgrad_kernel(F32Args a, int tiles_per_product, int n_products)
+__global__ __launch_bounds__(F32_THREADS) void ffn_f32_wgrad_kernel(F32Args a, int n_products)
 {
     __shared__ __attribute__((aligned(16))) float lds[lds_floats<TL, false, false, false>()];
-    const int g = blockIdx.x / (tiles_per_product * n_products), in_g = blockIdx.x % (tiles_per_product * n_products);
-    const int which = in_g / tiles_per_product, tile = in_g % tiles_per_product;
+    const int g = blockIdx.y / n_products, which = blockIdx.y % n_products, tile = blockIdx.x;
     int first, ng;
     hosted_range(a.dest_slots, a.self, a.Gcap, first, ng);
     int row0 = 0, rows = 0;
@@ -355,8 +354,8 @@ template <int MODE, class TL, bool DUAL>
 void launch_rows_t(const moe_shape_t& s, const F32Args& f, int N, bool vec, hipStream_t st)
 {
     const int ct = cdiv(N, TL::BN), rt = cdiv(s.T * s.k, TL::BM) + s.G;
-    if (vec) hipLaunchKernelGGL((ffn_f32_kernel<MODE, TL, DUAL, true>), dim3((unsigned)ct * rt), dim3(F32_THREADS), 0, st, f, ct);
-    else hipLaunchKernelGGL((ffn_f32_kernel<MODE, TL, DUAL, false>), dim3((unsigned)ct * rt), dim3(F32_THREADS), 0, st, f, ct);
+    if (vec) hipLaunchKernelGGL((ffn_f32_kernel<MODE, TL, DUAL, true>), dim3(ct, rt), dim3(F32_THREADS), 0, st, f);
+    else hipLaunchKernelGGL((ffn_f32_kernel<MODE, TL, DUAL, false>), dim3(ct, rt), dim3(F32_THREADS), 0, st, f);
 }
 
 template <int MODE, bool DUAL>
@@ -372,9 +371,9 @@ hipError_t launch_wgrad(const moe_shape_t& s, const F32Args& f, bool vec, hipStr
 {
     const int tiles = cdiv(s.d, TL::BM) * cdiv(s.h, TL::BN), np = s.act == MOE_ACT_SWIGLU ? 3 : 2;
     static_assert(TL::BM == TL::BN, "d x h and h x d have the same number of tiles");
-    const dim3 grid((unsigned)tiles * np * s.G);
-    if (vec) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, true>), grid, dim3(F32_THREADS), 0, st, f, tiles, np);
-    else hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, false>), grid, dim3(F32_THREADS), 0, st, f, tiles, np);
+    const dim3 grid(tiles, np * s.G);
+    if (vec) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, true>), grid, dim3(F32_THREADS), 0, st, f, np);
+    else hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, false>), grid, dim3(F32_THREADS), 0, st, f, np);
     return hipGetLastError();
 }
 

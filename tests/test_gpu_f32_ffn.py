@@ -75,3 +75,47 @@ def test_unaligned_operands_give_the_same_bits(G, act):
         assert (a is None) == (c is None)
         if a is not None:
             assert np.array_equal(G.host(a).view(np.uint32), G.host(c).view(np.uint32))
+
+
+@pytest.mark.timeout(300)
+def test_more_tiles_than_the_threads_of_one_axis(G):
+    """The most groups, the narrowest rows and a wide hidden layer: 2^24 blocks of 256 threads and more, of which a few have
+    rows.  Against a float64 product; tolerance as above for the weight gradients.  Yp and dXp are sums of K = h terms taken one
+    after the other: partial sum i is about i^0.5 terms large and rounded by 2^-24 / 3^0.5 of itself (rms), together
+    (K / 2)^0.5 2^-24 / 3^0.5 = 2.5e-5 of the whole sum, of which four times is allowed."""
+    E, d, h = 1024, 4, (1 << 20) + 64
+    assert 1024 * (h // 64) * 256 > 1 << 32
+    used = {0: 3, 1: 1, 700: 40, 1023: 20}
+    A = sum(used.values())
+    hd = G.binding.Handle(T=A, d=d, h=h, E=E, k=1, P=1, self_dest=0, G=E, dtype="f32", act="gelu", renorm=0, device=G.DEV)
+    g = torch.Generator(device=G.DEV).manual_seed(9)
+    idx = torch.tensor([e for e, n in used.items() for _ in range(n)], dtype=torch.int32, device=G.DEV)
+    counts, lay = torch.zeros(E, dtype=torch.int32, device=G.DEV), hd.new_layout()
+    X, dYp = torch.randn(A, d, device=G.DEV, generator=g), torch.randn(A, d, device=G.DEV, generator=g)
+    Xp, Z = torch.empty(A, d, device=G.DEV), torch.zeros(A, h, device=G.DEV)
+    hd.expert_counts(idx, counts)
+    hd.dispatch(torch.zeros(E, dtype=torch.int32, device=G.DEV), X, idx, counts, lay, Xp)
+    W1, W2 = torch.zeros(E, d, h, device=G.DEV), torch.zeros(E, h, d, device=G.DEV)
+    for e in used:
+        W1[e] = torch.randn(d, h, device=G.DEV, generator=g) * d ** -0.5
+        W2[e] = torch.randn(h, d, device=G.DEV, generator=g) * h ** -0.5
+    Yp, dXp = torch.full((A, d), 7.0, device=G.DEV), torch.full((A, d), 7.0, device=G.DEV)
+    dW1, dW2 = torch.full((E, d, h), 7.0, device=G.DEV), torch.full((E, h, d), 7.0, device=G.DEV)
+    hd.expert_ffn_fwd(Xp, lay, W1, W2, None, Yp, Z, None)
+    hd.expert_ffn_bwd(dYp, Xp, Z, None, lay, W1, W2, None, dXp, dW1, dW2, None)
+    torch.cuda.synchronize()
+    chain = 4 * (h / 2 / 3) ** 0.5 * 2.0 ** -24
+    o = 0
+    for e, n in used.items():
+        x, dy, w1, w2 = Xp[o:o + n].double(), dYp[o:o + n].double(), W1[e].double(), W2[e].double()
+        z = x @ w1
+        cdf = 0.5 * (1 + torch.erf(z * 0.5 ** 0.5))
+        dz = (dy @ w2.t()) * (cdf + z * torch.exp(-0.5 * z * z) * (2 * np.pi) ** -0.5)
+        for got, want, what in ((Yp[o:o + n], (z * cdf) @ w2, "Yp"), (dXp[o:o + n], dz @ w1.t(), "dXp"),
+                                (dW1[e], x.t() @ dz, "dW1"), (dW2[e].t(), dy.t() @ (z * cdf), "dW2")):
+            G.assert_rows_close(G.host(got), want.cpu().numpy(), 1e-5 if what[:2] == "dW" else chain, f"{what} {e}")
+        o += n
+    for e in (2, 512, 1022):
+        assert not bool(dW1[e].any()) and not bool(dW2[e].any())
+    del W1, W2, dW1, dW2
+    torch.cuda.empty_cache()
