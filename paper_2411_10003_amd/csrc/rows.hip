@@ -247,77 +247,106 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void dispatch_bwd_kernel(
 
 inline dim3 row_grid(int T) { return dim3((T + ROW_WAVES - 1) / ROW_WAVES); }
 
+// A launch has fewer than 2^32 threads, a token takes 64 of them, T may be just short of 2^30: tokens are taken 2^25 at a
+// time (one launch for all but the largest batches).
+constexpr int ROW_LAUNCH_TOK = 1 << 25;
+template <typename LAUNCH>                               // launch(first token, shape of the part)
+hipError_t for_token_parts(const moe_shape_t& s, LAUNCH launch)
+{
+    moe_shape_t part = s;
+    hipError_t e = hipSuccess;
+    for (int t0 = 0; t0 < s.T && e == hipSuccess; t0 += part.T) {
+        part.T = s.T - t0 < ROW_LAUNCH_TOK ? s.T - t0 : ROW_LAUNCH_TOK;
+        launch((size_t)t0, part);
+        e = hipGetLastError();
+    }
+    return e;
+}
+inline size_t row_bytes(const moe_shape_t& s) { return (size_t)s.d * (s.dtype == MOE_BF16 ? 2 : 4); }
+inline const void* at(const void* p, size_t bytes) { return (const char*)p + bytes; }
+inline void* at(void* p, size_t bytes) { return (char*)p + bytes; }
+
 }  // namespace
 
-hipError_t launch_scatter_rows(const moe_shape_t& s, const void* X, const int32_t* pos, void* Xp, hipStream_t st)
+hipError_t launch_scatter_rows(const moe_shape_t& all, const void* X0, const int32_t* pos0, void* Xp, hipStream_t st)
 {
-    if (s.T == 0) return hipSuccess;
-    const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
-    if (s.dtype == MOE_F32) {
-        hipLaunchKernelGGL(scatter_rows_kernel<float>, g, b, 0, st, (const float*)X, pos, (float*)Xp, s.T, s.d, s.k);
-    } else if (s.k == 1) {
-        hipLaunchKernelGGL((scatter_rows_k_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d);
-    } else if (s.k == 2) {
-        hipLaunchKernelGGL((scatter_rows_k_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d);
-    } else {
-        hipLaunchKernelGGL(scatter_rows_kernel<bf16_t>, g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d, s.k);
-    }
-    return hipGetLastError();
+    return for_token_parts(all, [&](size_t t0, const moe_shape_t& s) {
+        const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
+        const void* X = at(X0, t0 * row_bytes(s));
+        const int32_t* pos = pos0 + t0 * s.k;
+        if (s.dtype == MOE_F32)
+            hipLaunchKernelGGL(scatter_rows_kernel<float>, g, b, 0, st, (const float*)X, pos, (float*)Xp, s.T, s.d, s.k);
+        else if (s.k == 1)
+            hipLaunchKernelGGL((scatter_rows_k_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d);
+        else if (s.k == 2)
+            hipLaunchKernelGGL((scatter_rows_k_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d);
+        else
+            hipLaunchKernelGGL(scatter_rows_kernel<bf16_t>, g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d, s.k);
+    });
 }
 
-hipError_t launch_combine(const moe_shape_t& s, const void* Yp, const int32_t* pos, const float* w, void* out, hipStream_t st)
+hipError_t launch_combine(const moe_shape_t& all, const void* Yp, const int32_t* pos0, const float* w0, void* out0, hipStream_t st)
 {
-    if (s.T == 0) return hipSuccess;
-    const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
-    if (s.dtype == MOE_F32)
-        hipLaunchKernelGGL((combine_kernel<float, 0>), g, b, 0, st, (const float*)Yp, pos, w, (float*)out, s.T, s.d, s.k);
-    else if (s.k == 1)
-        hipLaunchKernelGGL((combine_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
-    else if (s.k == 2)
-        hipLaunchKernelGGL((combine_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
-    else if (s.k == 4)
-        hipLaunchKernelGGL((combine_kernel<bf16_t, 4>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
-    else
-        hipLaunchKernelGGL((combine_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
-    return hipGetLastError();
+    return for_token_parts(all, [&](size_t t0, const moe_shape_t& s) {
+        const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
+        const int32_t* pos = pos0 + t0 * s.k;
+        const float* w = w0 + t0 * s.k;
+        void* out = at(out0, t0 * row_bytes(s));
+        if (s.dtype == MOE_F32)
+            hipLaunchKernelGGL((combine_kernel<float, 0>), g, b, 0, st, (const float*)Yp, pos, w, (float*)out, s.T, s.d, s.k);
+        else if (s.k == 1)
+            hipLaunchKernelGGL((combine_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
+        else if (s.k == 2)
+            hipLaunchKernelGGL((combine_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
+        else if (s.k == 4)
+            hipLaunchKernelGGL((combine_kernel<bf16_t, 4>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
+        else
+            hipLaunchKernelGGL((combine_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
+    });
 }
 
-hipError_t launch_combine_bwd(const moe_shape_t& s, const void* dOut, const void* Yp, const int32_t* pos,
-                              const float* w, void* dYp, float* dw, hipStream_t st)
+hipError_t launch_combine_bwd(const moe_shape_t& all, const void* dOut0, const void* Yp, const int32_t* pos0,
+                              const float* w0, void* dYp, float* dw0, hipStream_t st)
 {
-    if (s.T == 0) return hipSuccess;
-    const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
-    if (s.dtype == MOE_F32)
-        hipLaunchKernelGGL((combine_bwd_kernel<float, 0>), g, b, 0, st, (const float*)dOut, (const float*)Yp, pos, w,
-                           (float*)dYp, dw, s.T, s.d, s.k);
-    else if (s.k == 1)
-        hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
-                           (bf16_t*)dYp, dw, s.T, s.d, s.k);
-    else if (s.k == 2)
-        hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
-                           (bf16_t*)dYp, dw, s.T, s.d, s.k);
-    else if (s.k == 4)
-        hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 4>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
-                           (bf16_t*)dYp, dw, s.T, s.d, s.k);
-    else
-        hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
-                           (bf16_t*)dYp, dw, s.T, s.d, s.k);
-    return hipGetLastError();
+    return for_token_parts(all, [&](size_t t0, const moe_shape_t& s) {
+        const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
+        const void* dOut = at(dOut0, t0 * row_bytes(s));
+        const int32_t* pos = pos0 + t0 * s.k;
+        const float* w = w0 + t0 * s.k;
+        float* dw = dw0 + t0 * s.k;
+        if (s.dtype == MOE_F32)
+            hipLaunchKernelGGL((combine_bwd_kernel<float, 0>), g, b, 0, st, (const float*)dOut, (const float*)Yp, pos, w,
+                               (float*)dYp, dw, s.T, s.d, s.k);
+        else if (s.k == 1)
+            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
+                               (bf16_t*)dYp, dw, s.T, s.d, s.k);
+        else if (s.k == 2)
+            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
+                               (bf16_t*)dYp, dw, s.T, s.d, s.k);
+        else if (s.k == 4)
+            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 4>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
+                               (bf16_t*)dYp, dw, s.T, s.d, s.k);
+        else
+            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
+                               (bf16_t*)dYp, dw, s.T, s.d, s.k);
+    });
 }
 
-hipError_t launch_dispatch_bwd(const moe_shape_t& s, const void* dXp, const int32_t* pos, void* dX, hipStream_t st)
+hipError_t launch_dispatch_bwd(const moe_shape_t& all, const void* dXp, const int32_t* pos0, void* dX0, hipStream_t st)
 {
-    if (s.T == 0) return hipSuccess;
-    const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
-    if (s.dtype == MOE_F32)
-        hipLaunchKernelGGL((dispatch_bwd_kernel<float, 0>), g, b, 0, st, (const float*)dXp, pos, (float*)dX, s.T, s.d, s.k);
-    else if (s.k == 1)
-        hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
-    else if (s.k == 2)
-        hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
-    else
-        hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
-    return hipGetLastError();
+    return for_token_parts(all, [&](size_t t0, const moe_shape_t& s) {
+        const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
+        const int32_t* pos = pos0 + t0 * s.k;
+        void* dX = at(dX0, t0 * row_bytes(s));
+        if (s.dtype == MOE_F32)
+            hipLaunchKernelGGL((dispatch_bwd_kernel<float, 0>), g, b, 0, st, (const float*)dXp, pos, (float*)dX, s.T, s.d, s.k);
+        else if (s.k == 1)
+            hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
+        else if (s.k == 2)
+            hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
+        else
+            hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
+    });
 }
 
 // ---- Trans on one GPU (Section 4.1: the parameters of a selected expert are transferred to the devices

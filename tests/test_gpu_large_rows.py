@@ -123,3 +123,40 @@ def test_gate_of_more_tokens_than_a_launch_takes():
     assert not bool((idx < 0).any())
     del X, logits, idx, w
     torch.cuda.empty_cache()
+
+
+@pytest.mark.timeout(300)
+def test_row_movers_of_more_tokens_than_a_launch_takes():
+    """64 threads per token: 2^26 tokens are more threads than a launch may have.  Weights of one and zero logit gradients, so
+    that every result is a copy."""
+    T, d, E = (1 << 26) + 101, 64, 2
+    hd = binding.Handle(T=T, d=d, h=64, E=E, k=1, P=1, self_dest=0, G=2, dtype="bf16", act="gelu", renorm=0, device=G.DEV)
+    g = torch.Generator(device=G.DEV).manual_seed(3)
+    X = torch.randint(0x3e00, 0x4000, (T, d), dtype=torch.int16, device=G.DEV, generator=g).view(torch.bfloat16)     # 0.125 to 2
+    idx = torch.randint(0, E, (T, 1), dtype=torch.int32, device=G.DEV, generator=g)
+    counts, lay = torch.zeros(E, dtype=torch.int32, device=G.DEV), hd.new_layout()
+    Xp = torch.zeros(T, d, dtype=torch.bfloat16, device=G.DEV)
+    bits = lambda t: t.view(torch.int16)                          # noqa: E731
+    hd.expert_counts(idx, counts)
+    hd.dispatch(torch.zeros(E, dtype=torch.int32, device=G.DEV), X, idx, counts, lay, Xp)
+    torch.cuda.synchronize()
+    assert counts.tolist() == torch.bincount(idx.view(-1), minlength=E).tolist()
+    assert torch.equal(lay.perm.long(), torch.argsort(idx.view(-1), stable=True))
+    assert torch.equal(bits(Xp), bits(X)[lay.perm.long()])
+    del hd.ws
+    ones, out = torch.ones(T, 1, device=G.DEV), torch.zeros(T, d, dtype=torch.bfloat16, device=G.DEV)
+    hd.combine(Xp, lay.pos, ones, out)
+    assert torch.equal(out, X)
+    hd.dispatch_bwd(Xp, lay.pos, out.zero_())
+    assert torch.equal(out, X)
+    hd.input_grad(Xp, lay.pos, torch.zeros(T, E, device=G.DEV), torch.ones(d, E, device=G.DEV), out.zero_())
+    assert torch.equal(out, X)
+    dw = torch.full((T, 1), 7.0, device=G.DEV)
+    hd.combine_bwd(X, Xp, lay.pos, ones, out.zero_(), dw)
+    assert torch.equal(out, Xp)
+    for a, b in [(0, 40)] + [(t - 24, t + 40) for t in (1 << 25, 1 << 26)] + [(T - 33, T)]:
+        want = (X[a:b].double() ** 2).sum(1)
+        assert torch.allclose(dw[a:b, 0].double(), want, rtol=1e-5, atol=0)
+    assert not bool((dw == 7.0).any())
+    del X, Xp, idx, lay, ones, out, dw
+    torch.cuda.empty_cache()
