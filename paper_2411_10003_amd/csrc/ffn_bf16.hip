@@ -84,6 +84,27 @@ struct GemmParams {
     int split_max, split_slices; // parts of a tile at most, slices of a part at least
 };
 
+// How contractions are cut, for the kernel (which alone knows the rows) and for moe_ffn_tiling (which is told them).
+// NN/NT: parts of each of the `rem` tiles left over after the last full round of `nblk` blocks.
+__host__ __device__ inline int row_parts(int rem, int nblk, int slices, int split_max, int split_slices, int split_cap)
+{
+    if (rem <= 0) return 1;
+    const int fill = nblk / rem, worth = slices / split_slices;    // a part has to be worth its round trip
+    int S = fill < split_max ? fill : split_max;
+    if (S > worth) S = worth > 1 ? worth : 1;
+    return rem * S > split_cap ? 1 : S;
+}
+// TN: slices of a block's share of all the work (tiles: of one group; slices: of all groups), and the parts of a group of k
+// slices: of about that share, none under split_slices.
+__host__ __device__ inline int tn_share(int tiles, int slices, int groups, int tn_over, int nblk) { return (int)((long)tiles * (slices + groups * tn_over) / nblk); }
+__host__ __device__ inline int tn_parts(int k, int share, int tn_over, int split_max, int split_slices)
+{
+    if (k + tn_over <= share + share / 4) return 1;
+    const int len = share - tn_over > split_slices ? share - tn_over : split_slices;
+    const int n = (k + len - 1) / len;
+    return n < split_max ? n : split_max;
+}
+
 // GELU (Eq. 2 with the Gaussian CDF) and its derivative from one exponential and one reciprocal: erf by the
 // five-term rational approximation of Abramowitz & Stegun 7.1.26 (absolute error below 1.5e-7, two orders under
 // what a bf16 output resolves), whose exp(-x^2) at x = z / sqrt(2) is also the density the derivative needs.  The
@@ -280,11 +301,8 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     const int nblk = gridDim.x;
     const int n_full = (KIND == KIND_TN) ? 0 : (n_act / nblk) * nblk, rem = n_act - n_full;
     int S = 1;
-    if (KIND != KIND_TN && rem > 0 && p.split_ws != nullptr) {
-        S = min(p.split_max, nblk / rem);
-        S = min(S, max(1, p.n_seg * (p.Kseg / BK) / p.split_slices));   // a part has to be worth its round trip
-        if (rem * S > p.split_cap) S = 1;
-    }
+    if (KIND != KIND_TN && p.split_ws != nullptr)
+        S = row_parts(rem, nblk, p.n_seg * (p.Kseg / BK), p.split_max, p.split_slices, p.split_cap);
     if (KIND != KIND_TN && FIN && S == 1) return;
     const int n_items = n_full + rem * S;
     const int n_rounds = (n_items + q_stride - 1) / q_stride;
@@ -311,11 +329,7 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         int all = k;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) all += __shfl_xor(all, off, 64);
-        const int share = (int)((long)tiles_g * (all + p.Gcap * p.tn_over) / nblk);
-        if (k + p.tn_over > share + share / 4) {
-            const int len = max(share - p.tn_over, p.split_slices);
-            tn_split = min(p.split_max, (k + len - 1) / len);
-        }
+        tn_split = tn_parts(k, tn_share(tiles_g, all, p.Gcap, p.tn_over, nblk), p.tn_over, p.split_max, p.split_slices);
         tn_split_mask = __ballot(tn_split > 1);
         if (tn_split_mask) {
             tn_split = max(1, min(tn_split, p.split_cap / (tiles_g * __popcll(tn_split_mask))));    // what the workspace holds
@@ -1085,9 +1099,12 @@ double row_contraction_cost(const GeometryCost& c, double tiles, int slices, int
     return std::max(t, weight_mb / c.hbm);
 }
 constexpr int SMALL_SPLIT_SLICES = 16;
+constexpr int SMALL_BAND = 8;                              // 64 tiles in flight on an XCD: 8 x 8 of 128 x 128
 // weight gradients: what a tile costs beside its slices, in slices, and the least slices of a part
 template <class GEO> constexpr int TN_OVER = GEO::BLOCKS == 1 ? 24 : 16;
 template <class GEO> constexpr int TN_SPLIT_SLICES = GEO::BLOCKS == 1 ? 48 : 32;
+template <class GEO> constexpr int SPLIT_MAX = GEO::BLOCKS == 1 ? LARGE_COST.split_max : SMALL_COST.split_max;
+template <class GEO> constexpr int SPLIT_CAP = (int)((size_t)SPLIT_UNITS * Large::UNIT_BYTES / GEO::UNIT_BYTES);
 // Large: a part of a split tile has to be worth its 256-KB round trip, 64 slices where the split only shortens the last of
 // several rounds, 24 where it is what fills the chip (d = 768, h = 3072, 33 tiles of 96 slices: 69 us whole, 45 in four parts).
 inline int large_split_slices(double tiles) { return tiles <= 2.0 * LARGE_COST.tiles_at_once ? 24 : 64; }
@@ -1160,9 +1177,8 @@ hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, hipStream_
     }
     const int grid = cus * GEO::BLOCKS;
     p.tn_over = TN_OVER<GEO>;
-    p.split_max = GEO::BLOCKS == 1 ? LARGE_COST.split_max : SMALL_COST.split_max;
-    if (KIND != KIND_TN && p.n_seg * (p.Kseg / BK) < 2 * p.split_slices) p.split_ws = nullptr;     // too short to be split
-    p.split_cap = (int)((size_t)SPLIT_UNITS * Large::UNIT_BYTES / GEO::UNIT_BYTES);
+    p.split_max = SPLIT_MAX<GEO>;
+    p.split_cap = SPLIT_CAP<GEO>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.split_ws == nullptr) return e;
@@ -1171,25 +1187,31 @@ hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, hipStream_
     return hipGetLastError();
 }
 
+// The geometry of a contraction and whether it may be cut (then a finishing launch follows).
+struct Tiling { bool small, cut; int split_slices; };
+Tiling row_tiling(const moe_shape_t& s, int N, int slices, int n_seg, int epi)
+{
+    Tiling t;
+    t.small = small_wins_rows(s, N, slices, n_seg, epi);
+    t.split_slices = t.small ? SMALL_SPLIT_SLICES : large_split_slices(tiles_of(s, Large::BM, N, epi == EPI_FWD1_SWIGLU ? Large::BN / 2 : Large::BN));
+    t.cut = slices >= 2 * t.split_slices;                  // else too short
+    return t;
+}
+Tiling wgrad_tiling(const moe_shape_t& s, int Mout, int N)
+{
+    const WgradPlan l = wgrad_plan<Large>(s, Mout, N), m = wgrad_plan<Small>(s, Mout, N);
+    const bool small = m.us < l.us;
+    return Tiling{small, small ? m.cut : l.cut, small ? TN_SPLIT_SLICES<Small> : TN_SPLIT_SLICES<Large>};
+}
+
 template <int KIND, int EPI>
 hipError_t launch(GemmParams p, const moe_shape_t& s, hipStream_t st)
 {
-    const int A = s.T * s.k;
-    if constexpr (KIND == KIND_TN) {
-        const WgradPlan l = wgrad_plan<Large>(s, p.Mout, p.N), m = wgrad_plan<Small>(s, p.Mout, p.N);
-        const bool small = m.us < l.us;
-        if (!(small ? m.cut : l.cut)) p.split_ws = nullptr;
-        p.split_slices = small ? TN_SPLIT_SLICES<Small> : TN_SPLIT_SLICES<Large>;
-        return small ? launch_geo<KIND, EPI, Small>(p, A, s.G, st) : launch_geo<KIND, EPI, Large>(p, A, s.G, st);
-    } else {
-        if (small_wins_rows(s, p.N, p.n_seg * (p.Kseg / BK), p.n_seg, EPI)) {
-            p.band = 8;                                    // 64 tiles in flight on an XCD: 8 x 8 of 128 x 128
-            p.split_slices = SMALL_SPLIT_SLICES;
-            return launch_geo<KIND, EPI, Small>(p, A, s.G, st);
-        }
-        p.split_slices = large_split_slices(tiles_of(s, Large::BM, p.N, EPI == EPI_FWD1_SWIGLU ? Large::BN / 2 : Large::BN));
-        return launch_geo<KIND, EPI, Large>(p, A, s.G, st);
-    }
+    const Tiling t = KIND == KIND_TN ? wgrad_tiling(s, p.Mout, p.N) : row_tiling(s, p.N, p.n_seg * (p.Kseg / BK), p.n_seg, EPI);
+    if (!t.cut) p.split_ws = nullptr;
+    p.split_slices = t.split_slices;
+    if (KIND != KIND_TN && t.small) p.band = SMALL_BAND;
+    return t.small ? launch_geo<KIND, EPI, Small>(p, s.T * s.k, s.G, st) : launch_geo<KIND, EPI, Large>(p, s.T * s.k, s.G, st);
 }
 
 GemmParams base_params(const moe_shape_t& s, const ffn_args& a)
@@ -1280,4 +1302,46 @@ hipError_t launch_ffn_bwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
         if (e != hipSuccess) return e;
     }
     return wgrad(a.Act, h, s.h, a.dYp, d, s.d, a.dW2);
+}
+
+int moe_ffn_tiling(moe_handle_t hd, int contraction, int cus, int n_groups, const int32_t* rows, int32_t* out)
+{
+    if (!hd || !rows || !out) return MOE_ERR_NULL;
+    const moe_shape_t& s = hd->s;
+    if (s.dtype != MOE_BF16) return MOE_ERR_DTYPE;
+    if (contraction < 0 || contraction > 5 || cus < 8 || n_groups < 0 || n_groups > s.G) return MOE_ERR_SHAPE;
+    const bool swiglu = s.act == MOE_ACT_SWIGLU, wgrad = contraction >= 4, wide = contraction == 0 || contraction == 2;
+    const int epi = contraction == 0 ? (swiglu ? EPI_FWD1_SWIGLU : EPI_FWD1_GELU)
+                  : contraction == 2 ? (swiglu ? EPI_BWD1_SWIGLU : EPI_BWD1_GELU) : EPI_BF16;
+    const int Mout = contraction == 5 ? s.h : s.d, N = wgrad ? (contraction == 5 ? s.d : s.h) : (wide ? s.h : s.d);
+    const int n_seg = contraction == 3 && swiglu ? 2 : 1, slices = n_seg * ((wide ? s.d : s.h) / BK);
+    const Tiling t = wgrad ? wgrad_tiling(s, Mout, N) : row_tiling(s, N, slices, n_seg, epi);
+    const int side = t.small ? Small::BM : Large::BM, bn = epi == EPI_FWD1_SWIGLU ? side / 2 : side;
+    const int nblk = cus / 8 * 8 * (t.small ? Small::BLOCKS : Large::BLOCKS);
+    const int split_max = t.small ? SPLIT_MAX<Small> : SPLIT_MAX<Large>, cap = t.small ? SPLIT_CAP<Small> : SPLIT_CAP<Large>;
+    const int band[5] = {BAND_FWD1, BAND_FWD2, BAND_BWD1, BAND_BWD2, BAND_WGRAD};
+    int row_tiles = 0, all = 0;
+    for (int g = 0; g < n_groups; ++g) { row_tiles += (rows[g] + side - 1) / side; all += (rows[g] + BK - 1) / BK; }
+    if (wgrad) row_tiles = (Mout + side - 1) / side;
+    const int col_tiles = (N + bn - 1) / bn, tiles = row_tiles * col_tiles, n_full = wgrad ? tiles : tiles / nblk * nblk;
+    out[0] = side; out[1] = nblk; out[2] = row_tiles; out[3] = col_tiles; out[4] = n_full;
+    out[5] = !wgrad && t.cut ? row_parts(tiles - n_full, nblk, slices, split_max, t.split_slices, cap) : 1;
+    out[6] = t.small && !wgrad ? SMALL_BAND : band[wgrad ? 4 : contraction];
+    out[7] = t.cut; out[8] = wgrad ? all : slices; out[9] = (int32_t)estimated_rows(s);
+    if (!wgrad) return MOE_OK;
+    const int over = t.small ? TN_OVER<Small> : TN_OVER<Large>, share = tn_share(tiles, all, s.G, over, nblk);
+    int parts[64], n_cut = 0, total = 0;
+    for (int g = 0; g < s.G; ++g) {
+        parts[g] = t.cut && g < n_groups ? tn_parts((rows[g] + BK - 1) / BK, share, over, split_max, t.split_slices) : 1;
+        n_cut += parts[g] > 1;
+    }
+    for (int g = 0; g < s.G; ++g) {
+        if (n_cut > 0) { const int most = cap / (tiles * n_cut); if (parts[g] > most) parts[g] = most > 1 ? most : 1; }
+        total += parts[g];
+    }
+    for (int g = 0; g < s.G; ++g) {
+        out[10 + g] = total > 64 ? 1 : parts[g];
+        if (out[10 + g] > out[5]) out[5] = out[10 + g];
+    }
+    return MOE_OK;
 }

@@ -100,6 +100,13 @@ hipError_t launch_ffn_bwd_f32(const moe_shape_t& s, const ffn_args& a, hipStream
 hipError_t launch_ffn_fwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStream_t st);
 hipError_t launch_ffn_bwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStream_t st);
 
+// For the tests, not part of the interface: how the bf16 FFN lays out one of its contractions (0 fwd1, 1 fwd2, 2 bwd1, 3 bwd2,
+// 4 dW1 and dW3, 5 dW2) for hosted groups of rows[0 .. n_groups) rows on a GPU of `cus` CUs.  Host only, launches nothing.
+//   out[0..9]: side of a tile, blocks, row tiles, column tiles, tiles in full rounds, parts of the others (4, 5: of the
+//   group cut into most), row tiles per band, whether a finishing launch follows, slices of the contraction (4, 5: of all
+//   groups), rows the choice is made for.  4, 5: out[10 .. 10 + G) are the parts of each group.
+extern "C" int moe_ffn_tiling(moe_handle_t h, int contraction, int cus, int n_groups, const int32_t* rows, int32_t* out);
+
 // ---- small device helpers ----------------------------------------------------------------
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
 // Two floats to a pair of bf16, round-to-nearest-even, NaN stays NaN: the hardware conversion of gfx950

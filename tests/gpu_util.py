@@ -3,6 +3,7 @@ binding, and compute the oracle's answers for the same inputs (complete for smal
 sampled rows / hidden units for the full-size configurations)."""
 from __future__ import annotations
 
+import ctypes
 from typing import Dict, Optional
 
 import numpy as np
@@ -76,37 +77,45 @@ def assert_rows_close(got, want, tol: float, what: str = "", floor: float = 0.02
     return worst
 
 
-# ---- which tiles the grouped matrix kernel works on (the test picks its samples from this; it mirrors the
-# kernel's tile walk: 256-row tiles from each group's first row, bands of 8 row tiles walked column by column,
-# and the tiles left after the last full round of the chip, which are split along the contraction)
-FFN_BM, FFN_SPLIT_UNITS = 256, 320
-FFN_BAND = {"fwd1": 16, "fwd2": 8, "bwd1": 8, "bwd2": 8}     # row tiles per band of each contraction's tile walk
+# ---- which tiles the grouped matrix kernel works on: geometry, cuts and tile walk as the library itself gives them for the
+# handle and the rows of its groups (the tests pick their samples and check what they cover by this)
+FFN_CONTRACTIONS = ("fwd1", "fwd2", "bwd1", "bwd2", "dW1", "dW2")
 
 
-def ffn_row_tiles(group_rows):
-    """[(group, first row, end row)] of every 256-row tile, in the kernel's order."""
+def ffn_tiling(hd, rows, cus: Optional[int] = None) -> Dict[str, dict]:
+    """Per contraction: side of a tile, blocks, row and column tiles, tiles in full rounds, parts of each of the others (of the
+    weight gradients: of every group), row tiles per band, whether a finishing launch follows, slices."""
+    if cus is None:
+        cus = torch.cuda.get_device_properties(0).multi_processor_count
+    lib, n, got = binding.load(), len(rows), {}
+    r, out = (ctypes.c_int32 * max(n, 1))(*[int(x) for x in rows]), (ctypes.c_int32 * (10 + hd.G))()
+    for c, name in enumerate(FFN_CONTRACTIONS):
+        rc = lib.moe_ffn_tiling(hd._h, c, cus, n, r, out)
+        assert rc == 0, (name, rc)
+        got[name] = dict(zip(("side", "blocks", "row_tiles", "col_tiles", "n_full", "parts", "band", "finish", "slices", "est"), out))
+        if c >= 4:
+            got[name]["parts"] = list(out[10:10 + hd.G])
+    return got
+
+
+def ffn_row_tiles(group_rows, side: int = 256):
+    """[(group, first row, end row)] of every row tile, in the kernel's order."""
     tiles = []
     for g, (o, e) in enumerate(group_rows):
-        for r0 in range(o, e, FFN_BM):
-            tiles.append((g, r0, min(r0 + FFN_BM, e)))
+        for r0 in range(o, e, side):
+            tiles.append((g, r0, min(r0 + side, e)))
     return tiles
 
 
-def ffn_split_tiles(total_rt: int, col_tiles: int, k_slices: int, n_blocks: int, band: int = 8):
-    """(row tile, column tile) of the tiles the last, contraction-split round covers; empty if there is none."""
-    n_act = total_rt * col_tiles
-    n_full = (n_act // n_blocks) * n_blocks
-    rem = n_act - n_full
-    if rem == 0 or k_slices < 128:
+def ffn_split_tiles(t: dict):
+    """(row tile, column tile) of the tiles of a row contraction (an entry of ffn_tiling) that are cut along it."""
+    if t["parts"] <= 1:
         return []
-    S = min(4, n_blocks // rem, max(1, k_slices // 64))
-    if S <= 1 or rem * S > FFN_SPLIT_UNITS:
-        return []
-    out = []
-    for t in range(n_full, n_act):
-        b = t // (band * col_tiles)
-        in_band = t - b * band * col_tiles
-        band_rows = min(band, total_rt - b * band)
+    out, band, cols = [], t["band"], t["col_tiles"]
+    for i in range(t["n_full"], t["row_tiles"] * cols):
+        b = i // (band * cols)
+        in_band = i - b * band * cols
+        band_rows = min(band, t["row_tiles"] - b * band)
         out.append((b * band + in_band % band_rows, in_band // band_rows))
     return out
 
@@ -162,9 +171,9 @@ class Case:
             Yp[self.lay["pos"][self.hosted]] = self.oracle_ffn(self.hosted)
         return Yp
 
-    def sample_assignments(self, n_random: int, seed: int = 0, every_tile: bool = False) -> np.ndarray:
-        """Hosted assignments at group and tile boundaries plus random ones; with `every_tile` also one row,
-        at a random place, in every 256-row tile of every hosted group (the last, ragged tile included)."""
+    def sample_assignments(self, n_random: int, seed: int = 0, every_tile: int = 0) -> np.ndarray:
+        """Hosted assignments at group and tile boundaries plus random ones; with `every_tile` (the side of a tile)
+        also one row, at a random place, in every row tile of every hosted group (the last, ragged tile included)."""
         rng = np.random.default_rng(seed)
         rows = []
         for g in range(self.G):
@@ -173,7 +182,7 @@ class Case:
                 if o <= r < e:
                     rows.append(r)
         if every_tile:
-            for _, r0, r1 in ffn_row_tiles([self.group_rows(g) for g in range(self.G)]):
+            for _, r0, r1 in ffn_row_tiles([self.group_rows(g) for g in range(self.G)], every_tile):
                 rows.append(int(rng.integers(r0, r1)))
         perm = self.lay["perm"]
         a = [int(perm[r]) for r in rows]

@@ -1,0 +1,53 @@
+"""How the bf16 FFN says it lays out a contraction, without a GPU: arguments, and that every cut stays inside the workspace
+and the lanes it is made for."""
+import ctypes
+import random
+
+import pytest
+
+import gpu_util as G
+from paper_2411_10003_amd import binding
+
+
+def _handle(rows, other, d, h, act="gelu", dtype="bf16", G_cap=None, E=None):
+    n = len(rows) if G_cap is None else G_cap
+    return binding.Handle(T=sum(rows) + other, d=d, h=h, E=n + 1 if E is None else E, k=1, P=1, self_dest=0, G=n, dtype=dtype, act=act,
+                          renorm=0, alloc_workspace=False)
+
+
+def test_arguments():
+    lib, hd = binding.load(), _handle([100, 200], 0, 128, 256)
+    r, out = (ctypes.c_int32 * 2)(100, 200), (ctypes.c_int32 * 80)()
+    assert lib.moe_ffn_tiling(hd._h, 0, 256, 2, r, out) == 0
+    assert lib.moe_ffn_tiling(None, 0, 256, 2, r, out) == -1 and lib.moe_ffn_tiling(hd._h, 0, 256, 2, None, out) == -1
+    assert lib.moe_ffn_tiling(hd._h, 6, 256, 2, r, out) == -2 and lib.moe_ffn_tiling(hd._h, 0, 256, 3, r, out) == -2
+    f32 = _handle([100, 200], 0, 128, 256, dtype="f32")
+    assert lib.moe_ffn_tiling(f32._h, 0, 256, 2, r, out) == -5
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_cuts_fit(seed):
+    rng = random.Random(seed)
+    cut = {k: 0 for k in ((128, "row"), (256, "row"), (128, "wgrad"), (256, "wgrad"))}
+    for _ in range(400):
+        n = rng.choice([1, 2, 4, 7, 17, 30, 64])
+        rows = [int(10 ** rng.uniform(0, 4)) for _ in range(n)]
+        d, h = 64 * rng.randint(1, 40), 64 * rng.randint(1, 80)
+        hd = _handle(rows, rng.choice([0, 20000]), d, h, rng.choice(["gelu", "swiglu"]))
+        for name, t in G.ffn_tiling(hd, rows, 256).items():
+            side, units = t["side"], 320 * (256 // t["side"]) ** 2
+            assert side in (128, 256) and t["blocks"] == (512 if side == 128 else 256)
+            tiles = t["row_tiles"] * t["col_tiles"]
+            if name[0] == "d":
+                assert all(1 <= p <= (8 if side == 128 else 4) for p in t["parts"])
+                assert sum(t["parts"]) <= 64 and sum(p for p in t["parts"] if p > 1) * tiles <= units
+                cut[side, "wgrad"] += max(t["parts"]) > 1
+                assert t["finish"] or max(t["parts"]) == 1
+            else:
+                assert t["row_tiles"] == len(G.ffn_row_tiles([(0, x) for x in rows], side))
+                rest = tiles - t["n_full"]
+                assert t["n_full"] % t["blocks"] == 0 and 0 <= rest < t["blocks"]
+                assert t["parts"] == 1 or (t["finish"] and rest > 0 and rest * t["parts"] <= min(units, t["blocks"]) and t["slices"] >= 16 * t["parts"])
+                assert len(G.ffn_split_tiles(t)) == (rest if t["parts"] > 1 else 0)
+                cut[side, "row"] += t["parts"] > 1
+    assert all(cut.values()), cut

@@ -2,8 +2,8 @@
 bench.py times (the same calls on the same buffers).  Routing, counts, layout, permutation and the
 send buffer are compared completely and bit for bit; FFN outputs, layer outputs and gradients on
 sampled rows, tokens and hidden units that the oracle computes one by one, each compared row by
-row: a row in every 256-row tile of every hosted group (hence in every tile band, every ragged
-last tile and every tile of the contraction-split last round), group boundaries, random picks,
+row: a row in every row tile of every hosted group (hence in every tile band, every ragged
+last tile and every tile that is cut along its contraction), group boundaries, random picks,
 and a hidden unit in every 256-wide block of the weight gradients."""
 import numpy as np
 import pytest
@@ -51,25 +51,26 @@ def _check_pass(G, orc, case, hd, b, n_random=16, seed=0, label=""):
     G.assert_layout_equal(b, lay)
     assert np.array_equal(G.host(b.Xp), orc.dispatch(inp["X"], lay["perm"], k))
 
-    # ---- which tiles there are: one sampled row in every 256-row tile of every hosted group, so that every tile
-    # band, every ragged last tile and every tile of the contraction-split last round holds a compared row (a row
-    # is compared over all its columns, hence over every column tile)
+    # ---- which tiles there are: one sampled row in every row tile of every hosted group, of the smallest side that a
+    # contraction takes, so that every tile band, every ragged last tile and every tile that is cut along its contraction
+    # holds a compared row (a row is compared over all its columns, hence over every column tile)
     groups = [case.group_rows(g) for g in range(case.G)]
-    row_tiles = G.ffn_row_tiles(groups)
-    n_blocks = torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8
+    tiling = G.ffn_tiling(hd, [e - o for o, e in groups])
+    rows_of = {n: tiling[n] for n in ("fwd1", "fwd2", "bwd1", "bwd2")}
+    side = min(t["side"] for t in rows_of.values())
+    row_tiles = G.ffn_row_tiles(groups, side)
     swiglu = cfg.act == "swiglu"
-    launches = {"fwd1": (-(-cfg.h // (128 if swiglu else 256)), cfg.d // 32), "fwd2": (-(-cfg.d // 256), cfg.h // 32),
-                "bwd1": (-(-cfg.h // 256), cfg.d // 32), "bwd2": (-(-cfg.d // 256), (2 if swiglu else 1) * cfg.h // 32)}
-    split = {n: G.ffn_split_tiles(len(row_tiles), ct, ks, n_blocks, G.FFN_BAND[n]) for n, (ct, ks) in launches.items()}
-    for n, tiles in split.items():                               # every split tile lies in a sampled row tile
-        assert all(0 <= rt < len(row_tiles) for rt, _ in tiles), n
-    a_s = case.sample_assignments(n_random, seed, every_tile=True)
+    for n, t in rows_of.items():                                 # every cut tile lies in a row tile
+        assert t["row_tiles"] == len(G.ffn_row_tiles(groups, t["side"])), n
+        assert all(0 <= rt < t["row_tiles"] and 0 <= ct < t["col_tiles"] for rt, ct in G.ffn_split_tiles(t)), n
+    a_s = case.sample_assignments(n_random, seed, every_tile=side)
     sampled_rows = np.sort(pos[a_s])
     for ti, (g, r0, r1) in enumerate(row_tiles):
         i = np.searchsorted(sampled_rows, r0)
         assert i < sampled_rows.size and sampled_rows[i] < r1, f"row tile {ti} of group {g} holds no sampled row"
-    print(f"[{label}] {len(row_tiles)} row tiles in {-(-len(row_tiles) // 8)} bands, all sampled ({a_s.size} rows); "
-          f"tiles of the split last round: " + ", ".join(f"{n} {len(t)}" for n, t in split.items()), flush=True)
+    print(f"[{label}] {len(row_tiles)} row tiles of {side}, all sampled ({a_s.size} rows); side, tiles cut, parts: "
+          + ", ".join(f"{n} {t['side']} {len(G.ffn_split_tiles(t))} {t['parts']}" for n, t in rows_of.items())
+          + "; side and parts per group: " + ", ".join(f"{n} {tiling[n]['side']} {tiling[n]['parts']}" for n in ("dW1", "dW2")), flush=True)
 
     # ---- sampled assignments: forward FFN
     if a_s.size:
@@ -174,20 +175,27 @@ def test_full_config(G, orc, ci):
 
 
 @pytest.mark.timeout(600)
-@pytest.mark.parametrize("T,h,parts", [(10240, 6272, 3), (8192, 8256, 4)])
-def test_last_round_split_in_three_and_four_parts(G, orc, T, h, parts):
-    """Shapes whose last round of fwd2 and bwd2 is cut along the contraction into three and four parts, with part
-    boundaries that would fall on odd slices (196 and 258 slices) if the kernel did not move them to even ones."""
-    cfg = wl.scaled(wl.CONFIGS[2], T=T, d=256, h=h)
+@pytest.mark.parametrize("side,parts,kw", [
+    (256, 3, dict(T=12288, d=768, h=2368, alpha=0.3, n_replicas=1)),
+    (256, 4, dict(T=12288, d=768, h=3136, alpha=0.3, n_replicas=1)),
+    (128, 3, dict(T=2048, d=256, h=1600)),
+    (128, 5, dict(T=2048, d=256, h=2624)),
+    (128, 8, dict(T=2048, d=256, h=4160)),
+])
+def test_last_round_split_at_odd_slices(G, orc, side, parts, kw):
+    """Shapes whose last round of fwd2 and bwd2 is cut along the contraction, in either geometry, with part boundaries that
+    would fall on odd slices if the kernel did not move them to even ones."""
+    cfg = wl.scaled(wl.CONFIGS[2], **kw)
     case = G.Case(cfg)
-    row_tiles = G.ffn_row_tiles([case.group_rows(g) for g in range(case.G)])
-    n_blocks = torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8
-    k_slices = h // 32
-    assert min(4, n_blocks // len(row_tiles), k_slices // 64) == parts
-    assert any((i * k_slices // parts) % 2 == 1 for i in range(1, parts))
     hd = G.make_handle(cfg)
+    groups = [case.group_rows(g) for g in range(case.G)]
+    tiling = G.ffn_tiling(hd, [e - o for o, e in groups])
+    for n in ("fwd2", "bwd2"):
+        t = tiling[n]
+        assert (t["side"], t["parts"], t["finish"]) == (side, parts, 1) and t["n_full"] < t["row_tiles"] * t["col_tiles"], (n, t)
+        assert any((i * t["slices"] // parts) % 2 == 1 for i in range(1, parts))
     b = G.binding.LayerBuffers(hd, cfg.backward)
-    _check_pass(G, orc, case, hd, b, label=f"split{parts}")
+    _check_pass(G, orc, case, hd, b, label=f"split{parts} of {side}")
 
 
 @pytest.mark.timeout(900)
