@@ -30,6 +30,7 @@
 #include <type_traits>
 #include <algorithm>
 #include <cmath>
+#include <numeric>
 
 // Where the main loop starts relative to a 256-byte boundary of the code, in 4-byte steps.  The loop is one basic
 // block that every wave runs tens of thousands of times; how its two phases fall into the instruction fetch
@@ -94,16 +95,20 @@ __host__ __device__ inline int row_parts(int rem, int nblk, int slices, int spli
     if (S > worth) S = worth > 1 ? worth : 1;
     return rem * S > split_cap ? 1 : S;
 }
-// TN: slices of a block's share of all the work (tiles: of one group; slices: of all groups), and the parts of a group of k
-// slices: of about that share, none under split_slices.
-__host__ __device__ inline int tn_share(int tiles, int slices, int groups, int tn_over, int nblk) { return (int)((long)tiles * (slices + groups * tn_over) / nblk); }
-__host__ __device__ inline int tn_parts(int k, int share, int tn_over, int split_max, int split_slices)
+// TN: parts of a group of k slices.  Its rounds (a round: as many tiles as an XCD has blocks, or what there are) run on one
+// XCD each, so cutting it shortens the whole only where it is longer than an XCD's share of all rounds; the parts are then
+// about as long as a block's share of all tiles, and no shorter than split_slices.  tiles, rounds: of a group; slices: of all.
+// n_cut groups are cut into at most what the workspace holds.
+__host__ __device__ inline int tn_parts(int k, int tiles, int rounds, int slices, int groups, int nblk, int tn_over, int split_max, int split_slices)
 {
-    if (k + tn_over <= share + share / 4) return 1;
+    const long all = slices + (long)groups * tn_over;
+    const int xcd_share = (int)(rounds * all / 8), share = (int)(tiles * all / nblk);
+    if (k == 0 || k + tn_over <= xcd_share + xcd_share / 4) return 1;      // an empty group is one part: its zeros
     const int len = share - tn_over > split_slices ? share - tn_over : split_slices;
     const int n = (k + len - 1) / len;
     return n < split_max ? n : split_max;
 }
+__host__ __device__ inline int tn_most_units(int split_cap, int tiles, int n_cut) { const int n = split_cap / (tiles * n_cut); return n > 1 ? n : 1; }
 
 // GELU (Eq. 2 with the Gaussian CDF) and its derivative from one exponential and one reciprocal: erf by the
 // five-term rational approximation of Abramowitz & Stegun 7.1.26 (absolute error below 1.5e-7, two orders under
@@ -317,7 +322,9 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     // per product, whole groups dealt in turn (256 x 256 tiles, 128 x 128) -> now, with the finishing launch: d = 3136,
     // h = 576, 20623 rows in 8 uneven groups 310, 266 -> 142; d = 3968, h = 704, 12532 rows in 2 216, 179 -> 112 to 144;
     // d = 2944, h = 576, one group of 3002 71, 47 -> 35; d = 1024, h = 4096, 9279 rows in 4 150, 126 -> 118.  Where nothing is
-    // cut: d = 512, h = 14272, 2522 rows 93 -> 80; the largest configuration the same (4.12 ms).
+    // cut: d = 512, h = 14272, 2522 rows 93 -> 80; the largest configuration the same (4.12 ms).  Cut where whole groups fill
+    // the XCDs: d = 256, h = 512, eight groups of 3276 rows, the backward pass 178, whole 117; d = 384, h = 512, eight of 1866
+    // 119, whole 86; d = 64, h = 512, 37605 rows in 16 329, whole 246.
     int n_parts = 0, v_group = 0, v_row0 = 0, v_rows = 0, v_of = 1, v_unit = 0;     // unit of the part's tile 0
     int tn_split = 1, tn_unit = 0;                         // lane g: parts of group g, unit of its first part's tile 0
     unsigned long long tn_split_mask = 0ull;
@@ -329,10 +336,10 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         int all = k;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) all += __shfl_xor(all, off, 64);
-        tn_split = tn_parts(k, tn_share(tiles_g, all, p.Gcap, p.tn_over, nblk), p.tn_over, p.split_max, p.split_slices);
+        tn_split = tn_parts(k, tiles_g, rpg, all, p.Gcap, nblk, p.tn_over, p.split_max, p.split_slices);
         tn_split_mask = __ballot(tn_split > 1);
         if (tn_split_mask) {
-            tn_split = max(1, min(tn_split, p.split_cap / (tiles_g * __popcll(tn_split_mask))));    // what the workspace holds
+            tn_split = min(tn_split, tn_most_units(p.split_cap, tiles_g, __popcll(tn_split_mask)));
             tn_split_mask = __ballot(tn_split > 1);
         }
         int incl = lane < p.Gcap ? tn_split : 0, units = tn_split > 1 ? tn_split : 0;
@@ -1121,8 +1128,8 @@ bool small_wins_rows(const moe_shape_t& s, int N, int slices, int n_seg, int epi
 // Weight gradients.  Whole groups: a round of an XCD's blocks per 32 (64) tiles of a group, dealt to the 8 XCDs, 17 (9) us
 // per tile beside the slices (the fp32 tile is stored), and no less than the chain of a group with twice its even share of
 // the rows.  Cut groups: every block its share, and a finishing launch of about 20 (12) us.  A cut pays where a group has
-// fewer tiles than there are blocks, and the kernel only makes one where it finds a group that is too long; it is offered
-// where four times a group's even share would be.
+// fewer tiles than there are blocks and is longer than an XCD's share of all rounds, and the kernel only makes one where it
+// finds such a group; it is offered where four times a group's even share would be one.
 struct WgradPlan { double us; bool cut; };
 template <class GEO>
 WgradPlan wgrad_plan(const moe_shape_t& s, int Mout, int N)
@@ -1132,10 +1139,12 @@ WgradPlan wgrad_plan(const moe_shape_t& s, int Mout, int N)
     constexpr int blocks = large ? 256 : 512, over_slices = TN_OVER<GEO>, least = TN_SPLIT_SLICES<GEO>;
     const double tiles = (double)((Mout + GEO::BM - 1) / GEO::BM) * ((N + GEO::BN - 1) / GEO::BN);
     const double even = std::ceil(estimated_rows(s) / s.G / BK), all = std::ceil(estimated_rows(s) / BK);
-    const double whole = std::max(std::max(s.G * std::ceil(tiles / (blocks / 8)) / 8.0, 1.0) * (even * slice + over),
+    const double rounds = std::ceil(tiles / (blocks / 8));             // of a group, dealt to the 8 XCDs
+    const double whole = std::max(std::max(s.G * rounds / 8.0, 1.0) * (even * slice + over),
                                   std::min(2.0 * even, all) * slice + over);
-    const double share = tiles * s.G * (even + over_slices) / blocks, longest = std::min(4.0 * even, all);
-    if (tiles >= blocks || longest < 2 * least || longest + over_slices < 1.25 * share) return WgradPlan{whole, false};
+    const double share = tiles * s.G * (even + over_slices) / blocks, xcd_share = s.G * rounds / 8.0 * (even + over_slices);
+    const double longest = std::min(4.0 * even, all);
+    if (tiles >= blocks || longest < 2 * least || longest + over_slices < 1.25 * xcd_share) return WgradPlan{whole, false};
     const double cut = std::max(share, (double)least) * slice + over + finish;
     return cut < whole ? WgradPlan{cut, true} : WgradPlan{whole, false};
 }
@@ -1329,19 +1338,14 @@ int moe_ffn_tiling(moe_handle_t hd, int contraction, int cus, int n_groups, cons
     out[6] = t.small && !wgrad ? SMALL_BAND : band[wgrad ? 4 : contraction];
     out[7] = t.cut; out[8] = wgrad ? all : slices; out[9] = (int32_t)estimated_rows(s);
     if (!wgrad) return MOE_OK;
-    const int over = t.small ? TN_OVER<Small> : TN_OVER<Large>, share = tn_share(tiles, all, s.G, over, nblk);
-    int parts[64], n_cut = 0, total = 0;
-    for (int g = 0; g < s.G; ++g) {
-        parts[g] = t.cut && g < n_groups ? tn_parts((rows[g] + BK - 1) / BK, share, over, split_max, t.split_slices) : 1;
-        n_cut += parts[g] > 1;
-    }
-    for (int g = 0; g < s.G; ++g) {
-        if (n_cut > 0) { const int most = cap / (tiles * n_cut); if (parts[g] > most) parts[g] = most > 1 ? most : 1; }
-        total += parts[g];
-    }
-    for (int g = 0; g < s.G; ++g) {
-        out[10 + g] = total > 64 ? 1 : parts[g];
-        if (out[10 + g] > out[5]) out[5] = out[10 + g];
-    }
+    const int over = t.small ? TN_OVER<Small> : TN_OVER<Large>, rounds = (tiles + nblk / 8 - 1) / (nblk / 8);
+    int* parts = out + 10;
+    auto limit = [&](int most) { for (int g = 0; g < s.G; ++g) parts[g] = std::min<int>(parts[g], most); };
+    auto n_cut = [&] { return (int)std::count_if(parts, parts + s.G, [](int32_t n) { return n > 1; }); };
+    for (int g = 0; g < s.G; ++g)
+        parts[g] = t.cut && g < n_groups ? tn_parts((rows[g] + BK - 1) / BK, tiles, rounds, all, s.G, nblk, over, split_max, t.split_slices) : 1;
+    if (n_cut()) limit(tn_most_units(cap, tiles, n_cut()));
+    if (std::accumulate(parts, parts + s.G, 0) > 64) limit(1);
+    out[5] = *std::max_element(parts, parts + s.G);
     return MOE_OK;
 }

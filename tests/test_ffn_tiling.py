@@ -51,3 +51,18 @@ def test_cuts_fit(seed):
                 assert len(G.ffn_split_tiles(t)) == (rest if t["parts"] > 1 else 0)
                 cut[side, "row"] += t["parts"] > 1
     assert all(cut.values()), cut
+
+
+@pytest.mark.parametrize("n,rows,d,h", [(8, 3276, 256, 512), (16, 5000, 64, 64), (8, 1866, 384, 512), (24, 2000, 128, 448), (17, 3276, 256, 512)])
+def test_groups_that_fill_the_xcds_stay_whole(n, rows, d, h):
+    """Eight equal groups, or more, keep the eight XCDs busy whole: cutting them adds a finishing launch and shortens nothing."""
+    t = G.ffn_tiling(_handle([rows] * n, 0, d, h), [rows] * n, 256)
+    for name in ("dW1", "dW2"):
+        assert t[name]["parts"] == [1] * n, name
+
+
+def test_long_groups_are_cut():
+    rows = [9000, 200, 0, 33]
+    t = G.ffn_tiling(_handle(rows, 0, 320, 192), rows, 256)
+    for name in ("dW1", "dW2"):
+        assert t[name]["parts"] == [8, 1, 1, 1] and t[name]["finish"] == 1, name
