@@ -1128,8 +1128,8 @@ bool small_wins_rows(const moe_shape_t& s, int N, int slices, int n_seg, int epi
 // Weight gradients.  Whole groups: a round of an XCD's blocks per 32 (64) tiles of a group, dealt to the 8 XCDs, 17 (9) us
 // per tile beside the slices (the fp32 tile is stored), and no less than the chain of a group with twice its even share of
 // the rows.  Cut groups: every block its share, and a finishing launch of about 20 (12) us.  A cut pays where a group has
-// fewer tiles than there are blocks and is longer than an XCD's share of all rounds, and the kernel only makes one where it
-// finds such a group; it is offered where four times a group's even share would be one.
+// fewer tiles than there are blocks and is longer than an XCD's share of all rounds, and the kernel, which alone knows, only
+// makes one where it finds such a group; it is offered wherever four times a group's even share is longer than a block's.
 struct WgradPlan { double us; bool cut; };
 template <class GEO>
 WgradPlan wgrad_plan(const moe_shape_t& s, int Mout, int N)
@@ -1139,12 +1139,10 @@ WgradPlan wgrad_plan(const moe_shape_t& s, int Mout, int N)
     constexpr int blocks = large ? 256 : 512, over_slices = TN_OVER<GEO>, least = TN_SPLIT_SLICES<GEO>;
     const double tiles = (double)((Mout + GEO::BM - 1) / GEO::BM) * ((N + GEO::BN - 1) / GEO::BN);
     const double even = std::ceil(estimated_rows(s) / s.G / BK), all = std::ceil(estimated_rows(s) / BK);
-    const double rounds = std::ceil(tiles / (blocks / 8));             // of a group, dealt to the 8 XCDs
-    const double whole = std::max(std::max(s.G * rounds / 8.0, 1.0) * (even * slice + over),
+    const double whole = std::max(std::max(s.G * std::ceil(tiles / (blocks / 8)) / 8.0, 1.0) * (even * slice + over),
                                   std::min(2.0 * even, all) * slice + over);
-    const double share = tiles * s.G * (even + over_slices) / blocks, xcd_share = s.G * rounds / 8.0 * (even + over_slices);
-    const double longest = std::min(4.0 * even, all);
-    if (tiles >= blocks || longest < 2 * least || longest + over_slices < 1.25 * xcd_share) return WgradPlan{whole, false};
+    const double share = tiles * s.G * (even + over_slices) / blocks, longest = std::min(4.0 * even, all);
+    if (tiles >= blocks || longest < 2 * least || longest + over_slices < 1.25 * share) return WgradPlan{whole, false};
     const double cut = std::max(share, (double)least) * slice + over + finish;
     return cut < whole ? WgradPlan{cut, true} : WgradPlan{whole, false};
 }

@@ -66,3 +66,12 @@ def test_long_groups_are_cut():
     t = G.ffn_tiling(_handle(rows, 0, 320, 192), rows, 256)
     for name in ("dW1", "dW2"):
         assert t[name]["parts"] == [8, 1, 1, 1] and t[name]["finish"] == 1, name
+
+
+@pytest.mark.parametrize("rows,d,h", [([9000] + [1000] * 30, 256, 512), ([30000] + [400] * 23, 512, 256), ([44000] + [20] * 30, 64, 64)], ids=lambda v: str(len(v)) if isinstance(v, list) else str(v))
+def test_long_groups_among_many_are_cut(rows, d, h):
+    t = G.ffn_tiling(_handle(rows, 0, d, h), rows, 256)
+    for name in ("dW1", "dW2"):
+        assert t[name]["finish"] == 1, name
+        if rows[0] > 20 * rows[1]:
+            assert t[name]["parts"][0] > 1 and t[name]["parts"][1:] == [1] * (len(rows) - 1), name
