@@ -98,7 +98,8 @@ __host__ __device__ inline int row_parts(int rem, int nblk, int slices, int spli
 // TN: parts of a group of k slices.  Its rounds (a round: as many tiles as an XCD has blocks, or what there are) run on one
 // XCD each, so cutting it shortens the whole only where it is longer than an XCD's share of all rounds; the parts are then
 // about as long as a block's share of all tiles, and no shorter than split_slices.  tiles, rounds: of a group; slices: of all.
-// n_cut groups are cut into at most what the workspace holds.
+// n_cut groups are cut into at most what the workspace holds and, where all parts would be more than the 64 lanes that keep
+// them, an equal number of the lanes left beside one for each group.
 __host__ __device__ inline int tn_parts(int k, int tiles, int rounds, int slices, int groups, int nblk, int tn_over, int split_max, int split_slices)
 {
     const long all = slices + (long)groups * tn_over;
@@ -109,6 +110,7 @@ __host__ __device__ inline int tn_parts(int k, int tiles, int rounds, int slices
     return n < split_max ? n : split_max;
 }
 __host__ __device__ inline int tn_most_units(int split_cap, int tiles, int n_cut) { const int n = split_cap / (tiles * n_cut); return n > 1 ? n : 1; }
+__host__ __device__ inline int tn_most_lanes(int groups, int n_cut) { return 1 + (64 - groups) / n_cut; }
 
 // GELU (Eq. 2 with the Gaussian CDF) and its derivative from one exponential and one reciprocal: erf by the
 // five-term rational approximation of Abramowitz & Stegun 7.1.26 (absolute error below 1.5e-7, two orders under
@@ -342,18 +344,22 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
             tn_split = min(tn_split, tn_most_units(p.split_cap, tiles_g, __popcll(tn_split_mask)));
             tn_split_mask = __ballot(tn_split > 1);
         }
-        int incl = lane < p.Gcap ? tn_split : 0, units = tn_split > 1 ? tn_split : 0;
-        const int own_units = units;
+        int incl, units, own_units;
+        while (true) {
+            incl = lane < p.Gcap ? tn_split : 0;
+            own_units = units = tn_split > 1 ? tn_split : 0;
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int up = __shfl_up(incl, off, 64), uu = __shfl_up(units, off, 64);
-            if (lane >= off) { incl += up; units += uu; }
+            for (int off = 1; off < 64; off <<= 1) {
+                const int up = __shfl_up(incl, off, 64), uu = __shfl_up(units, off, 64);
+                if (lane >= off) { incl += up; units += uu; }
+            }
+            if (__builtin_amdgcn_readlane(incl, 63) <= 64) break;
+            tn_split = min(tn_split, tn_most_lanes(p.Gcap, __popcll(tn_split_mask)));      // then they do fit
+            tn_split_mask = __ballot(tn_split > 1);
         }
         tn_unit = (units - own_units) * tiles_g;
-        const int total = __builtin_amdgcn_readlane(incl, 63);
-        if (total > 64) tn_split_mask = 0ull;              // more parts than lanes: whole groups
         if (tn_split_mask != 0ull) {
-            n_parts = total;
+            n_parts = __builtin_amdgcn_readlane(incl, 63);
             const int first = incl - tn_split;
             for (int i = 0; i < p.Gcap; ++i) {
                 const int f = __builtin_amdgcn_readlane(first, i), n = __builtin_amdgcn_readlane(tn_split, i);
@@ -1343,7 +1349,7 @@ int moe_ffn_tiling(moe_handle_t hd, int contraction, int cus, int n_groups, cons
     for (int g = 0; g < s.G; ++g)
         parts[g] = t.cut && g < n_groups ? tn_parts((rows[g] + BK - 1) / BK, tiles, rounds, all, s.G, nblk, over, split_max, t.split_slices) : 1;
     if (n_cut()) limit(tn_most_units(cap, tiles, n_cut()));
-    if (std::accumulate(parts, parts + s.G, 0) > 64) limit(1);
+    if (std::accumulate(parts, parts + s.G, 0) > 64) limit(tn_most_lanes(s.G, n_cut()));
     out[5] = *std::max_element(parts, parts + s.G);
     return MOE_OK;
 }

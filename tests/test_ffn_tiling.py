@@ -75,3 +75,18 @@ def test_long_groups_among_many_are_cut(rows, d, h):
         assert t[name]["finish"] == 1, name
         if rows[0] > 20 * rows[1]:
             assert t[name]["parts"][0] > 1 and t[name]["parts"][1:] == [1] * (len(rows) - 1), name
+
+
+@pytest.mark.parametrize("rows,d,h,want", [
+    ([44000] + [20] * 59, 64, 192, 5),                         # 60 groups leave four lanes: five parts instead of eight
+    ([40000, 40000] + [30] * 58, 64, 64, 3),                   # shared by two
+    ([44000] + [20] * 63, 64, 64, 1),                          # a lane for each group and none left
+    ([44000] + [20] * 56, 64, 64, 8),                          # just enough
+], ids=lambda v: str(len(v)) if isinstance(v, list) else str(v))
+def test_more_parts_than_lanes(rows, d, h, want):
+    """All parts together are at most 64: long groups are cut into fewer parts, not left whole."""
+    t = G.ffn_tiling(_handle(rows, 0, d, h), rows, 256)
+    for name in ("dW1", "dW2"):
+        parts = t[name]["parts"]
+        n = sum(r > 1000 for r in rows)
+        assert parts[:n] == [want] * n and parts[n:] == [1] * (len(rows) - n) and sum(parts) <= 64, (name, parts)

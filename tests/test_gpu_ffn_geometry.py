@@ -34,9 +34,23 @@ CASES = [
     ([300] * 20 + [8000], 0, 64, 320, "swiglu"),
 ]
 
+# The same with what is covered: contraction -> side of its tiles and parts of a cut tile (weight gradients: of the first
+# group), as the library says it will run them.
+PLANNED = [
+    # all parts of the weight gradients together are one per lane: fewer parts than a group alone would be cut into
+    ([44000] + [20] * 59, 0, 64, 192, "gelu", dict(dW1=(128, 5), dW2=(128, 5))),
+    ([40000, 40000] + [30] * 58, 0, 64, 64, "swiglu", dict(dW1=(128, 3), dW2=(128, 3))),
+]
 
-@pytest.mark.parametrize("rows,other,d,h,act", CASES, ids=lambda v: str(v).replace(" ", "") if not isinstance(v, list) else f"{len(v)}g{sum(v)}r")
-def test_forward_backward(rows, other, d, h, act):
+
+def _id(v):
+    if isinstance(v, list):
+        return f"{len(v)}g{sum(v)}r"
+    return "-".join(f"{n}:{a}/{b}" for n, (a, b) in v.items()) if isinstance(v, dict) else str(v)
+
+
+@pytest.mark.parametrize("rows,other,d,h,act,plan", [(*c, {}) for c in CASES] + PLANNED, ids=_id)
+def test_forward_backward(rows, other, d, h, act, plan):
     Gn, M, A = len(rows), sum(rows), sum(rows) + other
     E = Gn + 1                                             # the last expert belongs to another destination
     g = torch.Generator(device=G.DEV).manual_seed(d + h + M)
@@ -45,6 +59,10 @@ def test_forward_backward(rows, other, d, h, act):
         return (torch.randn(*shape, generator=g, device=G.DEV) * std).to(torch.bfloat16)
 
     hd = binding.Handle(T=A, d=d, h=h, E=E, k=1, P=2, self_dest=0, G=Gn, dtype="bf16", act=act, renorm=0, device=G.DEV)
+    tiling = G.ffn_tiling(hd, rows)
+    for name, want in plan.items():
+        t = tiling[name]
+        assert (t["side"], t["parts"][0] if name[0] == "d" else t["parts"]) == want, (name, t)
     idx = torch.repeat_interleave(torch.arange(E, dtype=torch.int32), torch.tensor(rows + [other])).to(G.DEV)
     dest = torch.tensor([0] * Gn + [1], dtype=torch.int32, device=G.DEV)
     counts, lay = torch.zeros(E, dtype=torch.int32, device=G.DEV), hd.new_layout()
