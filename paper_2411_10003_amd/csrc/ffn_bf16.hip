@@ -111,6 +111,13 @@ __host__ __device__ inline int tn_parts(int k, int tiles, int rounds, int slices
 }
 __host__ __device__ inline int tn_most_units(int split_cap, int tiles, int n_cut) { const int n = split_cap / (tiles * n_cut); return n > 1 ? n : 1; }
 __host__ __device__ inline int tn_most_lanes(int groups, int n_cut) { return 1 + (64 - groups) / n_cut; }
+// Whether the cut is worth its finishing launch (about what a tile costs beside its slices): the longest chain, or the rounds
+// of the busiest XCD at the mean length, with n groups whole (the longest of k slices) and as `parts` of at most `len`.
+__host__ __device__ inline bool tn_pays(int k, int len, int slices, int n, int parts, int rounds, int tn_over)
+{
+    const int whole = (n * rounds + 7) / 8 * (slices / n + tn_over), cut = (parts * rounds + 7) / 8 * (slices / parts + tn_over);
+    return (cut > len + tn_over ? cut : len + tn_over) + tn_over < (whole > k + tn_over ? whole : k + tn_over);
+}
 
 // GELU (Eq. 2 with the Gaussian CDF) and its derivative from one exponential and one reciprocal: erf by the
 // five-term rational approximation of Abramowitz & Stegun 7.1.26 (absolute error below 1.5e-7, two orders under
@@ -326,7 +333,8 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     // d = 2944, h = 576, one group of 3002 71, 47 -> 35; d = 1024, h = 4096, 9279 rows in 4 150, 126 -> 118.  Where nothing is
     // cut: d = 512, h = 14272, 2522 rows 93 -> 80; the largest configuration the same (4.12 ms).  Cut where whole groups fill
     // the XCDs: d = 256, h = 512, eight groups of 3276 rows, the backward pass 178, whole 117; d = 384, h = 512, eight of 1866
-    // 119, whole 86; d = 64, h = 512, 37605 rows in 16 329, whole 246.
+    // 119, whole 86; d = 64, h = 512, 37605 rows in 16 329, whole 246; or nearly, and the parts would not: d = 1728, h = 64, six
+    // of 2128 192, whole 137; d = 1280, h = 1792, three of 1982 261, whole 217.
     int n_parts = 0, v_group = 0, v_row0 = 0, v_rows = 0, v_of = 1, v_unit = 0;     // unit of the part's tile 0
     int tn_split = 1, tn_unit = 0;                         // lane g: parts of group g, unit of its first part's tile 0
     unsigned long long tn_split_mask = 0ull;
@@ -358,6 +366,13 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
             tn_split_mask = __ballot(tn_split > 1);
         }
         tn_unit = (units - own_units) * tiles_g;
+        if (tn_split_mask != 0ull) {
+            int longest = k, len = (k + tn_split - 1) / tn_split;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) { longest = max(longest, __shfl_xor(longest, off, 64)); len = max(len, __shfl_xor(len, off, 64)); }
+            const int n = __popcll(__ballot(k > 0)), total = __builtin_amdgcn_readlane(incl, 63) - (p.Gcap - n);
+            if (!__builtin_amdgcn_readfirstlane(tn_pays(longest, len, all, n, total, rpg, p.tn_over))) tn_split_mask = 0ull;
+        }
         if (tn_split_mask != 0ull) {
             n_parts = __builtin_amdgcn_readlane(incl, 63);
             const int first = incl - tn_split;
@@ -1350,6 +1365,15 @@ int moe_ffn_tiling(moe_handle_t hd, int contraction, int cus, int n_groups, cons
         parts[g] = t.cut && g < n_groups ? tn_parts((rows[g] + BK - 1) / BK, tiles, rounds, all, s.G, nblk, over, split_max, t.split_slices) : 1;
     if (n_cut()) limit(tn_most_units(cap, tiles, n_cut()));
     if (std::accumulate(parts, parts + s.G, 0) > 64) limit(tn_most_lanes(s.G, n_cut()));
+    if (n_cut()) {
+        int longest = 0, len = 0, n = 0, total = 0;        // of the groups with rows
+        for (int g = 0; g < n_groups; ++g) {
+            const int k = (rows[g] + BK - 1) / BK;
+            longest = std::max(longest, k); len = std::max(len, (k + parts[g] - 1) / parts[g]);
+            n += k > 0; total += k > 0 ? parts[g] : 0;
+        }
+        if (!tn_pays(longest, len, all, n, total, rounds, over)) limit(1);
+    }
     out[5] = *std::max_element(parts, parts + s.G);
     return MOE_OK;
 }

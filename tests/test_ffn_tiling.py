@@ -61,6 +61,14 @@ def test_groups_that_fill_the_xcds_stay_whole(n, rows, d, h):
         assert t[name]["parts"] == [1] * n, name
 
 
+@pytest.mark.parametrize("n,rows,d,h,E", [(3, 1982, 1280, 1792, 12), (6, 2128, 1728, 64, 24), (6, 1286, 64, 2112, 24)])
+def test_cuts_that_would_not_pay_are_not_made(n, rows, d, h, E):
+    """Fewer groups than XCDs, but as many rounds or nearly: parts of them would take the XCDs as long as the whole groups."""
+    t = G.ffn_tiling(_handle([rows] * n, rows * n, d, h, E=E), [rows] * n, 256)
+    for name in ("dW1", "dW2"):
+        assert t[name]["parts"] == [1] * n, name
+
+
 def test_long_groups_are_cut():
     rows = [9000, 200, 0, 33]
     t = G.ffn_tiling(_handle(rows, 0, 320, 192), rows, 256)
