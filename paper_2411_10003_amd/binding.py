@@ -113,7 +113,7 @@ def _ptr(t: Optional[torch.Tensor], dtype: torch.dtype, numel: int, name: str) -
 def _stream() -> int:
     # The raw handle of the current stream.  torch.cuda.current_stream() builds a Stream object around it first: 2.9 us, a
     # third of the host time of a call; this takes 0.2 (the five calls of the tiny forward layer 43 -> 30 us).
-    if _raw_stream is None:
+    if _raw_stream is None or _current_device is None:
         return torch.cuda.current_stream().cuda_stream
     return _raw_stream(_current_device())
 

@@ -126,3 +126,20 @@ def test_static_counts_and_settings_validate_arguments(lib):
     assert lib.moe_set_act_saved(h, 2) == -2 and lib.moe_set_act_saved(h, 1) == 0 and lib.moe_set_act_saved(h, 0) == 0
     assert lib.moe_set_act_saved(None, 1) == -1
     assert lib.moe_destroy(h) == 0
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_current_device"])
+def test_stream_without_the_raw_handle(monkeypatch, missing):
+    """Either of torch's two private names may be missing: the stream then comes from its public interface."""
+    import torch
+    from paper_2411_10003_amd import binding
+
+    class Stream:
+        cuda_stream = 4711
+
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 42)
+    monkeypatch.setattr(binding, "_current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    assert binding._stream() == 42
+    monkeypatch.setattr(binding, missing, None)
+    assert binding._stream() == 4711
