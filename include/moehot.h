@@ -227,6 +227,7 @@ int moe_gate_bwd_params(moe_handle_t h, const void* X, const float* dlogits, flo
 
 /* Complete gradient of the layer input: the backward of the send (as moe_dispatch_bwd) plus the gate
  * path, rounded once:  dX[t,:] = sum_j dXp[pos[t*k+j],:] + sum_e dlogits[t,e] Wg[:,e].
+ * A negative position (an assignment whose expert id was out of range got no row) adds nothing.
  *   in : dXp[A,d] elt, pos[A], dlogits[T,E] float, Wg[d,E] float;  out: dX[T,d] elt */
 int moe_input_grad(moe_handle_t h, const void* dXp, const int32_t* pos, const float* dlogits, const float* Wg,
                    void* dX, void* stream);
