@@ -2,18 +2,18 @@
 // single-precision workloads and their 1e-5 tolerance.  Groups are ragged and may be empty; any h, d a multiple of 4.
 //
 // What bounds it: the fp32 matrix rate (157 TFLOP/s at the nominal clock).  Every contraction is v_mfma_f32_32x32x2_f32
-// on operands staged through LDS, 32 or 64 steps deep, the next slice requested into registers while the current one
-// is multiplied (one barrier per slice, two LDS buffers).  An operand whose contraction index is contiguous in memory
+// on operands staged through LDS, 32 or 64 steps deep, the next slice requested while the current one is multiplied (one
+// barrier per slice); requests go straight into LDS.  An operand whose contraction index is contiguous in memory
 // (token rows, the weights of the backward contractions) lies row-major in LDS and is read four steps at a time; one
 // whose contraction index is the slow one (the weights of the forward contractions, both operands of the weight
 // gradients) lies as it does in memory and is read a step at a time, 32 consecutive columns per read.  The half of a
 // wave that holds step 8 s + j of an instruction's pair holds 8 s + 4 + j in the other half, so that both layouts feed
 // the same order.
-// Tiles: 64 x 64 per block of four waves, or 32 x 32 with the four waves sharing the contraction where those are too
-// few to fill the chip (small configurations, whose time is the length of the serial chain; see medium_tiles).
-// Measured at T = 3000, d = 512, h = 2048, k = 2, GELU, 4900 hosted rows: forward and backward 4255 us with one output
-// per thread on the vector ALUs, 680 us now (91 TFLOP/s); the tiny configuration (T = 512, d = 64, h = 256): forward 18 us,
-// 12 us now.
+// Tiles: 64 x 64 per block of four waves, 64 x 32 or 32 x 32 with two or four waves sharing the contraction where those are
+// too few to fill the chip (see MEDIUM_TILES).
+// Measured at T = 3000, d = 512, h = 2048, k = 2, GELU, 4900 hosted rows, forward and backward: 4255 us with one output
+// per thread on the vector ALUs, 703 us staged through registers, 578 us now (107 TFLOP/s); the weight gradients of it 249,
+// 212 with the requests straight into LDS, 193 with the longest groups first.
 #include "internal.h"
 #include <initializer_list>
 
@@ -44,58 +44,99 @@ template <int WM_, int WN_, int WK_, int BK_> struct Tile {
     static constexpr int WM = WM_, WN = WN_, WK = WK_, BK = BK_;
     static constexpr int BM = 32 * WM, BN = 32 * WN;
     static constexpr int KW = BK / WK;                     // contraction steps of a slice one wave multiplies
+    static constexpr int STAGES = WK == 4 ? 4 : 2;         // LDS buffers of a block
     static_assert(WM * WN * WK == 4 && KW % 8 == 0, "four waves, whole groups of eight steps");
 };
 typedef Tile<2, 2, 1, 32> TileM;
+typedef Tile<2, 1, 2, 64> TileH;                          // half a TileM: slices of 32 steps took 10 us more of its 110
 typedef Tile<1, 1, 4, 64> TileS;
 
-// One operand slice: ROWS rows (or columns of the output) by BK steps.  KC: the contraction index is contiguous.
-// LDS pitches: 16-byte reads of 8 consecutive rows (KC) and 4-byte reads of steps 4 apart (not KC) meet all banks.
-template <int ROWS, int BK, bool KC> struct Slice {
-    static constexpr int PITCH = KC ? BK + 4 : ROWS + 8;
-    static constexpr int FLOATS = KC ? ROWS * PITCH : BK * PITCH;
-    static constexpr int N4 = ROWS * BK / 4 / F32_THREADS;
-    static_assert(ROWS * BK % (4 * F32_THREADS) == 0, "whole 16-byte pieces per thread");
-    // p: element (row 0, step 0); ld: leading dimension; n_rows, n_k: what exists from there (the rest is zero)
-    template <bool VEC>
-    static __device__ __forceinline__ void load(float4 (&r)[N4], const float* p, long ld, int n_rows, int n_k)
+typedef __attribute__((ext_vector_type(4))) int rsrc_t;     // raw buffer resource (4 scalar registers)
+constexpr uint32_t NOWHERE = 0xfffffffcu;                   // an offset past the end of every resource
+__device__ __forceinline__ rsrc_t make_rsrc(const float* base, long bytes)
+{
+    const unsigned long long b = (unsigned long long)base;
+    const unsigned n = bytes < 0 ? 0u : (bytes > 0xfffffff0l ? 0xfffffff0u : (unsigned)bytes);
+    rsrc_t r;
+    r[0] = __builtin_amdgcn_readfirstlane((int)(unsigned)b);
+    r[1] = __builtin_amdgcn_readfirstlane((int)((unsigned)(b >> 32) & 0xffffu));
+    r[2] = __builtin_amdgcn_readfirstlane((int)n);          // bytes past this limit read as zero
+    r[3] = 0x00020000;
+    return r;
+}
+// V floats per lane straight into LDS at lds_base + 4 V lane (lds_base is uniform).  As assembly, so that the compiler
+// does not wait for the request before it reads another buffer; complete after WAIT_REQUESTS.
+template <int V> __device__ __forceinline__ void request_lds(rsrc_t r, uint32_t lds_base, uint32_t voff)
+{
+    if (V == 4) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(lds_base), "v"(voff), "s"(r) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "s"(lds_base), "v"(voff), "s"(r) : "memory");
+}
+#define WAIT_REQUESTS(n) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(n) : "memory")
+
+// An operand slice as buffer loads leave it in LDS, ROWS rows (or columns of the output) by BK steps without padding.  KC:
+// the contraction index is contiguous.  V: floats per lane and request, 4 where rows of the operand begin at multiples of 16
+// bytes, else 1.  KC: 16-byte piece p of a row is kept at p ^ swizzle(row), 16 consecutive rows of one piece cover all banks.
+// Not KC: the two halves of a wave read steps 4 apart of the same 32 columns; the upper half's columns are swapped (64
+// columns: a row is all banks), or its steps lie between those of the lower half (32 columns: a row is half of them).
+template <int ROWS, int BK, bool KC, int V_> struct Slice {
+    static constexpr int V = V_ ? V_ : 1;
+    static constexpr int BYTES = ROWS * BK * 4;
+    static constexpr int REQUEST = 256 * V;                // bytes of a request
+    static constexpr int N = BYTES / REQUEST / 4;          // requests per wave
+    static constexpr int ROW = KC ? BK : ROWS;             // floats per row of the buffer
+    static constexpr int N_ADDR = KC ? BK / 8 : 1;         // address registers of the fragments of a slice
+    static_assert(BYTES % (4 * REQUEST) == 0 && (ROWS == 32 || ROWS == 64) && (BK == 32 || BK == 64) && (V == 1 || V == 4), "whole requests");
+    static __device__ __forceinline__ int swizzle(int row) { return ROW == 32 ? (row >> 1) & 7 : row & 15; }
+    // what lane `lane` of request i of wave w delivers: its row (not KC: step) and its place in it
+    static __device__ __forceinline__ void place(int i, int w, int lane, int& major, int& minor)
     {
-#pragma unroll
-        for (int i = 0; i < N4; ++i) {
-            const int it = i * F32_THREADS + (int)threadIdx.x;
-            const int major = it / (KC ? BK / 4 : ROWS / 4), minor = it % (KC ? BK / 4 : ROWS / 4) * 4;
-            const int nmaj = KC ? n_rows : n_k, nmin = KC ? n_k : n_rows;
-            const float* q = p + (long)major * ld + minor;
-            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (VEC) {                                     // nmin is a multiple of 4: a piece exists or does not
-                if (major < nmaj && minor < nmin) v = *reinterpret_cast<const float4*>(q);
-            } else if (major < nmaj) {
-                if (minor + 0 < nmin) v.x = q[0];
-                if (minor + 1 < nmin) v.y = q[1];
-                if (minor + 2 < nmin) v.z = q[2];
-                if (minor + 3 < nmin) v.w = q[3];
-            }
-            r[i] = v;
+        const int f = ((i * 4 + w) * 64 + lane) * V, r = f / ROW, c = f % ROW;
+        if (KC) { major = r; minor = c ^ (swizzle(r) << 2); }
+        else if (ROWS == 64) { major = r; minor = c ^ (32 * ((r >> 2) & 1)); }
+        else { major = (r & ~7) + 4 * (r & 1) + ((r >> 1) & 3); minor = c; }
+    }
+    // its byte offset from element (row 0, step 0) of the slice
+    static __device__ __forceinline__ uint32_t source(int i, int w, int lane, int ld)
+    {
+        int major, minor;
+        place(i, w, lane, major, minor);
+        return ((uint32_t)major * (uint32_t)ld + (uint32_t)minor) * 4u;
+    }
+    // and whether it lies past the n steps that are left of the contraction (not KC: those lie past the resource's end)
+    static __device__ __forceinline__ bool past(int i, int w, int lane, int n)
+    {
+        int major, minor;
+        place(i, w, lane, major, minor);
+        return KC && minor >= n;
+    }
+    // V_ = 0: the slice copied by the threads, with 64-bit addresses (n_rows rows or columns, n_k steps exist)
+    static __device__ __forceinline__ void copy(unsigned char* buf, const float* p, long ld, int n_rows, int n_k, int w, int lane)
+    {
+        for (int i = 0; i < N; ++i) {
+            int major, minor;
+            place(i, w, lane, major, minor);
+            const bool there = KC ? major < n_rows && minor < n_k : major < n_k && minor < n_rows;
+            reinterpret_cast<float*>(buf)[(i * 4 + w) * 64 + lane] = there ? p[major * ld + minor] : 0.0f;
         }
     }
-    static __device__ __forceinline__ void store(float* s, const float4 (&r)[N4])
+    // byte addresses in a buffer of row `row`, steps k0 + 4 hi (k0 a multiple of 8, the wave's first): KC one for each 8
+    // steps from there, else one, the others at a constant distance
+    static __device__ __forceinline__ uint32_t address(int row, int k0, int hi, int n)
     {
-#pragma unroll
-        for (int i = 0; i < N4; ++i) {
-            const int it = i * F32_THREADS + (int)threadIdx.x;
-            const int major = it / (KC ? BK / 4 : ROWS / 4), minor = it % (KC ? BK / 4 : ROWS / 4) * 4;
-            *reinterpret_cast<float4*>(s + major * PITCH + minor) = r[i];
-        }
+        if (KC) return row * (BK * 4) + (((k0 / 4 + 2 * n + hi) ^ swizzle(row)) << 4);
+        if (ROWS == 64) return k0 * 256 + hi * 1024 + ((row ^ (32 * hi)) * 4);
+        return k0 * 128 + hi * 128 + row * 4;
     }
-    // four steps k8 + 4 (lane / 32) .. + 3 of row `row`
-    static __device__ __forceinline__ void frag(float (&f)[4], const float* s, int row, int k)
+    // four steps of the fragments at 8 n steps past the wave's first
+    static __device__ __forceinline__ void frag(float (&f)[4], const unsigned char* buf, const uint32_t (&addr)[N_ADDR], int n)
     {
         if (KC) {
-            const float4 v = *reinterpret_cast<const float4*>(s + row * PITCH + k);
+            const float4 v = *reinterpret_cast<const float4*>(buf + addr[n]);
             f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) f[j] = s[(k + j) * PITCH + row];
+            for (int j = 0; j < 4; ++j)
+                f[j] = *reinterpret_cast<const float*>(buf + addr[0] + (ROWS == 64 ? n * 2048 + j * 256 : n * 1024 + j * 256));
         }
     }
 };
@@ -104,58 +145,102 @@ template <int ROWS, int BK, bool KC> struct Slice {
 struct Operand { const float* p; long ld; int n; };
 
 // acc = sum over K of A(m, k) B(k, n), acc2 the same with B2 (DUAL), or, without DUAL, acc over a second segment of
-// the contraction (n_seg = 2: A2, B2 over another K steps).
-template <class TL, bool AKC, bool BKC, bool DUAL, bool VEC>
-__device__ __forceinline__ void contract(f32x16& acc, f32x16& acc2, float* lds, Operand A, Operand B,
-                                         Operand A2, Operand B2, int n_seg, int K)
+// the contraction (n_seg = 2: A2, B2 over another K steps).  VA, VB: floats per request, 4 where the operand's pointer, its
+// leading dimension and, if its contraction index is contiguous, K are whole 16-byte pieces; 0 where the rows of a slice are
+// too far apart for a 32-bit offset.
+// Slices go from memory straight into a ring of LDS buffers while an earlier one is multiplied (two; four of the 32 x 32
+// tile, whose few products per slice don't cover a request).  On a SIMD a vector instruction of any wave takes about 8 cycles
+// from its matrix instructions, so the loop has next to none: the addresses of requests and fragments are fixed, what
+// moves is the resource's base, and what does not exist lies past the resource's end and arrives as zeros.  With the slices
+// staged through registers (predicated loads, LDS stores, 64 vector instructions per 16 products) the five launches of T =
+// 3000, d = 512, h = 2048, k = 2 took 131, 138, 154, 134 and 249 us, now 117, 121, 135, 124 and 212 in the same tiles and order.
+template <class TL, bool AKC, bool BKC, bool DUAL, int VA, int VB>
+__device__ __forceinline__ void contract(f32x16& acc, f32x16& acc2, float* lds_f, Operand A, Operand B, Operand A2, Operand B2, int n_seg, int K)
 {
-    typedef Slice<TL::BM, TL::BK, AKC> SA;
-    typedef Slice<TL::BN, TL::BK, BKC> SB;
-    constexpr int BUF = SA::FLOATS + (DUAL ? 2 : 1) * SB::FLOATS;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    typedef Slice<TL::BM, TL::BK, AKC, VA> SA;
+    typedef Slice<TL::BN, TL::BK, BKC, VB> SB;
+    static_assert((VA == 0) == (VB == 0), "both operands");
+    constexpr int BUF = SA::BYTES + (DUAL ? 2 : 1) * SB::BYTES, BK = TL::BK;
+    unsigned char* lds = reinterpret_cast<unsigned char*>(lds_f);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wk = wave % TL::WK, wn = (wave / TL::WK) % TL::WN, wm = wave / (TL::WK * TL::WN);
-    const int l32 = lane & 31, kh = 4 * (lane >> 5);
+    const int l32 = lane & 31, hi = lane >> 5;
 #pragma unroll
     for (int e = 0; e < 16; ++e) { acc[e] = 0.0f; acc2[e] = 0.0f; }
-    const int per = (K + TL::BK - 1) / TL::BK, ns = n_seg * per;
+    const int per = (K + BK - 1) / BK, ns = n_seg * per;
     if (ns == 0) return;
-    float4 ra[SA::N4], rb[SB::N4], rb2[DUAL ? SB::N4 : 1];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)lds_f;
+    uint32_t va[SA::N], vb[SB::N];                         // A2 and B2 have the leading dimensions of A and B
+#pragma unroll
+    for (int i = 0; i < SA::N; ++i) va[i] = SA::source(i, wave, lane, A.ld);
+#pragma unroll
+    for (int i = 0; i < SB::N; ++i) vb[i] = SB::source(i, wave, lane, B.ld);
+    uint32_t fa[SA::N_ADDR], fb[SB::N_ADDR];
+#pragma unroll
+    for (int n = 0; n < SA::N_ADDR; ++n) fa[n] = SA::address(wm * 32 + l32, wk * TL::KW, hi, n);
+#pragma unroll
+    for (int n = 0; n < SB::N_ADDR; ++n) fb[n] = SA::BYTES + SB::address(wn * 32 + l32, wk * TL::KW, hi, n);
+    // KC: the tile's rows, from step k0 on; else the steps from k0 on, all columns
+    auto rsrc = [&](bool kc, int rows, const Operand& o, int k0) {
+        const long n = kc ? (long)(o.n < rows ? o.n : rows) * o.ld - k0 : (long)(K - k0) * o.ld - (o.ld - o.n);
+        return make_rsrc(o.p + (kc ? (long)k0 : (long)k0 * o.ld), n * 4);
+    };
     auto request = [&](int s) {
         const bool second = s >= per;
-        const int k0 = (second ? s - per : s) * TL::BK;
+        const int k0 = (second ? s - per : s) * BK, left = K - k0;
         const Operand a = second ? A2 : A, b = second ? B2 : B;
-        SA::template load<VEC>(ra, a.p + (AKC ? (long)k0 : (long)k0 * a.ld), a.ld, a.n, K - k0);
-        SB::template load<VEC>(rb, b.p + (BKC ? (long)k0 : (long)k0 * b.ld), b.ld, b.n, K - k0);
-        if constexpr (DUAL) SB::template load<VEC>(rb2, B2.p + (BKC ? (long)k0 : (long)k0 * B2.ld), B2.ld, B2.n, K - k0);
-    };
-    auto keep = [&](float* buf) {
-        SA::store(buf, ra);
-        SB::store(buf + SA::FLOATS, rb);
-        if constexpr (DUAL) SB::store(buf + SA::FLOATS + SB::FLOATS, rb2);
-    };
-    request(0);
-    keep(lds);
-    __syncthreads();
-    for (int s = 0; s < ns; ++s) {
-        if (s + 1 < ns) request(s + 1);
-        const float* sa = lds + (s & 1) * BUF;
-        const float* sb = sa + SA::FLOATS;
+        if constexpr (VA == 0) {
+            unsigned char* to = lds + s % TL::STAGES * BUF;
+            SA::copy(to, a.p + (AKC ? (long)k0 : (long)k0 * a.ld), a.ld, a.n, left, wave, lane);
+            SB::copy(to + SA::BYTES, b.p + (BKC ? (long)k0 : (long)k0 * b.ld), b.ld, b.n, left, wave, lane);
+            if constexpr (DUAL) SB::copy(to + SA::BYTES + SB::BYTES, B2.p + (BKC ? (long)k0 : (long)k0 * B2.ld), B2.ld, B2.n, left, wave, lane);
+            return;
+        }
+        const rsrc_t ra = rsrc(AKC, TL::BM, a, k0), rb = rsrc(BKC, TL::BN, b, k0);
+        const uint32_t dst = lds0 + s % TL::STAGES * BUF, da = dst + wave * SA::REQUEST, db = dst + SA::BYTES + wave * SB::REQUEST;
+        if ((AKC || BKC) && left < BK) {                   // past the contraction lies the next row, not the end
 #pragma unroll
-        for (int k8 = 0; k8 < TL::KW; k8 += 8) {
-            const int k = wk * TL::KW + k8 + kh;
+            for (int i = 0; i < SA::N; ++i) request_lds<VA>(ra, da + i * 4 * SA::REQUEST, SA::past(i, wave, lane, left) ? NOWHERE : va[i]);
+#pragma unroll
+            for (int i = 0; i < SB::N; ++i) request_lds<VB>(rb, db + i * 4 * SB::REQUEST, SB::past(i, wave, lane, left) ? NOWHERE : vb[i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < SA::N; ++i) request_lds<VA>(ra, da + i * 4 * SA::REQUEST, va[i]);
+#pragma unroll
+            for (int i = 0; i < SB::N; ++i) request_lds<VB>(rb, db + i * 4 * SB::REQUEST, vb[i]);
+        }
+        if constexpr (DUAL) {
+            static_assert(!DUAL || !BKC, "the second matrix ends with its steps");
+            const rsrc_t rb2 = rsrc(BKC, TL::BN, B2, k0);
+#pragma unroll
+            for (int i = 0; i < SB::N; ++i) request_lds<VB>(rb2, db + SB::BYTES + i * 4 * SB::REQUEST, vb[i]);
+        }
+    };
+    // Slice s + AHEAD is requested into the buffer of slice s - 1, which everybody has left at the barrier of slice s.
+    constexpr int AHEAD = TL::STAGES - 1, OPS = SA::N + (DUAL ? 2 : 1) * SB::N;
+    static_assert((AHEAD - 1) * OPS < 64, "what the counter of requests can say");
+    for (int s = 0; s < AHEAD && s < ns; ++s) request(s);
+    for (int s = 0, cur = 0; s < ns; ++s) {
+        if (s + AHEAD <= ns) WAIT_REQUESTS((AHEAD - 1) * OPS);     // slice s has landed, AHEAD - 1 later ones are on their way
+        else WAIT_REQUESTS(0);
+        __syncthreads();
+        if (s + AHEAD < ns) request(s + AHEAD);
+        const unsigned char* buf = lds + cur * BUF;
+        cur = cur + 1 == TL::STAGES ? 0 : cur + 1;
+#pragma unroll
+        for (int n = 0; n < TL::KW / 8; ++n) {
             float a[4], b[4], b2[4];
-            SA::frag(a, sa, wm * 32 + l32, k);
-            SB::frag(b, sb, wn * 32 + l32, k);
-            if constexpr (DUAL) SB::frag(b2, sb + SB::FLOATS, wn * 32 + l32, k);
+            SA::frag(a, buf, fa, n);
+            SB::frag(b, buf, fb, n);
+            if constexpr (DUAL) SB::frag(b2, buf + SB::BYTES, fb, n);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], acc, 0, 0, 0);
                 if constexpr (DUAL) acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b2[q], acc2, 0, 0, 0);
             }
         }
-        if (s + 1 < ns) keep(lds + ((s + 1) & 1) * BUF);   // the buffer of slice s - 1, which everybody has left
-        __syncthreads();
     }
+    __syncthreads();                                       // the buffers are free
 }
 
 // Calls out(m, n, acc, acc2) for every element of the tile (m, n inside the tile).  Waves that shared the contraction
@@ -170,7 +255,8 @@ __device__ __forceinline__ void for_each_output(f32x16& acc, f32x16& acc2, float
 #pragma unroll
         for (int e = 0; e < 16; ++e) out(wm * 32 + 8 * (e >> 2) + kh + (e & 3), wn * 32 + l32, acc[e], acc2[e]);
     } else {
-        static_assert(TL::WK == 1 || TL::WK == 4, "one tile, four parts of its contraction");
+        constexpr int OWN = 16 / TL::WK;                   // registers a wave adds up and hands out
+        const int wk = wave % TL::WK;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             lds[(wave * 16 + e) * 64 + lane] = acc[e];
@@ -178,22 +264,22 @@ __device__ __forceinline__ void for_each_output(f32x16& acc, f32x16& acc2, float
         }
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = wave * 4 + q;
+        for (int q = 0; q < OWN; ++q) {
+            const int e = wk * OWN + q;
             float v = 0.0f, v2 = 0.0f;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                v += lds[(w * 16 + e) * 64 + lane];
-                if constexpr (DUAL) v2 += lds[4096 + (w * 16 + e) * 64 + lane];
+            for (int w = 0; w < TL::WK; ++w) {
+                v += lds[((wave - wk + w) * 16 + e) * 64 + lane];
+                if constexpr (DUAL) v2 += lds[4096 + ((wave - wk + w) * 16 + e) * 64 + lane];
             }
-            out(8 * wave + kh + q, l32, v, v2);
+            out(wm * 32 + 8 * (e >> 2) + kh + (e & 3), wn * 32 + l32, v, v2);
         }
     }
 }
 
-template <class TL, bool AKC, bool BKC, bool DUAL> constexpr int lds_floats()
+template <class TL, bool DUAL> constexpr int lds_floats()
 {
-    constexpr int ring = 2 * (Slice<TL::BM, TL::BK, AKC>::FLOATS + (DUAL ? 2 : 1) * Slice<TL::BN, TL::BK, BKC>::FLOATS);
+    constexpr int ring = TL::STAGES * (TL::BM + (DUAL ? 2 : 1) * TL::BN) * TL::BK;
     constexpr int fold = TL::WK == 1 ? 0 : (DUAL ? 8192 : 4096);
     return ring > fold ? ring : fold;
 }
@@ -222,23 +308,23 @@ __device__ __forceinline__ bool find_row_tile(const F32Args& a, int rt, int bm, 
         if (past) {
             const int l = __ffsll((long long)past) - 1;
             g = g0 + l;
-            row0 = __shfl(r0, l, 64);
-            rows = __shfl(n, l, 64);
-            first_row = (rt - before - (__shfl(incl, l, 64) - __shfl(nt, l, 64))) * bm;
+            row0 = __builtin_amdgcn_readlane(r0, l);
+            rows = __builtin_amdgcn_readlane(n, l);
+            first_row = (rt - before - (__builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(nt, l))) * bm;
             return true;
         }
-        before += __shfl(incl, 63, 64);
+        before += __builtin_amdgcn_readlane(incl, 63);
     }
     return false;
 }
 
 // grid: column tiles x row tiles (an upper bound), so that the columns of a row tile run next to each other.  (Two axes: a
 // grid has fewer than 2^32 threads along each, and wide layers of many groups need more in all.)
-template <int MODE, class TL, bool DUAL, bool VEC>
+template <int MODE, class TL, bool DUAL, int VD, int VH>
 __global__ __launch_bounds__(F32_THREADS) void ffn_f32_kernel(F32Args a)
 {
     constexpr bool BKC = (MODE == BWD1 || MODE == BWD2);
-    __shared__ __attribute__((aligned(16))) float lds[lds_floats<TL, true, BKC, DUAL>()];
+    __shared__ __attribute__((aligned(1024))) float lds[lds_floats<TL, DUAL>()];
     int g, first_row, row0, rows;
     if (!find_row_tile(a, blockIdx.y, TL::BM, g, first_row, row0, rows)) return;
     const int d = a.d, h = a.h, n0 = blockIdx.x * TL::BN, nr = rows - first_row;
@@ -247,7 +333,7 @@ __global__ __launch_bounds__(F32_THREADS) void ffn_f32_kernel(F32Args a)
     f32x16 acc, acc2;
     if (MODE == FWD1) {
         const Operand A{a.Xp + r0 * d, d, nr}, B{a.W1 + wdh + n0, h, h - n0}, B2{DUAL ? a.W3 + wdh + n0 : nullptr, h, h - n0};
-        contract<TL, true, BKC, DUAL, VEC>(acc, acc2, lds, A, B, A, B2, 1, d);
+        contract<TL, true, BKC, DUAL, VD, VH>(acc, acc2, lds, A, B, A, B2, 1, d);
         for_each_output<TL, DUAL>(acc, acc2, lds, [&](int m, int n, float z, float u) {
             if (m >= nr || n0 + n >= h) return;
             const long o = (r0 + m) * h + n0 + n;
@@ -257,13 +343,13 @@ __global__ __launch_bounds__(F32_THREADS) void ffn_f32_kernel(F32Args a)
         });
     } else if (MODE == FWD2) {
         const Operand A{a.Actc + r0 * h, h, nr}, B{a.W2 + wdh + n0, d, d - n0};
-        contract<TL, true, BKC, false, VEC>(acc, acc2, lds, A, B, A, B, 1, h);
+        contract<TL, true, BKC, false, VH, VD>(acc, acc2, lds, A, B, A, B, 1, h);
         for_each_output<TL, false>(acc, acc2, lds, [&](int m, int n, float y, float) {
             if (m < nr && n0 + n < d) a.Yp[(r0 + m) * d + n0 + n] = y;
         });
     } else if (MODE == BWD1) {                              // dA[m, n] = sum_c dYp[m, c] W2[n, c]
         const Operand A{a.dYp + r0 * d, d, nr}, B{a.W2 + wdh + (long)n0 * d, d, h - n0};
-        contract<TL, true, BKC, false, VEC>(acc, acc2, lds, A, B, A, B, 1, d);
+        contract<TL, true, BKC, false, VD, VD>(acc, acc2, lds, A, B, A, B, 1, d);
         for_each_output<TL, false>(acc, acc2, lds, [&](int m, int n, float v, float) {
             if (m >= nr || n0 + n >= h) return;
             const long o = (r0 + m) * h + n0 + n;
@@ -281,22 +367,40 @@ __global__ __launch_bounds__(F32_THREADS) void ffn_f32_kernel(F32Args a)
     } else {                                                // dXp[m, n] = sum_j dZ[m, j] W1[n, j] (+ dU[m, j] W3[n, j])
         const Operand A{a.dZc + r0 * h, h, nr}, B{a.W1 + wdh + (long)n0 * h, h, d - n0};
         const Operand A2 = swiglu ? Operand{a.dUc + r0 * h, h, nr} : A, B2 = swiglu ? Operand{a.W3 + wdh + (long)n0 * h, h, d - n0} : B;
-        contract<TL, true, BKC, false, VEC>(acc, acc2, lds, A, B, A2, B2, swiglu ? 2 : 1, h);
+        contract<TL, true, BKC, false, VH, VH>(acc, acc2, lds, A, B, A2, B2, swiglu ? 2 : 1, h);
         for_each_output<TL, false>(acc, acc2, lds, [&](int m, int n, float v, float) {
             if (m < nr && n0 + n < d) a.dXp[(r0 + m) * d + n0 + n] = v;
         });
     }
 }
 
+// The group with the nth most rows (ties: the lower group first; groups past the hosted ones have none), so that the blocks
+// with the longest contraction start first and the short ones fill the chip while they end.  More than 64 groups: as they come.
+__device__ __forceinline__ int nth_longest(const F32Args& a, int nth, int first, int ng)
+{
+    if (a.Gcap > 64) return nth;
+    const int lane = threadIdx.x & 63;
+    int n = lane < a.Gcap ? 0 : -1;
+    if (lane < ng) n = a.slot_offsets[first + lane + 1] - a.slot_offsets[first + lane];
+    int rank = 0;
+    for (int i = 0; i < a.Gcap; ++i) {
+        const int o = __builtin_amdgcn_readlane(n, i);
+        rank += (o > n || (o == n && i < lane)) ? 1 : 0;
+    }
+    return __ffsll((long long)__ballot(lane < a.Gcap && rank == nth)) - 1;
+}
+
 // Weight gradients, all products of all groups in one launch: out[m, n] = sum over the group's rows r of L[r, m] R[r, n]
 // (dW1 = Xp^T dZ, dW2 = Act^T dYp, dW3 = Xp^T dU).  grid: tiles of a product x (products of group 0, of group 1, ...).
-template <class TL, bool VEC>
+template <class TL, int VD, int VH>
 __global__ __launch_bounds__(F32_THREADS) void ffn_f32_wgrad_kernel(F32Args a, int n_products)
 {
-    __shared__ __attribute__((aligned(16))) float lds[lds_floats<TL, false, false, false>()];
-    const int g = blockIdx.y / n_products, which = blockIdx.y % n_products, tile = blockIdx.x;
+    __shared__ __attribute__((aligned(1024))) float lds[lds_floats<TL, false>()];
+    const int which = blockIdx.y % n_products, tile = blockIdx.x;
     int first, ng;
     hosted_range(a.dest_slots, a.self, a.Gcap, first, ng);
+    // (32 x 32 tiles: too little work for the order to pay for itself, 0.6 us of 34)
+    const int g = TL::WK == 1 ? nth_longest(a, blockIdx.y / n_products, first, ng) : blockIdx.y / n_products;
     int row0 = 0, rows = 0;
     if (g < ng) { row0 = a.slot_offsets[first + g]; rows = a.slot_offsets[first + g + 1] - row0; }
     const int Mo = which == 1 ? a.h : a.d, No = which == 1 ? a.d : a.h;
@@ -307,7 +411,8 @@ __global__ __launch_bounds__(F32_THREADS) void ffn_f32_wgrad_kernel(F32Args a, i
     const float* R = which == 0 ? a.dZc : (which == 1 ? a.dYp : a.dUc);
     const Operand A{L + (long)row0 * Mo + m0, Mo, Mo - m0}, B{R + (long)row0 * No + n0, No, No - n0};
     f32x16 acc, acc2;
-    contract<TL, false, false, false, VEC>(acc, acc2, lds, A, B, A, B, 1, rows);
+    if (VD == VH || which != 1) contract<TL, false, false, false, VD, VH>(acc, acc2, lds, A, B, A, B, 1, rows);
+    else contract<TL, false, false, false, VH, VD>(acc, acc2, lds, A, B, A, B, 1, rows);
     float* dst = (which == 0 ? a.dW1 : (which == 1 ? a.dW2 : a.dW3)) + (long)g * a.d * a.h;
     for_each_output<TL, false>(acc, acc2, lds, [&](int m, int n, float v, float) {
         if (m0 + m >= Mo || n0 + n >= No) return;
@@ -334,46 +439,64 @@ F32Args make_args(const moe_shape_t& s, const ffn_args& a)
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-// 16-byte loads need every row of every operand 16-byte aligned: d is a multiple of 4 (moe_create), h and the pointers
-// are looked at here; anything else takes 4-byte loads.
-bool vec_ok(const moe_shape_t& s, std::initializer_list<const void*> ps)
+// How operands are requested.  d is a multiple of 4 (moe_create), so rows of d floats begin at multiples of 16 bytes where
+// their tensors do; rows of h floats also need h to be a multiple of 4.  A 32-bit offset reaches the 64 rows or steps of a
+// slice.  Requests of 4 bytes instead of 16 cost little: T = 3000, d = 512, k = 2, forward and backward, h = 2048 578 us, 2047
+// 602 (1023 with predicated 4-byte loads into registers).
+enum Requests { ALL_16 = 0, ROWS_OF_D_16 = 1, ALL_4 = 2, COPIED = 3 };
+Requests requests_of(const moe_shape_t& s, std::initializer_list<const void*> rows_of_d, std::initializer_list<const void*> rows_of_h)
 {
-    uintptr_t bits = 0;
-    for (const void* p : ps) bits |= reinterpret_cast<uintptr_t>(p);
-    return s.h % 4 == 0 && (bits & 15) == 0;
+    constexpr int FAR = (1 << 24) - 64;
+    if (s.d > FAR || s.h > FAR) return COPIED;
+    uintptr_t bits_d = 0, bits_h = s.h % 4;
+    for (const void* p : rows_of_d) bits_d |= reinterpret_cast<uintptr_t>(p);
+    for (const void* p : rows_of_h) bits_h |= reinterpret_cast<uintptr_t>(p);
+    return (bits_d & 15) ? ALL_4 : ((bits_h & 15) ? ROWS_OF_D_16 : ALL_16);
 }
 
-// 64 x 64 tiles where there are enough of them (rows: all T * k of them, of which a part is hosted here).  Forward and
-// backward of the two contractions, us, 32 x 32 against 64 x 64: 512 and 128 tiles (T = 1000, d = 256, h = 1024, k = 2)
-// 38 + 67 against 48 + 82; 3008 and 752 tiles (T = 3000, d = 512, h = 2048) 245 + 471 against 229 + 447; 6000 and 2000
-// tiles (T = 4000, d = 1024, h = 3072) 877 + 1732 against 768 + 1513.  128 x 128 was the slower one everywhere (287 + 545,
-// 799 + 1626 on the latter two: fewer blocks to hide a load behind, a longer last round).
-bool medium_tiles(long rows, long cols) { return ((rows + 63) / 64) * ((cols + 63) / 64) >= 700; }
+// Which tile, by the number of 64 x 64 tiles of all T k rows (a part of them is hosted here).  Few: 32 x 32, the serial chain
+// is what counts.  A few per CU: 64 x 32 with two waves along the contraction, because a CU that gets three tiles where
+// others get two is what the launch waits for.  More: 64 x 64, which requests and reads least per product.  Measured, us, one
+// row contraction, 32 x 32 | 64 x 32 | 64 x 64 (T, k = 2, contraction, width; tiles): 600, 1024, 512 (152) 22.0 | 24.0 | 28.2;
+// 4000, 3000, 128 (250) 75 | 67 | 86;  600, 512, 1024 (304) 23.4 | 20.8 | 25.4;  4000, 1024, 256 (500) 46 | 36 | 45;  3000, 2048,
+// 512 (752) 130 | 111 | 121;  1500, 3000, 1000 (752) 193 | 166 | 176;  4000, 200, 640 (1250) 35 | 33 | 30;  1500, 512, 2048
+// (1504) 76 | 74 | 68;  4000, 3000, 1000 (2000) 439 | 382 | 384;  3000, 512, 2048 (3008) 148 | 135 | 115.  128 x 128 was the slower
+// one everywhere (fewer blocks to hide a request behind, a longer last round).  The weight gradients, whose tiles are all of
+// one launch, take 64 x 64 from 700 tiles on.
+constexpr long HALF_TILES = 200, MEDIUM_TILES = 1100, MEDIUM_TILES_WGRAD = 700;
+long tiles64(long rows, long cols) { return ((rows + 63) / 64) * ((cols + 63) / 64); }
 
 template <int MODE, class TL, bool DUAL>
-void launch_rows_t(const moe_shape_t& s, const F32Args& f, int N, bool vec, hipStream_t st)
+void launch_rows_t(const moe_shape_t& s, const F32Args& f, int N, Requests r, hipStream_t st)
 {
-    const int ct = cdiv(N, TL::BN), rt = cdiv(s.T * s.k, TL::BM) + s.G;
-    if (vec) hipLaunchKernelGGL((ffn_f32_kernel<MODE, TL, DUAL, true>), dim3(ct, rt), dim3(F32_THREADS), 0, st, f);
-    else hipLaunchKernelGGL((ffn_f32_kernel<MODE, TL, DUAL, false>), dim3(ct, rt), dim3(F32_THREADS), 0, st, f);
+    const dim3 grid(cdiv(N, TL::BN), cdiv(s.T * s.k, TL::BM) + s.G);
+    if (r == ALL_16) hipLaunchKernelGGL((ffn_f32_kernel<MODE, TL, DUAL, 4, 4>), grid, dim3(F32_THREADS), 0, st, f);
+    else if (r == ROWS_OF_D_16) hipLaunchKernelGGL((ffn_f32_kernel<MODE, TL, DUAL, 4, 1>), grid, dim3(F32_THREADS), 0, st, f);
+    else hipLaunchKernelGGL((ffn_f32_kernel<MODE, TL, DUAL, 1, 1>), grid, dim3(F32_THREADS), 0, st, f);
 }
 
 template <int MODE, bool DUAL>
-hipError_t launch_rows(const moe_shape_t& s, const F32Args& f, int N, bool vec, hipStream_t st)
+hipError_t launch_rows(const moe_shape_t& s, const F32Args& f, int N, Requests r, hipStream_t st)
 {
-    if (medium_tiles((long)s.T * s.k, N)) launch_rows_t<MODE, TileM, DUAL>(s, f, N, vec, st);
-    else launch_rows_t<MODE, TileS, DUAL>(s, f, N, vec, st);
+    const long tiles = tiles64((long)s.T * s.k, N);
+    if (r == COPIED)
+        hipLaunchKernelGGL((ffn_f32_kernel<MODE, TileS, DUAL, 0, 0>), dim3(cdiv(N, TileS::BN), cdiv(s.T * s.k, TileS::BM) + s.G), dim3(F32_THREADS), 0, st, f);
+    else if (tiles >= MEDIUM_TILES) launch_rows_t<MODE, TileM, DUAL>(s, f, N, r, st);
+    else if (tiles >= HALF_TILES) launch_rows_t<MODE, TileH, DUAL>(s, f, N, r, st);
+    else launch_rows_t<MODE, TileS, DUAL>(s, f, N, r, st);
     return hipGetLastError();
 }
 
 template <class TL>
-hipError_t launch_wgrad(const moe_shape_t& s, const F32Args& f, bool vec, hipStream_t st)
+hipError_t launch_wgrad(const moe_shape_t& s, const F32Args& f, Requests r, hipStream_t st)
 {
     const int tiles = cdiv(s.d, TL::BM) * cdiv(s.h, TL::BN), np = s.act == MOE_ACT_SWIGLU ? 3 : 2;
     static_assert(TL::BM == TL::BN, "d x h and h x d have the same number of tiles");
     const dim3 grid(tiles, np * s.G);
-    if (vec) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, true>), grid, dim3(F32_THREADS), 0, st, f, np);
-    else hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, false>), grid, dim3(F32_THREADS), 0, st, f, np);
+    if (r == ALL_16) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 4, 4>), grid, dim3(F32_THREADS), 0, st, f, np);
+    else if (r == ROWS_OF_D_16) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 4, 1>), grid, dim3(F32_THREADS), 0, st, f, np);
+    else if (r == ALL_4) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 1, 1>), grid, dim3(F32_THREADS), 0, st, f, np);
+    else hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 0, 0>), grid, dim3(F32_THREADS), 0, st, f, np);
     return hipGetLastError();
 }
 
@@ -382,19 +505,19 @@ hipError_t launch_wgrad(const moe_shape_t& s, const F32Args& f, bool vec, hipStr
 hipError_t launch_ffn_fwd_f32(const moe_shape_t& s, const ffn_args& a, hipStream_t st)
 {
     const F32Args f = make_args(s, a);
-    const bool vec = vec_ok(s, {a.Xp, a.W1, a.W2, a.W3, a.Act});
-    hipError_t e = s.act == MOE_ACT_SWIGLU ? launch_rows<FWD1, true>(s, f, s.h, vec, st) : launch_rows<FWD1, false>(s, f, s.h, vec, st);
-    if (e == hipSuccess) e = launch_rows<FWD2, false>(s, f, s.d, vec, st);
+    const Requests r = requests_of(s, {a.Xp, a.W2}, {a.W1, a.W3, a.Act});
+    hipError_t e = s.act == MOE_ACT_SWIGLU ? launch_rows<FWD1, true>(s, f, s.h, r, st) : launch_rows<FWD1, false>(s, f, s.h, r, st);
+    if (e == hipSuccess) e = launch_rows<FWD2, false>(s, f, s.d, r, st);
     return e;
 }
 
 hipError_t launch_ffn_bwd_f32(const moe_shape_t& s, const ffn_args& a, hipStream_t st)
 {
     const F32Args f = make_args(s, a);
-    const bool vec = vec_ok(s, {a.dYp, a.Xp, a.W1, a.W2, a.W3, a.Act, a.dZ, a.dU});
-    hipError_t e = launch_rows<BWD1, false>(s, f, s.h, vec, st);
-    if (e == hipSuccess) e = launch_rows<BWD2, false>(s, f, s.d, vec, st);
+    const Requests r = requests_of(s, {a.dYp, a.Xp, a.W2}, {a.W1, a.W3, a.Act, a.dZ, a.dU});
+    hipError_t e = launch_rows<BWD1, false>(s, f, s.h, r, st);
+    if (e == hipSuccess) e = launch_rows<BWD2, false>(s, f, s.d, r, st);
     if (e != hipSuccess) return e;
     const int np = s.act == MOE_ACT_SWIGLU ? 3 : 2;
-    return medium_tiles((long)s.d * np, (long)s.h * s.G) ? launch_wgrad<TileM>(s, f, vec, st) : launch_wgrad<TileS>(s, f, vec, st);
+    return tiles64((long)s.d * np, (long)s.h * s.G) >= MEDIUM_TILES_WGRAD ? launch_wgrad<TileM>(s, f, r, st) : launch_wgrad<TileS>(s, f, r, st);
 }

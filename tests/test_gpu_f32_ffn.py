@@ -1,5 +1,5 @@
-"""The fp32 grouped FFN on the fp32 matrix cores against the oracle, at the sizes where its tiles can go wrong: both tile
-sizes (32 x 32 with a shared contraction, 64 x 64), widths that are no multiple of a tile, a slice or four floats, ragged
+"""The fp32 grouped FFN on the fp32 matrix cores against the oracle, at the sizes where its tiles can go wrong: the tile
+sizes (32 x 32 and 64 x 32 with a shared contraction, 64 x 64), widths that are no multiple of a tile, a slice or four floats, ragged
 and empty groups, more groups than lanes, and operands that are not 16-byte aligned.  Checks and tolerance (1e-5, row by
 row) are those of test_gpu_parity.py."""
 import numpy as np
@@ -22,12 +22,14 @@ def _cfg(**kw):
 
 CASES = [
     _cfg(T=70, d=64, h=32),                                     # one tile across, contractions of one slice and less
-    _cfg(T=97, d=68, h=33, act="swiglu"),                       # widths one past a tile; h odd: 4-byte loads
+    _cfg(T=97, d=68, h=33, act="swiglu"),                       # widths one past a tile; h odd: 4-byte requests
     _cfg(T=200, d=60, h=127),
     _cfg(T=333, d=132, h=260, act="swiglu", alpha=2.5),         # h a multiple of four only, very uneven groups
     _cfg(T=640, d=256, h=64, k=1, E=80, P=1, n_replicas=0),     # 80 hosted groups, some of them empty
-    _cfg(T=2500, d=516, h=1092),                                # 64 x 64 tiles in every contraction, remainders in all
-    _cfg(T=2500, d=516, h=1090, act="swiglu", alpha=2.0),       # the same with 4-byte loads
+    _cfg(T=2500, d=516, h=1092),                                # 64 x 64 tiles, 64 x 32 where 516 wide, remainders in all
+    _cfg(T=1100, d=292, h=612, act="swiglu"),                   # 64 x 32 tiles of two weight matrices, last slices of 36 steps
+    _cfg(T=2500, d=260, h=1092, act="swiglu", alpha=2.0),       # 64 x 64 tiles of two weight matrices, last slices of 4 steps
+    _cfg(T=2500, d=516, h=1090, act="swiglu", alpha=2.0),       # the same with 4-byte requests
 ]
 _ids = lambda c: f"{c.act}-T{c.T}-d{c.d}-h{c.h}-E{c.E}-k{c.k}"   # noqa: E731
 
@@ -53,7 +55,7 @@ def _shifted(t):
 
 @pytest.mark.parametrize("act", ["gelu", "swiglu"])
 def test_unaligned_operands_give_the_same_bits(G, act):
-    """4-byte loads feed the same order of multiply-adds as 16-byte loads."""
+    """4-byte requests feed the same order of multiply-adds as 16-byte requests."""
     cfg = _cfg(T=300, d=128, h=192, act=act)
     case = G.Case(cfg)
     hd = G.make_handle(cfg)
@@ -119,3 +121,33 @@ def test_more_tiles_than_the_threads_of_one_axis(G):
         assert not bool(dW1[e].any()) and not bool(dW2[e].any())
     del W1, W2, dW1, dW2
     torch.cuda.empty_cache()
+
+
+def test_rows_too_far_apart_for_an_offset(G):
+    """A hidden layer of 2^24: 64 rows of it are 2^32 bytes.  Against a float64 product; tolerance as for the many tiles above."""
+    d, h, rows = 4, 1 << 24, [3, 0, 2]
+    hd = G.binding.Handle(T=5, d=d, h=h, E=3, k=1, P=1, self_dest=0, G=3, dtype="f32", act="gelu", renorm=0, device=G.DEV)
+    g = torch.Generator(device=G.DEV).manual_seed(11)
+    idx = torch.repeat_interleave(torch.arange(3, dtype=torch.int32), torch.tensor(rows)).to(G.DEV)
+    counts, lay = torch.zeros(3, dtype=torch.int32, device=G.DEV), hd.new_layout()
+    X, dYp = torch.randn(5, d, device=G.DEV, generator=g), torch.randn(5, d, device=G.DEV, generator=g)
+    Xp, Z = torch.empty(5, d, device=G.DEV), torch.zeros(5, h, device=G.DEV)
+    hd.expert_counts(idx, counts)
+    hd.dispatch(torch.zeros(3, dtype=torch.int32, device=G.DEV), X, idx, counts, lay, Xp)
+    W1 = torch.randn(3, d, h, device=G.DEV, generator=g) * d ** -0.5
+    W2 = torch.randn(3, h, d, device=G.DEV, generator=g) * h ** -0.5
+    Yp, dXp, dW1, dW2 = torch.zeros(5, d, device=G.DEV), torch.zeros(5, d, device=G.DEV), torch.full_like(W1, 7.0), torch.full_like(W2, 7.0)
+    hd.expert_ffn_fwd(Xp, lay, W1, W2, None, Yp, Z, None)
+    hd.expert_ffn_bwd(dYp, Xp, Z, None, lay, W1, W2, None, dXp, dW1, dW2, None)
+    torch.cuda.synchronize()
+    assert not bool(dW1[1].any()) and not bool(dW2[1].any())
+    chain = 4 * (h / 2 / 3) ** 0.5 * 2.0 ** -24
+    rel = lambda a, b: float((a.double() - b).norm() / b.norm())   # noqa: E731
+    for e, o in ((0, 0), (2, 3)):
+        n = rows[e]
+        x, dy, w1, w2 = Xp[o:o + n].double(), dYp[o:o + n].double(), W1[e].double(), W2[e].double()
+        z = x @ w1
+        cdf = 0.5 * (1 + torch.erf(z * 0.5 ** 0.5))
+        dz = (dy @ w2.t()) * (cdf + z * torch.exp(-0.5 * z * z) * (2 * np.pi) ** -0.5)
+        assert rel(Yp[o:o + n], (z * cdf) @ w2) < chain and rel(dXp[o:o + n], dz @ w1.t()) < chain
+        assert rel(dW1[e], x.t() @ dz) < 1e-5 and rel(dW2[e], (z * cdf).t() @ dy) < 1e-5
