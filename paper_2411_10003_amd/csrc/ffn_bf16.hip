@@ -83,7 +83,14 @@ struct GemmParams {
     int split_cap;               // units that fit there
     int tn_over;                 // TN: what a tile costs beside its slices, in slices
     int split_max, split_slices; // parts of a tile at most, slices of a part at least
+    int uneven_cap;              // units an uneven cut may use (0: none is made)
+    int* arrived;                // uneven cut: parts of a tile that have been stored, a counter per tile; all zero between two launches
+    int clear_arrived;           // the first launch of a call: make them so
 };
+
+// Row contractions whose tiles may be cut unevenly, the part that is done last finishing its tile.  The counters that takes are
+// cleared by the first launch of a call (fwd1, bwd1), which therefore has no such tiles itself.
+constexpr bool last_finishes(int epi) { return epi == EPI_BF16; }
 
 // How contractions are cut, for the kernel (which alone knows the rows) and for moe_ffn_tiling (which is told them).
 // NN/NT: parts of each of the `rem` tiles left over after the last full round of `nblk` blocks.
@@ -94,6 +101,20 @@ __host__ __device__ inline int row_parts(int rem, int nblk, int slices, int spli
     int S = fill < split_max ? fill : split_max;
     if (S > worth) S = worth > 1 ? worth : 1;
     return rem * S > split_cap ? 1 : S;
+}
+// NN/NT, epilogues of last_finishes: where the tiles left over are more than half of the blocks (and stay whole by the rule
+// above), each keeps a block for its first slices and the other blocks share the rest, `turns` remainders each.  Returns the
+// first slices (0: the tiles stay whole).  A remainder costs its block about UNEVEN_OVER slices beside its own (ring filled,
+// 256 KB stored), and the block that finishes a tile about as much again to add it, so a remainder has to be worth twice that.
+constexpr int UNEVEN_OVER = 14, UNEVEN_SLICES = 28;
+__host__ __device__ inline int uneven_cut(int rem, int nblk, int slices, int cap, int& turns)
+{
+    const int others = nblk - rem;
+    turns = 0;
+    if (rem <= others || others <= 0 || 2 * rem > cap) return 0;
+    turns = (rem + others - 1) / others;
+    const int rest = (slices - turns * UNEVEN_OVER) / (turns + 1) & ~1;
+    return rest >= UNEVEN_SLICES ? slices - rest : 0;
 }
 // TN: parts of a group of k slices.  Its rounds (a round: as many tiles as an XCD has blocks, or what there are) run on one
 // XCD each, so cutting it shortens the whole only where it is longer than an XCD's share of all rounds; the parts are then
@@ -268,6 +289,7 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     constexpr bool A_KMAJOR = (KIND == KIND_TN);
     constexpr bool B_KMAJOR = (KIND != KIND_NT);
     constexpr bool DUAL = (EPI == EPI_FWD1_SWIGLU);
+    constexpr bool LAST = last_finishes(EPI) && !FIN;
     static_assert(!DUAL || (TN % 2 == 0), "dual-B needs an even number of column fragments per wave");
 
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -276,6 +298,9 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
+
+    if (!FIN && p.clear_arrived)
+        for (int i = blockIdx.x * GEO::THREADS + tid; i < SPLIT_COUNTERS; i += gridDim.x * GEO::THREADS) p.arrived[i] = 0;
 
     // ---- group table, once per block: lane i of every wave holds hosted group i (at most 64 groups)
     int first_slot, n_groups;
@@ -318,7 +343,9 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     if (KIND != KIND_TN && p.split_ws != nullptr)
         S = row_parts(rem, nblk, p.n_seg * (p.Kseg / BK), p.split_max, p.split_slices, p.split_cap);
     if (KIND != KIND_TN && FIN && S == 1) return;
-    const int n_items = n_full + rem * S;
+    int turns = 0, first_slices = 0;                       // uneven cut: remainders per block, slices of a tile's first part
+    if (LAST && S == 1) first_slices = uneven_cut(rem, nblk, p.n_seg * (p.Kseg / BK), p.uneven_cap, turns);
+    const int n_items = LAST && first_slices ? n_full + nblk : n_full + rem * S;
     const int n_rounds = (n_items + q_stride - 1) / q_stride;
 
     // TN: the contraction of a group is as long as its rows are many, and a group may have fewer tiles than there are
@@ -425,7 +452,8 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     const int q_end = FIN ? (KIND == KIND_TN ? __popcll(tn_split_mask) * tiles_g : rem) * TM       // FIN: a row of fragments of a tile is an item
                           : (KIND == KIND_TN ? 0x7fffffff : ((n_rounds + 7) >> 3) * q_stride);
 
-  for (int q = q_first; q < q_end; q += q_step) {
+  int turn = 0, next = q_step;
+  for (int q = q_first; q < q_end; q += next) {
     int g, rt, ct;
     int part = 0, parts = 1, unit = 0;                     // K-split: which part of how many, and where it is kept
     long a_row0, a_row_end;      // valid rows of the A tile (NN/NT) or of the contraction (TN)
@@ -474,7 +502,22 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
             const int item = (((q - q0) / q_stride) * 8 + xcd) * q_stride + q0;
             if (item >= n_items) break;
             t = item;
-            if (item >= n_full) { t = n_full + (item - n_full) / S; part = (item - n_full) % S; parts = S; unit = item - n_full; }
+            if (item >= n_full) {
+                int i = item - n_full;
+                if (LAST && first_slices) {
+                    if (i >= rem) {                        // the remainders of tiles i, i + others, ..: one iteration each
+                        const int others = nblk - rem;
+                        i += turn * others - rem;
+                        if (i >= rem) break;
+                        ++turn;
+                        next = turn < turns ? 0 : q_step;
+                        part = 1;
+                    }
+                    t = n_full + i; parts = 2; unit = 2 * i + part;
+                } else {
+                    t = n_full + i / S; part = i % S; parts = S; unit = i;
+                }
+            }
         }
         const int band = t / (BAND * p.col_tiles);
         const int in_band = t - band * BAND * p.col_tiles;
@@ -494,8 +537,9 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     // slices of this item: all of them, or one part of a split tile; none in the finishing launch
     // (a K-contiguous operand is fetched two slices at a time: parts begin at even slices)
     // (TN: the rows are those of the part)
-    const int k_lo = (KIND == KIND_TN) ? 0 : ((int)((long)part * k_tiles / parts) & ~1);
-    const int k_hi = (KIND == KIND_TN || part + 1 == parts) ? k_tiles : ((int)((long)(part + 1) * k_tiles / parts) & ~1);
+    auto part_begin = [&](int i) { return LAST && first_slices ? first_slices * i : ((int)((long)i * k_tiles / parts) & ~1); };
+    const int k_lo = (KIND == KIND_TN) ? 0 : part_begin(part);
+    const int k_hi = (KIND == KIND_TN || part + 1 == parts) ? k_tiles : part_begin(part + 1);
     const int k_cnt = FIN ? 0 : k_hi - k_lo;
 
     // ---- buffer resources: everything outside the valid rows of an operand reads as zero --------
@@ -866,8 +910,9 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     }
 
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");     // the last MFMAs have written back before the accumulators are read
-    // partial tiles: [unit][wave][register / 4][lane] as float4, every instruction moves 1 KB
-    if (!FIN && parts > 1) {
+    // partial tiles of a finishing launch: [unit][wave][register / 4][lane] as float4, every instruction moves 1 KB
+    const bool uneven = LAST && first_slices && parts > 1;
+    if (!FIN && parts > 1 && !uneven) {
         float4* ws4 = reinterpret_cast<float4*>(p.split_ws) + ((size_t)unit * NWAVES + wave) * (TM * TN * 4) * 64 + lane;
         // fragments past the group's last row (TN: the last row of the gradient) are not kept
         const long rows_left = (KIND == KIND_TN ? p.Mout - m0 : a_row_end - a_row0) - wm * WM;
@@ -936,9 +981,34 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
             if (EPI == EPI_BWD1_SWIGLU) ui[k] = *reinterpret_cast<const uint4*>(p.Uin + row * p.ldo + col);
         }
     };
+    // WHOLE: the tile's results.  Of a tile cut unevenly (LAST): KEEP leaves what this part holds in the workspace as it comes
+    // out of the patches, [unit][wave][row of fragments][pass][half][lane] as float4; SUM adds the other part from there to this
+    // one's and goes on with the sum (of two terms: the same whichever part comes last).
+    // Both go past the L2 of the XCD (sc1: coherent on the device, where every XCD has an L2 of its own), so that no L2 has to be
+    // written back or invalidated for them: with plain accesses between agent-scope fences d = 1024, h = 4096, 152 tiles of 128
+    // slices took 114 us where this takes 90 and whole tiles 108.
+    constexpr int WHOLE = 0, KEEP = 1, SUM = 2, AT_DEVICE = 16;
+    static_assert(!LAST || GEO::UNIT_BYTES == NWAVES * TM * N_PASS * 2 * 1024, "a part fills its unit");
+    const long rows_left = row_limit - m0 - wm * WM;           // rows of fragments past the last row are not kept
+    auto part_rsrc = [&](int u) {
+        return __builtin_amdgcn_make_buffer_rsrc((void*)((char*)p.split_ws + (size_t)u * GEO::UNIT_BYTES), 0, GEO::UNIT_BYTES, 0x00020000);
+    };
+    auto epilogue = [&](auto MODE) {
+    constexpr int mode = decltype(MODE)::value;
     if (BWD1 && !FIN) request(0, 0, zin[0], uin[0]);
 #pragma unroll
     for (int fr = 0; fr < TM; ++fr) {
+        if (mode != WHOLE && fr * 32 >= rows_left) continue;
+        const int part_ofs = ((wave * TM + fr) * (N_PASS * 2 * 64) + lane) * 16;
+        float4 other[mode == SUM ? N_PASS : 1][2];
+        if (mode == SUM) {
+            const buf_rsrc_t from = part_rsrc(unit ^ 1);
+#pragma unroll
+            for (int i = 0; i < N_PASS; ++i)
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    other[i][k] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(from, part_ofs + (i * 2 + k) * 1024, 0, AT_DEVICE));
+        }
         if (FIN && fr != q % TM) continue;                     // the tile's other rows of fragments are items of other blocks
         if (BWD1 && FIN) request(fr, 0, zin[(fr * NB) & 1], uin[EPI == EPI_BWD1_SWIGLU ? (fr * NB) & 1 : 0]);
         float4 fsum[FIN ? TN : 1][4];
@@ -950,15 +1020,31 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
             if (fr * 32 < row_limit - m0 - wm * WM) {
                 constexpr long PART = (long)NWAVES * (TM * TN * 4) * 64;
                 const float4* ws4 = reinterpret_cast<const float4*>(p.split_ws) + unit * PART + (wave * (TM * TN * 4) + fr * TN * 4) * 64 + lane;
-#pragma unroll 2
-                for (int s = 0; s < parts; ++s)                // the loads of two parts, 16 KB of a wave, on their way together
+                // All loads of up to four parts, 32 KB of a wave, are on their way before the first is added (the compiler left to
+                // itself waits for each: 13 us instead of 8 for 96 tiles in five parts).
+                auto add_parts = [&](auto N, int s0) {
+                    constexpr int n = decltype(N)::value;
+                    float4 x[n][TN * 4];
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
+                    for (int s = 0; s < n; ++s)
 #pragma unroll
-                        for (int e4 = 0; e4 < 4; ++e4) {
-                            const float4 v = ws4[s * PART + (j * 4 + e4) * 64];
-                            fsum[j][e4].x += v.x; fsum[j][e4].y += v.y; fsum[j][e4].z += v.z; fsum[j][e4].w += v.w;
+                        for (int i = 0; i < TN * 4; ++i) x[s][i] = ws4[min(s0 + s, parts - 1) * PART + i * 64];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int s = 0; s < n; ++s) {
+                        if (s0 + s >= parts) break;
+#pragma unroll
+                        for (int i = 0; i < TN * 4; ++i) {
+                            fsum[i / 4][i % 4].x += x[s][i].x; fsum[i / 4][i % 4].y += x[s][i].y;
+                            fsum[i / 4][i % 4].z += x[s][i].z; fsum[i / 4][i % 4].w += x[s][i].w;
                         }
+                    }
+                };
+                constexpr int AT_ONCE = BWD1 ? 2 : 4;          // BWD1 holds saved pre-activations as well
+                if (parts == 2) add_parts(std::integral_constant<int, 2>{}, 0);
+                else
+#pragma unroll 1
+                    for (int s = 0; s < parts; s += AT_ONCE) add_parts(std::integral_constant<int, AT_ONCE>{}, s);
             }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1001,6 +1087,16 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
                 const float4 x0 = *reinterpret_cast<const float4*>(patch + r * EP_PITCH + c1);
                 const float4 x1 = *reinterpret_cast<const float4*>(patch + r * EP_PITCH + c1 + 16);
                 u[0] = x0.x; u[1] = x0.y; u[2] = x0.z; u[3] = x0.w; u[4] = x1.x; u[5] = x1.y; u[6] = x1.z; u[7] = x1.w;
+            }
+            if (mode == KEEP) {
+                const buf_rsrc_t to = part_rsrc(unit);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, make_float4(v[0], v[1], v[2], v[3])), to, part_ofs + pass * 2048, 0, AT_DEVICE);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, make_float4(v[4], v[5], v[6], v[7])), to, part_ofs + pass * 2048 + 1024, 0, AT_DEVICE);
+                continue;
+            }
+            if (mode == SUM) {
+                const float4 x0 = other[pass][0], x1 = other[pass][1];
+                v[0] += x0.x; v[1] += x0.y; v[2] += x0.z; v[3] += x0.w; v[4] += x1.x; v[5] += x1.y; v[6] += x1.z; v[7] += x1.w;
             }
             const long o = row * p.ldo + col;
             const int bo = (int)(((long)trow * p.ldo + col) * 2);          // byte offset from the tile's first row
@@ -1081,6 +1177,35 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         }
         }
     }
+    };
+    if (uneven) {
+        int* word = reinterpret_cast<int*>(smem);              // ring slot 0: below the patches
+        int* counter = p.arrived + unit / 2;
+        auto tell = [&](int v) {                               // what thread 0 knows, to all
+            if (tid == 0) *word = v;
+            __syncthreads();
+            const int r = __builtin_amdgcn_readfirstlane(*word);
+            __syncthreads();
+            return r;
+        };
+        // the other part is there already: this one need not be kept
+        int before = tell(tid == 0 ? __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0);
+        if (before == 0) {
+            epilogue(std::integral_constant<int, KEEP>{});
+            // Every wave's stores are complete before the barrier, and thread 0 counts this part after it.  Nobody waits for
+            // the other part: whichever is counted last goes on with the tile.
+            WAIT_VMCNT(0);
+            __syncthreads();
+            if (tid == 0) before = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            before = tell(before);
+        }
+        if (before == 1) {
+            if (tid == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            epilogue(std::integral_constant<int, SUM>{});
+        }
+    } else {
+        epilogue(std::integral_constant<int, WHOLE>{});
+    }
     __syncthreads();             // every wave is done with its patch before the next tile's DMA lands there
   }
 }
@@ -1134,6 +1259,7 @@ template <class GEO> constexpr int TN_OVER = GEO::BLOCKS == 1 ? 24 : 16;
 template <class GEO> constexpr int TN_SPLIT_SLICES = GEO::BLOCKS == 1 ? 48 : 32;
 template <class GEO> constexpr int SPLIT_MAX = GEO::BLOCKS == 1 ? LARGE_COST.split_max : SMALL_COST.split_max;
 template <class GEO> constexpr int SPLIT_CAP = (int)((size_t)SPLIT_UNITS * Large::UNIT_BYTES / GEO::UNIT_BYTES);
+template <class GEO> constexpr int UNEVEN_CAP = (int)((size_t)SPLIT_ALLOC * Large::UNIT_BYTES / GEO::UNIT_BYTES);
 // Large: a part of a split tile has to be worth its 256-KB round trip, 64 slices where the split only shortens the last of
 // several rounds, 24 where it is what fills the chip (d = 768, h = 3072, 33 tiles of 96 slices: 69 us whole, 45 in four parts).
 inline int large_split_slices(double tiles) { return tiles <= 2.0 * LARGE_COST.tiles_at_once ? 24 : 64; }
@@ -1170,7 +1296,7 @@ WgradPlan wgrad_plan(const moe_shape_t& s, int Mout, int N)
 }
 
 template <int KIND, int EPI, class GEO>
-hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, hipStream_t st)
+hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, bool finish, hipStream_t st)
 {
     constexpr bool DUAL = (EPI == EPI_FWD1_SWIGLU);
     constexpr int BM = GEO::BM;
@@ -1210,37 +1336,40 @@ hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, hipStream_
     p.split_cap = SPLIT_CAP<GEO>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.split_ws == nullptr) return e;
+    if (e != hipSuccess || !finish) return e;
     // the tiles of split contractions: add their parts, run their epilogues
     hipLaunchKernelGGL(kern_fin, dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
     return hipGetLastError();
 }
 
 // The geometry of a contraction and whether it may be cut (then a finishing launch follows).
-struct Tiling { bool small, cut; int split_slices; };
+// uneven: the tiles of a last round may be cut unevenly.
+struct Tiling { bool small, cut; int split_slices; bool uneven; };
 Tiling row_tiling(const moe_shape_t& s, int N, int slices, int n_seg, int epi)
 {
     Tiling t;
     t.small = small_wins_rows(s, N, slices, n_seg, epi);
     t.split_slices = t.small ? SMALL_SPLIT_SLICES : large_split_slices(tiles_of(s, Large::BM, N, epi == EPI_FWD1_SWIGLU ? Large::BN / 2 : Large::BN));
     t.cut = slices >= 2 * t.split_slices;                  // else too short
+    t.uneven = last_finishes(epi) && slices >= 3 * UNEVEN_SLICES + 2 * UNEVEN_OVER;      // two remainders a block at least
     return t;
 }
 Tiling wgrad_tiling(const moe_shape_t& s, int Mout, int N)
 {
     const WgradPlan l = wgrad_plan<Large>(s, Mout, N), m = wgrad_plan<Small>(s, Mout, N);
     const bool small = m.us < l.us;
-    return Tiling{small, small ? m.cut : l.cut, small ? TN_SPLIT_SLICES<Small> : TN_SPLIT_SLICES<Large>};
+    return Tiling{small, small ? m.cut : l.cut, small ? TN_SPLIT_SLICES<Small> : TN_SPLIT_SLICES<Large>, false};
 }
 
 template <int KIND, int EPI>
 hipError_t launch(GemmParams p, const moe_shape_t& s, hipStream_t st)
 {
     const Tiling t = KIND == KIND_TN ? wgrad_tiling(s, p.Mout, p.N) : row_tiling(s, p.N, p.n_seg * (p.Kseg / BK), p.n_seg, EPI);
-    if (!t.cut) p.split_ws = nullptr;
-    p.split_slices = t.split_slices;
+    if (!t.cut && !t.uneven) p.split_ws = nullptr;
+    p.split_slices = t.cut ? t.split_slices : 0x7fffffff;  // none is worth it
+    p.uneven_cap = t.uneven ? (t.small ? UNEVEN_CAP<Small> : UNEVEN_CAP<Large>) : 0;
     if (KIND != KIND_TN && t.small) p.band = SMALL_BAND;
-    return t.small ? launch_geo<KIND, EPI, Small>(p, s.T * s.k, s.G, st) : launch_geo<KIND, EPI, Large>(p, s.T * s.k, s.G, st);
+    return t.small ? launch_geo<KIND, EPI, Small>(p, s.T * s.k, s.G, t.cut, st) : launch_geo<KIND, EPI, Large>(p, s.T * s.k, s.G, t.cut, st);
 }
 
 GemmParams base_params(const moe_shape_t& s, const ffn_args& a)
@@ -1250,6 +1379,7 @@ GemmParams base_params(const moe_shape_t& s, const ffn_args& a)
     p.self = s.self; p.Gcap = s.G;
     p.n_seg = 1;
     p.split_ws = a.split_ws;
+    p.arrived = a.arrived;
     return p;
 }
 
@@ -1266,6 +1396,7 @@ hipError_t launch_ffn_fwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
     {   // fwd1: [rows, d] x W1[g] (d x h)
         GemmParams p = base_params(s, a);
         p.band = BAND_FWD1;
+        p.clear_arrived = 1;
         p.A[0] = (const bf16_t*)a.Xp; p.B[0] = (const bf16_t*)a.W1; p.B_dual = (const bf16_t*)a.W3;
         p.lda = d; p.ldb = h; p.b_group_stride = d * h; p.Kseg = s.d; p.N = s.h;
         p.O0 = (bf16_t*)a.Z; p.O1 = (bf16_t*)a.U; p.O2 = (bf16_t*)a.Act; p.ldo = h;
@@ -1294,6 +1425,7 @@ hipError_t launch_ffn_bwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
         {   // bwd1: dA = dYp [rows, d] x W2[g]^T (W2 is h x d: contraction index contiguous)
             GemmParams p = base_params(s, a);
             p.band = BAND_BWD1;
+            p.clear_arrived = 1;
             p.A[0] = (const bf16_t*)a.dYp; p.B[0] = (const bf16_t*)a.W2;
             p.lda = d; p.ldb = d; p.b_group_stride = d * h; p.Kseg = s.d; p.N = s.h;
             p.O0 = (bf16_t*)a.dZ; p.O1 = (bf16_t*)a.dU; p.O2 = (bf16_t*)a.Act; p.ldo = h;
@@ -1357,7 +1489,11 @@ int moe_ffn_tiling(moe_handle_t hd, int contraction, int cus, int n_groups, cons
     out[5] = !wgrad && t.cut ? row_parts(tiles - n_full, nblk, slices, split_max, t.split_slices, cap) : 1;
     out[6] = t.small && !wgrad ? SMALL_BAND : band[wgrad ? 4 : contraction];
     out[7] = t.cut; out[8] = wgrad ? all : slices; out[9] = (int32_t)estimated_rows(s);
-    if (!wgrad) return MOE_OK;
+    if (!wgrad) {
+        int turns;
+        out[10] = t.uneven && out[5] == 1 ? uneven_cut(tiles - n_full, nblk, slices, t.small ? UNEVEN_CAP<Small> : UNEVEN_CAP<Large>, turns) : 0;
+        return MOE_OK;
+    }
     const int over = t.small ? TN_OVER<Small> : TN_OVER<Large>, rounds = (tiles + nblk / 8 - 1) / (nblk / 8);
     int* parts = out + 10;
     auto limit = [&](int most) { for (int g = 0; g < s.G; ++g) parts[g] = std::min<int>(parts[g], most); };

@@ -18,7 +18,8 @@ struct moe_ctx {
     size_t off_dz;         // elt [A,h]  dZ
     size_t off_du;         // elt [A,h]  dU (SwiGLU)
     size_t off_gate_part;  // float [partitions][d*E + E] partial sums of the gate parameter gradients
-    size_t off_split;      // float [SPLIT_UNITS][256*256] partial tiles of the grouped GEMM's last, K-split round (bf16 path)
+    size_t off_split;      // float [SPLIT_ALLOC][256*256] partial tiles of the grouped GEMM's last, K-split round (bf16 path)
+    size_t off_arrived;    // int32 [SPLIT_COUNTERS] which of those of an uneven cut are there
     size_t ws_bytes;
     int n_chunks;          // ceil(A / ROUTE_CHUNK)
     // apart from this setting (moe_set_act_saved) a handle is immutable: every call is a function of its arguments
@@ -84,6 +85,8 @@ hipError_t launch_plan(const moe_planner_t& cfg, const int32_t* gating, const mo
 hipError_t launch_dispatch_bwd(const moe_shape_t& s, const void* dXp, const int32_t* pos, void* dX, hipStream_t st);
 
 constexpr int SPLIT_UNITS = 320;       // partial tiles the K-split of a last round may need: at most one per block
+constexpr int SPLIT_ALLOC = 512;       // and an uneven cut: two for each of fewer tiles than there are blocks
+constexpr int SPLIT_COUNTERS = 1024;   // a counter for each of them, in the smaller tiles
 struct ffn_args {
     const void *Xp, *W1, *W2, *W3;
     const int32_t *slot_offsets, *dest_slots;
@@ -93,7 +96,8 @@ struct ffn_args {
     float *dW1, *dW2, *dW3;
     bool accumulate = false;           // weight gradients are added to what dW holds instead of overwriting it
     bool act_saved = false;            // backward: Act still holds the forward pass's activation (not recomputed)
-    float* split_ws = nullptr;         // workspace for K-split partial tiles (SPLIT_UNITS tiles of 256 x 256 floats)
+    float* split_ws = nullptr;         // workspace for K-split partial tiles (SPLIT_ALLOC tiles of 256 x 256 floats)
+    int32_t* arrived = nullptr;        // workspace, SPLIT_COUNTERS: cleared by the first launch of a pass, zero after every launch
 };
 hipError_t launch_ffn_fwd_f32(const moe_shape_t& s, const ffn_args& a, hipStream_t st);
 hipError_t launch_ffn_bwd_f32(const moe_shape_t& s, const ffn_args& a, hipStream_t st);
@@ -104,7 +108,8 @@ hipError_t launch_ffn_bwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
 // 4 dW1 and dW3, 5 dW2) for hosted groups of rows[0 .. n_groups) rows on a GPU of `cus` CUs.  Host only, launches nothing.
 //   out[0..9]: side of a tile, blocks, row tiles, column tiles, tiles in full rounds, parts of the others (4, 5: of the
 //   group cut into most), row tiles per band, whether a finishing launch follows, slices of the contraction (4, 5: of all
-//   groups), rows the choice is made for.  4, 5: out[10 .. 10 + G) are the parts of each group.
+//   groups), rows the choice is made for.  4, 5: out[10 .. 10 + G) are the parts of each group.  0 .. 3: out[10] is 0, or the
+//   slices of the first part of each of the other tiles where those are cut unevenly in two.
 extern "C" int moe_ffn_tiling(moe_handle_t h, int contraction, int cus, int n_groups, const int32_t* rows, int32_t* out);
 
 // ---- small device helpers ----------------------------------------------------------------

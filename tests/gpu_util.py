@@ -95,6 +95,8 @@ def ffn_tiling(hd, rows, cus: Optional[int] = None) -> Dict[str, dict]:
         got[name] = dict(zip(("side", "blocks", "row_tiles", "col_tiles", "n_full", "parts", "band", "finish", "slices", "est"), out))
         if c >= 4:
             got[name]["parts"] = list(out[10:10 + hd.G])
+        else:
+            got[name]["first"] = out[10]                       # slices of the first part of a tile cut unevenly, else 0
     return got
 
 

@@ -98,3 +98,21 @@ def test_more_parts_than_lanes(rows, d, h, want):
         parts = t[name]["parts"]
         n = sum(r > 1000 for r in rows)
         assert parts[:n] == [want] * n and parts[n:] == [1] * (len(rows) - n) and sum(parts) <= 64, (name, parts)
+
+
+def test_uneven_cuts_fit():
+    """Two units per tile in the workspace, both parts whole pairs of slices, and a remainder worth its way."""
+    rng, seen = random.Random(5), set()
+    for _ in range(3000):
+        rows = [int(10 ** rng.uniform(0, 4)) for _ in range(rng.choice([1, 3, 8]))]
+        d, h = 64 * rng.randint(1, 40), 64 * rng.randint(20, 120)
+        hd = _handle(rows, rng.choice([0, 20000]), d, h, rng.choice(["gelu", "swiglu"]))
+        for name, t in G.ffn_tiling(hd, rows, 256).items():
+            if name[0] == "d" or not t["first"]:
+                continue
+            rem, rest = t["row_tiles"] * t["col_tiles"] - t["n_full"], t["slices"] - t["first"]
+            assert name in ("fwd2", "bwd2") and t["parts"] == 1
+            assert t["blocks"] // 2 < rem < t["blocks"] and 2 * rem * t["side"] ** 2 <= 512 * 256 ** 2
+            assert t["first"] % 2 == 0 and rest % 2 == 0 and rest >= 28 and t["first"] >= rest
+            seen.add((t["side"], -(-rem // (t["blocks"] - rem))))
+    assert {(256, 2), (256, 3), (128, 2), (128, 3)} <= seen

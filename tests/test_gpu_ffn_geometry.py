@@ -133,3 +133,55 @@ def test_forward_backward(rows, other, d, h, act, plan):
         close(dW[0][i], x.t() @ dz, "dW1")
         close(dW[1][i], a.t() @ dy, "dW2")
         o += n
+
+
+# Tiles left over by the full rounds that are more than half of the blocks: each cut in two unevenly, two to four remainders per
+# block.  Contraction -> side of the tiles and slices of the first part.  (No group of a few rows, for the sake of the weight
+# gradients: of two rows a hidden unit's gradient is one activation times dYp, and one three times the typical, off by its three
+# roundings, 3 x 3^0.5 x 2^-9 = 1.0e-2 of the typical row, is no error.)
+UNEVEN = [
+    ([7230, 7370, 2263, 590, 2238], 0, 320, 3584, "gelu", dict(fwd2=(256, 84), bwd2=(256, 84))),
+    ([5254, 86, 272, 495, 4572], 20000, 576, 1792, "swiglu", dict(bwd2=(256, 84))),        # the remainder in the second segment
+    ([4108, 3421, 7092], 0, 576, 2560, "swiglu", dict(bwd2=(256, 132))),                   # three remainders
+    ([2859, 6751], 20000, 1088, 3136, "swiglu", dict(bwd2=(256, 168))),                    # four, the last block has three
+    ([1662, 5275, 1374, 1478, 1981], 0, 320, 3840, "gelu", dict(fwd2=(128, 90), bwd2=(128, 90))),
+    ([74, 7199, 7190], 0, 320, 2496, "swiglu", dict(bwd2=(128, 128))),
+    ([1375, 7446], 0, 1344, 1984, "swiglu", dict(bwd2=(128, 92))),                         # after a full round
+]
+
+
+def _uneven(hd, rows, plan, cus=None):
+    tiling = G.ffn_tiling(hd, rows, cus)
+    for name, want in plan.items():
+        assert (tiling[name]["side"], tiling[name]["first"]) == want and tiling[name]["parts"] == 1, (name, tiling[name])
+
+
+@pytest.mark.parametrize("rows,other,d,h,act,plan", UNEVEN, ids=_id)
+def test_uneven_cuts(rows, other, d, h, act, plan):
+    """Right, and the same bits whatever the workspace held and whichever part of a tile came last."""
+    test_forward_backward(rows, other, d, h, act, {})
+    Gn, A = len(rows), sum(rows) + other
+    hd = binding.Handle(T=A, d=d, h=h, E=Gn + 1, k=1, P=2, self_dest=0, G=Gn, dtype="bf16", act=act, renorm=0, device=G.DEV)
+    _uneven(hd, rows, plan)
+    g = torch.Generator(device=G.DEV).manual_seed(1)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=G.DEV).to(torch.bfloat16)   # noqa: E731
+    counts, lay = torch.tensor(rows + [other], dtype=torch.int32, device=G.DEV), hd.new_layout()
+    idx = torch.repeat_interleave(torch.arange(Gn + 1, dtype=torch.int32, device=G.DEV), counts)
+    Xp, dYp = torch.empty(A, d, dtype=torch.bfloat16, device=G.DEV), rnd(A, d)
+    hd.dispatch(torch.tensor([0] * Gn + [1], dtype=torch.int32, device=G.DEV), rnd(A, d), idx, counts, lay, Xp)
+    W = [rnd(Gn, d, h), rnd(Gn, h, d), rnd(Gn, d, h) if act == "swiglu" else None]
+    dW = [torch.empty_like(w, dtype=torch.float32) if w is not None else None for w in W]
+    seen = None
+    for i in range(4):
+        Yp, dXp, Z = torch.zeros_like(Xp), torch.zeros_like(Xp), torch.zeros(A, h, dtype=torch.bfloat16, device=G.DEV)
+        U = torch.zeros_like(Z) if act == "swiglu" else None
+        if i % 2 == 0:
+            hd.ws.fill_(255)
+        hd.expert_ffn_fwd(Xp, lay, *W, Yp, Z, U)
+        if i % 2 == 0:
+            hd.ws.fill_(1)
+        hd.expert_ffn_bwd(dYp, Xp, Z, U, lay, *W, dXp, *dW)
+        torch.cuda.synchronize()
+        if seen is None:
+            seen = (Yp, dXp)
+        assert torch.equal(Yp.view(torch.int16), seen[0].view(torch.int16)) and torch.equal(dXp.view(torch.int16), seen[1].view(torch.int16))
