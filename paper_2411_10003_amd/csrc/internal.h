@@ -73,7 +73,7 @@ hipError_t launch_input_grad(const moe_shape_t& s, const void* dXp, const int32_
 hipError_t launch_gate_wgrad(const moe_shape_t& s, const void* X, const float* dlogits, float* partial, float* partial_b,
                              float* dWg, float* dbg, hipStream_t st);
 hipError_t launch_trans_gather(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* pool_version,
-                               const int32_t* slot_expert, const int32_t* slot_version,
+                               int32_t* slot_expert, const int32_t* slot_version,
                                int n, const void* const* pools, void* const* groups, const size_t* bytes_per_expert, hipStream_t st);
 hipError_t launch_trans_commit(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* pool_version,
                                int32_t* slot_expert, int32_t* slot_version, hipStream_t st);

@@ -380,13 +380,16 @@ __device__ __forceinline__ int hosted_expert_of_group(const int32_t* __restrict_
 constexpr int MAX_TENSORS = 8, MOVE_UNROLL = 4;
 struct MoveArgs { const uint4* src[MAX_TENSORS]; uint4* dst[MAX_TENSORS]; long vec[MAX_TENSORS]; };
 
+// commit: the slot's expert, written here where no versions are kept (nobody reads it then); with versions other blocks of the
+// slot still compare it, and a launch of its own writes both afterwards (4.8 us of 126 in a pass that moves 134 MB).
 __global__ __launch_bounds__(256) void trans_gather_kernel(
     const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ pool_version,
-    const int32_t* __restrict__ slot_expert, const int32_t* __restrict__ slot_version, const MoveArgs a, int E, int self)
+    const int32_t* slot_expert, const int32_t* __restrict__ slot_version, int32_t* commit, const MoveArgs a, int E, int self)
 {
     const int g = blockIdx.y;
     const int e = hosted_expert_of_group(expert_dest, E, self, g);
-    if (e < 0) return;                                     // unused slot
+    if (e < 0) return;                                     // unused slot: it keeps what it holds
+    if (commit != nullptr && blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) commit[g] = e;
     // the expert is already there, in the version the pool holds now (no versions given: always copied)
     if (pool_version != nullptr && e == slot_expert[g] && slot_version[g] == pool_version[e]) return;
     const long vec_per_expert = a.vec[blockIdx.z], lanes = (long)gridDim.x * blockDim.x;
@@ -415,7 +418,7 @@ __global__ __launch_bounds__(64) void trans_commit_kernel(const int32_t* __restr
     const int e = hosted_expert_of_group(expert_dest, E, self, g);
     if (e >= 0 && threadIdx.x == 0) {                      // an unused slot keeps what it holds
         slot_expert[g] = e;
-        if (pool_version != nullptr) slot_version[g] = pool_version[e];
+        slot_version[g] = pool_version[e];
     }
 }
 
@@ -466,19 +469,20 @@ hipError_t launch_agg_add(const moe_shape_t& s, const int32_t* expert_dest, int 
 }
 
 hipError_t launch_trans_gather(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* pool_version,
-                               const int32_t* slot_expert, const int32_t* slot_version,
+                               int32_t* slot_expert, const int32_t* slot_version,
                                int n, const void* const* pools, void* const* groups, const size_t* bytes_per_expert, hipStream_t st)
 {
     MoveArgs a{};
     for (int i = 0; i < n; ++i) { a.src[i] = (const uint4*)pools[i]; a.dst[i] = (uint4*)groups[i]; a.vec[i] = (long)(bytes_per_expert[i] / 16); }
     hipLaunchKernelGGL(trans_gather_kernel, dim3(move_blocks(a, n), s.G, n), dim3(256), 0, st, expert_dest, pool_version, slot_expert,
-                       slot_version, a, s.E, s.self);
+                       slot_version, pool_version == nullptr ? slot_expert : nullptr, a, s.E, s.self);
     return hipGetLastError();
 }
 
 hipError_t launch_trans_commit(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* pool_version,
                                int32_t* slot_expert, int32_t* slot_version, hipStream_t st)
 {
+    if (pool_version == nullptr) return hipSuccess;        // the gather has
     hipLaunchKernelGGL(trans_commit_kernel, dim3(s.G), dim3(64), 0, st, expert_dest, pool_version, slot_expert,
                        slot_version, s.E, s.self);
     return hipGetLastError();
