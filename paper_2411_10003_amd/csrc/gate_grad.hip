@@ -9,6 +9,7 @@
 // in chunks.
 #include "internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -38,12 +39,14 @@ __device__ __forceinline__ void unpack_bf16x8(const uint4& v, float* f)
 // and adds zeros.
 // Measured, us before -> after (bf16): T = 16384, d = 2048, k = 2, E = 32: 81 -> 52 (2.1 GFLOP beside 201 MB); k = 1, E = 64:
 // 377 -> 61; T = 8001, k = 4, E = 128: 524 -> 94; T = 1000, d = 512, E = 16: 43 -> 10 (16 blocks before); T = 32768,
-// d = 4096, E = 16: 172 -> 172 (807 MB, 4.7 TB/s).
+// d = 4096, E = 16: 172 -> 172 (807 MB, 4.7 TB/s).  Requesting the next group's rows before the matrix instructions of the current
+// one pays with 33 to 64 experts (T = 16384, d = 2048, k = 1, E = 64 61 -> 58; T = 20000, d = 1024, k = 2, E = 48 58 -> 53), where
+// those take long enough; with fewer it costs a wave per SIMD and bandwidth (E = 32 54 -> 60, E = 16 159 -> 204).
 typedef __attribute__((ext_vector_type(4))) float ig_f32x4_t;
 
-// waves per SIMD the compiler is held to: 4, or 2 where the row pieces (16 KMAX registers) or the LDS leave no room for that
+// waves per SIMD the compiler is held to: 4, 3 with two row pieces requested ahead, 2 where the row pieces (16 KMAX registers) or the LDS leave no room for that
 template <typename ET, int NE, int KMAX>
-__global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? 4 : 2) void input_grad_kernel(
+__global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? (NE == 4 && KMAX == 2 ? 3 : 4) : 2) void input_grad_kernel(
     const ET* __restrict__ dXp, const int32_t* __restrict__ pos, const float* __restrict__ dlogits,
     const float* __restrict__ Wg, ET* __restrict__ dX, int T, int d, int E, int k, int groups_per_wave, int vec)
 {
@@ -81,9 +84,12 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? 4 : 2) void input_grad_k
     bool skip_zeros = false;
     if (!CHUNKS || E <= EC) skip_zeros = __syncthreads_or(stage(0));
 
-    for (int gi = 0; gi < groups_per_wave; ++gi) {
-        const int tg = (blockIdx.y * groups_per_wave + gi) * 64 + wave * 16;
-        raw_t raw[4][KMAX];
+    // rows of a group of 16 tokens; PREFETCH: the next group's are requested before the current one's matrix instructions
+    constexpr bool PREFETCH = KMAX <= 2 && NE == 4;
+    raw_t raw[4][KMAX], ahead[PREFETCH ? 4 : 1][KMAX];
+    auto first_token = [&](int gi) { return (blockIdx.y * groups_per_wave + gi) * 64 + wave * 16; };
+    auto request_rows = [&](int gi, raw_t (&to)[4][KMAX]) {
+        const int tg = first_token(gi);
         int lowest = 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -92,7 +98,7 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? 4 : 2) void input_grad_k
             for (int j = 0; j < KMAX; ++j) {
                 const int row = pos[(size_t)t * k + (j < k ? j : 0)];
                 lowest = min(lowest, row);
-                raw[r][j] = *reinterpret_cast<const raw_t*>(dXp + (size_t)max(row, 0) * d + cc);
+                to[r][j] = *reinterpret_cast<const raw_t*>(dXp + (size_t)max(row, 0) * d + cc);
             }
         }
         if (__any(lowest < 0))
@@ -100,7 +106,12 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? 4 : 2) void input_grad_k
             for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int j = 0; j < KMAX; ++j)
-                    if (j < k && pos[(size_t)min(tg + 4 * lq + r, T - 1) * k + j] < 0) raw[r][j] = raw_t{};
+                    if (j < k && pos[(size_t)min(tg + 4 * lq + r, T - 1) * k + j] < 0) to[r][j] = raw_t{};
+    };
+    if (PREFETCH) request_rows(0, raw);
+    for (int gi = 0; gi < groups_per_wave; ++gi) {
+        const int tg = first_token(gi);
+        if (!PREFETCH) request_rows(gi, raw);
         ig_f32x4_t acc[VN];
 #pragma unroll
         for (int j = 0; j < VN; ++j) acc[j] = ig_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
@@ -126,6 +137,7 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? 4 : 2) void input_grad_k
                     }
                 }
             }
+            if constexpr (PREFETCH) if (gi + 1 < groups_per_wave) request_rows(gi + 1, ahead);
             // the weights are read from LDS again for every group: hoisted out of the loop over the groups they would spill
             if (NE > 1) asm volatile("" ::: "memory");
             if (!MANY || !skip_zeros) {
@@ -188,6 +200,11 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? 4 : 2) void input_grad_k
                 *reinterpret_cast<float4*>(dX + (size_t)t * d + c) = make_float4(sum[0], sum[1], sum[2], sum[3]);
             }
         }
+        if constexpr (PREFETCH)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < KMAX; ++j) raw[r][j] = ahead[r][j];
     }
 }
 
@@ -201,17 +218,17 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? 4 : 2) void input_grad_k
 // lane l, register r is column index i = 4 (l / 16) + r, expert l % 16.
 // A block's four waves take every fourth group of 4 tokens of the partition; their sums are folded through
 // LDS in a fixed order and written as one partial per token partition (the reduce kernel adds those).
-// What bounds it: HBM (X once) beside the matrix rate from E = 32 on, and before either the latency of a wave's loads:
-// with the accumulators of 32 experts there are two waves per SIMD, so a wave requests its next 16 tokens before it
-// multiplies the current ones (held to 256 registers; without the bound the compiler takes a whole SIMD for one wave,
-// 52 us).  More than 32 experts are further blocks of the same launch: X comes from cache for them, and twice the blocks
-// with half the accumulators (64 experts in one wave) fill the chip.  Both kernels, us, before -> after: T = 16384,
-// d = 2048, E = 32: 45 -> 40, E = 64: 85 -> 65; T = 32768, d = 4096, E = 16: 79 -> 68; T = 8001, d = 2048, E = 128:
-// 109 -> 72; T = 4000, d = 1024, E = 100: 52 -> 24.
+// What bounds it: HBM (X once) beside the matrix rate from E = 32 on, and before either the latency of a wave's loads: a
+// wave requests its next 16 tokens before it multiplies the current ones, four waves per SIMD.  More than 32 experts are
+// further blocks of the same launch: X comes from cache for them.  Product | sum of the partials, us, with two waves per SIMD,
+// loads under selects, 32 partitions of 256 tokens and more, and waves folded one after the other -> now: T = 16384, d = 2048, E
+// = 32: 30 | 12 -> 28 | 5, E = 64: 57 | 12 -> 45 | 5; T = 8001, d = 2048, E = 128: 61 | 13 -> 42 | 5; T = 9000, d = 3072, E = 100:
+// 102 | 14 -> 69 | 5; T = 32768, d = 4096, E = 16: 79 | 8 -> 79 | 5; T = 4000, d = 1024, E = 16: 14 | 4 -> 7 | 4; T = 584, d =
+// 1984, E = 8: 13.5 | 4 -> 5.7 | 2.8.  (The sum's bias took its partitions one by one and was what the launch waited for.)
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 template <typename ET, int VN, int NE, int CS>
-__global__ __launch_bounds__(256, 2) void gate_wgrad_mfma_kernel(
+__global__ __launch_bounds__(256, sizeof(ET) == 2 ? 4 : 2) void gate_wgrad_mfma_kernel(
     const ET* __restrict__ X, const float* __restrict__ dlogits, float* __restrict__ partial,
     float* __restrict__ partial_b, int T, int d, int E, int tok_per_part)
 {
@@ -220,8 +237,9 @@ __global__ __launch_bounds__(256, 2) void gate_wgrad_mfma_kernel(
     constexpr int NACC = CS * VN * NE;                             // 16 x 16 accumulators of a wave
     typedef typename std::conditional<sizeof(ET) == 2, uint4, float4>::type raw_t;
     static_assert(sizeof(ET) * VN == 16, "a lane loads 16 bytes of a row");
-    __shared__ float fold[NACC * 4 * 64];
-    __shared__ float fold_b[NE * 16];
+    __shared__ __attribute__((aligned(16))) float fold[4 * NACC / 2 * 4 * 64];
+    __shared__ float fold_b[4 * NE * 16];
+    static_assert(NACC % 8 == 0, "a quarter of half of the accumulators per wave");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lk = lane >> 4;                      // column / expert of the lane, token of the lane
@@ -241,33 +259,59 @@ __global__ __launch_bounds__(256, 2) void gate_wgrad_mfma_kernel(
     for (int n = 0; n < NE; ++n) accb[n] = 0.0f;
 
     constexpr int U = 4;                                           // groups of 4 tokens requested together: one trip
-    // unconditional loads (tokens past the partition and columns past d read valid ones, replaced by zeros when used)
+    // bf16: buffer loads from the trip's first token on, whose resource ends with the partition: tokens past it, columns past d
+    // and experts past E arrive as zeros, and a trip has no vector instruction beside the conversions (each takes about 8
+    // cycles from the matrix units).  fp32, whose rows may be too long for an offset: unconditional loads (tokens past the
+    // partition and columns past d read valid ones, replaced by zeros when used).
+    constexpr bool BUF = sizeof(ET) == 2;
+    constexpr int NOWHERE = (int)0x80000000u;
+    int voff_x[CS], voff_dl[NE];
+    if (BUF) {
+#pragma unroll
+        for (int s = 0; s < CS; ++s) voff_x[s] = c0 + s * SW + li * VN < d ? (lk * d + c0 + s * SW + li * VN) * 2 : NOWHERE;
+#pragma unroll
+        for (int n = 0; n < NE; ++n) voff_dl[n] = e0 + n * 16 + li < E ? (lk * E + e0 + n * 16 + li) * 4 : NOWHERE;
+    }
     auto load_trip = [&](int tg, raw_t (&raw)[U][CS], float (&dl)[U][NE]) {
+        if constexpr (BUF) {
+            auto rsrc = [&](const void* base, long bytes) {
+                return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(bytes < 0 ? 0 : (bytes > 0x7fffffffl ? 0x7fffffffl : bytes)), 0x00020000);
+            };
+            const auto rx = rsrc(X + (size_t)tg * d, (long)(t_end - tg) * d * 2), rd = rsrc(dlogits + (size_t)tg * E, (long)(t_end - tg) * E * 4);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int t = min(tg + 16 * u + lk, T - 1);
+            for (int u = 0; u < U; ++u) {
 #pragma unroll
-            for (int n = 0; n < NE; ++n) {
-                const int e = e0 + n * 16 + li;
-                dl[u][n] = dlogits[(size_t)t * E + (e < E ? e : 0)];
+                for (int n = 0; n < NE; ++n) dl[u][n] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rd, voff_dl[n], 16 * u * E * 4, 0));
+#pragma unroll
+                for (int s = 0; s < CS; ++s) raw[u][s] = __builtin_bit_cast(raw_t, __builtin_amdgcn_raw_buffer_load_b128(rx, voff_x[s], 16 * u * d * 2, 0));
             }
+        } else {
 #pragma unroll
-            for (int s = 0; s < CS; ++s) {
-                const int c = c0 + s * SW + li * VN;
-                raw[u][s] = *reinterpret_cast<const raw_t*>(X + (size_t)t * d + (c < d ? c : 0));
+            for (int u = 0; u < U; ++u) {
+                const int t = min(tg + 16 * u + lk, T - 1);
+#pragma unroll
+                for (int n = 0; n < NE; ++n) {
+                    const int e = e0 + n * 16 + li;
+                    dl[u][n] = dlogits[(size_t)t * E + (e < E ? e : 0)];
+                }
+#pragma unroll
+                for (int s = 0; s < CS; ++s) {
+                    const int c = c0 + s * SW + li * VN;
+                    raw[u][s] = *reinterpret_cast<const raw_t*>(X + (size_t)t * d + (c < d ? c : 0));
+                }
             }
         }
     };
     auto use_trip = [&](int tg, const raw_t (&raw)[U][CS], const float (&dl)[U][NE]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool tv = tg + 16 * u + lk < t_end;
+            const bool tv = BUF || tg + 16 * u + lk < t_end;
             float g[NE];
 #pragma unroll
-            for (int n = 0; n < NE; ++n) g[n] = (tv && e0 + n * 16 + li < E) ? dl[u][n] : 0.0f;
+            for (int n = 0; n < NE; ++n) g[n] = (BUF || (tv && e0 + n * 16 + li < E)) ? dl[u][n] : 0.0f;
 #pragma unroll
             for (int s = 0; s < CS; ++s) {
-                const raw_t w = (tv && c0 + s * SW + li * VN < d) ? raw[u][s] : raw_t{};
+                const raw_t w = (BUF || (tv && c0 + s * SW + li * VN < d)) ? raw[u][s] : raw_t{};
                 float x[VN];
                 if constexpr (sizeof(ET) == 2) {
                     unpack_bf16x8(w, x);
@@ -305,94 +349,94 @@ __global__ __launch_bounds__(256, 2) void gate_wgrad_mfma_kernel(
         accb[n] += __shfl_xor(accb[n], 16, 64);
         accb[n] += __shfl_xor(accb[n], 32, 64);
     }
-    // fold the four waves: waves 1, 2, 3 hand their sums to wave 0 one after the other
-    for (int w = 1; w < 4; ++w) {
-        if (wave == w) {
+    // fold the four waves, in wave order: every wave leaves its sums in LDS, half of them at a time, and adds up and writes a
+    // quarter of those
+    if (lane < 16)
 #pragma unroll
-            for (int s = 0; s < CS; ++s)
+        for (int n = 0; n < NE; ++n) fold_b[(wave * NE + n) * 16 + lane] = accb[n];
 #pragma unroll
-                for (int j = 0; j < VN; ++j)
+    for (int half = 0; half < 2; ++half) {
+        if (half) __syncthreads();
 #pragma unroll
-                    for (int n = 0; n < NE; ++n)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) fold[((((s * VN + j) * NE + n) * 4) + r) * 64 + lane] = acc[s][j][n][r];
-            if (lane < 16)
-#pragma unroll
-                for (int n = 0; n < NE; ++n) fold_b[n * 16 + lane] = accb[n];
+        for (int i = 0; i < NACC / 2; ++i) {
+            const int a = half * (NACC / 2) + i;
+            *reinterpret_cast<f32x4_t*>(fold + ((wave * (NACC / 2) + i) * 64 + lane) * 4) = acc[a / NE / VN][a / NE % VN][a % NE];
         }
         __syncthreads();
-        if (wave == 0) {
 #pragma unroll
-            for (int s = 0; s < CS; ++s)
+        for (int i = 0; i < NACC / 8; ++i) {
+            const int h = wave * (NACC / 8) + i, a = half * (NACC / 2) + h, n = a % NE, j = a / NE % VN, s = a / NE / VN;
+            f32x4_t sum = *reinterpret_cast<const f32x4_t*>(fold + (h * 64 + lane) * 4);
 #pragma unroll
-                for (int j = 0; j < VN; ++j)
+            for (int w = 1; w < 4; ++w) sum += *reinterpret_cast<const f32x4_t*>(fold + ((w * (NACC / 2) + h) * 64 + lane) * 4);
 #pragma unroll
-                    for (int n = 0; n < NE; ++n)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[s][j][n][r] += fold[((((s * VN + j) * NE + n) * 4) + r) * 64 + lane];
-            if (lane < 16)
-#pragma unroll
-                for (int n = 0; n < NE; ++n) accb[n] += fold_b[n * 16 + lane];
+            for (int r = 0; r < 4; ++r) {
+                const int c = c0 + s * SW + (4 * lk + r) * VN + j, e = e0 + n * 16 + li;
+                if (c < d && e < E) partial[((size_t)part * d + c) * E + e] = sum[r];
+            }
         }
-        __syncthreads();
     }
-    if (wave == 0) {
+    if (blockIdx.x == 0 && tid < NE * 16 && e0 + tid < E) {
+        float sum = fold_b[tid];
 #pragma unroll
-        for (int s = 0; s < CS; ++s)
-#pragma unroll
-            for (int j = 0; j < VN; ++j)
-#pragma unroll
-                for (int n = 0; n < NE; ++n)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int c = c0 + s * SW + (4 * lk + r) * VN + j, e = e0 + n * 16 + li;
-                        if (c < d && e < E) partial[((size_t)part * d + c) * E + e] = acc[s][j][n][r];
-                    }
-        if (blockIdx.x == 0 && lane < 16)
-#pragma unroll
-            for (int n = 0; n < NE; ++n)
-                if (e0 + n * 16 + lane < E) partial_b[(size_t)part * E + e0 + n * 16 + lane] = accb[n];
+        for (int w = 1; w < 4; ++w) sum += fold_b[w * NE * 16 + tid];
+        partial_b[(size_t)part * E + e0 + tid] = sum;
     }
 }
+
+
+// Columns and experts of a block of gate_wgrad_mfma_kernel.
+inline int wgrad_columns(const moe_shape_t& s) { return s.dtype == MOE_BF16 ? (s.E <= 16 ? 256 : 128) : 128; }
+inline int wgrad_experts(const moe_shape_t& s) { return s.E <= 16 ? 16 : 32; }
 
 template <typename ET, int VN, int NE, int CS>
 hipError_t launch_wgrad_mfma_t(const moe_shape_t& s, const void* X, const float* dlogits, float* partial, float* partial_b,
                                int n_part, int tok_per_part, hipStream_t st)
 {
     const int cw = CS * 16 * VN;
+    if (cw != wgrad_columns(s) || 16 * NE != wgrad_experts(s)) return hipErrorInvalidValue;
     const dim3 grid((s.d + cw - 1) / cw, n_part, (s.E + 16 * NE - 1) / (16 * NE));
     hipLaunchKernelGGL((gate_wgrad_mfma_kernel<ET, VN, NE, CS>), grid, dim3(256), 0, st, (const ET*)X, dlogits, partial,
                        partial_b, s.T, s.d, s.E, tok_per_part);
     return hipGetLastError();
 }
 
-__global__ void gate_wgrad_reduce_kernel(const float* __restrict__ partial, const float* __restrict__ partial_b,
-                                         float* __restrict__ dWg, float* __restrict__ dbg, int n_part, int dE, int E)
+// Partials in partition order, up to 32 loads on their way at once (past the last one the last one again, not added).
+__device__ __forceinline__ float sum_partials(const float* __restrict__ p, size_t stride, int n_part)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < dE) {
-        float s = 0.0f;
-        int p = 0;
-        for (; p + 16 <= n_part; p += 16) {                        // sixteen loads in flight, added in partition order
-            float v[16];
+    float s = 0.0f;
+    for (int p0 = 0; p0 < n_part; p0 += 32) {
+        float v[32];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) v[q] = partial[(size_t)(p + q) * dE + i];
+        for (int q = 0; q < 32; ++q) v[q] = p[(size_t)min(p0 + q, n_part - 1) * stride];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) s += v[q];
-        }
-        for (; p < n_part; ++p) s += partial[(size_t)p * dE + i];
-        dWg[i] = s;
+        for (int q = 0; q < 32; ++q) if (p0 + q < n_part) s += v[q];
     }
-    if (i < E) {
-        float s = 0.0f;
-        for (int p = 0; p < n_part; ++p) s += partial_b[(size_t)p * E + i];
-        dbg[i] = s;
+    return s;
+}
+// The last block adds up the bias.
+__global__ __launch_bounds__(256) void gate_wgrad_reduce_kernel(const float* __restrict__ partial, const float* __restrict__ partial_b,
+                                                                float* __restrict__ dWg, float* __restrict__ dbg, int n_part, int dE, int E)
+{
+    if (blockIdx.x + 1 == gridDim.x) {
+        for (int e = threadIdx.x; e < E; e += 256) dbg[e] = sum_partials(partial_b + e, E, n_part);
+        return;
     }
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < dE) dWg[i] = sum_partials(partial + i, dE, n_part);
 }
 
 }  // namespace
 
-int gate_grad_partitions(const moe_shape_t& s) { return s.T < 32 * 256 ? (s.T + 255) / 256 : 32; }
+// Token partitions: as many as give the 1024 blocks that run at once (four per CU, held to 128 registers and 32 KB of LDS for
+// it), at most 64, of at least 64 tokens (a trip of the four waves).  More blocks than run at once pay their first loads and
+// their fold a second time.
+int gate_grad_partitions(const moe_shape_t& s)
+{
+    const long blocks = (long)((s.d + wgrad_columns(s) - 1) / wgrad_columns(s)) * ((s.E + wgrad_experts(s) - 1) / wgrad_experts(s));
+    const long want = std::min<long>(64, std::max<long>(1, 1024 / blocks));
+    return (int)std::min<long>(want, (s.T + 63) / 64);
+}
 
 template <typename ET, int NE, int KMAX>
 hipError_t launch_input_grad_t(const moe_shape_t& s, const void* dXp, const int32_t* pos, const float* dlogits,
@@ -452,6 +496,6 @@ hipError_t launch_gate_wgrad(const moe_shape_t& s, const void* X, const float* d
                                : launch_wgrad_mfma_t<float, 4, 2, 2>(s, X, dlogits, partial, partial_b, n_part, tok_per_part, st);
     if (e != hipSuccess) return e;
     const int dE = s.d * s.E;
-    hipLaunchKernelGGL(gate_wgrad_reduce_kernel, dim3((dE + 255) / 256), dim3(256), 0, st, partial, partial_b, dWg, dbg, n_part, dE, s.E);
+    hipLaunchKernelGGL(gate_wgrad_reduce_kernel, dim3((dE + 255) / 256 + 1), dim3(256), 0, st, partial, partial_b, dWg, dbg, n_part, dE, s.E);
     return hipGetLastError();
 }

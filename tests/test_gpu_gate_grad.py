@@ -101,6 +101,8 @@ def _ig_cfg(**kw):
     _ig_cfg(T=129, d=128, E=132, k=2),                         # a second chunk of four experts
     _ig_cfg(T=70, d=128, E=257, k=2, P=1),                     # a third chunk of one expert
     _ig_cfg(T=8200, d=2048, E=32, k=2),                        # several groups of tokens per wave
+    _ig_cfg(T=8200, d=2048, E=48, k=2),                        # and their rows requested ahead
+    _ig_cfg(T=8201, d=2048, E=64, k=1),
     _ig_cfg(T=77, d=36, E=33, k=2, P=3, dtype="f32"),          # fp32: half a strip, 4-byte loads
 ], ids=lambda c: f"{c.dtype}-T{c.T}-d{c.d}-E{c.E}-k{c.k}")
 def test_input_grad_edges(cfg):
@@ -146,6 +148,9 @@ def test_input_grad_leaves_out_experts_without_a_gradient(E):
     dict(T=257, d=192, E=36, k=2, P=4),                        # a second pass of four experts, two partitions
     dict(T=1100, d=128, E=48, k=2, P=8),                       # one pass and a half
     dict(T=300, d=100, E=40, k=1, P=4, dtype="f32"),           # fp32 tokens, strips that are not full
+    dict(T=65, d=320, E=17, k=2, P=1),                         # two partitions, a pass of one expert
+    dict(T=4097, d=128, E=16, k=2, P=4),                       # 64 partitions, the last of two tokens
+    dict(T=9001, d=1088, E=100, k=2, P=4),                     # partitions of a few trips, strips that are not full
 ], ids=lambda kw: f"T{kw['T']}-d{kw['d']}-E{kw['E']}")
 def test_gate_gradients_pass_edges(kw):
     cfg, case = _case(1, h=64, n_replicas=0, **kw)
