@@ -280,15 +280,15 @@ __global__ __launch_bounds__(GATE_THREADS) void gate_mfma_kernel(
     }
 }
 
-// ---- bf16 tokens (d % 64 == 0), E % 4 == 0: the same contraction with both operands delivered by buffer loads that write
+// ---- E % 4 == 0, bf16 tokens (d % 64 == 0) or fp32 (d % 4 == 0): the same contraction with both operands delivered by buffer loads that write
 // LDS directly, so that nothing asynchronous ever targets a register and the waits can be written by hand (the compiler's
 // own counts allow a third of the requests that may be outstanding).
 // A tile of 16 tokens belongs to two waves, one per partial sum: wave s visits the 32-column blocks s, s + 2, s + 4, ..
 // in order, which is the order the interface fixes, and the two sums meet in LDS at the end.  That halves the serial chain
 // of a tile (512 matrix instructions of 32 cycles at d = 4096, E = 16) and gives a CU twice the waves.  A step is two of a
 // wave's blocks (128 columns of the rows).
-// A ring of RING steps of a tile's tokens (4 KB each, shared by its two waves: each requests 8 of the 16 rows, so that a
-// request is whole 128-byte lines; 64-byte halves, a wave its own columns, asked L2 for every line twice); per partial
+// A ring of RING steps of a tile's tokens (4 KB each, 8 in fp32, shared by its two waves: each requests 8 of the 16 rows, so that
+// a request is whole 128-byte lines; 64-byte halves, a wave its own columns, asked L2 for every line twice); per partial
 // sum a ring of RING steps of the gate matrix (64 columns x 16 NT experts), fetched in equal shares by the waves that
 // use it.  A gate-matrix piece (4 consecutive experts of one column) lands where the instruction that uses it finds the 64
 // values of its lanes side by side: piece (block of the step, j, tile, q, i / 4) at 16 * ((((8 b + j) NT + tile) 4 + q) 4 +
@@ -314,7 +314,7 @@ __device__ __forceinline__ void gate_dma16(gate_rsrc_t r, uint32_t lds_base, uin
                  :: "s"(lds_base), "v"(voff), "s"(r), "s"(soff) : "memory");
 }
 
-template <int NT, int TILES, int RING> constexpr int gate_split_lds() { return RING * (4096 * TILES + 2 * 4096 * NT); }
+template <typename XT, int NT, int TILES, int RING> constexpr int gate_split_lds() { return RING * (2048 * (int)sizeof(XT) * TILES + 2 * 4096 * NT); }
 
 // TILES: token tiles of a block (2 TILES waves).  blockIdx.y: pass of 16 NT experts.  ROUTE: one pass, routing fused.
 // What bounds it: few tokens, the chain of dependent matrix instructions of a partial sum, whose order is fixed (0.45 us per
@@ -323,36 +323,46 @@ template <int NT, int TILES, int RING> constexpr int gate_split_lds() { return R
 // back to back and with the caches swept before it, separate reads, products and requests and half lines -> now: T = 64,
 // d = 4096, E = 16 20.4, 23 -> 18.6, 21.4; T = 8192, d = 1024 10.8, 15.3 -> 10.3, 14.1; T = 8001, d = 2048, E = 128 55, 62 ->
 // 52, 55; T = 16384, E = 64 48, 58 -> 45, 50; T = 32768, d = 4096, E = 16 64, 113 -> 60, 112.
-template <int NT, int TILES, int RING, bool ROUTE>
-__global__ __launch_bounds__(TILES * 128) void gate_split_kernel(
-    const bf16_t* __restrict__ X, const float* __restrict__ Wg, const float* __restrict__ bg,
+// fp32 tokens, from the general kernel, whose loads wait for each other: T = 512, d = 64, E = 8 8.1 -> 4.4; T = 3291, d = 364, E = 8
+// 11.9 -> 5.5; T = 67, d = 640, E = 16 13.4 -> 6.6; with the routing T = 1500, d = 512, E = 64 23 -> 9.5.
+// ET: the block's waves share one token tile but not its experts: ET units of two waves, 16 experts each, with rings of their own
+// (few tokens: the chain of a wave is as short as with a block per 16 experts, and the routing needs no launch of its own).
+template <typename XT, int NT, int TILES, int RING, bool ROUTE, int ET>
+__global__ __launch_bounds__(TILES * ET * 128) void gate_split_kernel(
+    const XT* __restrict__ X, const float* __restrict__ Wg, const float* __restrict__ bg,
     float* __restrict__ logits, int32_t* __restrict__ idx, float* __restrict__ wout,
     int T, int d, int E, int k, int renorm)
 {
-    constexpr int XSTEP = 4096, WSTEP = 4096 * NT, XRING = TILES * RING * XSTEP;
-    constexpr int WOPS = 4 * NT / TILES, OPS = 2 + WOPS;   // requests of one wave per step
+    constexpr bool F32 = sizeof(XT) == 4;
+    constexpr int XSTEP = 2048 * (int)sizeof(XT), WSTEP = 4096 * NT, XRING = TILES * RING * XSTEP;
+    constexpr int XOPS = XSTEP / 2048, WOPS = 4 * NT / TILES, OPS = XOPS + WOPS;   // requests of one wave per step
     static_assert(4 * NT % TILES == 0 && OPS <= 8, "equal shares of the gate matrix, a request per column of a block");
     static_assert(RING >= 2, "a step is requested while the one before it is multiplied");
-    constexpr int PITCH = 16 * NT + 1;                     // logits of a token in LDS
-    static_assert(TILES * 16 * PITCH * 4 + TILES * NT * 1024 <= gate_split_lds<NT, TILES, RING>(), "logits and sums fit the rings");
-    extern __shared__ __attribute__((aligned(1024))) unsigned char gsm[];   // token rings | gate-matrix rings; then sums | logits
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(GATE_LDS_PTR(unsigned char))gsm;
+    constexpr int PITCH = 16 * NT * ET + 1;                // logits of a token in LDS
+    static_assert(TILES * 16 * PITCH * 4 + TILES * ET * NT * 1024 <= ET * gate_split_lds<XT, NT, TILES, RING>(), "logits and sums fit the rings");
+    static_assert(ET == 1 || (TILES == 1 && NT == 1 && ROUTE), "units of experts share one tile of tokens and all experts");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char all_lds[];   // token rings | gate-matrix rings, per unit; then sums | logits
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int s = wave & 1, tile = wave >> 1;              // partial sum, token tile
+    const int s = wave & 1, tile = ET == 1 ? wave >> 1 : 0, unit = ET == 1 ? 0 : wave >> 1;      // partial sum, token tile, unit
+    unsigned char* gsm = all_lds + unit * gate_split_lds<XT, NT, TILES, RING>();
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(GATE_LDS_PTR(unsigned char))gsm;
     const int q = lane >> 4, i16 = lane & 15;
     const int blk_tok0 = blockIdx.x * (16 * TILES), tok0w = blk_tok0 + tile * 16, tok = tok0w + i16;
-    const int ec0 = blockIdx.y * (16 * NT);
-    const int nb = d / 64, steps = (nb + 1) / 2;           // 32-column blocks of each partial sum
+    const int ec0 = (ET == 1 ? (int)blockIdx.y : unit) * (16 * NT);
+    const int nb = (d + 63) / 64, steps = (nb + 1) / 2;    // 32-column blocks of each partial sum
 
     // tokens: rows of this block onwards; a token past the end reads the last one (never stored); a block past the
     // end of a row reads into the next rows or, after the last row, zeros: never multiplied.  The two waves of a tile
     // share its ring: a wave requests 8 of the 16 rows, whole 128-byte lines (64 columns, 32 of either sum); in LDS a
     // row's eight 16-byte pieces are XOR-swizzled by the row, so that the 16 rows of a piece cover all banks.
-    const gate_rsrc_t rX = gate_make_rsrc(X + (size_t)blk_tok0 * d, (unsigned long long)(T - blk_tok0) * d * 2);
+    // fp32: a line is the 32 columns of one sum; rows end inside a block, and pieces past the end are asked for nowhere (zeros).
+    constexpr uint32_t NOWHERE = 0x80000000u;              // past the rows of a block, also with a step's offset added
+    const gate_rsrc_t rX = gate_make_rsrc(X + (size_t)blk_tok0 * d, (unsigned long long)(F32 ? min(T - blk_tok0, 16 * TILES) : T - blk_tok0) * d * sizeof(XT));
     const int xrow = 8 * s + (lane >> 3);                  // row of the tile this lane requests a piece of
     const int rowrel = (tok0w + xrow < T ? tok0w + xrow : T - 1) - blk_tok0;
-    const uint32_t xv = (uint32_t)(rowrel * d * 2 + (((lane & 7) ^ ((xrow >> 1) & 7)) << 4));
+    const int xpiece = (lane & 7) ^ ((xrow >> 1) & 7);
+    const uint32_t xv = (uint32_t)(rowrel * d * (int)sizeof(XT) + (xpiece << 4));
     const uint32_t xl = lds0 + (uint32_t)(tile * RING * XSTEP + s * 1024);
     // gate matrix: this wave's share of a step
     const gate_rsrc_t rW = gate_make_rsrc(Wg + ec0, ((unsigned long long)d * E - ec0) * 4);     // past the last column: zeros
@@ -365,24 +375,30 @@ __global__ __launch_bounds__(TILES * 128) void gate_split_kernel(
     }
     const uint32_t wl = lds0 + (uint32_t)(XRING + s * RING * WSTEP + tile * WOPS * 1024);
     auto request = [&](int n, int P, int slot) {           // request n of this wave for step P
-        if (n < 2) gate_dma16(rX, xl + (uint32_t)(slot * XSTEP + n * 2048), xv + 128u * n, (uint32_t)P * 256u);
-        else gate_dma16(rW, wl + (uint32_t)(slot * WSTEP + (n - 2) * 1024), wv[n - 2], (uint32_t)P * (uint32_t)(128 * E * 4));
+        if (n < XOPS) {
+            const bool there = !F32 || P * 128 + n * 32 + xpiece * 4 < d;
+            gate_dma16(rX, xl + (uint32_t)(slot * XSTEP + n * 2048), there ? xv + 128u * n : NOWHERE, (uint32_t)P * (128u * sizeof(XT)));
+        } else gate_dma16(rW, wl + (uint32_t)(slot * WSTEP + (n - XOPS) * 1024), wv[n - XOPS], (uint32_t)P * (uint32_t)(128 * E * 4));
     };
     gate_f4 acc[NT];
 #pragma unroll
     for (int tl = 0; tl < NT; ++tl) acc[tl] = gate_f4{0.0f, 0.0f, 0.0f, 0.0f};
-    // operands of a block: 8 columns of a token per lane (bf16 pairs), 8 x NT elements of the gate matrix
-    struct Block { gate_u4 x; float w[8][NT]; };
-    const uint32_t xr = (uint32_t)(tile * RING * XSTEP + i16 * 128 + (((4 * s + q) ^ ((i16 >> 1) & 7)) << 4));
+    // operands of a block: 8 columns of a token per lane (as loaded), 8 x NT elements of the gate matrix
+    struct Block { gate_u4 x[F32 ? 2 : 1]; float w[8][NT]; };
+    const uint32_t xr = (uint32_t)(tile * RING * XSTEP + i16 * 128 + (F32 ? s * 2048 : 0) + (((F32 ? 2 * q : 4 * s + q) ^ ((i16 >> 1) & 7)) << 4));
     const uint32_t wr = (uint32_t)(XRING + s * RING * WSTEP + lane * 4);
-    auto read_x = [&](Block& o, int slot, int b) { o.x = *reinterpret_cast<const gate_u4*>(gsm + xr + slot * XSTEP + b * 2048); };
+    auto read_x = [&](Block& o, int slot, int b) {
+        o.x[0] = *reinterpret_cast<const gate_u4*>(gsm + xr + slot * XSTEP + b * (XSTEP / 2));
+        if constexpr (F32) o.x[1] = *reinterpret_cast<const gate_u4*>(gsm + (xr ^ 16u) + slot * XSTEP + b * (XSTEP / 2));
+    };
     auto read_w = [&](Block& o, int slot, int b, int j) {
 #pragma unroll
         for (int tl = 0; tl < NT; ++tl) o.w[j][tl] = *reinterpret_cast<const float*>(gsm + wr + slot * WSTEP + ((b * 8 + j) * NT + tl) * 256);
     };
     auto multiply = [&](const Block& o, int j) {
-        const uint32_t w = o.x[j / 2];
-        const float a = __uint_as_float((j & 1) ? (w & 0xffff0000u) : (w << 16));
+        float a;
+        if constexpr (F32) a = __uint_as_float(o.x[j / 4][j % 4]);
+        else a = __uint_as_float((j & 1) ? (o.x[0][j / 2] & 0xffff0000u) : (o.x[0][j / 2] << 16));
 #pragma unroll
         for (int tl = 0; tl < NT; ++tl) acc[tl] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.w[j][tl], a, acc[tl], 0, 0, 0);
     };
@@ -426,8 +442,8 @@ __global__ __launch_bounds__(TILES * 128) void gate_split_kernel(
     // requests past the end are still on their way into the rings: nothing may reuse LDS before they land
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    float* sums = reinterpret_cast<float*>(gsm) + tile * NT * 256 + lane;
-    float* logit_lds = reinterpret_cast<float*>(gsm) + TILES * NT * 256 + tile * 16 * PITCH;
+    float* sums = reinterpret_cast<float*>(all_lds) + (tile + unit) * NT * 256 + lane;
+    float* logit_lds = reinterpret_cast<float*>(all_lds) + TILES * ET * NT * 256 + tile * 16 * PITCH;
     if (s == 1)
 #pragma unroll
         for (int tl = 0; tl < NT; ++tl)
@@ -449,13 +465,14 @@ __global__ __launch_bounds__(TILES * 128) void gate_split_kernel(
             }
     if (ROUTE) {
         __syncthreads();
+        if (unit > 0) return;
         if (s == 1) {
             for (int i = lane; i < 16 * E; i += 64) {             // the tile's 16 rows of logits are contiguous
                 const int tk = i / E, e = i - tk * E;
                 if (tok0w + tk < T) logits[(size_t)tok0w * E + i] = logit_lds[tk * PITCH + e];
             }
         } else {
-            route_lanes<4, 4 * NT>(logit_lds + (lane >> 2) * PITCH, lane & 3, tok0w + (lane >> 2), tok0w + (lane >> 2) < T, E, k, renorm, idx, wout);
+            route_lanes<4, 4 * NT * ET>(logit_lds + (lane >> 2) * PITCH, lane & 3, tok0w + (lane >> 2), tok0w + (lane >> 2) < T, E, k, renorm, idx, wout);
         }
     }
 }
@@ -566,12 +583,12 @@ hipError_t run_gate(const moe_shape_t& s, const void* X, const float* Wg, const 
     return run_gate_route(s, logits, idx, w, st);
 }
 
-template <int NT, int TILES, int RING, bool ROUTE>
+template <typename XT, int NT, int TILES, int RING, bool ROUTE, int ET = 1>
 hipError_t run_gate_split(const moe_shape_t& s, const void* X, const float* Wg, const float* bg,
                           float* logits, int32_t* idx, float* w, hipStream_t st)
 {
-    constexpr int lds = gate_split_lds<NT, TILES, RING>();
-    auto kern = gate_split_kernel<NT, TILES, RING, ROUTE>;
+    constexpr int lds = ET * gate_split_lds<XT, NT, TILES, RING>();
+    auto kern = gate_split_kernel<XT, NT, TILES, RING, ROUTE, ET>;
     static PerDeviceOnce once;                             // per instantiation
     const int dev = current_device();
     if (!once.is_done(dev)) {
@@ -579,8 +596,8 @@ hipError_t run_gate_split(const moe_shape_t& s, const void* X, const float* Wg, 
         if (e != hipSuccess) return e;
         once.mark(dev);
     }
-    const dim3 grid((s.T + 16 * TILES - 1) / (16 * TILES), (s.E + 16 * NT - 1) / (16 * NT));
-    hipLaunchKernelGGL(kern, grid, dim3(TILES * 128), lds, st, (const bf16_t*)X, Wg, bg, logits, idx, w, s.T, s.d, s.E, s.k, s.renorm);
+    const dim3 grid((s.T + 16 * TILES - 1) / (16 * TILES), ET > 1 ? 1 : (s.E + 16 * NT - 1) / (16 * NT));
+    hipLaunchKernelGGL(kern, grid, dim3(TILES * ET * 128), lds, st, (const XT*)X, Wg, bg, logits, idx, w, s.T, s.d, s.E, s.k, s.renorm);
     const hipError_t e = hipGetLastError();
     return (e != hipSuccess || ROUTE) ? e : run_gate_route(s, logits, idx, w, st);
 }
@@ -613,14 +630,42 @@ hipError_t run_gate_t(const moe_shape_t& s, const void* X, const float* Wg, cons
 constexpr int GATE_LAUNCH_TOK = 1 << 26;
 static_assert(GATE_LAUNCH_TOK % GATE_TOK == 0 && GATE_LAUNCH_TOK <= (1ll << 32) / 32, "whole blocks, within a launch");
 
+// Few tokens and 17 to 64 experts: whether a block takes all experts of its tokens and routes them (a launch of 4 us fewer), or
+// every 16 experts are a block of their own.  In one block the operands of two or more units come in through one CU, which
+// delivers those of two units in the time a step takes, of four in twice that: kernels, us, blocks of 16 experts + routing | one
+// block, bf16: T = 1999, d = 768, E = 32 6.2 + 4.5 | 7.9; T = 1075, d = 2304, E = 24 12.5 + 4.1 | 13.9; T = 2040, d = 1024, E = 64
+// 9.5 + 4.2 | 12.7; T = 600, d = 4096, E = 64 18.7 + 4.1 | 29.2; fp32: T = 1931, d = 700, E = 32 5.8 + 4.8 | 8.1.
+static bool one_block(const moe_shape_t& s)
+{
+    const long row = (long)s.d * (s.dtype == MOE_BF16 ? 2 : 4);
+    return s.E <= 32 ? row <= 8192 : (s.E <= 64 && row <= 2048);
+}
+
 static hipError_t launch_gate_part(const moe_shape_t& s, const void* X, const float* Wg, const float* bg,
                                    float* logits, int32_t* idx, float* w, hipStream_t st)
 {
-    if (s.dtype == MOE_F32) return run_gate_t<float>(s, X, Wg, bg, logits, idx, w, st);
+    const long tiles = (long)((s.T + 15) / 16) * ((s.E + 15) / 16);
+    if (s.dtype == MOE_F32) {
+        // the same choice for fp32, whose tokens take twice the LDS
+        if (s.E % 4 == 0 && (long long)s.d * 4 * (GATE_TOK + 1) < (1ll << 31) && (long long)s.d * s.E * 4 < (1ll << 31)) {
+            if (tiles <= 512) {
+                if (s.E <= 16) return run_gate_split<float, 1, 1, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+                if (one_block(s) && s.E <= 32) return run_gate_split<float, 1, 1, 3, true, 2>(s, X, Wg, bg, logits, idx, w, st);
+                if (one_block(s) && s.E <= 48) return run_gate_split<float, 1, 1, 3, true, 3>(s, X, Wg, bg, logits, idx, w, st);
+                if (one_block(s)) return run_gate_split<float, 1, 1, 2, true, 4>(s, X, Wg, bg, logits, idx, w, st);
+                return run_gate_split<float, 1, 1, 3, false>(s, X, Wg, bg, logits, idx, w, st);
+            }
+            if (s.E <= 16) return run_gate_split<float, 1, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+            if (s.E <= 32) return run_gate_split<float, 2, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+            if (s.E <= 64) return run_gate_split<float, 4, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
+            return run_gate_split<float, 4, 4, 2, false>(s, X, Wg, bg, logits, idx, w, st);
+        }
+        return run_gate_t<float>(s, X, Wg, bg, logits, idx, w, st);
+    }
     // rows of 64 tokens must stay inside the 32-bit offsets of a buffer load; a load that writes LDS moves whole aligned
     // words, so tokens that begin at an odd bf16 take the general kernel (ordinary loads need no alignment)
     if (s.E % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 3) == 0 && (long long)s.d * 2 * (GATE_TOK + 1) < (1ll << 31) && (long long)s.d * s.E * 4 < (1ll << 31)) {
-        // Few tokens: a block per 16 tokens and 16 experts (more experts: the routing is a launch of its own), so that the
+        // Few tokens: a block per 16 tokens and 16 experts (more experts: as one_block says), so that the
         // gate matrix comes in through as many CUs as there are.  Up to 512 such blocks; beyond, 64 tokens share a block's
         // gate matrix.  The call, us, before -> now: T = 64, d = 4096, E = 16 34 -> 20; T = 1, d = 2048 19 -> 13; T = 3000,
         // d = 1024, E = 48 45 -> 21; T = 2000, E = 100, k = 8 85 -> 34; T = 8001, d = 2048, E = 128 95 -> 56; T = 4000, E = 24
@@ -628,17 +673,19 @@ static hipError_t launch_gate_part(const moe_shape_t& s, const void* X, const fl
         // few percent more since, see there).
         // Rings: three steps, or two where that puts a second block on a CU that has one to run: T = 30000, d = 1984, E = 48
         // 68 -> 61 us; T = 40000, d = 2048, E = 32 76 -> 67 (but T = 16384, one block per CU anyway, caches swept, 37 -> 39).
-        const long tiles = (long)((s.T + 15) / 16) * ((s.E + 15) / 16);
         if (tiles <= 512) {
-            if (s.E <= 16) return run_gate_split<1, 1, 3, true>(s, X, Wg, bg, logits, idx, w, st);
-            return run_gate_split<1, 1, 3, false>(s, X, Wg, bg, logits, idx, w, st);
+            if (s.E <= 16) return run_gate_split<bf16_t, 1, 1, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+            if (one_block(s) && s.E <= 32) return run_gate_split<bf16_t, 1, 1, 3, true, 2>(s, X, Wg, bg, logits, idx, w, st);
+            if (one_block(s) && s.E <= 48) return run_gate_split<bf16_t, 1, 1, 3, true, 3>(s, X, Wg, bg, logits, idx, w, st);
+            if (one_block(s)) return run_gate_split<bf16_t, 1, 1, 3, true, 4>(s, X, Wg, bg, logits, idx, w, st);
+            return run_gate_split<bf16_t, 1, 1, 3, false>(s, X, Wg, bg, logits, idx, w, st);
         }
-        if (s.E <= 16) return run_gate_split<1, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
-        if (s.E <= 32 && s.T <= 64 * 256) return run_gate_split<2, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
-        if (s.E <= 32) return run_gate_split<2, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
-        if (s.E <= 48) return run_gate_split<3, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
-        if (s.E <= 64) return run_gate_split<4, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
-        return run_gate_split<4, 4, 3, false>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 16) return run_gate_split<bf16_t, 1, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 32 && s.T <= 64 * 256) return run_gate_split<bf16_t, 2, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 32) return run_gate_split<bf16_t, 2, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 48) return run_gate_split<bf16_t, 3, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
+        if (s.E <= 64) return run_gate_split<bf16_t, 4, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+        return run_gate_split<bf16_t, 4, 4, 3, false>(s, X, Wg, bg, logits, idx, w, st);
     }
     return run_gate_t<bf16_t>(s, X, Wg, bg, logits, idx, w, st);
 }

@@ -95,6 +95,8 @@ def test_routing_of_many_experts(E, k):
     (4100, 320, 36), (5000, 128, 64), (3000, 192, 68),           # 64 tokens per block: three and four tiles of experts, two passes
     (5000, 320, 20), (16384, 192, 24), (16385, 448, 32),         # two tiles of experts: rings of three steps, the last T with them, of two
     (90, 128, 18),                                               # no multiple of four: the general kernel
+    (33, 4096, 32), (49, 4160, 32), (20, 1024, 48), (65, 64, 36), (2000, 1024, 64), (30, 1088, 64), (17, 512, 52),   # experts of a
+    # block of 16 tokens in two, three and four units that route them, up to the longest rows, and past those
 ], ids=str)
 def test_gate_logits_bit_for_bit(T, d, E):
     cfg = _cfg(T=T, d=d, E=E, k=min(2, E), P=1, renorm=1)
@@ -106,6 +108,33 @@ def test_gate_logits_bit_for_bit(T, d, E):
     hd = G.make_handle(cfg, G=1)
     b = G.binding.LayerBuffers(hd, False)
     hd.gate_topk(G.dev(X, "bf16"), G.dev(Wg), G.dev(bg), b.logits, b.idx, b.w)
+    torch.cuda.synchronize()
+    assert np.array_equal(G.host(b.logits).view(np.uint32), ref["logits"].view(np.uint32))
+    assert np.array_equal(G.host(b.idx), ref["idx"])
+    assert np.allclose(G.host(b.w), ref["w"], rtol=1e-5, atol=1e-7)
+
+
+@pytest.mark.parametrize("T,d,E,off", [
+    (1, 4, 4, 0), (17, 68, 8, 0), (16, 192, 12, 1),              # one wave per partial sum; rows that end inside a block of columns
+    (33, 4100, 16, 0), (100, 316, 20, 3), (50, 132, 132, 0),     # experts in blocks of 16, the last one partly empty
+    (8200, 36, 16, 0), (8193, 100, 16, 0), (5000, 324, 20, 2),   # 64 tokens per block, one and two tiles of experts
+    (4100, 260, 36, 0), (5000, 72, 64, 0), (3000, 132, 68, 0),   # four tiles of experts, two passes
+    (40, 2048, 32, 0), (40, 2052, 32, 0), (31, 512, 48, 0), (700, 500, 64, 1), (15, 516, 64, 0), (64, 4, 20, 0),   # units, as above
+    (90, 100, 18, 0),                                            # no multiple of four: the general kernel
+], ids=str)
+def test_fp32_gate_logits_bit_for_bit(T, d, E, off):
+    """off: floats by which the tokens begin past a 16-byte boundary."""
+    cfg = _cfg(T=T, d=d, E=E, k=min(2, E), P=1, renorm=1, dtype="f32")
+    rng = np.random.default_rng(T + d + E)
+    X = rng.standard_normal((T, d)).astype(np.float32)
+    Wg = (rng.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    bg = rng.standard_normal(E).astype(np.float32)
+    ref = orc.route(X, Wg, bg, cfg.k, 1)
+    hd = G.make_handle(cfg, G=1)
+    b = G.binding.LayerBuffers(hd, False)
+    dX = torch.zeros(T * d + off, device=G.DEV)[off:]
+    dX.copy_(G.dev(X, "f32").reshape(-1))
+    hd.gate_topk(dX.view(T, d), G.dev(Wg), G.dev(bg), b.logits, b.idx, b.w)
     torch.cuda.synchronize()
     assert np.array_equal(G.host(b.logits).view(np.uint32), ref["logits"].view(np.uint32))
     assert np.array_equal(G.host(b.idx), ref["idx"])
