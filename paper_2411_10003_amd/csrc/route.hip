@@ -156,51 +156,89 @@ __global__ __launch_bounds__(ROUTE_WAVES * 64) void positions_kernel(
     });
 }
 
-// The layout from the counts and the placement, rebuilt by a whole block in LDS.  lds: 4 E + 2 words: dest, slot of
-// each expert, count and first row of each slot (E + 1), a flag.
-struct BlockLayout { int32_t *dest, *slot_of, *slot_cnt, *slot_off, *flag; };
+// The layout from the counts and the placement, rebuilt by a whole block in LDS.  lds: 5 E + 3 words: dest, slot of each expert,
+// count and first row of each slot (E + 1), first slot of each destination (P + 1, P <= E), a flag.
+// Slots are ranks by (destination, id).  Up to WALK_EXPERTS experts every expert walks over all of them.  Beyond, one wave finds
+// the ranks 64 experts at a time, like the rows of a chunk: the lanes with the same destination find each other by ballots,
+// and a counter per destination carries over.  The launch that finds layout and positions, us, walk | wave: E = 16, 65536
+// assignments 9.4 | 10.2; E = 32, 32768 6.3 | 6.9; E = 40, 6000 7.7 | 7.0; E = 64, 10000 9.2 | 7.4; E = 128, 32004 11.5 | 8.7,
+// 24000 11.4 | 8.1.
+constexpr int WALK_EXPERTS = 32;
+struct BlockLayout { int32_t *dest, *slot_of, *slot_cnt, *slot_off, *first, *flag; };
 __device__ __forceinline__ BlockLayout block_layout_lds(int32_t* lds, int E)
 {
-    return BlockLayout{lds, lds + E, lds + 2 * E, lds + 3 * E, lds + 4 * E + 1};
+    return BlockLayout{lds, lds + E, lds + 2 * E, lds + 3 * E, lds + 4 * E + 1, lds + 5 * E + 2};
 }
-__host__ __device__ __forceinline__ constexpr int block_layout_words(int E) { return 4 * E + 2; }
+__host__ __device__ __forceinline__ constexpr int block_layout_words(int E) { return 5 * E + 3; }
+
+// One wave: v[0 .. n) replaced by the sums before them, v[n] by the sum of all.
+__device__ __forceinline__ void wave_exclusive_scan(const int32_t* v, int32_t* out, int n, int lane)
+{
+    int carry = 0;
+    for (int s0 = 0; s0 < n; s0 += 64) {
+        const int x = s0 + lane < n ? v[s0 + lane] : 0;
+        int incl = x;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int up = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += up;
+        }
+        if (s0 + lane < n) out[s0 + lane] = carry + incl - x;
+        carry += __shfl(incl, 63, 64);
+    }
+    if (lane == 0) out[n] = carry;
+    __builtin_amdgcn_wave_barrier();
+}
 
 __device__ __forceinline__ void build_layout(const BlockLayout& L, const int32_t* __restrict__ expert_dest,
                                              const int32_t* __restrict__ counts, int E, int P)
 {
     const int tid = threadIdx.x, lane = tid & 63;
     if (tid == 0) *L.flag = 0;
+    for (int p = tid; p <= P; p += blockDim.x) L.first[p] = 0;
     __syncthreads();
     for (int e = tid; e < E; e += blockDim.x) {
         int p = expert_dest[e];
+        L.slot_off[e] = counts[e];                          // for now
         if (p < 0 || p >= P) { atomicOr(L.flag, 1); p = p < 0 ? 0 : P - 1; }
         L.dest[e] = p;
     }
     __syncthreads();
-    for (int e = tid; e < E; e += blockDim.x) {             // slot = rank by (destination, id)
-        const int p = L.dest[e], n = counts[e];
-        int sl = 0;
+    if (E <= WALK_EXPERTS) {
+        for (int e = tid; e < E; e += blockDim.x) {
+            const int p = L.dest[e];
+            int sl = 0;
 #pragma unroll 4
-        for (int f = 0; f < E; ++f) sl += (L.dest[f] < p) || (L.dest[f] == p && f < e);
-        L.slot_of[e] = sl;
-        L.slot_cnt[sl] = n;
-    }
-    __syncthreads();
-    if (tid < 64) {                                         // exclusive scan of the slot counts, one wave
-        int carry = 0;
-        for (int s0 = 0; s0 < E; s0 += 64) {
-            const int v = s0 + lane < E ? L.slot_cnt[s0 + lane] : 0;
-            int incl = v;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int up = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += up;
-            }
-            if (s0 + lane < E) L.slot_off[s0 + lane] = carry + incl - v;
-            carry += __shfl(incl, 63, 64);
+            for (int f = 0; f < E; ++f) sl += (L.dest[f] < p) || (L.dest[f] == p && f < e);
+            L.slot_of[e] = sl;
+            L.slot_cnt[sl] = L.slot_off[e];
         }
-        if (lane == 0) L.slot_off[E] = carry;
+        __syncthreads();
+    } else if (tid < 64) {
+        const int bits = id_bits(P);
+        volatile int32_t* in_dest = L.first;                // experts of each destination so far
+        for (int s0 = 0; s0 < E; s0 += 64) {
+            const int e = s0 + lane, p = e < E ? L.dest[e] : -1;
+            const unsigned long long peers = same_expert(p, bits);
+            const int rank = __popcll(peers & lanemask_lt(lane));
+            int base = 0;
+            if (p >= 0) base = in_dest[p];
+            __builtin_amdgcn_wave_barrier();
+            if (p >= 0) {
+                L.slot_of[e] = base + rank;
+                if (rank == 0) in_dest[p] = base + __popcll(peers);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        wave_exclusive_scan(L.first, L.first, P, lane);
+        for (int e = lane; e < E; e += 64) {
+            const int sl = L.first[L.dest[e]] + L.slot_of[e];
+            L.slot_of[e] = sl;
+            L.slot_cnt[sl] = L.slot_off[e];
+        }
+        __builtin_amdgcn_wave_barrier();
     }
+    if (tid < 64) wave_exclusive_scan(L.slot_cnt, L.slot_off, E, lane);
     __syncthreads();
 }
 
@@ -213,7 +251,12 @@ __device__ __forceinline__ void publish_layout(const BlockLayout& L, const moe_l
     for (int s = tid; s <= E; s += blockDim.x) out.slot_offsets[s] = L.slot_off[s];
     for (int p = tid; p <= P; p += blockDim.x) {
         int first = 0, mine = 0;                            // slots of destinations below p, of p
-        for (int f = 0; f < E; ++f) { first += (L.dest[f] < p); mine += (L.dest[f] == p); }
+        if (E <= WALK_EXPERTS) {
+            for (int f = 0; f < E; ++f) { first += (L.dest[f] < p); mine += (L.dest[f] == p); }
+        } else {
+            first = L.first[p];
+            mine = p < P ? L.first[p + 1] - first : 0;
+        }
         out.dest_slots[p] = first;
         out.dest_offsets[p] = L.slot_off[first];
         if (p == self) *status = (*L.flag || mine > Gcap) ? (int32_t)MOE_ERR_PLAN : (int32_t)MOE_OK;
