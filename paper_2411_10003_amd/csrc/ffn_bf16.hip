@@ -989,21 +989,43 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     // Both go past the L2 of the XCD (sc1: coherent on the device, where every XCD has an L2 of its own), so that no L2 has to be
     // written back or invalidated for them: with plain accesses between agent-scope fences d = 1024, h = 4096, 152 tiles of 128
     // slices took 114 us where this takes 90 and whole tiles 108.
-    constexpr int WHOLE = 0, KEEP = 1, SUM = 2, AT_DEVICE = 16;
+    constexpr int WHOLE = 0, SUM = 1, KEEP = 2, AT_DEVICE = 16;
     static_assert(!LAST || GEO::UNIT_BYTES == NWAVES * TM * N_PASS * 2 * 1024, "a part fills its unit");
     const long rows_left = row_limit - m0 - wm * WM;           // rows of fragments past the last row are not kept
     auto part_rsrc = [&](int u) {
         return __builtin_amdgcn_make_buffer_rsrc((void*)((char*)p.split_ws + (size_t)u * GEO::UNIT_BYTES), 0, GEO::UNIT_BYTES, 0x00020000);
     };
-    auto epilogue = [&](auto MODE) {
-    constexpr int mode = decltype(MODE)::value;
+    int* counter = LAST ? p.arrived + unit / 2 : nullptr;
+    auto tell = [&](int v) {                                   // what thread 0 knows, to all
+        int* word = reinterpret_cast<int*>(smem);              // ring slot 0: below the patches
+        if (tid == 0) *word = v;
+        __syncthreads();
+        const int r = __builtin_amdgcn_readfirstlane(*word);
+        __syncthreads();
+        return r;
+    };
+    // the other part is there already: this one need not be kept
+    int before = 0;
+    if (LAST && uneven) before = tell(tid == 0 ? __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0);
+    // A loop, unrolled, and not a function called per mode: in the kernels without LAST it is no loop at all.  (As a lambda the
+    // 256 x 256 bwd1 kernels, which have no mode but WHOLE, spilled 2 and 12 vector registers.)
+#pragma unroll
+    for (int mode = LAST ? KEEP : WHOLE; mode >= WHOLE; --mode) {
+    if (LAST) {
+        if (mode == WHOLE ? uneven : !uneven) continue;
+        if (mode == KEEP && before != 0) continue;
+        if (mode == SUM) {
+            if (before != 1) continue;
+            if (tid == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
     if (BWD1 && !FIN) request(0, 0, zin[0], uin[0]);
 #pragma unroll
     for (int fr = 0; fr < TM; ++fr) {
         if (mode != WHOLE && fr * 32 >= rows_left) continue;
         const int part_ofs = ((wave * TM + fr) * (N_PASS * 2 * 64) + lane) * 16;
-        float4 other[mode == SUM ? N_PASS : 1][2];
-        if (mode == SUM) {
+        float4 other[LAST ? N_PASS : 1][2];
+        if (LAST && mode == SUM) {
             const buf_rsrc_t from = part_rsrc(unit ^ 1);
 #pragma unroll
             for (int i = 0; i < N_PASS; ++i)
@@ -1096,7 +1118,7 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, make_float4(v[4], v[5], v[6], v[7])), to, part_ofs + pass * 2048 + 1024, 0, AT_DEVICE);
                 continue;
             }
-            if (mode == SUM) {
+            if (LAST && mode == SUM) {
                 const float4 x0 = other[pass][0], x1 = other[pass][1];
                 v[0] += x0.x; v[1] += x0.y; v[2] += x0.z; v[3] += x0.w; v[4] += x1.x; v[5] += x1.y; v[6] += x1.z; v[7] += x1.w;
             }
@@ -1179,34 +1201,14 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         }
         }
     }
-    };
-    if (uneven) {
-        int* word = reinterpret_cast<int*>(smem);              // ring slot 0: below the patches
-        int* counter = p.arrived + unit / 2;
-        auto tell = [&](int v) {                               // what thread 0 knows, to all
-            if (tid == 0) *word = v;
-            __syncthreads();
-            const int r = __builtin_amdgcn_readfirstlane(*word);
-            __syncthreads();
-            return r;
-        };
-        // the other part is there already: this one need not be kept
-        int before = tell(tid == 0 ? __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0);
-        if (before == 0) {
-            epilogue(std::integral_constant<int, KEEP>{});
-            // Every wave's stores are complete before the barrier, and thread 0 counts this part after it.  Nobody waits for
-            // the other part: whichever is counted last goes on with the tile.
-            WAIT_VMCNT(0);
-            __syncthreads();
-            if (tid == 0) before = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            before = tell(before);
-        }
-        if (before == 1) {
-            if (tid == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            epilogue(std::integral_constant<int, SUM>{});
-        }
-    } else {
-        epilogue(std::integral_constant<int, WHOLE>{});
+    if (mode == KEEP) {
+        // Every wave's stores are complete before the barrier, and thread 0 counts this part after it.  Nobody waits for the
+        // other part: whichever is counted last goes on with the tile.
+        WAIT_VMCNT(0);
+        __syncthreads();
+        if (tid == 0) before = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before = tell(before);
+    }
     }
     __syncthreads();             // every wave is done with its patch before the next tile's DMA lands there
   }
