@@ -179,3 +179,21 @@ def test_input_grad_of_assignments_without_a_row(E, k, dtype):
     dX = torch.zeros(T, d, dtype=hd.elt, device=G.DEV)
     hd.input_grad(G.dev(dXp, dtype), G.dev(pos), G.dev(dl), G.dev(Wg), dX)
     G.assert_rows_close(G.host(dX), want, G.TOL[dtype], "dX")
+
+
+@pytest.mark.parametrize("x_off,dl_off", [(1, 0), (2, 0), (3, 1), (5, 2), (6, 3), (0, 1)], ids=str)
+@pytest.mark.parametrize("T,d,E", [(33, 64, 12), (300, 320, 16), (1030, 192, 40), (2100, 1088, 100)], ids=str)
+def test_gate_gradients_of_operands_at_any_address(T, d, E, x_off, dl_off):
+    """Tokens that begin at any bf16, logit gradients at any float: the bits of the aligned call."""
+    hd = G.make_handle(_ig_cfg(T=T, d=d, E=E, k=1, P=1), G=1)
+    g = torch.Generator(device=G.DEV).manual_seed(T + E)
+    X, dl = torch.randn(T, d, device=G.DEV, generator=g).to(torch.bfloat16), torch.randn(T, E, device=G.DEV, generator=g)
+    got = []
+    for off_x, off_dl in ((0, 0), (x_off, dl_off)):
+        x = torch.full((T * d + off_x,), float("nan"), dtype=torch.bfloat16, device=G.DEV)[off_x:].view(T, d)
+        l = torch.full((T * E + off_dl,), float("nan"), device=G.DEV)[off_dl:].view(T, E)   # noqa: E741
+        x.copy_(X), l.copy_(dl)
+        dWg, dbg = torch.zeros(d, E, device=G.DEV), torch.zeros(E, device=G.DEV)
+        hd.gate_bwd_params(x, l, dWg, dbg)
+        got.append((dWg, dbg))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
