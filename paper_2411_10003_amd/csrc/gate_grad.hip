@@ -222,8 +222,8 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? (NE == 4 && KMAX == 2 ? 
 // wave requests its next 16 tokens before it multiplies the current ones, four waves per SIMD.  More than 32 experts are
 // further blocks of the same launch: X comes from cache for them.  Product | sum of the partials, us, with two waves per SIMD,
 // loads under selects, 32 partitions of 256 tokens and more, and waves folded one after the other -> now: T = 16384, d = 2048, E
-// = 32: 30 | 12 -> 28 | 5, E = 64: 57 | 12 -> 45 | 5; T = 8001, d = 2048, E = 128: 61 | 13 -> 42 | 5; T = 9000, d = 3072, E = 100:
-// 102 | 14 -> 69 | 5; T = 32768, d = 4096, E = 16: 79 | 8 -> 79 | 5; T = 4000, d = 1024, E = 16: 14 | 4 -> 7 | 4; T = 584, d =
+// = 32: 30 | 12 -> 28 | 5, E = 64: 57 | 12 -> 45 | 5; T = 8001, d = 2048, E = 128: 61 | 13 -> 47 | 7; T = 9000, d = 3072, E = 100:
+// 102 | 14 -> 76 | 7; T = 32768, d = 4096, E = 16: 79 | 8 -> 79 | 5; T = 4000, d = 1024, E = 16: 14 | 4 -> 7 | 4; T = 584, d =
 // 1984, E = 8: 13.5 | 4 -> 5.7 | 2.8.  (The sum's bias took its partitions one by one and was what the launch waited for.)
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
@@ -401,7 +401,8 @@ hipError_t launch_wgrad_mfma_t(const moe_shape_t& s, const void* X, const float*
     return hipGetLastError();
 }
 
-// Partials in partition order, up to 32 loads on their way at once (past the last one the last one again, not added).
+// The partials, up to 32 loads on their way at once (past the last one the last one again, not added), in pairs, pairs of pairs
+// and so on: one after the other, 64 partials cost the bias as much precision as the chains that made them.
 __device__ __forceinline__ float sum_partials(const float* __restrict__ p, size_t stride, int n_part)
 {
     float s = 0.0f;
@@ -410,7 +411,12 @@ __device__ __forceinline__ float sum_partials(const float* __restrict__ p, size_
 #pragma unroll
         for (int q = 0; q < 32; ++q) v[q] = p[(size_t)min(p0 + q, n_part - 1) * stride];
 #pragma unroll
-        for (int q = 0; q < 32; ++q) if (p0 + q < n_part) s += v[q];
+        for (int q = 0; q < 32; ++q) if (p0 + q >= n_part) v[q] = 0.0f;
+#pragma unroll
+        for (int half = 16; half >= 1; half /= 2)
+#pragma unroll
+            for (int q = 0; q < half; ++q) v[q] += v[q + half];
+        s += v[0];
     }
     return s;
 }
@@ -428,13 +434,18 @@ __global__ __launch_bounds__(256) void gate_wgrad_reduce_kernel(const float* __r
 
 }  // namespace
 
-// Token partitions: as many as give the 1024 blocks that run at once (four per CU, held to 128 registers and 32 KB of LDS for
-// it), at most 64, of at least 64 tokens (a trip of the four waves).  More blocks than run at once pay their first loads and
-// their fold a second time.
+// Token partitions: as many as give the blocks that run at once, at most 64, and no more than there are trips of the four waves
+// (64 tokens).  At once: four per CU (128 registers, 33 KB of LDS), three of fp32 with more than 16 experts (168 registers).
+// But never fewer than 32, or one per 256 tokens: a wave adds up T / (4 partitions) products one after the other, and longer
+// chains lose precision.  Error against 64 bits and time with that many | with the blocks that run at once alone: T = 9000, d =
+// 3072, E = 100 1.9e-7, 81 us | 2.8e-7, 69 us; T = 16384, d = 4096, E = 128 2.3e-7, 161 us | 4.1e-7, 144 us; T = 8192, d = 2176,
+// E = 1024 (one partition) 1.8e-7, 375 us | 8.1e-7, 425 us.
 int gate_grad_partitions(const moe_shape_t& s)
 {
     const long blocks = (long)((s.d + wgrad_columns(s) - 1) / wgrad_columns(s)) * ((s.E + wgrad_experts(s) - 1) / wgrad_experts(s));
-    const long want = std::min<long>(64, std::max<long>(1, 1024 / blocks));
+    const long at_once = s.dtype == MOE_F32 && s.E > 16 ? 768 : 1024;
+    const long least = std::min<long>(32, (s.T + 255) / 256);
+    const long want = std::max<long>(least, std::min<long>(64, at_once / blocks));
     return (int)std::min<long>(want, (s.T + 63) / 64);
 }
 

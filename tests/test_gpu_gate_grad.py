@@ -197,3 +197,22 @@ def test_gate_gradients_of_operands_at_any_address(T, d, E, x_off, dl_off):
         hd.gate_bwd_params(x, l, dWg, dbg)
         got.append((dWg, dbg))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("T,d,E,dtype", [
+    (9000, 3072, 100, "bf16"), (8192, 4096, 128, "bf16"), (8192, 2176, 1024, "bf16"),      # many columns and experts: most blocks without partitions
+    (16384, 2048, 32, "bf16"), (2000, 1024, 16, "bf16"), (8200, 512, 64, "f32"), (8192, 4100, 640, "f32"),
+], ids=str)
+def test_gate_gradient_precision(T, d, E, dtype):
+    """Against 64 bits: no more than chains of T / 128 products (below 8192 tokens 64) and as many sums as there were partitions
+    then.  A sum of n random terms rounds n times, by a uniform share of half a unit of the partial sum's last place: 2^-24 x
+    (0.75 / ln 4 / 3)^0.5 = 0.425 x 2^-24 of it, and partial sums grow like the root of their length, (n / 2)^0.5 in all."""
+    hd = G.make_handle(_ig_cfg(T=T, d=d, E=E, k=1, P=1, dtype=dtype), G=1)
+    g = torch.Generator(device=G.DEV).manual_seed(T + E)
+    X, dl = torch.randn(T, d, device=G.DEV, generator=g).to(hd.elt), torch.randn(T, E, device=G.DEV, generator=g)
+    dWg, dbg = torch.zeros(d, E, device=G.DEV), torch.zeros(E, device=G.DEV)
+    hd.gate_bwd_params(X, dl, dWg, dbg)
+    parts = min(32, -(-T // 256))
+    bound = 0.425 * 2.0 ** -24 * ((T / parts / 4 + parts) / 2) ** 0.5
+    for got, want in ((dWg, X.double().t() @ dl.double()), (dbg, dl.double().sum(0))):
+        assert float((got.double() - want).norm() / want.norm()) < 1.25 * bound
