@@ -97,7 +97,7 @@ int moe_create(moe_handle_t* out, const moe_shape_t* shape)
     c->off_dz = off;          off += ah;
     c->off_du = off;          off += (shape->act == MOE_ACT_SWIGLU) ? ah : 0;
     c->off_gate_part = off;   off += align256((size_t)gate_grad_partitions(*shape) * ((size_t)shape->d * shape->E + shape->E) * sizeof(float));
-    c->off_split = off;       off += (shape->dtype == MOE_BF16) ? align256((size_t)SPLIT_ALLOC * 256 * 256 * sizeof(float)) : 0;
+    c->off_split = off;       off += (shape->dtype == MOE_BF16) ? align256((size_t)ffn_split_units(*shape) * 256 * 256 * sizeof(float)) : 0;
     c->off_arrived = off;     off += (shape->dtype == MOE_BF16) ? align256((size_t)SPLIT_COUNTERS * sizeof(int32_t)) : 0;
     c->ws_bytes = off;
     *out = c;

@@ -1263,7 +1263,7 @@ template <class GEO> constexpr int TN_OVER = GEO::BLOCKS == 1 ? 24 : 16;
 template <class GEO> constexpr int TN_SPLIT_SLICES = GEO::BLOCKS == 1 ? 48 : 32;
 template <class GEO> constexpr int SPLIT_MAX = GEO::BLOCKS == 1 ? LARGE_COST.split_max : SMALL_COST.split_max;
 template <class GEO> constexpr int SPLIT_CAP = (int)((size_t)SPLIT_UNITS * Large::UNIT_BYTES / GEO::UNIT_BYTES);
-template <class GEO> constexpr int UNEVEN_CAP = (int)((size_t)SPLIT_ALLOC * Large::UNIT_BYTES / GEO::UNIT_BYTES);
+template <class GEO> constexpr int UNEVEN_CAP = (int)((size_t)UNEVEN_UNITS * Large::UNIT_BYTES / GEO::UNIT_BYTES);
 // Large: a part of a split tile has to be worth its 256-KB round trip, 64 slices where the split only shortens the last of
 // several rounds, 24 where it is what fills the chip (d = 768, h = 3072, 33 tiles of 96 slices: 69 us whole, 45 in four parts).
 inline int large_split_slices(double tiles) { return tiles <= 2.0 * LARGE_COST.tiles_at_once ? 24 : 64; }
@@ -1349,6 +1349,9 @@ hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, bool finis
     return hipGetLastError();
 }
 
+// Two remainders a block at least.
+inline bool long_enough_for_uneven(int slices) { return slices >= 3 * UNEVEN_SLICES + 2 * UNEVEN_OVER; }
+
 // The geometry of a contraction and whether it may be cut (then a finishing launch follows).
 // uneven: the tiles of a last round may be cut unevenly.
 struct Tiling { bool small, cut; int split_slices; bool uneven; };
@@ -1358,7 +1361,7 @@ Tiling row_tiling(const moe_shape_t& s, int N, int slices, int n_seg, int epi)
     t.small = small_wins_rows(s, N, slices, n_seg, epi);
     t.split_slices = t.small ? SMALL_SPLIT_SLICES : large_split_slices(tiles_of(s, Large::BM, N, epi == EPI_FWD1_SWIGLU ? Large::BN / 2 : Large::BN));
     t.cut = slices >= 2 * t.split_slices;                  // else too short
-    t.uneven = last_finishes(epi) && slices >= 3 * UNEVEN_SLICES + 2 * UNEVEN_OVER;      // two remainders a block at least
+    t.uneven = last_finishes(epi) && long_enough_for_uneven(slices);
     return t;
 }
 Tiling wgrad_tiling(const moe_shape_t& s, int Mout, int N)
@@ -1392,7 +1395,11 @@ GemmParams base_params(const moe_shape_t& s, const ffn_args& a)
 
 }  // namespace
 
-
+// The longest contractions that may be cut unevenly are those over h, of dZ and dU together where there are two.
+int ffn_split_units(const moe_shape_t& s)
+{
+    return long_enough_for_uneven((s.act == MOE_ACT_SWIGLU ? 2 : 1) * (s.h / BK)) ? UNEVEN_UNITS : SPLIT_UNITS;
+}
 
 hipError_t launch_ffn_fwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStream_t st)
 {

@@ -18,7 +18,7 @@ struct moe_ctx {
     size_t off_dz;         // elt [A,h]  dZ
     size_t off_du;         // elt [A,h]  dU (SwiGLU)
     size_t off_gate_part;  // float [partitions][d*E + E] partial sums of the gate parameter gradients
-    size_t off_split;      // float [SPLIT_ALLOC][256*256] partial tiles of the grouped GEMM's last, K-split round (bf16 path)
+    size_t off_split;      // float [ffn_split_units][256*256] partial tiles of the grouped GEMM's last, K-split round (bf16 path)
     size_t off_arrived;    // int32 [SPLIT_COUNTERS] which of those of an uneven cut are there
     size_t ws_bytes;
     int n_chunks;          // ceil(A / ROUTE_CHUNK)
@@ -85,7 +85,7 @@ hipError_t launch_plan(const moe_planner_t& cfg, const int32_t* gating, const mo
 hipError_t launch_dispatch_bwd(const moe_shape_t& s, const void* dXp, const int32_t* pos, void* dX, hipStream_t st);
 
 constexpr int SPLIT_UNITS = 320;       // partial tiles the K-split of a last round may need: at most one per block
-constexpr int SPLIT_ALLOC = 512;       // and an uneven cut: two for each of fewer tiles than there are blocks
+constexpr int UNEVEN_UNITS = 512;      // and an uneven cut: two for each of fewer tiles than there are blocks
 constexpr int SPLIT_COUNTERS = 1024;   // a counter for each of them, in the smaller tiles
 struct ffn_args {
     const void *Xp, *W1, *W2, *W3;
@@ -96,9 +96,10 @@ struct ffn_args {
     float *dW1, *dW2, *dW3;
     bool accumulate = false;           // weight gradients are added to what dW holds instead of overwriting it
     bool act_saved = false;            // backward: Act still holds the forward pass's activation (not recomputed)
-    float* split_ws = nullptr;         // workspace for K-split partial tiles (SPLIT_ALLOC tiles of 256 x 256 floats)
+    float* split_ws = nullptr;         // workspace for K-split partial tiles (ffn_split_units tiles of 256 x 256 floats)
     int32_t* arrived = nullptr;        // workspace, SPLIT_COUNTERS: cleared by the first launch of a pass, zero after every launch
 };
+int ffn_split_units(const moe_shape_t& s);     // partial tiles the bf16 FFN of these sizes may keep
 hipError_t launch_ffn_fwd_f32(const moe_shape_t& s, const ffn_args& a, hipStream_t st);
 hipError_t launch_ffn_bwd_f32(const moe_shape_t& s, const ffn_args& a, hipStream_t st);
 hipError_t launch_ffn_fwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStream_t st);

@@ -116,3 +116,22 @@ def test_uneven_cuts_fit():
             assert t["first"] % 2 == 0 and rest % 2 == 0 and rest >= 28 and t["first"] >= rest
             seen.add((t["side"], -(-rem // (t["blocks"] - rem))))
     assert {(256, 2), (256, 3), (128, 2), (128, 3)} <= seen
+
+
+@pytest.mark.parametrize("act,longest", [("gelu", 3584), ("swiglu", 1792)])
+def test_workspace_for_uneven_cuts_only_where_they_are_made(act, longest):
+    """320 partial tiles of 256 x 256 floats, 512 from the shortest contraction over h that may be cut unevenly."""
+    def rest(h):                                               # beside the T x h intermediates
+        return _handle([128], 0, 64, h, act).workspace_bytes - (3 if act == "swiglu" else 2) * 128 * h * 2
+    tile = 256 * 256 * 4
+    assert 320 * tile < rest(64) < 321 * tile
+    assert rest(longest - 64) == rest(64) and rest(longest) == rest(64) + 192 * tile == rest(2 * longest)
+    rng, seen = random.Random(6), 0
+    for _ in range(600):                                       # every cut that is made finds its place
+        rows, h = [int(10 ** rng.uniform(2, 4)) for _ in range(rng.choice([1, 3, 8]))], 64 * rng.randint(20, 80)
+        hd = _handle(rows, 0, 64 * rng.randint(1, 40), h, act)
+        for t in G.ffn_tiling(hd, rows, 256).values():
+            if t.get("first"):
+                assert 2 * (t["row_tiles"] * t["col_tiles"] - t["n_full"]) * t["side"] ** 2 * 4 <= 512 * tile and h >= longest
+                seen += 1
+    assert seen
