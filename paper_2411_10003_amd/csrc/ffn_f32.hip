@@ -109,14 +109,40 @@ template <int ROWS, int BK, bool KC, int V_> struct Slice {
         place(i, w, lane, major, minor);
         return KC && minor >= n;
     }
-    // V_ = 0: the slice copied by the threads, with 64-bit addresses (n_rows rows or columns, n_k steps exist)
-    static __device__ __forceinline__ void copy(unsigned char* buf, const float* p, long ld, int n_rows, int n_k, int w, int lane)
+    // V_ = 0: requests of a wave for a slice whose rows are too far apart for an offset, from element (row 0, step 0) on (n_rows
+    // rows or columns, n_k steps exist).  A row of the buffer is 64 or 32 floats, so a request is one row with a resource of its
+    // own, or two, 4 apart, half a wave each: from one resource where an offset reaches 4 rows, else asked for one after the other.
+    // (Few scalar instructions per request: a wave of a long contraction has nothing else to hide them behind.)
+    static __device__ __forceinline__ void request_far(uint32_t dst, const float* p, long ld, int n_rows, int n_k, int w, int lane)
     {
+        static_assert(ROW == 64 || !KC, "a row of 32 floats lies as in memory");
+        constexpr int HALVES = 64 / ROW;
+        const int n_major = KC ? n_rows : n_k, bytes = min(KC ? n_k : n_rows, ROW) * 4;
+        const bool all = n_major >= 4 * HALVES * N;
+        if (HALVES == 1 || ld < (1l << 28) - 64) {
+            if (all) far_rows<true, HALVES, HALVES == 2>(dst, p, ld, 0, n_major, bytes, w, lane);
+            else far_rows<false, HALVES, HALVES == 2>(dst, p, ld, 0, n_major, bytes, w, lane);
+        } else {
+            if (lane < 32) far_rows<false, HALVES, false>(dst, p, ld, 0, n_major, bytes, w, lane);
+            else far_rows<false, HALVES, false>(dst, p, ld, 4, n_major, bytes, w, lane);
+        }
+    }
+    // place(): request i brings the rows (steps) 4 HALVES i + w + from and, for two, the one 4 further
+    template <bool ALL, int HALVES, bool TWO>
+    static __device__ __forceinline__ void far_rows(uint32_t dst, const float* p, long ld, int from, int n_major, int bytes, int w, int lane)
+    {
+        const uint32_t two = TWO ? (uint32_t)(16 * ld) : 0;
+        rsrc_t row = make_rsrc(p + (w + from) * ld, (long)two + bytes);
+#pragma unroll
         for (int i = 0; i < N; ++i) {
             int major, minor;
             place(i, w, lane, major, minor);
-            const bool there = KC ? major < n_rows && minor < n_k : major < n_k && minor < n_rows;
-            reinterpret_cast<float*>(buf)[(i * 4 + w) * 64 + lane] = there ? p[major * ld + minor] : 0.0f;
+            const int r = 4 * HALVES * i + w + from;
+            if (!ALL) row[2] = r < n_major ? (int)(r + 4 < n_major ? two + bytes : bytes) : 0;
+            request_lds<1>(row, dst + i * 1024, minor * 4 + (TWO && lane >= 32 ? two : 0));
+            const unsigned long long next = ((unsigned long long)(unsigned)row[1] << 32 | (unsigned)row[0]) + 16ull * HALVES * ld;
+            row[0] = (int)(unsigned)next;
+            row[1] = (int)(unsigned)(next >> 32);
         }
     }
     // byte addresses in a buffer of row `row`, steps k0 + 4 hi (k0 a multiple of 8, the wave's first): KC one for each 8
@@ -146,8 +172,8 @@ struct Operand { const float* p; long ld; int n; };
 
 // acc = sum over K of A(m, k) B(k, n), acc2 the same with B2 (DUAL), or, without DUAL, acc over a second segment of
 // the contraction (n_seg = 2: A2, B2 over another K steps).  VA, VB: floats per request, 4 where the operand's pointer, its
-// leading dimension and, if its contraction index is contiguous, K are whole 16-byte pieces; 0 where the rows of a slice are
-// too far apart for a 32-bit offset.
+// leading dimension and, if its contraction index is contiguous, K are whole 16-byte pieces; 0 (requests of one float) where the
+// rows of a slice are too far apart for a 32-bit offset.
 // Slices go from memory straight into a ring of LDS buffers while an earlier one is multiplied (two; four of the 32 x 32
 // tile, whose few products per slice don't cover a request).  On a SIMD a vector instruction of any wave takes about 8 cycles
 // from its matrix instructions, so the loop has next to none: the addresses of requests and fragments are fixed, what
@@ -160,6 +186,7 @@ __device__ __forceinline__ void contract(f32x16& acc, f32x16& acc2, float* lds_f
     typedef Slice<TL::BM, TL::BK, AKC, VA> SA;
     typedef Slice<TL::BN, TL::BK, BKC, VB> SB;
     static_assert((VA == 0) == (VB == 0), "both operands");
+    constexpr bool FAR = VA == 0;
     constexpr int BUF = SA::BYTES + (DUAL ? 2 : 1) * SB::BYTES, BK = TL::BK;
     unsigned char* lds = reinterpret_cast<unsigned char*>(lds_f);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -189,11 +216,11 @@ __device__ __forceinline__ void contract(f32x16& acc, f32x16& acc2, float* lds_f
         const bool second = s >= per;
         const int k0 = (second ? s - per : s) * BK, left = K - k0;
         const Operand a = second ? A2 : A, b = second ? B2 : B;
-        if constexpr (VA == 0) {
-            unsigned char* to = lds + s % TL::STAGES * BUF;
-            SA::copy(to, a.p + (AKC ? (long)k0 : (long)k0 * a.ld), a.ld, a.n, left, wave, lane);
-            SB::copy(to + SA::BYTES, b.p + (BKC ? (long)k0 : (long)k0 * b.ld), b.ld, b.n, left, wave, lane);
-            if constexpr (DUAL) SB::copy(to + SA::BYTES + SB::BYTES, B2.p + (BKC ? (long)k0 : (long)k0 * B2.ld), B2.ld, B2.n, left, wave, lane);
+        if constexpr (FAR) {
+            const uint32_t to = lds0 + s % TL::STAGES * BUF + wave * 256;
+            SA::request_far(to, a.p + (AKC ? (long)k0 : (long)k0 * a.ld), a.ld, a.n, left, wave, lane);
+            SB::request_far(to + SA::BYTES, b.p + (BKC ? (long)k0 : (long)k0 * b.ld), b.ld, b.n, left, wave, lane);
+            if constexpr (DUAL) SB::request_far(to + SA::BYTES + SB::BYTES, B2.p + (BKC ? (long)k0 : (long)k0 * B2.ld), B2.ld, B2.n, left, wave, lane);
             return;
         }
         const rsrc_t ra = rsrc(AKC, TL::BM, a, k0), rb = rsrc(BKC, TL::BN, b, k0);
@@ -217,7 +244,7 @@ __device__ __forceinline__ void contract(f32x16& acc, f32x16& acc2, float* lds_f
         }
     };
     // Slice s + AHEAD is requested into the buffer of slice s - 1, which everybody has left at the barrier of slice s.
-    constexpr int AHEAD = TL::STAGES - 1, OPS = SA::N + (DUAL ? 2 : 1) * SB::N;
+    constexpr int AHEAD = TL::STAGES - 1, OPS = SA::N + (DUAL ? 2 : 1) * SB::N;      // (FAR: or more)
     static_assert((AHEAD - 1) * OPS < 64, "what the counter of requests can say");
     for (int s = 0; s < AHEAD && s < ns; ++s) request(s);
     for (int s = 0, cur = 0; s < ns; ++s) {
@@ -441,13 +468,15 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 // How operands are requested.  d is a multiple of 4 (moe_create), so rows of d floats begin at multiples of 16 bytes where
 // their tensors do; rows of h floats also need h to be a multiple of 4.  A 32-bit offset reaches the 64 rows or steps of a
-// slice.  Requests of 4 bytes instead of 16 cost little: T = 3000, d = 512, k = 2, forward and backward, h = 2048 578 us, 2047
+// slice; in wider layers (2^24 and more) every row has a resource of its own: h = 2^24, d = 4, five rows, GELU, forward 178 ms
+// with predicated loads and 64-bit addresses, 157 now, backward 178 and 176; d = 2^24, h = 8, 40 rows, SwiGLU, 246 and 256, 195
+// and 169.  Requests of 4 bytes instead of 16 cost little: T = 3000, d = 512, k = 2, forward and backward, h = 2048 578 us, 2047
 // 602 (1023 with predicated 4-byte loads into registers).
-enum Requests { ALL_16 = 0, ROWS_OF_D_16 = 1, ALL_4 = 2, COPIED = 3 };
+enum Requests { ALL_16 = 0, ROWS_OF_D_16 = 1, ALL_4 = 2, FAR_APART = 3 };
 Requests requests_of(const moe_shape_t& s, std::initializer_list<const void*> rows_of_d, std::initializer_list<const void*> rows_of_h)
 {
     constexpr int FAR = (1 << 24) - 64;
-    if (s.d > FAR || s.h > FAR) return COPIED;
+    if (s.d > FAR || s.h > FAR) return FAR_APART;
     uintptr_t bits_d = 0, bits_h = s.h % 4;
     for (const void* p : rows_of_d) bits_d |= reinterpret_cast<uintptr_t>(p);
     for (const void* p : rows_of_h) bits_h |= reinterpret_cast<uintptr_t>(p);
@@ -479,7 +508,7 @@ template <int MODE, bool DUAL>
 hipError_t launch_rows(const moe_shape_t& s, const F32Args& f, int N, Requests r, hipStream_t st)
 {
     const long tiles = tiles64((long)s.T * s.k, N);
-    if (r == COPIED)
+    if (r == FAR_APART)
         hipLaunchKernelGGL((ffn_f32_kernel<MODE, TileS, DUAL, 0, 0>), dim3(cdiv(N, TileS::BN), cdiv(s.T * s.k, TileS::BM) + s.G), dim3(F32_THREADS), 0, st, f);
     else if (tiles >= MEDIUM_TILES) launch_rows_t<MODE, TileM, DUAL>(s, f, N, r, st);
     else if (tiles >= HALF_TILES) launch_rows_t<MODE, TileH, DUAL>(s, f, N, r, st);
@@ -496,7 +525,8 @@ hipError_t launch_wgrad(const moe_shape_t& s, const F32Args& f, Requests r, hipS
     if (r == ALL_16) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 4, 4>), grid, dim3(F32_THREADS), 0, st, f, np);
     else if (r == ROWS_OF_D_16) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 4, 1>), grid, dim3(F32_THREADS), 0, st, f, np);
     else if (r == ALL_4) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 1, 1>), grid, dim3(F32_THREADS), 0, st, f, np);
-    else hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 0, 0>), grid, dim3(F32_THREADS), 0, st, f, np);
+    else if constexpr (TL::WK == 1) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 0, 0>), grid, dim3(F32_THREADS), 0, st, f, np);
+    else return hipErrorInvalidValue;                      // layers that wide have more than MEDIUM_TILES_WGRAD tiles
     return hipGetLastError();
 }
 

@@ -123,31 +123,71 @@ def test_more_tiles_than_the_threads_of_one_axis(G):
     torch.cuda.empty_cache()
 
 
-def test_rows_too_far_apart_for_an_offset(G):
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+def test_rows_too_far_apart_for_an_offset(G, act):
     """A hidden layer of 2^24: 64 rows of it are 2^32 bytes.  Against a float64 product; tolerance as for the many tiles above."""
     d, h, rows = 4, 1 << 24, [3, 0, 2]
-    hd = G.binding.Handle(T=5, d=d, h=h, E=3, k=1, P=1, self_dest=0, G=3, dtype="f32", act="gelu", renorm=0, device=G.DEV)
+    hd = G.binding.Handle(T=5, d=d, h=h, E=3, k=1, P=1, self_dest=0, G=3, dtype="f32", act=act, renorm=0, device=G.DEV)
     g = torch.Generator(device=G.DEV).manual_seed(11)
     idx = torch.repeat_interleave(torch.arange(3, dtype=torch.int32), torch.tensor(rows)).to(G.DEV)
     counts, lay = torch.zeros(3, dtype=torch.int32, device=G.DEV), hd.new_layout()
     X, dYp = torch.randn(5, d, device=G.DEV, generator=g), torch.randn(5, d, device=G.DEV, generator=g)
     Xp, Z = torch.empty(5, d, device=G.DEV), torch.zeros(5, h, device=G.DEV)
+    U = torch.zeros_like(Z) if act == "swiglu" else None
     hd.expert_counts(idx, counts)
     hd.dispatch(torch.zeros(3, dtype=torch.int32, device=G.DEV), X, idx, counts, lay, Xp)
     W1 = torch.randn(3, d, h, device=G.DEV, generator=g) * d ** -0.5
     W2 = torch.randn(3, h, d, device=G.DEV, generator=g) * h ** -0.5
+    W3 = torch.randn(3, d, h, device=G.DEV, generator=g) * d ** -0.5 if act == "swiglu" else None
     Yp, dXp, dW1, dW2 = torch.zeros(5, d, device=G.DEV), torch.zeros(5, d, device=G.DEV), torch.full_like(W1, 7.0), torch.full_like(W2, 7.0)
-    hd.expert_ffn_fwd(Xp, lay, W1, W2, None, Yp, Z, None)
-    hd.expert_ffn_bwd(dYp, Xp, Z, None, lay, W1, W2, None, dXp, dW1, dW2, None)
+    dW3 = torch.full_like(W1, 7.0) if act == "swiglu" else None
+    hd.expert_ffn_fwd(Xp, lay, W1, W2, W3, Yp, Z, U)
+    hd.expert_ffn_bwd(dYp, Xp, Z, U, lay, W1, W2, W3, dXp, dW1, dW2, dW3)
     torch.cuda.synchronize()
-    assert not bool(dW1[1].any()) and not bool(dW2[1].any())
+    assert not bool(dW1[1].any()) and not bool(dW2[1].any()) and (dW3 is None or not bool(dW3[1].any()))
     chain = 4 * (h / 2 / 3) ** 0.5 * 2.0 ** -24
     rel = lambda a, b: float((a.double() - b).norm() / b.norm())   # noqa: E731
     for e, o in ((0, 0), (2, 3)):
         n = rows[e]
         x, dy, w1, w2 = Xp[o:o + n].double(), dYp[o:o + n].double(), W1[e].double(), W2[e].double()
-        z = x @ w1
-        cdf = 0.5 * (1 + torch.erf(z * 0.5 ** 0.5))
-        dz = (dy @ w2.t()) * (cdf + z * torch.exp(-0.5 * z * z) * (2 * np.pi) ** -0.5)
-        assert rel(Yp[o:o + n], (z * cdf) @ w2) < chain and rel(dXp[o:o + n], dz @ w1.t()) < chain
-        assert rel(dW1[e], x.t() @ dz) < 1e-5 and rel(dW2[e], (z * cdf).t() @ dy) < 1e-5
+        z, dA = x @ w1, dy @ w2.t()
+        if act == "swiglu":
+            w3 = W3[e].double()
+            u, sg = x @ w3, torch.sigmoid(z)
+            a, dz, du = z * sg * u, dA * u * (sg * (1 + z * (1 - sg))), dA * z * sg
+            dx = dz @ w1.t() + du @ w3.t()
+            assert rel(dW3[e], x.t() @ du) < 1e-5 and rel(U[o:o + n], u) < 1e-5
+        else:
+            cdf = 0.5 * (1 + torch.erf(z * 0.5 ** 0.5))
+            a, dz = z * cdf, dA * (cdf + z * torch.exp(-0.5 * z * z) * (2 * np.pi) ** -0.5)
+            dx = dz @ w1.t()
+        assert rel(Yp[o:o + n], a @ w2) < chain and rel(dXp[o:o + n], dx) < chain
+        assert rel(dW1[e], x.t() @ dz) < 1e-5 and rel(dW2[e], a.t() @ dy) < 1e-5
+
+
+def test_rows_too_far_apart_for_four_of_them(G):
+    """A hidden layer of 2^28: 4 rows of it are 2^32 bytes.  The forward pass, its matrices in one array, two slices of steps."""
+    d, h, n = 68, 1 << 28, 2
+    hd = G.binding.Handle(T=n, d=d, h=h, E=1, k=1, P=1, self_dest=0, G=1, dtype="f32", act="swiglu", renorm=0, device=G.DEV)
+    g = torch.Generator(device=G.DEV).manual_seed(12)
+    W = torch.empty(d * h + 8, device=G.DEV)
+    for i in range(0, W.numel(), 1 << 28):
+        W[i:i + (1 << 28)].normal_(std=d ** -0.5, generator=g)
+    W1, W2, W3 = W[:d * h].view(1, d, h), W[4:4 + d * h].view(1, h, d), W[8:].view(1, d, h)
+    idx, counts, lay = torch.zeros(n, dtype=torch.int32, device=G.DEV), torch.zeros(1, dtype=torch.int32, device=G.DEV), hd.new_layout()
+    Xp, Yp = torch.empty(n, d, device=G.DEV), torch.zeros(n, d, device=G.DEV)
+    Z, U = torch.zeros(n, h, device=G.DEV), torch.zeros(n, h, device=G.DEV)
+    hd.expert_counts(idx, counts)
+    hd.dispatch(torch.zeros(1, dtype=torch.int32, device=G.DEV), torch.randn(n, d, device=G.DEV, generator=g), idx, counts, lay, Xp)
+    hd.expert_ffn_fwd(Xp, lay, W1, W2, W3, Yp, Z, U)
+    torch.cuda.synchronize()
+    y, x = torch.zeros(n, d, dtype=torch.float64, device=G.DEV), Xp.double()
+    rel = lambda a, b: float((a.double() - b).norm() / b.norm())   # noqa: E731
+    for c in range(0, h, 1 << 23):
+        cols = slice(c, c + (1 << 23))
+        z, u = x @ W1[0, :, cols].double(), x @ W3[0, :, cols].double()
+        assert rel(Z[:, cols], z) < 1e-5 and rel(U[:, cols], u) < 1e-5
+        y += (z * torch.sigmoid(z) * u) @ W2[0, cols].double()
+    assert rel(Yp, y) < 4 * (h / 2 / 3) ** 0.5 * 2.0 ** -24
+    del W, W1, W2, W3, Z, U, hd
+    torch.cuda.empty_cache()
