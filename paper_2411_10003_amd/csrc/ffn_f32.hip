@@ -194,6 +194,10 @@ __device__ __forceinline__ void contract(f32x16& acc, f32x16& acc2, float* lds_f
     const int l32 = lane & 31, hi = lane >> 5;
 #pragma unroll
     for (int e = 0; e < 16; ++e) { acc[e] = 0.0f; acc2[e] = 0.0f; }
+    // Where two waves share a contraction, every second group of eight steps goes into sums of its own: chains as long as with
+    // four waves (error of a contraction of 3000 steps against 64 bits 6.9e-7 without, 4.9e-7 with them; no time).
+    constexpr bool TWICE = TL::WK == 2;
+    f32x16 odd{}, odd2{};
     const int per = (K + BK - 1) / BK, ns = n_seg * per;
     if (ns == 0) return;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)lds_f;
@@ -262,11 +266,13 @@ __device__ __forceinline__ void contract(f32x16& acc, f32x16& acc2, float* lds_f
             if constexpr (DUAL) SB::frag(b2, buf + SB::BYTES, fb, n);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], acc, 0, 0, 0);
-                if constexpr (DUAL) acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b2[q], acc2, 0, 0, 0);
+                f32x16 &sum = TWICE && n % 2 ? odd : acc, &sum2 = TWICE && n % 2 ? odd2 : acc2;
+                sum = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], sum, 0, 0, 0);
+                if constexpr (DUAL) sum2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b2[q], sum2, 0, 0, 0);
             }
         }
     }
+    if (TWICE) { acc += odd; acc2 += odd2; }
     __syncthreads();                                       // the buffers are free
 }
 

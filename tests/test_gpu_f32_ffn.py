@@ -123,6 +123,32 @@ def test_more_tiles_than_the_threads_of_one_axis(G):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("T,h,parts", [(60, 128, 4), (1100, 320, 4), (3000, 512, 4), (2500, 1092, 1)])
+@pytest.mark.parametrize("act", ["gelu", "swiglu"])
+def test_precision_of_a_contraction(G, T, h, parts, act):
+    """Against 64 bits, in the tiles that T k rows and h columns take: chains of d / parts products (32 x 32 tiles: a wave each for a
+    quarter of them; 64 x 32: two waves with two sums each).  Each rounds by 0.425 x 2^-24 of a partial sum that grows like the
+    root of the chain (test_gpu_gate_grad.py): (n / 2)^0.5 of that, and the parts' sums."""
+    cfg = _cfg(T=T, d=3000, h=h, act=act, n_replicas=0, P=1)
+    d, A, E = cfg.d, cfg.A, cfg.E
+    hd = G.make_handle(cfg, G=E)
+    g = torch.Generator(device=G.DEV).manual_seed(T + h)
+    idx = torch.arange(A, device=G.DEV, dtype=torch.int32) % E
+    counts, lay = torch.zeros(E, dtype=torch.int32, device=G.DEV), hd.new_layout()
+    X, Xp = torch.randn(T, d, device=G.DEV, generator=g), torch.empty(A, d, device=G.DEV)
+    hd.expert_counts(idx, counts)
+    hd.dispatch(torch.zeros(E, dtype=torch.int32, device=G.DEV), X, idx, counts, lay, Xp)
+    W1, W2 = torch.randn(E, d, h, device=G.DEV, generator=g), torch.randn(E, h, d, device=G.DEV, generator=g)
+    W3 = torch.randn(E, d, h, device=G.DEV, generator=g) if act == "swiglu" else None
+    Yp, Z = torch.zeros(A, d, device=G.DEV), torch.zeros(A, h, device=G.DEV)
+    U = torch.zeros_like(Z) if act == "swiglu" else None
+    hd.expert_ffn_fwd(Xp, lay, W1, W2, W3, Yp, Z, U)
+    bound = 0.425 * 2.0 ** -24 * ((d / parts + parts) / 2) ** 0.5
+    for got, W in ((Z, W1), (U, W3)) if act == "swiglu" else ((Z, W1),):
+        want = torch.cat([x.double() @ w.double() for x, w in zip(Xp.split(counts.tolist()), W)])
+        assert float((got.double() - want).norm() / want.norm()) < 1.15 * bound
+
+
 @pytest.mark.parametrize("act", ["gelu", "swiglu"])
 def test_rows_too_far_apart_for_an_offset(G, act):
     """A hidden layer of 2^24: 64 rows of it are 2^32 bytes.  Against a float64 product; tolerance as for the many tiles above."""
