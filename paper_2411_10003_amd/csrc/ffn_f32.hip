@@ -10,7 +10,7 @@
 // wave that holds step 8 s + j of an instruction's pair holds 8 s + 4 + j in the other half, so that both layouts feed
 // the same order.
 // Tiles: 64 x 64 per block of four waves, 64 x 32 or 32 x 32 with two or four waves sharing the contraction where those are
-// too few to fill the chip (see MEDIUM_TILES).
+// too few to fill the chip (see HALF_TILES).
 // Measured at T = 3000, d = 512, h = 2048, k = 2, GELU, 4900 hosted rows, forward and backward: 4255 us with one output
 // per thread on the vector ALUs, 703 us staged through registers, 578 us now (107 TFLOP/s); the weight gradients of it 249,
 // 212 with the requests straight into LDS, 193 with the longest groups first.
@@ -40,16 +40,17 @@ struct F32Args {
 constexpr int F32_THREADS = 256;
 
 // The four waves of a block cover WM x WN x WK (rows, columns, contraction) with 32 x 32 outputs each.
-template <int WM_, int WN_, int WK_, int BK_> struct Tile {
+template <int WM_, int WN_, int WK_, int BK_, int STAGES_ = 2> struct Tile {
     static constexpr int WM = WM_, WN = WN_, WK = WK_, BK = BK_;
     static constexpr int BM = 32 * WM, BN = 32 * WN;
     static constexpr int KW = BK / WK;                     // contraction steps of a slice one wave multiplies
-    static constexpr int STAGES = WK == 4 ? 4 : 2;         // LDS buffers of a block
+    static constexpr int STAGES = STAGES_;                 // LDS buffers of a block
     static_assert(WM * WN * WK == 4 && KW % 8 == 0, "four waves, whole groups of eight steps");
 };
 typedef Tile<2, 2, 1, 32> TileM;
 typedef Tile<2, 1, 2, 64> TileH;                          // half a TileM: slices of 32 steps took 10 us more of its 110
 typedef Tile<1, 1, 4, 64> TileS;
+typedef Tile<1, 1, 4, 64, 4> TileF;                       // few of them
 
 typedef __attribute__((ext_vector_type(4))) int rsrc_t;     // raw buffer resource (4 scalar registers)
 constexpr uint32_t NOWHERE = 0xfffffffcu;                   // an offset past the end of every resource
@@ -175,7 +176,7 @@ struct Operand { const float* p; long ld; int n; };
 // leading dimension and, if its contraction index is contiguous, K are whole 16-byte pieces; 0 (requests of one float) where the
 // rows of a slice are too far apart for a 32-bit offset.
 // Slices go from memory straight into a ring of LDS buffers while an earlier one is multiplied (two; four of the 32 x 32
-// tile, whose few products per slice don't cover a request).  On a SIMD a vector instruction of any wave takes about 8 cycles
+// tile where there are few of them, whose products don't cover a request).  On a SIMD a vector instruction of any wave takes about 8 cycles
 // from its matrix instructions, so the loop has next to none: the addresses of requests and fragments are fixed, what
 // moves is the resource's base, and what does not exist lies past the resource's end and arrives as zeros.  With the slices
 // staged through registers (predicated loads, LDS stores, 64 vector instructions per 16 products) the five launches of T =
@@ -490,15 +491,21 @@ Requests requests_of(const moe_shape_t& s, std::initializer_list<const void*> ro
 }
 
 // Which tile, by the number of 64 x 64 tiles of all T k rows (a part of them is hosted here).  Few: 32 x 32, the serial chain
-// is what counts.  A few per CU: 64 x 32 with two waves along the contraction, because a CU that gets three tiles where
-// others get two is what the launch waits for.  More: 64 x 64, which requests and reads least per product.  Measured, us, one
-// row contraction, 32 x 32 | 64 x 32 | 64 x 64 (T, k = 2, contraction, width; tiles): 600, 1024, 512 (152) 22.0 | 24.0 | 28.2;
-// 4000, 3000, 128 (250) 75 | 67 | 86;  600, 512, 1024 (304) 23.4 | 20.8 | 25.4;  4000, 1024, 256 (500) 46 | 36 | 45;  3000, 2048,
-// 512 (752) 130 | 111 | 121;  1500, 3000, 1000 (752) 193 | 166 | 176;  4000, 200, 640 (1250) 35 | 33 | 30;  1500, 512, 2048
-// (1504) 76 | 74 | 68;  4000, 3000, 1000 (2000) 439 | 382 | 384;  3000, 512, 2048 (3008) 148 | 135 | 115.  128 x 128 was the slower
-// one everywhere (fewer blocks to hide a request behind, a longer last round).  The weight gradients, whose tiles are all of
-// one launch, take 64 x 64 from 700 tiles on.
-constexpr long HALF_TILES = 200, MEDIUM_TILES = 1100, MEDIUM_TILES_WGRAD = 700;
+// is what counts, and many small tiles are spread evenly.  More: 64 x 32 with two waves along the contraction, because a CU that
+// gets three 64 x 64 tiles where others get two is what the launch waits for.  Yet more: 64 x 64, which requests and reads least
+// per product.  The line between the first two lies where three 64 x 32 tiles per CU, as many as run at once, are surely
+// exceeded: between 400 and 700 either may win, by how many rows are hosted.  Measured, us, one row contraction, 32 x 32 | 64 x 32 |
+// 64 x 64 (T, k = 2, contraction, width; tiles): 600, 1024, 512 (152) 19.7 | 23.5 | 26.0;  1200, 512, 512 (304) 17.2 | 20.7 | 24.8,
+// backward 18.7 | 24.6 | 31;  4000, 1024, 256 (500) 38.7 | 35.9 | 42.8;  1000, 256, 1024 (512) 19.6 | 22.4 | 19.2, backward 21.6 |
+// 27.9 | 25.3;  900, 384, 1500 (696) 32.6 | 29.9 | 29.1;  3000, 2048, 512 (752) 112 | 107 | 117;  1500, 3000, 1000 (752) 159 | 151 |
+// 167;  4000, 200, 640 (1250) 32.6 | 32.5 | 27.8;  1500, 512, 2048 (1504) 71 | 71 | 67;  4000, 3000, 1000 (2000) 389 | 372 | 365;
+// 3000, 512, 2048 (3008) 134 | 129 | 113.  128 x 128 was the slower one everywhere (fewer blocks to hide a request behind, a longer
+// last round).  The weight gradients, whose tiles are all of one launch, take 64 x 64 from 700 tiles on.
+// 32 x 32 tiles that all find room at once with four buffers (two blocks per CU, one of two weight matrices; the weight
+// gradients: one per CU) have four, which hide a request that two don't: T = 512, d = 64, h = 256 fwd2 5.4 | 5.0; 144 tiles of K =
+// 1500 15.8 | 14.1.  Others have two, and four or five blocks per CU: 640 tiles of K = 512 14.2 | 17.1, backward 15.7 | 19.9, SwiGLU
+// 20.5 | 27.3; weight gradients of d = 300, h = 900, four groups of 100 rows 14.4 | 18.3.
+constexpr long HALF_TILES = 700, MEDIUM_TILES = 1100, MEDIUM_TILES_WGRAD = 700, CUS = 256;
 long tiles64(long rows, long cols) { return ((rows + 63) / 64) * ((cols + 63) / 64); }
 
 template <int MODE, class TL, bool DUAL>
@@ -515,9 +522,10 @@ hipError_t launch_rows(const moe_shape_t& s, const F32Args& f, int N, Requests r
 {
     const long tiles = tiles64((long)s.T * s.k, N);
     if (r == FAR_APART)
-        hipLaunchKernelGGL((ffn_f32_kernel<MODE, TileS, DUAL, 0, 0>), dim3(cdiv(N, TileS::BN), cdiv(s.T * s.k, TileS::BM) + s.G), dim3(F32_THREADS), 0, st, f);
+        hipLaunchKernelGGL((ffn_f32_kernel<MODE, TileF, DUAL, 0, 0>), dim3(cdiv(N, TileF::BN), cdiv(s.T * s.k, TileF::BM) + s.G), dim3(F32_THREADS), 0, st, f);
     else if (tiles >= MEDIUM_TILES) launch_rows_t<MODE, TileM, DUAL>(s, f, N, r, st);
     else if (tiles >= HALF_TILES) launch_rows_t<MODE, TileH, DUAL>(s, f, N, r, st);
+    else if ((cdiv(s.T * s.k, TileF::BM) + s.G) * (long)cdiv(N, TileF::BN) <= (DUAL ? 1 : 2) * CUS) launch_rows_t<MODE, TileF, DUAL>(s, f, N, r, st);
     else launch_rows_t<MODE, TileS, DUAL>(s, f, N, r, st);
     return hipGetLastError();
 }
@@ -555,5 +563,7 @@ hipError_t launch_ffn_bwd_f32(const moe_shape_t& s, const ffn_args& a, hipStream
     if (e == hipSuccess) e = launch_rows<BWD2, false>(s, f, s.d, r, st);
     if (e != hipSuccess) return e;
     const int np = s.act == MOE_ACT_SWIGLU ? 3 : 2;
-    return tiles64((long)s.d * np, (long)s.h * s.G) >= MEDIUM_TILES_WGRAD ? launch_wgrad<TileM>(s, f, r, st) : launch_wgrad<TileS>(s, f, r, st);
+    if (tiles64((long)s.d * np, (long)s.h * s.G) >= MEDIUM_TILES_WGRAD) return launch_wgrad<TileM>(s, f, r, st);
+    if (cdiv(s.d, TileF::BM) * cdiv(s.h, TileF::BN) * np * s.G <= CUS) return launch_wgrad<TileF>(s, f, r, st);
+    return launch_wgrad<TileS>(s, f, r, st);
 }
