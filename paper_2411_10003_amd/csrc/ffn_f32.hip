@@ -10,7 +10,7 @@
 // wave that holds step 8 s + j of an instruction's pair holds 8 s + 4 + j in the other half, so that both layouts feed
 // the same order.
 // Tiles: 64 x 64 per block of four waves, 64 x 32 or 32 x 32 with two or four waves sharing the contraction where those are
-// too few to fill the chip (see HALF_TILES).
+// too few to fill the chip (see MEDIUM_TILES).
 // Measured at T = 3000, d = 512, h = 2048, k = 2, GELU, 4900 hosted rows, forward and backward: 4255 us with one output
 // per thread on the vector ALUs, 703 us staged through registers, 578 us now (107 TFLOP/s); the weight gradients of it 249,
 // 212 with the requests straight into LDS, 193 with the longest groups first.
@@ -491,21 +491,22 @@ Requests requests_of(const moe_shape_t& s, std::initializer_list<const void*> ro
 }
 
 // Which tile, by the number of 64 x 64 tiles of all T k rows (a part of them is hosted here).  Few: 32 x 32, the serial chain
-// is what counts, and many small tiles are spread evenly.  More: 64 x 32 with two waves along the contraction, because a CU that
-// gets three 64 x 64 tiles where others get two is what the launch waits for.  Yet more: 64 x 64, which requests and reads least
-// per product.  The line between the first two lies where three 64 x 32 tiles per CU, as many as run at once, are surely
-// exceeded: between 400 and 700 either may win, by how many rows are hosted.  Measured, us, one row contraction, 32 x 32 | 64 x 32 |
-// 64 x 64 (T, k = 2, contraction, width; tiles): 600, 1024, 512 (152) 19.7 | 23.5 | 26.0;  1200, 512, 512 (304) 17.2 | 20.7 | 24.8,
-// backward 18.7 | 24.6 | 31;  4000, 1024, 256 (500) 38.7 | 35.9 | 42.8;  1000, 256, 1024 (512) 19.6 | 22.4 | 19.2, backward 21.6 |
-// 27.9 | 25.3;  900, 384, 1500 (696) 32.6 | 29.9 | 29.1;  3000, 2048, 512 (752) 112 | 107 | 117;  1500, 3000, 1000 (752) 159 | 151 |
-// 167;  4000, 200, 640 (1250) 32.6 | 32.5 | 27.8;  1500, 512, 2048 (1504) 71 | 71 | 67;  4000, 3000, 1000 (2000) 389 | 372 | 365;
-// 3000, 512, 2048 (3008) 134 | 129 | 113.  128 x 128 was the slower one everywhere (fewer blocks to hide a request behind, a longer
-// last round).  The weight gradients, whose tiles are all of one launch, take 64 x 64 from 700 tiles on.
+// is what counts, and many small tiles are spread evenly.  More: 64 x 64, which requests and reads least per product.  Between
+// them, for long contractions, 64 x 32 with two waves along the contraction, because a CU that gets three 64 x 64 tiles where
+// others get two is what the launch waits for (of short ones it is the fourth 64 x 32 tile, which has to wait for room).
+// Measured, us, one row contraction, 32 x 32 | 64 x 32 | 64 x 64 (T, k = 2, contraction, width; tiles): 600, 1024, 512 (152) 19.7 |
+// 23.5 | 26.0;  1200, 512, 512 (304) 17.2 | 20.7 | 24.8, backward 18.7 | 24.6 | 31;  1500, 2048, 512 (376) 61 | 62 | 80;  4000, 1024, 256
+// (500) 38.7 | 35.9 | 42.8;  1000, 256, 1024 (512) 19.6 | 22.4 | 19.2, backward 21.6 | 27.9 | 25.3;  3000, 2048, 512 (752) 112 | 107 |
+// 117;  1500, 3000, 1000 (752) 159 | 151 | 167;  2500, 292, 612 (790) - | 32.7 | 28.0;  3000, 1020, 640 (940), SwiGLU - | 144 | 150;  700,
+// 128, 2800 (968) - | 23.7 | 20.0, backward - | 33.1 | 27.2;  1000, 700, 2000 (1024) - | 67 | 61;  4000, 200, 640 (1250) 32.6 | 32.5 | 27.8;
+// 1500, 512, 2048 (1504) 71 | 71 | 67;  4000, 3000, 1000 (2000) 389 | 372 | 365;  3000, 512, 2048 (3008) 134 | 129 | 113.  128 x 128 was the
+// slower one everywhere (fewer blocks to hide a request behind, a longer last round).  The weight gradients, whose tiles are
+// all of one launch, take 64 x 64 from 700 tiles on.
 // 32 x 32 tiles that all find room at once with four buffers (two blocks per CU, one of two weight matrices; the weight
 // gradients: one per CU) have four, which hide a request that two don't: T = 512, d = 64, h = 256 fwd2 5.4 | 5.0; 144 tiles of K =
 // 1500 15.8 | 14.1.  Others have two, and four or five blocks per CU: 640 tiles of K = 512 14.2 | 17.1, backward 15.7 | 19.9, SwiGLU
 // 20.5 | 27.3; weight gradients of d = 300, h = 900, four groups of 100 rows 14.4 | 18.3.
-constexpr long HALF_TILES = 700, MEDIUM_TILES = 1100, MEDIUM_TILES_WGRAD = 700, CUS = 256;
+constexpr long MEDIUM_TILES = 700, LONG = 1000, HALF_TILES_LONG = 400, MEDIUM_TILES_LONG = 1100, CUS = 256;
 long tiles64(long rows, long cols) { return ((rows + 63) / 64) * ((cols + 63) / 64); }
 
 template <int MODE, class TL, bool DUAL>
@@ -518,13 +519,13 @@ void launch_rows_t(const moe_shape_t& s, const F32Args& f, int N, Requests r, hi
 }
 
 template <int MODE, bool DUAL>
-hipError_t launch_rows(const moe_shape_t& s, const F32Args& f, int N, Requests r, hipStream_t st)
+hipError_t launch_rows(const moe_shape_t& s, const F32Args& f, int N, long K, Requests r, hipStream_t st)
 {
     const long tiles = tiles64((long)s.T * s.k, N);
     if (r == FAR_APART)
         hipLaunchKernelGGL((ffn_f32_kernel<MODE, TileF, DUAL, 0, 0>), dim3(cdiv(N, TileF::BN), cdiv(s.T * s.k, TileF::BM) + s.G), dim3(F32_THREADS), 0, st, f);
-    else if (tiles >= MEDIUM_TILES) launch_rows_t<MODE, TileM, DUAL>(s, f, N, r, st);
-    else if (tiles >= HALF_TILES) launch_rows_t<MODE, TileH, DUAL>(s, f, N, r, st);
+    else if (tiles >= (K >= LONG ? MEDIUM_TILES_LONG : MEDIUM_TILES)) launch_rows_t<MODE, TileM, DUAL>(s, f, N, r, st);
+    else if (K >= LONG && tiles >= HALF_TILES_LONG) launch_rows_t<MODE, TileH, DUAL>(s, f, N, r, st);
     else if ((cdiv(s.T * s.k, TileF::BM) + s.G) * (long)cdiv(N, TileF::BN) <= (DUAL ? 1 : 2) * CUS) launch_rows_t<MODE, TileF, DUAL>(s, f, N, r, st);
     else launch_rows_t<MODE, TileS, DUAL>(s, f, N, r, st);
     return hipGetLastError();
@@ -540,7 +541,7 @@ hipError_t launch_wgrad(const moe_shape_t& s, const F32Args& f, Requests r, hipS
     else if (r == ROWS_OF_D_16) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 4, 1>), grid, dim3(F32_THREADS), 0, st, f, np);
     else if (r == ALL_4) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 1, 1>), grid, dim3(F32_THREADS), 0, st, f, np);
     else if constexpr (TL::WK == 1) hipLaunchKernelGGL((ffn_f32_wgrad_kernel<TL, 0, 0>), grid, dim3(F32_THREADS), 0, st, f, np);
-    else return hipErrorInvalidValue;                      // layers that wide have more than MEDIUM_TILES_WGRAD tiles
+    else return hipErrorInvalidValue;                      // layers that wide have more than MEDIUM_TILES tiles
     return hipGetLastError();
 }
 
@@ -550,8 +551,8 @@ hipError_t launch_ffn_fwd_f32(const moe_shape_t& s, const ffn_args& a, hipStream
 {
     const F32Args f = make_args(s, a);
     const Requests r = requests_of(s, {a.Xp, a.W2}, {a.W1, a.W3, a.Act});
-    hipError_t e = s.act == MOE_ACT_SWIGLU ? launch_rows<FWD1, true>(s, f, s.h, r, st) : launch_rows<FWD1, false>(s, f, s.h, r, st);
-    if (e == hipSuccess) e = launch_rows<FWD2, false>(s, f, s.d, r, st);
+    hipError_t e = s.act == MOE_ACT_SWIGLU ? launch_rows<FWD1, true>(s, f, s.h, s.d, r, st) : launch_rows<FWD1, false>(s, f, s.h, s.d, r, st);
+    if (e == hipSuccess) e = launch_rows<FWD2, false>(s, f, s.d, s.h, r, st);
     return e;
 }
 
@@ -559,11 +560,11 @@ hipError_t launch_ffn_bwd_f32(const moe_shape_t& s, const ffn_args& a, hipStream
 {
     const F32Args f = make_args(s, a);
     const Requests r = requests_of(s, {a.dYp, a.Xp, a.W2}, {a.W1, a.W3, a.Act, a.dZ, a.dU});
-    hipError_t e = launch_rows<BWD1, false>(s, f, s.h, r, st);
-    if (e == hipSuccess) e = launch_rows<BWD2, false>(s, f, s.d, r, st);
+    hipError_t e = launch_rows<BWD1, false>(s, f, s.h, s.d, r, st);
+    if (e == hipSuccess) e = launch_rows<BWD2, false>(s, f, s.d, s.act == MOE_ACT_SWIGLU ? 2l * s.h : s.h, r, st);
     if (e != hipSuccess) return e;
     const int np = s.act == MOE_ACT_SWIGLU ? 3 : 2;
-    if (tiles64((long)s.d * np, (long)s.h * s.G) >= MEDIUM_TILES_WGRAD) return launch_wgrad<TileM>(s, f, r, st);
+    if (tiles64((long)s.d * np, (long)s.h * s.G) >= MEDIUM_TILES) return launch_wgrad<TileM>(s, f, r, st);
     if (cdiv(s.d, TileF::BM) * cdiv(s.h, TileF::BN) * np * s.G <= CUS) return launch_wgrad<TileF>(s, f, r, st);
     return launch_wgrad<TileS>(s, f, r, st);
 }

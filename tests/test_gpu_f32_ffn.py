@@ -30,7 +30,8 @@ CASES = [
     _cfg(T=1100, d=292, h=612, act="swiglu"),                   # 32 x 32 tiles of two weight matrices, last slices of 36 steps
     _cfg(T=2500, d=260, h=1092, act="swiglu", alpha=2.0),       # 64 x 64 tiles of two weight matrices, last slices of 4 steps
     _cfg(T=2500, d=516, h=1090, act="swiglu", alpha=2.0),       # the same with 4-byte requests
-    _cfg(T=2500, d=292, h=612, act="swiglu", alpha=0.5),        # 64 x 32 tiles of two weight matrices where 612 wide, else 32 x 32
+    _cfg(T=2500, d=292, h=612, act="swiglu", alpha=0.5),        # 64 x 64 tiles where 612 wide, else 32 x 32
+    _cfg(T=1100, d=1004, h=804, act="swiglu"),                  # 64 x 32 tiles, also of two weight matrices, last slices of 44 and 36 steps
     _cfg(T=250, d=160, h=517),                                  # 32 x 32 tiles, a few more than run at once with four buffers
 ]
 _ids = lambda c: f"{c.act}-T{c.T}-d{c.d}-h{c.h}-E{c.E}-k{c.k}"   # noqa: E731
