@@ -401,41 +401,52 @@ hipError_t launch_wgrad_mfma_t(const moe_shape_t& s, const void* X, const float*
     return hipGetLastError();
 }
 
-// The partials, up to 32 loads on their way at once (past the last one the last one again, not added), in pairs, pairs of pairs
-// and so on: one after the other, 64 partials cost the bias as much precision as the chains that made them.
-__device__ __forceinline__ float sum_partials(const float* __restrict__ p, size_t stride, int n_part)
+// N partials (FULL) or the n < N that are left, all loads on their way at once, added to four sums: one after the other, 64 partials
+// would cost the bias as much precision as the chains that made them.  An addition per load: with the address of each computed
+// from its number they went out slowly.
+template <int N, bool FULL>
+__device__ __forceinline__ void add_partials(float (&sum)[4], const float* __restrict__ p, int i, size_t stride, int n)
 {
-    float s = 0.0f;
-    for (int p0 = 0; p0 < n_part; p0 += 32) {
-        float v[32];
+    float v[N];
 #pragma unroll
-        for (int q = 0; q < 32; ++q) v[q] = p[(size_t)min(p0 + q, n_part - 1) * stride];
+    for (int q = 0; q < N; ++q) { v[q] = p[i]; if (FULL || q + 1 < n) p += stride; }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < 32; ++q) if (p0 + q >= n_part) v[q] = 0.0f;
-#pragma unroll
-        for (int half = 16; half >= 1; half /= 2)
-#pragma unroll
-            for (int q = 0; q < half; ++q) v[q] += v[q + half];
-        s += v[0];
-    }
-    return s;
+    for (int q = 0; q < N; ++q) if (FULL || q < n) sum[q % 4] += v[q];
+}
+// As few loads as there are partials: 32 of them for one or two were most of the launch (T = 17, d = 3584, E = 256, with the product
+// 14.7 us, now 9.9; T = 130, d = 3520, three partials 19.9, two now 14.4).
+__device__ __forceinline__ float sum_partials(const float* __restrict__ p, int i, size_t stride, int n_part)
+{
+    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (; n_part >= 32; n_part -= 32, p += 32 * stride) add_partials<32, true>(sum, p, i, stride, 32);
+    if (n_part > 16) add_partials<32, false>(sum, p, i, stride, n_part);
+    else if (n_part > 4) add_partials<16, false>(sum, p, i, stride, n_part);
+    else if (n_part > 0) add_partials<4, false>(sum, p, i, stride, n_part);
+    return (sum[0] + sum[1]) + (sum[2] + sum[3]);
 }
 // The last block adds up the bias.
 __global__ __launch_bounds__(256) void gate_wgrad_reduce_kernel(const float* __restrict__ partial, const float* __restrict__ partial_b,
                                                                 float* __restrict__ dWg, float* __restrict__ dbg, int n_part, int dE, int E)
 {
     if (blockIdx.x + 1 == gridDim.x) {
-        for (int e = threadIdx.x; e < E; e += 256) dbg[e] = sum_partials(partial_b + e, E, n_part);
+        for (int e = threadIdx.x; e < E; e += 256) dbg[e] = sum_partials(partial_b, e, E, n_part);
         return;
     }
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < dE) dWg[i] = sum_partials(partial + i, dE, n_part);
+    const size_t first = (size_t)blockIdx.x * 256;
+    if (first + threadIdx.x < (size_t)dE) dWg[first + threadIdx.x] = sum_partials(partial + first, threadIdx.x, dE, n_part);
 }
 
 }  // namespace
 
-// Token partitions: as many as give the blocks that run at once, at most 64, and no more than there are trips of the four waves
-// (64 tokens).  At once: four per CU (128 registers, 33 KB of LDS), three of fp32 with more than 16 experts (168 registers).
+// Token partitions: as many as give the blocks that run at once, at most 64, of whole trips of the four waves (64 tokens; a trip
+// that is nearly empty takes as long as a full one, and every partition is a partial to write and to add: fp32, T = 4894, d = 1180,
+// E = 16, 64 partitions of two trips, the second of 13 tokens, 18.1 us, 39 partitions 13.4).  At once: four per CU (128
+// registers, 33 KB of LDS), three of fp32 with more than 16 experts (168 registers).  More than 128 experts: no more than have 8 MB
+// of partials (T = 199, d = 3648, E = 256, 14.9 MB 18.5, 7.5 MB 15.3; fewer experts have not been slower than with 256
+// tokens a partition).
+// Where the experts are several blocks, a multiple of eight if one is near, so that those which read the same tokens run on one
+// XCD and share its L2 (blocks are dealt to the XCDs in turn; fp32, T = 28001, d = 468, E = 64 63 partitions 33.3, 64 30.4).
 // But never fewer than 32, or one per 256 tokens: a wave adds up T / (4 partitions) products one after the other, and longer
 // chains lose precision.  Error against 64 bits and time with that many | with the blocks that run at once alone: T = 9000, d =
 // 3072, E = 100 1.9e-7, 81 us | 2.8e-7, 69 us; T = 16384, d = 4096, E = 128 2.3e-7, 161 us | 4.1e-7, 144 us; T = 8192, d = 2176,
@@ -444,9 +455,12 @@ int gate_grad_partitions(const moe_shape_t& s)
 {
     const long blocks = (long)((s.d + wgrad_columns(s) - 1) / wgrad_columns(s)) * ((s.E + wgrad_experts(s) - 1) / wgrad_experts(s));
     const long at_once = s.dtype == MOE_F32 && s.E > 16 ? 768 : 1024;
-    const long least = std::min<long>(32, (s.T + 255) / 256);
-    const long want = std::max<long>(least, std::min<long>(64, at_once / blocks));
-    return (int)std::min<long>(want, (s.T + 63) / 64);
+    const long trips = (s.T + 63) / 64, least = std::min<long>(32, (s.T + 255) / 256);
+    long want = std::min<long>(64, at_once / blocks);
+    if (s.E > 128) want = std::min<long>(want, (8l << 20) / ((long)s.d * s.E * 4));
+    want = std::min(trips, std::max(least, want));
+    const long each = (trips + want - 1) / want, n = std::max(least, (trips + each - 1) / each), eights = (n + 7) / 8 * 8;
+    return (int)(s.E > wgrad_experts(s) && eights * 8 <= n * 9 && eights <= trips && eights * blocks <= at_once ? eights : n);
 }
 
 template <typename ET, int NE, int KMAX>
