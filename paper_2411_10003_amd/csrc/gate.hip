@@ -635,10 +635,16 @@ static_assert(GATE_LAUNCH_TOK % GATE_TOK == 0 && GATE_LAUNCH_TOK <= (1ll << 32) 
 // delivers those of two units in the time a step takes, of four in twice that: kernels, us, blocks of 16 experts + routing | one
 // block, bf16: T = 1999, d = 768, E = 32 6.2 + 4.5 | 7.9; T = 1075, d = 2304, E = 24 12.5 + 4.1 | 13.9; T = 2040, d = 1024, E = 64
 // 9.5 + 4.2 | 12.7; T = 600, d = 4096, E = 64 18.7 + 4.1 | 29.2; fp32: T = 1931, d = 700, E = 32 5.8 + 4.8 | 8.1.
-static bool one_block(const moe_shape_t& s)
+// Where the blocks of 16 experts have a CU each (tiles of 16 tokens x 16 experts: up to 256), three units win up to 512 columns, four
+// up to 256.  The call, us: bf16 T = 241, d = 512, E = 48 8.1 | 7.8; T = 136, d = 960, E = 36 9.4 | 9.8; T = 187, d = 64, E = 64 6.9 |
+// 6.6; T = 13, d = 320, E = 64 7.4 | 7.7; T = 6, d = 960, E = 64 9.1 | 10.4; fp32 T = 94, d = 1400, E = 48 13.1 | 14.0; T = 19, d = 236, E
+// = 64 6.6 | 6.5; T = 1, d = 332, E = 52 6.9 | 7.2.  Where they share CUs: bf16 T = 1272, d = 320, E = 52 8.2 | 7.3; fp32 T = 1799, d = 192,
+// E = 52 10.3 | 8.7.
+static bool one_block(const moe_shape_t& s, long tiles)
 {
     const long row = (long)s.d * (s.dtype == MOE_BF16 ? 2 : 4);
-    return s.E <= 32 ? row <= 8192 : (s.E <= 64 && row <= 2048);
+    if (s.E <= 32) return row <= 8192;
+    return s.E <= 64 && row <= 2048 && (tiles > 256 || s.d <= (s.E <= 48 ? 512 : 256));
 }
 
 static hipError_t launch_gate_part(const moe_shape_t& s, const void* X, const float* Wg, const float* bg,
@@ -650,9 +656,9 @@ static hipError_t launch_gate_part(const moe_shape_t& s, const void* X, const fl
         if (s.E % 4 == 0 && (long long)s.d * 4 * (GATE_TOK + 1) < (1ll << 31) && (long long)s.d * s.E * 4 < (1ll << 31)) {
             if (tiles <= 512) {
                 if (s.E <= 16) return run_gate_split<float, 1, 1, 3, true>(s, X, Wg, bg, logits, idx, w, st);
-                if (one_block(s) && s.E <= 32) return run_gate_split<float, 1, 1, 3, true, 2>(s, X, Wg, bg, logits, idx, w, st);
-                if (one_block(s) && s.E <= 48) return run_gate_split<float, 1, 1, 3, true, 3>(s, X, Wg, bg, logits, idx, w, st);
-                if (one_block(s)) return run_gate_split<float, 1, 1, 2, true, 4>(s, X, Wg, bg, logits, idx, w, st);
+                if (one_block(s, tiles) && s.E <= 32) return run_gate_split<float, 1, 1, 3, true, 2>(s, X, Wg, bg, logits, idx, w, st);
+                if (one_block(s, tiles) && s.E <= 48) return run_gate_split<float, 1, 1, 3, true, 3>(s, X, Wg, bg, logits, idx, w, st);
+                if (one_block(s, tiles)) return run_gate_split<float, 1, 1, 2, true, 4>(s, X, Wg, bg, logits, idx, w, st);
                 return run_gate_split<float, 1, 1, 3, false>(s, X, Wg, bg, logits, idx, w, st);
             }
             if (s.E <= 16) return run_gate_split<float, 1, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
@@ -675,9 +681,9 @@ static hipError_t launch_gate_part(const moe_shape_t& s, const void* X, const fl
         // 68 -> 61 us; T = 40000, d = 2048, E = 32 76 -> 67 (but T = 16384, one block per CU anyway, caches swept, 37 -> 39).
         if (tiles <= 512) {
             if (s.E <= 16) return run_gate_split<bf16_t, 1, 1, 3, true>(s, X, Wg, bg, logits, idx, w, st);
-            if (one_block(s) && s.E <= 32) return run_gate_split<bf16_t, 1, 1, 3, true, 2>(s, X, Wg, bg, logits, idx, w, st);
-            if (one_block(s) && s.E <= 48) return run_gate_split<bf16_t, 1, 1, 3, true, 3>(s, X, Wg, bg, logits, idx, w, st);
-            if (one_block(s)) return run_gate_split<bf16_t, 1, 1, 3, true, 4>(s, X, Wg, bg, logits, idx, w, st);
+            if (one_block(s, tiles) && s.E <= 32) return run_gate_split<bf16_t, 1, 1, 3, true, 2>(s, X, Wg, bg, logits, idx, w, st);
+            if (one_block(s, tiles) && s.E <= 48) return run_gate_split<bf16_t, 1, 1, 3, true, 3>(s, X, Wg, bg, logits, idx, w, st);
+            if (one_block(s, tiles)) return run_gate_split<bf16_t, 1, 1, 3, true, 4>(s, X, Wg, bg, logits, idx, w, st);
             return run_gate_split<bf16_t, 1, 1, 3, false>(s, X, Wg, bg, logits, idx, w, st);
         }
         if (s.E <= 16) return run_gate_split<bf16_t, 1, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);

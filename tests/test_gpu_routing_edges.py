@@ -96,6 +96,7 @@ def test_routing_of_many_experts(E, k):
     (5000, 320, 20), (16384, 192, 24), (16385, 448, 32),         # two tiles of experts: rings of three steps, the last T with them, of two
     (90, 128, 18),                                               # no multiple of four: the general kernel
     (33, 4096, 32), (49, 4160, 32), (20, 1024, 48), (65, 64, 36), (2000, 1024, 64), (30, 1088, 64), (17, 512, 52),   # experts of a
+    (30, 512, 48), (30, 576, 48), (1025, 320, 64), (1024, 320, 64), (30, 256, 64),
     # block of 16 tokens in two, three and four units that route them, up to the longest rows, and past those
 ], ids=str)
 def test_gate_logits_bit_for_bit(T, d, E):
@@ -119,7 +120,8 @@ def test_gate_logits_bit_for_bit(T, d, E):
     (33, 4100, 16, 0), (100, 316, 20, 3), (50, 132, 132, 0),     # experts in blocks of 16, the last one partly empty
     (8200, 36, 16, 0), (8193, 100, 16, 0), (5000, 324, 20, 2),   # 64 tokens per block, one and two tiles of experts
     (4100, 260, 36, 0), (5000, 72, 64, 0), (3000, 132, 68, 0),   # four tiles of experts, two passes
-    (40, 2048, 32, 0), (40, 2052, 32, 0), (31, 512, 48, 0), (700, 500, 64, 1), (15, 516, 64, 0), (64, 4, 20, 0),   # units, as above
+    (40, 2048, 32, 0), (40, 2052, 32, 0), (31, 512, 48, 0), (700, 500, 64, 1), (15, 516, 64, 0), (64, 4, 20, 0),
+    (31, 516, 48, 0), (1500, 500, 64, 1), (30, 256, 64, 0), (30, 260, 64, 2),   # units, as above
     (90, 100, 18, 0),                                            # no multiple of four: the general kernel
 ], ids=str)
 def test_fp32_gate_logits_bit_for_bit(T, d, E, off):
