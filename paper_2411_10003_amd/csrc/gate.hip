@@ -662,6 +662,11 @@ static hipError_t launch_gate_part(const moe_shape_t& s, const void* X, const fl
                 return run_gate_split<float, 1, 1, 3, false>(s, X, Wg, bg, logits, idx, w, st);
             }
             if (s.E <= 16) return run_gate_split<float, 1, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
+            // 17 to 32 experts: 144 KB of rings, one block per CU.  A second round of such blocks does little but fill them where rows
+            // are short; the general kernel has several per CU (us, general | split: T = 50676, d = 8, E = 20 17.7 | 27.9; T = 21561, d
+            // = 56, E = 24 10.3 | 15.0; T = 24527, d = 152, E = 32 12.9 | 15.1; T = 16628, d = 372, E = 24 17.1 | 17.8; T = 42692, d = 348, E
+            // = 20 36.7 | 33.3; one round, T = 15276, d = 36, E = 20 8.8 | 8.4)
+            if (s.E <= 32 && s.T > 64 * 256 && s.d <= 256) return run_gate_t<float>(s, X, Wg, bg, logits, idx, w, st);
             if (s.E <= 32) return run_gate_split<float, 2, 4, 3, true>(s, X, Wg, bg, logits, idx, w, st);
             if (s.E <= 64) return run_gate_split<float, 4, 4, 2, true>(s, X, Wg, bg, logits, idx, w, st);
             return run_gate_split<float, 4, 4, 2, false>(s, X, Wg, bg, logits, idx, w, st);

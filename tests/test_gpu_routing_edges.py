@@ -121,6 +121,7 @@ def test_gate_logits_bit_for_bit(T, d, E):
     (8200, 36, 16, 0), (8193, 100, 16, 0), (5000, 324, 20, 2),   # 64 tokens per block, one and two tiles of experts
     (4100, 260, 36, 0), (5000, 72, 64, 0), (3000, 132, 68, 0),   # four tiles of experts, two passes
     (40, 2048, 32, 0), (40, 2052, 32, 0), (31, 512, 48, 0), (700, 500, 64, 1), (15, 516, 64, 0), (64, 4, 20, 0),
+    (16384, 60, 24, 0), (16385, 60, 24, 0), (16385, 64, 32, 3), (16400, 256, 20, 0), (16400, 260, 20, 0),    # one round of blocks, short rows past it
     (31, 516, 48, 0), (1500, 500, 64, 1), (30, 256, 64, 0), (30, 260, 64, 2),   # units, as above
     (90, 100, 18, 0),                                            # no multiple of four: the general kernel
 ], ids=str)
