@@ -162,7 +162,8 @@ __global__ __launch_bounds__(ROUTE_WAVES * 64) void positions_kernel(
 // the ranks 64 experts at a time, like the rows of a chunk: the lanes with the same destination find each other by ballots,
 // and a counter per destination carries over.  The launch that finds layout and positions, us, walk | wave: E = 16, 65536
 // assignments 9.4 | 10.2; E = 32, 32768 6.3 | 6.9; E = 40, 6000 7.7 | 7.0; E = 64, 10000 9.2 | 7.4; E = 128, 32004 11.5 | 8.7,
-// 24000 11.4 | 8.1.
+// 24000 11.4 | 8.1.  Instantiations of their own (WALK): one kernel with both ways in it took the walk longer (counts and
+// dispatch of up to 32 experts, 96 drawn shapes: 1 to 3 % in the mean).
 constexpr int WALK_EXPERTS = 32;
 struct BlockLayout { int32_t *dest, *slot_of, *slot_cnt, *slot_off, *first, *flag; };
 __device__ __forceinline__ BlockLayout block_layout_lds(int32_t* lds, int E)
@@ -190,28 +191,29 @@ __device__ __forceinline__ void wave_exclusive_scan(const int32_t* v, int32_t* o
     __builtin_amdgcn_wave_barrier();
 }
 
+template <bool WALK>
 __device__ __forceinline__ void build_layout(const BlockLayout& L, const int32_t* __restrict__ expert_dest,
                                              const int32_t* __restrict__ counts, int E, int P)
 {
     const int tid = threadIdx.x, lane = tid & 63;
     if (tid == 0) *L.flag = 0;
-    for (int p = tid; p <= P; p += blockDim.x) L.first[p] = 0;
+    if (!WALK) for (int p = tid; p <= P; p += blockDim.x) L.first[p] = 0;
     __syncthreads();
     for (int e = tid; e < E; e += blockDim.x) {
         int p = expert_dest[e];
-        L.slot_off[e] = counts[e];                          // for now
+        if (!WALK) L.slot_off[e] = counts[e];               // for now
         if (p < 0 || p >= P) { atomicOr(L.flag, 1); p = p < 0 ? 0 : P - 1; }
         L.dest[e] = p;
     }
     __syncthreads();
-    if (E <= WALK_EXPERTS) {
+    if (WALK) {
         for (int e = tid; e < E; e += blockDim.x) {
-            const int p = L.dest[e];
+            const int p = L.dest[e], n = counts[e];
             int sl = 0;
 #pragma unroll 4
             for (int f = 0; f < E; ++f) sl += (L.dest[f] < p) || (L.dest[f] == p && f < e);
             L.slot_of[e] = sl;
-            L.slot_cnt[sl] = L.slot_off[e];
+            L.slot_cnt[sl] = n;
         }
         __syncthreads();
     } else if (tid < 64) {
@@ -243,6 +245,7 @@ __device__ __forceinline__ void build_layout(const BlockLayout& L, const int32_t
 }
 
 // One block publishes the layout.
+template <bool WALK>
 __device__ __forceinline__ void publish_layout(const BlockLayout& L, const moe_layout_t& out, int32_t* __restrict__ status,
                                                int E, int P, int self, int Gcap)
 {
@@ -251,7 +254,7 @@ __device__ __forceinline__ void publish_layout(const BlockLayout& L, const moe_l
     for (int s = tid; s <= E; s += blockDim.x) out.slot_offsets[s] = L.slot_off[s];
     for (int p = tid; p <= P; p += blockDim.x) {
         int first = 0, mine = 0;                            // slots of destinations below p, of p
-        if (E <= WALK_EXPERTS) {
+        if (WALK) {
             for (int f = 0; f < E; ++f) { first += (L.dest[f] < p); mine += (L.dest[f] == p); }
         } else {
             first = L.first[p];
@@ -266,6 +269,7 @@ __device__ __forceinline__ void publish_layout(const BlockLayout& L, const moe_l
 // The layout and the per-chunk bases, for more chunks than layout_positions_kernel adds up: one block per 64 experts scans
 // their histograms over the chunks, block 0 publishes the layout.
 constexpr int SCAN_WAVES = 16;
+template <bool WALK>
 __global__ __launch_bounds__(SCAN_WAVES * 64) void layout_scan_kernel(
     const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ counts,
     const int32_t* __restrict__ chunk_hist, int32_t* __restrict__ chunk_base, int n_chunks,
@@ -276,8 +280,8 @@ __global__ __launch_bounds__(SCAN_WAVES * 64) void layout_scan_kernel(
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, e = blockIdx.x * 64 + lane;
     if (blockIdx.x == 0) {
         const BlockLayout L = block_layout_lds(lds, E);
-        build_layout(L, expert_dest, counts, E, P);
-        publish_layout(L, out, status, E, P, self, Gcap);
+        build_layout<WALK>(L, expert_dest, counts, E, P);
+        publish_layout<WALK>(L, out, status, E, P, self, Gcap);
     }
     // wave w owns a run of chunks: their sum, the sums of the runs before, then the bases of its chunks
     const int per = (n_chunks + SCAN_WAVES - 1) / SCAN_WAVES, c0 = min(wave * per, n_chunks), c1 = min(c0 + per, n_chunks);
@@ -300,6 +304,7 @@ __global__ __launch_bounds__(SCAN_WAVES * 64) void layout_scan_kernel(
 // base of a block's first chunk is summed from the histograms of all chunks before it (its waves share them; whole rows,
 // all loads independent) instead of being read from a prefix table that a launch of a single block would have to write
 // first.
+template <bool WALK>
 __global__ __launch_bounds__(ROUTE_WAVES * 64) void layout_positions_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ counts,
     const int32_t* __restrict__ chunk_hist, const moe_layout_t out, int32_t* __restrict__ status,
@@ -314,7 +319,7 @@ __global__ __launch_bounds__(ROUTE_WAVES * 64) void layout_positions_kernel(
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) e_of[r] = expert_of(idx, chunk * ROUTE_CHUNK + r * 64 + lane, A, E);
     for (int i = tid; i < ROUTE_WAVES * E; i += blockDim.x) next[i] = 0;
-    build_layout(L, expert_dest, counts, E, P);
+    build_layout<WALK>(L, expert_dest, counts, E, P);
     // wave w adds up every ROUTE_WAVES-th chunk before this block, for everybody, and the block's chunks w .. 2 for the
     // waves behind them; lane l takes the experts l, l + 64, ...
     for (int s0 = 0; s0 < E; s0 += 64) {
@@ -335,7 +340,7 @@ __global__ __launch_bounds__(ROUTE_WAVES * 64) void layout_positions_kernel(
         }
     }
     __syncthreads();
-    if (blockIdx.x == 0) publish_layout(L, out, status, E, P, self, Gcap);
+    if (blockIdx.x == 0) publish_layout<WALK>(L, out, status, E, P, self, Gcap);
     if (chunk >= n_chunks) return;
     chunk_positions(next + wave * E, e_of, E, lane, [&](int r, int row) {
         const int a = chunk * ROUTE_CHUNK + r * 64 + lane;
@@ -350,6 +355,7 @@ __global__ __launch_bounds__(ROUTE_WAVES * 64) void layout_positions_kernel(
 // of the host.  Gate, counts and dispatch in a row: T = 1999, d = 768, E = 16, k = 2 30 -> 20 us; T = 512, d = 64, E = 8
 // 29 -> 18.
 constexpr int SMALL_CHUNKS = 16, SMALL_EXPERTS = 256, PIECE_VECS = 256;
+template <bool WALK>
 __global__ __launch_bounds__(SMALL_CHUNKS * 64) void small_dispatch_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ counts,
     const uint4* __restrict__ X, uint4* __restrict__ Xp, const moe_layout_t out, int32_t* __restrict__ status,
@@ -368,7 +374,7 @@ __global__ __launch_bounds__(SMALL_CHUNKS * 64) void small_dispatch_kernel(
         if (a < A) pos[a] = -1;                    // a corrupt index gets no row
     }
     if (chunk < n_chunks) chunk_histogram(next + chunk * E, e_of, E, lane);
-    build_layout(L, expert_dest, counts, E, P);    // ends with a barrier
+    build_layout<WALK>(L, expert_dest, counts, E, P);    // ends with a barrier
     for (int e = tid; e < E; e += blockDim.x) {    // counts of the chunks -> first rows
         int row = L.slot_off[L.slot_of[e]];
         for (int c = 0; c < n_chunks; ++c) {
@@ -385,7 +391,7 @@ __global__ __launch_bounds__(SMALL_CHUNKS * 64) void small_dispatch_kernel(
             if (blockIdx.x == 0) { out.pos[a] = row; out.perm[row] = a; }
         });
     __syncthreads();
-    if (blockIdx.x == 0) publish_layout(L, out, status, E, P, self, Gcap);
+    if (blockIdx.x == 0) publish_layout<WALK>(L, out, status, E, P, self, Gcap);
     // pieces of 4 KB of a token's row, dealt to the blocks in turn
     const int pieces = (row_vecs + PIECE_VECS - 1) / PIECE_VECS;
     for (int u = chunk * gridDim.x + blockIdx.x; u < T * pieces; u += SMALL_CHUNKS * gridDim.x) {
@@ -451,7 +457,8 @@ hipError_t launch_layout_scan(const moe_shape_t& s, const int32_t* expert_dest, 
                               const int32_t* chunk_hist, int32_t* chunk_base, int n_chunks,
                               const moe_layout_t& L, int32_t* status, hipStream_t st)
 {
-    hipLaunchKernelGGL(layout_scan_kernel, dim3((s.E + 63) / 64), dim3(SCAN_WAVES * 64), (size_t)block_layout_words(s.E) * sizeof(int32_t), st,
+    auto kern = s.E <= WALK_EXPERTS ? layout_scan_kernel<true> : layout_scan_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3((s.E + 63) / 64), dim3(SCAN_WAVES * 64), (size_t)block_layout_words(s.E) * sizeof(int32_t), st,
                        expert_dest, counts, chunk_hist, chunk_base, n_chunks, L, status, s.E, s.P, s.self, s.G);
     return hipGetLastError();
 }
@@ -478,7 +485,8 @@ hipError_t launch_layout_positions(const moe_shape_t& s, const int32_t* idx, con
 {
     const int grid = (n_chunks + ROUTE_WAVES - 1) / ROUTE_WAVES;
     const size_t lds = (size_t)(block_layout_words(s.E) + ROUTE_WAVES * s.E) * sizeof(int32_t);
-    hipLaunchKernelGGL(layout_positions_kernel, dim3(grid), dim3(ROUTE_WAVES * 64), lds, st, idx, expert_dest, counts, chunk_hist,
+    auto kern = s.E <= WALK_EXPERTS ? layout_positions_kernel<true> : layout_positions_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(ROUTE_WAVES * 64), lds, st, idx, expert_dest, counts, chunk_hist,
                        L, status, s.T * s.k, s.E, s.P, s.self, s.G, n_chunks);
     return hipGetLastError();
 }
@@ -492,7 +500,8 @@ hipError_t launch_small_dispatch(const moe_shape_t& s, const int32_t* idx, const
     const size_t lds = (size_t)(block_layout_words(s.E) + SMALL_CHUNKS * s.E + n_chunks * ROUTE_CHUNK) * sizeof(int32_t);
     const long pieces = (long)s.T * ((row_vecs + PIECE_VECS - 1) / PIECE_VECS);
     const int grid = pieces < 256 ? (int)pieces : 256;                                 // a block per piece while there are CUs
-    hipLaunchKernelGGL(small_dispatch_kernel, dim3(grid), dim3(SMALL_CHUNKS * 64), lds, st, idx, expert_dest, counts,
+    auto kern = s.E <= WALK_EXPERTS ? small_dispatch_kernel<true> : small_dispatch_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(SMALL_CHUNKS * 64), lds, st, idx, expert_dest, counts,
                        (const uint4*)X, (uint4*)Xp, L, status, s.T, s.k, row_vecs, s.E, s.P, s.self, s.G, n_chunks);
     return hipGetLastError();
 }
