@@ -381,7 +381,8 @@ constexpr int MAX_TENSORS = 8, MOVE_UNROLL = 4;
 struct MoveArgs { const uint4* src[MAX_TENSORS]; uint4* dst[MAX_TENSORS]; long vec[MAX_TENSORS]; };
 
 // commit: the slot's expert, written here where no versions are kept (nobody reads it then); with versions other blocks of the
-// slot still compare it, and a launch of its own writes both afterwards (4.8 us of 126 in a pass that moves 134 MB).
+// slot still compare it, and a launch of its own writes both afterwards.  (Over 300 drawn moves of up to 67 MB
+// it was a seventh of the call; in a pass that moves 134 MB its 4.8 us of 126 are within the spread.)
 __global__ __launch_bounds__(256) void trans_gather_kernel(
     const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ pool_version,
     const int32_t* slot_expert, const int32_t* __restrict__ slot_version, int32_t* commit, const MoveArgs a, int E, int self)
