@@ -14,7 +14,7 @@
 //
 // Tiling: 256 x 256 output tile per block (128 x 128 where those leave the chip idle, see GeometryCost), 32-deep
 // contraction slices moved from HBM/L2 straight into a 5-deep ring of LDS buffers by buffer loads (no
-// register staging; rows outside a ragged group arrive as zeros because they lie past the end of the buffer resource), 32x32x16 bf16 MFMA
+// register staging; rows outside a ragged group arrive as zeros because they lie past the end of the buffer resource), 16x16x32 bf16 MFMA
 // with the accumulators in AGPRs.  An operand whose contraction index is contiguous in memory is
 // kept row-major in LDS and read with 16-byte loads; one whose contraction index is the slow one
 // is kept as it is and read with the transposing LDS load, so no operand is ever transposed in
@@ -52,7 +52,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 enum Kind { KIND_NN = 0, KIND_NT = 1, KIND_TN = 2 };
@@ -209,23 +209,27 @@ typedef Geometry<2, 2, 2, 2, 5, 2> Small;
 // slices of 32), 128 bytes per row, its eight 16-byte pieces XOR-swizzled by the row so that 16 consecutive rows of
 // one piece cover all banks.
 __device__ __forceinline__ uint32_t halfpair_off(int row, int piece8) { return row * 128 + ((piece8 ^ ((row >> 1) & 7)) << 4); }
-// K-major operand: [32 steps][COLS columns]; 64-byte granules of a row XOR-swizzled by the step so
-// that the four steps a transposing load touches fall into different banks (rows of 64 columns are 128 bytes: steps two
-// apart share their banks and are kept apart by the one bit there is).
-template <int COLS> __device__ __forceinline__ int kmajor_swizzle(int krow) { return COLS >= 128 ? (krow & 3) : ((krow >> 1) & 1); }
+// K-major operand, 32 steps x COLS columns: two steps beside each other, 64 columns (a 128-byte line of memory) of one and of
+// the other in turn, the four 16-column chunks of a line XOR-swizzled by bits 1 and 3 of the step.  A transposing load takes
+// four steps of every lane block, and its lane blocks are eight steps apart: the eight steps that 32 lanes touch differ in
+// bits 0, 1 and 3, and their chunks of one column group cover all banks.
+__device__ __forceinline__ int kmajor_swizzle(int krow) { return ((krow >> 1) & 1) | ((krow >> 2) & 2); }
 template <int COLS>
-__device__ __forceinline__ uint32_t kmajor_off(int krow, int col) { return krow * (COLS * 2) + ((((col >> 5) ^ kmajor_swizzle<COLS>(krow))) << 6) + (col & 31) * 2; }
+__device__ __forceinline__ uint32_t kmajor_off(int krow, int col)
+{
+    return (krow >> 1) * (COLS * 4) + (col >> 6) * 256 + (krow & 1) * 128 + ((((col >> 4) & 3) ^ kmajor_swizzle(krow)) << 5) + (col & 15) * 2;
+}
 // The inverse for the DMA: byte offset in memory of the 16-byte piece that belongs at slot L of such a buffer.
 template <int COLS>
 __device__ __forceinline__ uint32_t kmajor_source(int L, long ld)
 {
-    constexpr int PER_ROW = COLS / 8;
-    const int krow = L / PER_ROW, pp = L % PER_ROW;
-    const int col = (((pp >> 2) ^ kmajor_swizzle<COLS>(krow)) << 5) + (pp & 3) * 8;
+    constexpr int PER_PAIR = COLS / 4;                     // slots of two steps
+    const int in_pair = L % PER_PAIR, part = L & 7, krow = L / PER_PAIR * 2 + ((in_pair >> 3) & 1);
+    const int col = (in_pair >> 4) * 64 + (((part >> 1) ^ kmajor_swizzle(krow)) << 4) + (part & 1) * 8;
     return (uint32_t)((krow * ld + col) * 2);
 }
 
-// Fragment = 32 rows (or columns) x 16 contraction steps; lane l holds row l%32, steps 8*(l/32)..+7.
+// Fragment = 16 rows (or columns) x 32 contraction steps; lane l holds row l%16, steps 8*(l/16)..+7.
 // Fragment reads are issued as assembly and waited for by hand (WAIT_FRAGS below): the compiler's
 // own wait insertion cannot express "the set loaded one iteration ago is complete" and would stall
 // every MFMA group on the fragments that were only just requested for the next iteration.
@@ -237,12 +241,12 @@ __device__ __forceinline__ void lds_frag_kcontig_at(bf16x8& f, uint32_t addr)
 // The transposing load works on blocks of 16 lanes: lane s of a block points at 4 consecutive columns
 // of step s/4; lane i of the block receives column i of steps 0..3.  Two loads give the 8 steps of a
 // lane in the same order as the K-contiguous fragment.  IMM: a constant distance added to the address.
-template <int ROW4_BYTES, int IMM>
+template <int STEP4_BYTES, int IMM>
 __device__ __forceinline__ void lds_frag_kmajor_at(bf16x8& f, uint32_t addr)
 {
     s16x4 lo, hi;
     asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
-                 : "=&v"(lo), "=&v"(hi) : "v"(addr), "n"(IMM), "n"(IMM + ROW4_BYTES));
+                 : "=&v"(lo), "=&v"(hi) : "v"(addr), "n"(IMM), "n"(IMM + STEP4_BYTES));
     const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     f = __builtin_bit_cast(bf16x8, v);
 }
@@ -611,16 +615,20 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     int iss_stage = 0;
     int iss_seg = (KIND == KIND_TN) ? 0 : k_lo / k_per_seg, iss_in_seg = (KIND == KIND_TN) ? 0 : k_lo - iss_seg * k_per_seg;
     uint32_t soffA = (uint32_t)iss_in_seg * stepA, soffB = (uint32_t)iss_in_seg * stepB;
-    // The requests of one slice into stage iss_stage, with the resources the caller has picked: no decision in it.
+    // The requests of one slice (or, NN and NT, of one group, below) into stage iss_stage, with the resources the caller has
+    // picked: no decision in it.  The caller says when each of them goes out.
+    constexpr int SLICE_OPS = PA + PB;                     // of one wave
+    auto request_piece = [&](int n, uint32_t st, const rsrc_t ra, const rsrc_t rb0, const rsrc_t rb1, uint32_t oa, uint32_t ob) {
+        if (n < PA) dma16(ra, st + ldsA[n], voffA[n], oa);
+        else dma16((DUAL && ((n - PA) & 1)) ? rb1 : rb0, st + A_BYTES + ldsB[n - PA], voffB[n - PA], ob);
+    };
+    auto next_stage = [&]() { iss_stage = (iss_stage + 1 == STAGES) ? 0 : iss_stage + 1; };
+    auto slice_done = [&]() { next_stage(); ++iss_in_seg; soffA += stepA; soffB += stepB; };
     auto issue_with = [&](const rsrc_t ra, const rsrc_t rb0, const rsrc_t rb1) {
         const uint32_t st = lds0 + (uint32_t)iss_stage * STAGE_BYTES;
-        iss_stage = (iss_stage + 1 == STAGES) ? 0 : iss_stage + 1;
 #pragma unroll
-        for (int i = 0; i < PA; ++i) dma16(ra, st + ldsA[i], voffA[i], soffA);
-#pragma unroll
-        for (int i = 0; i < PB; ++i) dma16((DUAL && (i & 1)) ? rb1 : rb0, st + A_BYTES + ldsB[i], voffB[i], soffB);
-        ++iss_in_seg;
-        soffA += stepA; soffB += stepB;
+        for (int n = 0; n < SLICE_OPS; ++n) request_piece(n, st, ra, rb0, rb1, soffA, soffB);
+        slice_done();
     };
     // What may have to change between two slices: the next contraction segment (NN/NT), or, for TN, whose offset
     // runs over all rows of the group, the base of the resources: buffer offsets are 32 bits, so the resources are
@@ -652,19 +660,25 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     // one slice per group.  PAR: the parity of the group, known where the loop is written out.
     constexpr bool A_PAIR = !A_KMAJOR, B_PAIR = !B_KMAJOR;
     const uint32_t halfA = (uint32_t)(BM / 2 * p.lda * 2), halfB = (uint32_t)(BN / 2 * p.ldb * 2);   // to the lower half
-    auto issue_group = [&](auto PAR, const rsrc_t ra, const rsrc_t rb0, const rsrc_t rb1) {
+    auto group_offsets = [&](auto PAR, uint32_t& oa, uint32_t& ob) {
         constexpr int par = decltype(PAR)::value;
-        const uint32_t st = lds0 + (uint32_t)iss_stage * STAGE_BYTES;
-        iss_stage = (iss_stage + 1 == STAGES) ? 0 : iss_stage + 1;
-        const uint32_t oa = (A_PAIR && par) ? soffA + halfA : soffA;
-        const uint32_t ob = (B_PAIR && par) ? soffB + halfB : soffB;
-#pragma unroll
-        for (int i = 0; i < PA; ++i) dma16(ra, st + ldsA[i], voffA[i], oa);
-#pragma unroll
-        for (int i = 0; i < PB; ++i) dma16((DUAL && (i & 1)) ? rb1 : rb0, st + A_BYTES + ldsB[i], voffB[i], ob);
+        oa = (A_PAIR && par) ? soffA + halfA : soffA;
+        ob = (B_PAIR && par) ? soffB + halfB : soffB;
+    };
+    auto group_done = [&](auto PAR) {
+        constexpr int par = decltype(PAR)::value;
+        next_stage();
         ++iss_in_seg;
         if (!A_PAIR || par) soffA += A_PAIR ? 2 * stepA : stepA;
         if (!B_PAIR || par) soffB += B_PAIR ? 2 * stepB : stepB;
+    };
+    auto issue_group = [&](auto PAR, const rsrc_t ra, const rsrc_t rb0, const rsrc_t rb1) {
+        const uint32_t st = lds0 + (uint32_t)iss_stage * STAGE_BYTES;
+        uint32_t oa, ob;
+        group_offsets(PAR, oa, ob);
+#pragma unroll
+        for (int n = 0; n < SLICE_OPS; ++n) request_piece(n, st, ra, rb0, rb1, oa, ob);
+        group_done(PAR);
     };
     // after an odd group (segments hold an even number of slices): the next contraction segment
     auto group_fixups = [&]() {
@@ -675,65 +689,84 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     // address that changes from slice to slice, and every vector instruction of the fetching wave takes an issue
     // slot from the matrix instructions of its partner: fragments that lie a constant distance apart share one
     // address register and differ in the instruction's immediate offset.
-    static_assert((TM == 4 || TM == 2) && TN == 2, "the fragment reads below are written out for 4 x 2 or 2 x 2 fragments");
-    // K-major operands (step half 0; half 1 is 16 steps further down)
-    uint32_t fa_addr[TM], fb_addr[TN];
-    constexpr uint32_t A_HALF = 16 * (BM * 2);
+    constexpr int FM = 2 * TM, FN = 2 * TN;                // fragments of 16 rows, of 16 columns
+    static_assert((FM == 8 || FM == 4) && FN == 4 && WN == 64, "the fragment reads below are written out for 8 x 4 or 4 x 4 fragments");
+    // K-major operands: one address per 16-column chunk of 64 columns; 64 columns lie a constant distance apart.
     constexpr int BCOLS = DUAL ? BN / 2 : BN;
-    constexpr uint32_t B_HALF = 16 * (BCOLS * 2);
+    constexpr int STEP4_A = BM * 8, STEP4_B = BCOLS * 8;         // four steps further on
+    static_assert(KIND != KIND_TN || BM == BN, "one set of addresses for both operands");
+    uint32_t fk_addr[4];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
+    for (int c = 0; c < 4; ++c) {
         const int b = lane >> 4, s = lane & 15;
-        fa_addr[i] = kmajor_off<BM>(8 * (b >> 1) + (s >> 2), wm * WM + i * 32 + 16 * (b & 1) + 4 * (s & 3));
+        fk_addr[c] = kmajor_off<BCOLS>(8 * b + (s >> 2), c * 16 + 4 * (s & 3));
     }
+    const uint32_t a_cols = wm * (WM / 64) * 256;        // this wave's columns inside a buffer
+    const uint32_t b_cols = A_BYTES + (DUAL ? wn >> 1 : wn) * 256;
+    // DUAL: 32 columns of either weight matrix, two chunks of a line
+    const uint32_t fd_addr[2] = {(wn & 1) ? fk_addr[2] : fk_addr[0], (wn & 1) ? fk_addr[3] : fk_addr[1]};
+    // `after(n)`: what goes out between the reads, after the n-th fragment's
+    auto load_kmajor_b = [&](bf16x8 (&fb)[FN], uint32_t st, auto after) {
+        if constexpr (DUAL) {                              // fragments 0, 1 from the W1 sub-buffer, 2, 3 from the W3 sub-buffer
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int b = lane >> 4, s = lane & 15;
-        const int krow = 8 * (b >> 1) + (s >> 2), cofs = 16 * (b & 1) + 4 * (s & 3);
-        if (DUAL)   // even fragments from the W1 sub-buffer, odd ones from the W3 sub-buffer
-            fb_addr[j] = A_BYTES + (j & 1) * (GEO::B_BYTES / 2) + kmajor_off<BN / 2>(krow, wn * (WN / 2) + (j >> 1) * 32 + cofs);
-        else
-            fb_addr[j] = A_BYTES + kmajor_off<BN>(krow, wn * WN + j * 32 + cofs);
-    }
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t a = st + b_cols + fd_addr[j];
+                lds_frag_kmajor_at<STEP4_B, 0>(fb[j], a);
+                after(FM + 2 * j);
+                lds_frag_kmajor_at<STEP4_B, (int)GEO::B_BYTES / 2>(fb[2 + j], a);
+                after(FM + 2 * j + 1);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) { lds_frag_kmajor_at<STEP4_B, 0>(fb[j], st + b_cols + fk_addr[j]); after(FM + j); }
+        }
+    };
     // TN: both operands K-major, a slice per ring buffer
-    auto load_frags = [&](bf16x8 (&fa)[TM], bf16x8 (&fb)[TN], int stage, auto HALF) {
-        constexpr int half = decltype(HALF)::value;
+    auto load_frags = [&](bf16x8 (&fa)[FM], bf16x8 (&fb)[FN], int stage, auto after) {
         const uint32_t st = lds0 + (uint32_t)stage * STAGE_BYTES;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) lds_frag_kmajor_at<4 * BM * 2, half * (int)A_HALF>(fa[i], st + fa_addr[i]);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) lds_frag_kmajor_at<4 * BCOLS * 2, half * (int)B_HALF>(fb[j], st + fb_addr[j]);
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t a = st + a_cols + fk_addr[i];
+            lds_frag_kmajor_at<STEP4_A, 0>(fa[i], a);
+            after(FM / 4 * i);
+            if constexpr (FM == 8) { lds_frag_kmajor_at<STEP4_A, 256>(fa[4 + i], a); after(2 * i + 1); }
+        }
+        load_kmajor_b(fb, st, after);
     };
-    // Operands fetched in 128-byte lines: fragment 0 of this wave in a 128-row buffer, at the four quarters (16
-    // steps each) of the buffer's two slices; the wave's other fragments lie 32 rows = 4 KB further on.  The upper
-    // row of waves (A) and the waves of the two left columns (B) read the buffer of an even group, the others that
-    // of the odd group after it.
-    uint32_t fpa[4], fpb[4];
+    // Operands fetched in 128-byte lines: fragment 0 of this wave in a 128-row buffer, at the buffer's two slices; the
+    // wave's other fragments lie 16 rows = 2 KB further on.  The upper row of waves (A) and the waves of the two left
+    // columns (B) read the buffer of an even group, the others that of the odd group after it.
+    uint32_t fpa[2], fpb[2];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        fpa[v] = halfpair_off(lane & 31, lane >> 5) ^ (uint32_t)(v << 5);
-        fpb[v] = A_BYTES + (halfpair_off((wn % (WGN / 2)) * WN + (lane & 31), lane >> 5) ^ (uint32_t)(v << 5));
+    for (int v = 0; v < 2; ++v) {
+        fpa[v] = halfpair_off(lane & 15, lane >> 4) ^ (uint32_t)(v << 6);
+        fpb[v] = A_BYTES + (halfpair_off((wn % (WGN / 2)) * WN + (lane & 15), lane >> 4) ^ (uint32_t)(v << 6));
     }
-    auto load_group_frags = [&](bf16x8 (&fa)[TM], bf16x8 (&fb)[TN], uint32_t stA, uint32_t stB, auto Q) {
-        constexpr int quarter = decltype(Q)::value;        // 2 * (slice of the pair) + (16-step half of the slice)
-        {
-            const uint32_t a = stA + fpa[quarter];
-            lds_frag_kcontig_at<0>(fa[0], a);
-            lds_frag_kcontig_at<4096>(fa[1], a);
-            if constexpr (TM == 4) {
-                lds_frag_kcontig_at<8192>(fa[2], a);
-                lds_frag_kcontig_at<12288>(fa[3], a);
-            }
+    auto load_group_frags = [&](bf16x8 (&fa)[FM], bf16x8 (&fb)[FN], uint32_t stA, uint32_t stB, auto PAR, auto after) {
+        constexpr int par = decltype(PAR)::value;          // which slice of the pair
+        const uint32_t a = stA + fpa[par];
+        auto frag_a = [&](auto I) { lds_frag_kcontig_at<decltype(I)::value * 2048>(fa[decltype(I)::value], a); after(decltype(I)::value); };
+        frag_a(std::integral_constant<int, 0>{}); frag_a(std::integral_constant<int, 1>{});
+        frag_a(std::integral_constant<int, 2>{}); frag_a(std::integral_constant<int, 3>{});
+        if constexpr (FM == 8) {
+            frag_a(std::integral_constant<int, 4>{}); frag_a(std::integral_constant<int, 5>{});
+            frag_a(std::integral_constant<int, 6>{}); frag_a(std::integral_constant<int, 7>{});
         }
         if constexpr (B_KMAJOR) {                          // stB: the buffer of the slice
-#pragma unroll
-            for (int j = 0; j < TN; ++j) lds_frag_kmajor_at<4 * BCOLS * 2, (quarter & 1) * (int)B_HALF>(fb[j], stB + fb_addr[j]);
+            load_kmajor_b(fb, stB, after);
         } else {
-            const uint32_t bb = stB + fpb[quarter];
-            lds_frag_kcontig_at<0>(fb[0], bb);
-            lds_frag_kcontig_at<4096>(fb[1], bb);
+            const uint32_t bb = stB + fpb[par];
+            auto frag_b = [&](auto J) { lds_frag_kcontig_at<decltype(J)::value * 2048>(fb[decltype(J)::value], bb); after(FM + decltype(J)::value); };
+            frag_b(std::integral_constant<int, 0>{}); frag_b(std::integral_constant<int, 1>{});
+            frag_b(std::integral_constant<int, 2>{}); frag_b(std::integral_constant<int, 3>{});
         }
     };
+    // Which request follows the n-th fragment of a slice: one after every quarter of them.  LDS takes the reads of the four
+    // waves of a row and the vector memory path their requests side by side; one after the other they make the fetch phase of a
+    // K-major operand longer than the multiply phase it hides behind.  In turn, against all requests after the last read (us):
+    // fwd2 3957 -> 3784, weight gradients 4428 -> 4125, fwd1 8702 -> 8645, bwd2 7612 -> 7556 (d = 4096, h = 14336, 46695 rows);
+    // d = 1024, h = 4096, 9279 rows: fwd1 121 -> 116, fwd2 92 -> 88.
+    auto goes_out = [](int n) { return (n + 1) % ((FM + FN) / SLICE_OPS) == 0 ? (n + 1) / ((FM + FN) / SLICE_OPS) - 1 : -1; };
     auto wait_frags = [&]() {
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -742,43 +775,47 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
 
     // NN and NT start their accumulators with the first products of slice 0 (a matrix instruction that takes zero
     // as its addend) instead of clearing 128 registers per tile; TN, whose groups may be empty, clears them.
-    f32x16 acc[TM][TN];
+    f32x4 acc[FM][FN];
     if (KIND == KIND_TN || FIN) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+                for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0f;
     }
 
-    // the TM*TN products of one 16-step.  The accumulators are pinned to AGPRs, which leaves the
-    // VGPRs of the wave to fragments and addresses.
-    auto mma = [&](const bf16x8 (&fa)[TM], const bf16x8 (&fb)[TN]) {
+    // The FM*FN products of a slice.  The accumulators are pinned to AGPRs, which leaves the VGPRs of the wave to fragments
+    // and addresses.  These kernels run at the package's power cap, and 16x16x32 takes less energy per flop than 32x32x16,
+    // least in an order in which two instructions in a row share an operand: this loop with LDS reads and products alone
+    // sustains 1660 TFLOP/s with 32x32x16, 1850 with 16x16x32 row by row and 1880 with every other row backwards.  In the
+    // kernels, with the requests between the reads (goes_out): clock 1.47 -> 1.62 GHz, and d = 4096, h = 14336, SwiGLU, forward
+    // and backward 38.9 -> 36.9 ms; d = 2048, h = 8192, GELU 5.39 -> 5.11; d = 1024, h = 4096, forward 264 -> 250 us.
+    auto mma = [&](const bf16x8 (&fa)[FM], const bf16x8 (&fb)[FN]) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-                asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fb[j]), "v"(fa[i]));
+            for (int jj = 0; jj < FN; ++jj) {
+                const int j = (i & 1) ? FN - 1 - jj : jj;
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fb[j]), "v"(fa[i]));
+            }
     };
 
     // ---- main loop, two phases per slice.  In its fetch phase a wave reads the fragments of slice t
     // from LDS and requests its share of what lies three or four slices ahead; one barrier later, in its multiply phase, it issues
-    // the 16 MFMAs of the slice back to back.  The upper row of waves runs one barrier interval behind
+    // the 32 MFMAs of the slice back to back.  The upper row of waves runs one barrier interval behind
     // the lower one; waves w and w+4 share a SIMD, so while one of them feeds the matrix pipe the other
     // collects its operands.  With LDS reads and MFMAs alone this loop runs at the MFMA rate; what it
-    // waits for in practice is the delivery of the slices from L2/HBM.  All fragment reads are issued
-    // before the DMA requests so that a request held up by the memory system never delays them (a
-    // request placed between MFMAs stalls the matrix pipe for several MFMA slots instead).
+    // waits for in practice is the delivery of the slices from L2/HBM.  (A request placed between MFMAs stalls the matrix pipe
+    // for several MFMA slots.)
     // Two blocks on a CU (Small) need no such order: a wave of each shares a SIMD, and while one block collects operands,
     // waits or runs an epilogue, the other multiplies.  One barrier per slice then: the waits before it cover this wave's
     // pieces of the next slice and its reads of the current one, and what a request overwrites was last read before the
     // barrier of the slice before.
     if (!FIN && k_cnt > 0) {
       if constexpr (KIND == KIND_TN) {
-        bf16x8 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
+        bf16x8 fa[FM], fb[FN];
         constexpr int L = STAGES - 1;                      // slices requested ahead
-        constexpr int SLICE_OPS = PA + PB;              // DMA instructions of one wave per slice
         // Every slice t is preceded by exactly t + L request groups of this wave (the prologue issues L of them,
         // every slice one more), so "my pieces of slice t + 1 have landed" is always "at most L - 1 groups are still
         // on their way": one fixed wait count for the whole contraction.  Where there is no slice left to request
@@ -807,16 +844,14 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
             const rsrc_t rb0 = more ? ((KIND == KIND_NT && iss_seg) ? rB[1] : rB[0]) : rnull;
             const rsrc_t rb1 = more ? rB[1] : rnull;
             for (int i = 0; i < n; ++i) {
-                load_frags(fa0, fb0, cur, std::integral_constant<int, 0>{});
-                load_frags(fa1, fb1, cur, std::integral_constant<int, 1>{});
-                __builtin_amdgcn_sched_barrier(0);
-                issue_with(ra, rb0, rb1);
+                const uint32_t to = lds0 + (uint32_t)iss_stage * STAGE_BYTES;
+                load_frags(fa, fb, cur, [&](int n) { if (goes_out(n) >= 0) { __builtin_amdgcn_sched_barrier(0); request_piece(goes_out(n), to, ra, rb0, rb1, soffA, soffB); __builtin_amdgcn_sched_barrier(0); } });
+                slice_done();
                 WAIT_VMCNT((L - 1) * SLICE_OPS);
                 wait_frags();
                 BLOCK_BARRIER();
                 __builtin_amdgcn_s_setprio(1);
-                mma(fa0, fb0);
-                mma(fa1, fb1);
+                mma(fa, fb);
                 __builtin_amdgcn_s_setprio(0);
                 __builtin_amdgcn_sched_barrier(0);
                 if (GEO::TWO_PHASE) BLOCK_BARRIER();
@@ -829,7 +864,7 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         if (GEO::TWO_PHASE && wm == 0) BLOCK_BARRIER();    // both rows have passed the same number of barriers
         BLOCK_BARRIER();                                   // and everybody's requests have landed
       } else {
-        bf16x8 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
+        bf16x8 fa[FM], fb[FN];
         // NN and NT.  One request group per slice, three ahead: before slice t come the groups 0 .. t + 2, slice t adds
         // group t + 3 into ring slot (t + 3) % 5, which held group t - 2, last read in slice t - 1.  Slice 2p and 2p + 1
         // read the K-contiguous operands from the buffers of the groups 2p (upper 128 rows) and 2p + 1 (lower 128
@@ -840,7 +875,6 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         // so the loop is written out for pairs: slice 0, then pairs of an odd and an even slice, whose two groups are
         // the two halves of one later pair of slices and need no fixup between them, then the last slice.
         constexpr int L = 3;
-        constexpr int SLICE_OPS = PA + PB;              // DMA instructions of one wave per group
         const rsrc_t rnull = make_rsrc(p.A[0], 0);
         auto real_a = [&]() { return iss_seg ? rA[1] : rA[0]; };
         auto real_b0 = [&]() { return (KIND == KIND_NT && iss_seg) ? rB[1] : rB[0]; };
@@ -858,27 +892,29 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         const int hA = wm, hB = wn / (WGN / 2);                   // which group of a pair holds this wave's rows of A and B
         auto slot_base = [&](int slot) { return lds0 + (uint32_t)(slot >= STAGES ? slot - STAGES : slot) * STAGE_BYTES; };
         // One slice of parity PAR; ra .. rb1: the resources of the group it requests (of the opposite parity).
-        auto mma_first = [&](const bf16x8 (&fa)[TM], const bf16x8 (&fb)[TN]) {      // acc = products (+ 0)
+        auto mma_first = [&](const bf16x8 (&fa)[FM], const bf16x8 (&fb)[FN]) {      // acc = products (+ 0)
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < FM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=a"(acc[i][j]) : "v"(fb[j]), "v"(fa[i]));
+                for (int jj = 0; jj < FN; ++jj) {
+                    const int j = (i & 1) ? FN - 1 - jj : jj;
+                    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc[i][j]) : "v"(fb[j]), "v"(fa[i]));
+                }
         };
         auto slice = [&](auto PAR, auto FIRST, const rsrc_t ra, const rsrc_t rb0, const rsrc_t rb1) {
             constexpr int par = decltype(PAR)::value;
             const uint32_t stA = slot_base(pair0 + hA);
             const uint32_t stB = B_KMAJOR ? slot_base(cur) : slot_base(pair0 + hB);
-            load_group_frags(fa0, fb0, stA, stB, std::integral_constant<int, 2 * par>{});
-            load_group_frags(fa1, fb1, stA, stB, std::integral_constant<int, 2 * par + 1>{});
-            __builtin_amdgcn_sched_barrier(0);
-            issue_group(std::integral_constant<int, 1 - par>{}, ra, rb0, rb1);
+            const uint32_t to = lds0 + (uint32_t)iss_stage * STAGE_BYTES;
+            uint32_t oa, ob;
+            group_offsets(std::integral_constant<int, 1 - par>{}, oa, ob);
+            load_group_frags(fa, fb, stA, stB, PAR, [&](int n) { if (goes_out(n) >= 0) { __builtin_amdgcn_sched_barrier(0); request_piece(goes_out(n), to, ra, rb0, rb1, oa, ob); __builtin_amdgcn_sched_barrier(0); } });
+            group_done(std::integral_constant<int, 1 - par>{});
             WAIT_VMCNT(par ? SLICE_OPS : 2 * SLICE_OPS);
             wait_frags();
             BLOCK_BARRIER();
             __builtin_amdgcn_s_setprio(1);
-            if constexpr (decltype(FIRST)::value) mma_first(fa0, fb0); else mma(fa0, fb0);
-            mma(fa1, fb1);
+            if constexpr (decltype(FIRST)::value) mma_first(fa, fb); else mma(fa, fb);
             __builtin_amdgcn_s_setprio(0);
             __builtin_amdgcn_sched_barrier(0);
             if (GEO::TWO_PHASE) BLOCK_BARRIER();
@@ -915,29 +951,26 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     // partial tiles of a finishing launch: [unit][wave][register / 4][lane] as float4, every instruction moves 1 KB
     const bool uneven = LAST && first_slices && parts > 1;
     if (!FIN && parts > 1 && !uneven) {
-        float4* ws4 = reinterpret_cast<float4*>(p.split_ws) + ((size_t)unit * NWAVES + wave) * (TM * TN * 4) * 64 + lane;
+        float4* ws4 = reinterpret_cast<float4*>(p.split_ws) + ((size_t)unit * NWAVES + wave) * (FM * FN) * 64 + lane;
         // fragments past the group's last row (TN: the last row of the gradient) are not kept
         const long rows_left = (KIND == KIND_TN ? p.Mout - m0 : a_row_end - a_row0) - wm * WM;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < FM; ++i) {
+            if (i / 2 * 32 >= rows_left) continue;
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                if (i * 32 >= rows_left) continue;
-#pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4)
-                    ws4[((i * TN + j) * 4 + e4) * 64] = make_float4(acc[i][j][e4 * 4], acc[i][j][e4 * 4 + 1], acc[i][j][e4 * 4 + 2], acc[i][j][e4 * 4 + 3]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int j = 0; j < FN; ++j) ws4[(i * FN + j) * 64] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         __syncthreads();
         continue;
     }
-    // ---- epilogue.  A lane holds, per fragment, row l%32 and columns q*8 + (l/32)*4 + 0..3: storing
-    // from there would touch 16-byte pieces of 32 different rows per instruction.  Instead every wave
+    // ---- epilogue.  A lane holds, per fragment, row l%16 and columns (l/16)*4 + 0..3: storing
+    // from there would touch 8-byte pieces of 16 different rows per instruction.  Instead every wave
     // passes its 128 x 64 accumulators through its own LDS patch (one row of fragments, 32 rows, at a time,
     // fp32) and reads them back row-major, 8 consecutive columns per lane, so that global loads and stores
     // move whole 128/256-byte row segments.  The patches lie at the top of LDS, above ring slots 0 and 1.
     unsigned char* patch = smem + (LDS_BYTES - (size_t)NWAVES * EP_WAVE) + wave * EP_WAVE;
-    const int lrow = lane & 31, lcol = (lane >> 5) * 4;
+    const int lrow = lane & 15, lcol = (lane >> 4) * 4;
     const long row_limit = (KIND == KIND_TN) ? (long)p.Mout : a_row_end;
     constexpr int CG = DUAL ? WN / 16 : WN / 8;            // 8-column groups per staged row that carry outputs
     const int erow = lane / CG, ecg = lane % CG;
@@ -1035,31 +1068,29 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         }
         if (FIN && fr != q % TM) continue;                     // the tile's other rows of fragments are items of other blocks
         if (BWD1 && FIN) request(fr, 0, zin[(fr * NB) & 1], uin[EPI == EPI_BWD1_SWIGLU ? (fr * NB) & 1 : 0]);
-        float4 fsum[FIN ? TN : 1][4];
+        float4 fsum[FIN ? 2 * FN : 1];
         if (FIN) {                                             // the parts of a split tile, added in ascending order
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4) fsum[j][e4] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            for (int i = 0; i < 2 * FN; ++i) fsum[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             if (fr * 32 < row_limit - m0 - wm * WM) {
-                constexpr long PART = (long)NWAVES * (TM * TN * 4) * 64;
-                const float4* ws4 = reinterpret_cast<const float4*>(p.split_ws) + unit * PART + (wave * (TM * TN * 4) + fr * TN * 4) * 64 + lane;
+                constexpr long PART = (long)NWAVES * (FM * FN) * 64;
+                const float4* ws4 = reinterpret_cast<const float4*>(p.split_ws) + unit * PART + (wave * (FM * FN) + fr * 2 * FN) * 64 + lane;
                 // All loads of up to four parts, 32 KB of a wave, are on their way before the first is added (the compiler left to
                 // itself waits for each: 13 us instead of 8 for 96 tiles in five parts).
                 auto add_parts = [&](auto N, int s0) {
                     constexpr int n = decltype(N)::value;
-                    float4 x[n][TN * 4];
+                    float4 x[n][2 * FN];
 #pragma unroll
                     for (int s = 0; s < n; ++s)
 #pragma unroll
-                        for (int i = 0; i < TN * 4; ++i) x[s][i] = ws4[(s0 + s) * PART + i * 64];
+                        for (int i = 0; i < 2 * FN; ++i) x[s][i] = ws4[(s0 + s) * PART + i * 64];
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int s = 0; s < n; ++s)
 #pragma unroll
-                        for (int i = 0; i < TN * 4; ++i) {
-                            fsum[i / 4][i % 4].x += x[s][i].x; fsum[i / 4][i % 4].y += x[s][i].y;
-                            fsum[i / 4][i % 4].z += x[s][i].z; fsum[i / 4][i % 4].w += x[s][i].w;
+                        for (int i = 0; i < 2 * FN; ++i) {
+                            fsum[i].x += x[s][i].x; fsum[i].y += x[s][i].y;
+                            fsum[i].z += x[s][i].z; fsum[i].w += x[s][i].w;
                         }
                 };
                 constexpr int AT_ONCE = BWD1 ? 2 : 4;          // BWD1 holds saved pre-activations as well
@@ -1074,13 +1105,13 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x16& a = acc[fr][j];
-                float4 val = make_float4(a[q * 4 + 0], a[q * 4 + 1], a[q * 4 + 2], a[q * 4 + 3]);
-                if (FIN) val = fsum[j][q];
-                *reinterpret_cast<float4*>(patch + lrow * EP_PITCH + (j * 32 + q * 8 + lcol) * 4) = val;
+            for (int j = 0; j < FN; ++j) {
+                const f32x4& a = acc[2 * fr + i][j];
+                float4 val = make_float4(a[0], a[1], a[2], a[3]);
+                if (FIN) val = fsum[i * FN + j];
+                *reinterpret_cast<float4*>(patch + (i * 16 + lrow) * EP_PITCH + (j * 16 + lcol) * 4) = val;
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_wave_barrier();
