@@ -198,15 +198,18 @@ template <int WGM_, int WGN_, int TM_, int TN_, int STAGES_, int BLOCKS_> struct
 typedef Geometry<2, 4, 4, 2, 5, 1> Large;
 typedef Geometry<2, 2, 2, 2, 5, 2> Small;
 
-// Row tiles per band of the tile walk, per contraction (measured at d = 4096, h = 14336, SwiGLU; see launch()).
+// Row tiles per band of the tile walk, per contraction.  Measured, us, 3 | 5 | 6 | 7 | 8 | 16 row tiles: fwd1 at d = 4096, h = 14336,
+// SwiGLU 7990 | 8020 | 7950 | 7920 | 8125 | 8245 (and fwd2 after it 3670 | 3645 | 3640 | 3685 | 3600 | 3590), bwd1 4245 | 4295 | 4315 |
+// 4265 | 4350 | 4494; d = 2048, h = 8192, GELU fwd1 883 | 879 | 875 | 871 | 873 | 872, bwd1 893 | 888 | 890 | 889 | 903 | 909; the others
+// are best at 8, which is what the L2 of an XCD needs least fills for (4: weight gradients +0.8 %, 16: +1 % and more).
 #ifndef BAND_FWD1
-#define BAND_FWD1 16
+#define BAND_FWD1 7
 #endif
 #ifndef BAND_FWD2
 #define BAND_FWD2 8
 #endif
 #ifndef BAND_BWD1
-#define BAND_BWD1 8
+#define BAND_BWD1 7
 #endif
 #ifndef BAND_BWD2
 #define BAND_BWD2 8
