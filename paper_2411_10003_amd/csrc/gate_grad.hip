@@ -45,7 +45,7 @@ __device__ __forceinline__ void unpack_bf16x8(const uint4& v, float* f)
 typedef __attribute__((ext_vector_type(4))) float ig_f32x4_t;
 
 // waves per SIMD the compiler is held to: 4, 3 with two row pieces requested ahead, 2 where the row pieces (16 KMAX registers) or the LDS leave no room for that
-template <typename ET, int NE, int KMAX>
+template <typename ET, int NE, int KMAX, bool NT>
 __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? (NE == 4 && KMAX == 2 ? 3 : 4) : 2) void input_grad_kernel(
     const ET* __restrict__ dXp, const int32_t* __restrict__ pos, const float* __restrict__ dlogits,
     const float* __restrict__ Wg, ET* __restrict__ dX, int T, int d, int E, int k, int groups_per_wave, int vec)
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? (NE == 4 && KMAX == 2 ? 
             for (int j = 0; j < KMAX; ++j) {
                 const int row = pos[(size_t)t * k + (j < k ? j : 0)];
                 lowest = min(lowest, row);
-                to[r][j] = *reinterpret_cast<const raw_t*>(dXp + (size_t)max(row, 0) * d + cc);
+                to[r][j] = load_piece_of<NT>(reinterpret_cast<const raw_t*>(dXp + (size_t)max(row, 0) * d + cc));
             }
         }
         if (__any(lowest < 0))
@@ -193,11 +193,11 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? (NE == 4 && KMAX == 2 ? 
             for (int i = 0; i < VN; ++i) sum[i] += acc[i][r];
             if (t >= T || c >= d) continue;
             if constexpr (sizeof(ET) == 2) {
-                *reinterpret_cast<uint4*>(dX + (size_t)t * d + c) =
+                store_piece_of<NT>(reinterpret_cast<uint4*>(dX + (size_t)t * d + c),
                     make_uint4(pack_bf16x2(sum[0], sum[1]), pack_bf16x2(sum[2], sum[3]),
-                               pack_bf16x2(sum[4 % VN], sum[5 % VN]), pack_bf16x2(sum[6 % VN], sum[7 % VN]));
+                               pack_bf16x2(sum[4 % VN], sum[5 % VN]), pack_bf16x2(sum[6 % VN], sum[7 % VN])));
             } else {
-                *reinterpret_cast<float4*>(dX + (size_t)t * d + c) = make_float4(sum[0], sum[1], sum[2], sum[3]);
+                store_piece_of<NT>(reinterpret_cast<float4*>(dX + (size_t)t * d + c), make_float4(sum[0], sum[1], sum[2], sum[3]));
             }
         }
         if constexpr (PREFETCH)
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256, KMAX <= 2 && NE < 8 ? (NE == 4 && KMAX == 2 ? 
 // 1984, E = 8: 13.5 | 4 -> 5.7 | 2.8.  (The sum's bias took its partitions one by one and was what the launch waited for.)
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
-template <typename ET, int VN, int NE, int CS>
+template <typename ET, int VN, int NE, int CS, bool NT>
 __global__ __launch_bounds__(256, sizeof(ET) == 2 ? 4 : 2) void gate_wgrad_mfma_kernel(
     const ET* __restrict__ X, const float* __restrict__ dlogits, float* __restrict__ partial,
     float* __restrict__ partial_b, int T, int d, int E, int tok_per_part)
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(256, sizeof(ET) == 2 ? 4 : 2) void gate_wgrad_mfma_
 #pragma unroll
                 for (int n = 0; n < NE; ++n) dl[u][n] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rd, voff_dl[n], 16 * u * E * 4, 0));
 #pragma unroll
-                for (int s = 0; s < CS; ++s) raw[u][s] = __builtin_bit_cast(raw_t, __builtin_amdgcn_raw_buffer_load_b128(rx, voff_x[s], 16 * u * d * 2, 0));
+                for (int s = 0; s < CS; ++s) raw[u][s] = __builtin_bit_cast(raw_t, __builtin_amdgcn_raw_buffer_load_b128(rx, voff_x[s], 16 * u * d * 2, NT ? 2 : 0));
             }
         } else {
 #pragma unroll
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(256, sizeof(ET) == 2 ? 4 : 2) void gate_wgrad_mfma_
 #pragma unroll
                 for (int s = 0; s < CS; ++s) {
                     const int c = c0 + s * SW + li * VN;
-                    raw[u][s] = *reinterpret_cast<const raw_t*>(X + (size_t)t * d + (c < d ? c : 0));
+                    raw[u][s] = load_piece_of<NT>(reinterpret_cast<const raw_t*>(X + (size_t)t * d + (c < d ? c : 0)));
                 }
             }
         }
@@ -396,9 +396,13 @@ hipError_t launch_wgrad_mfma_t(const moe_shape_t& s, const void* X, const float*
     const int cw = CS * 16 * VN;
     if (cw != wgrad_columns(s) || 16 * NE != wgrad_experts(s)) return hipErrorInvalidValue;
     const dim3 grid((s.d + cw - 1) / cw, n_part, (s.E + 16 * NE - 1) / (16 * NE));
-    hipLaunchKernelGGL((gate_wgrad_mfma_kernel<ET, VN, NE, CS>), grid, dim3(256), 0, st, (const ET*)X, dlogits, partial,
-                       partial_b, s.T, s.d, s.E, tok_per_part);
-    return hipGetLastError();
+    // X for the last time, and once: further blocks of experts find it in the caches
+    auto launch = [&](auto NT) {
+        hipLaunchKernelGGL((gate_wgrad_mfma_kernel<ET, VN, NE, CS, decltype(NT)::value>), grid, dim3(256), 0, st, (const ET*)X, dlogits, partial,
+                           partial_b, s.T, s.d, s.E, tok_per_part);
+        return hipGetLastError();
+    };
+    return grid.z == 1 && streams((size_t)s.T * s.d * sizeof(ET)) ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 // N partials (FULL) or the n < N that are left, all loads on their way at once, added to four sums: one after the other, 64 partials
@@ -476,9 +480,12 @@ hipError_t launch_input_grad_t(const moe_shape_t& s, const void* dXp, const int3
     gpw = gpw < 1 ? 1 : (gpw > 8 ? 8 : gpw);
     const dim3 grid(strips, (unsigned)((t64 + gpw - 1) / gpw));
     const int vec = s.E % 4 == 0 && ((reinterpret_cast<uintptr_t>(Wg) | reinterpret_cast<uintptr_t>(dlogits)) & 15) == 0;
-    hipLaunchKernelGGL((input_grad_kernel<ET, NE, KMAX>), grid, dim3(256), lds, st, (const ET*)dXp, pos, dlogits, Wg,
-                       (ET*)dX, s.T, s.d, s.E, s.k, (int)gpw, vec);
-    return hipGetLastError();
+    auto launch = [&](auto NT) {
+        hipLaunchKernelGGL((input_grad_kernel<ET, NE, KMAX, decltype(NT)::value>), grid, dim3(256), lds, st, (const ET*)dXp, pos, dlogits, Wg,
+                           (ET*)dX, s.T, s.d, s.E, s.k, (int)gpw, vec);
+        return hipGetLastError();
+    };
+    return streams((size_t)s.T * s.d * sizeof(ET)) ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 template <typename ET, int NE>

@@ -40,6 +40,30 @@ constexpr int ROUTE_CHUNK = 256;
 
 typedef uint16_t bf16_t;  // storage only
 
+// Rows that are written once and are many more than the caches between here and HBM can keep until they are read (256 MB on the
+// memory side, shared with everything else that passes) go out by nontemporal stores, and with them what is read for the last time:
+// left dirty in those caches they are written back under the next kernel's reads.  T = 32768, d = 4096, k = 2: dispatch 126 -> 119 us
+// and the gate that follows 88 -> 52; T = 16384, d = 2048, k = 2, inputs that change from pass to pass: combine, its gradient, the
+// gate's gradients and the input gradient 182 -> 169 us; T = 8001, d = 2048, k = 4: gate to dispatch 95 -> 89.  The line: at 34 MB
+// (dispatch of T = 8192, d = 1024, k = 2, the experts reading the rows at once) 230.5 us a pass with plain stores, 232.4 without;
+// from 64 MB on no pass has been slower.
+constexpr size_t STREAM_BYTES = (size_t)64 << 20;
+inline bool streams(size_t bytes) { return bytes >= STREAM_BYTES; }
+typedef unsigned moe_piece_t __attribute__((ext_vector_type(4)));
+// 16 bytes, by a plain or a nontemporal access
+template <bool NT, typename V> __device__ __forceinline__ V load_piece_of(const V* p)
+{
+    static_assert(sizeof(V) == 16, "16 bytes");
+    if constexpr (NT) return __builtin_bit_cast(V, __builtin_nontemporal_load(reinterpret_cast<const moe_piece_t*>(p)));
+    else return *p;
+}
+template <bool NT, typename V> __device__ __forceinline__ void store_piece_of(V* p, const V& v)
+{
+    static_assert(sizeof(V) == 16, "16 bytes");
+    if constexpr (NT) __builtin_nontemporal_store(__builtin_bit_cast(moe_piece_t, v), reinterpret_cast<moe_piece_t*>(p));
+    else *p = v;
+}
+
 // MOE_OK, or MOE_ERR_HIP with the error remembered for moe_last_hip_error() (per thread).
 int moe_hip_status(hipError_t e);
 

@@ -7,6 +7,8 @@
 // (1 + k) * T * d elements.  Lanes move 16 bytes per access.
 #include "internal.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr int ROW_WAVES = 4;   // tokens per block
@@ -41,7 +43,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 // Xp[pos[t*k+j], :] = X[t, :]
-template <typename ET>
+template <typename ET, bool NT>
 __global__ __launch_bounds__(ROW_WAVES * 64) void scatter_rows_kernel(
     const ET* __restrict__ X, const int32_t* __restrict__ pos, ET* __restrict__ Xp, int T, int d, int k)
 {
@@ -55,12 +57,12 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void scatter_rows_kernel(
         // the row is re-read from cache for j > 0; HBM sees it once
         uint4* dst = reinterpret_cast<uint4*>(Xp + (size_t)pos[(size_t)t * k + j] * d);
 #pragma unroll 4
-        for (int v = lane; v < nv; v += 64) dst[v] = src[v];
+        for (int v = lane; v < nv; v += 64) store_piece_of<NT>(dst + v, src[v]);
     }
 }
 
 // K-specialised variant: every 16-byte piece is loaded once and stored K times.
-template <typename ET, int K>
+template <typename ET, int K, bool NT>
 __global__ __launch_bounds__(ROW_WAVES * 64) void scatter_rows_k_kernel(
     const ET* __restrict__ X, const int32_t* __restrict__ pos, ET* __restrict__ Xp, int T, int d)
 {
@@ -77,7 +79,7 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void scatter_rows_k_kernel(
     for (int v = lane; v < nv; v += 64) {
         const uint4 x = src[v];
 #pragma unroll
-        for (int j = 0; j < K; ++j) dst[j][v] = x;
+        for (int j = 0; j < K; ++j) store_piece_of<NT>(dst[j] + v, x);
     }
 }
 
@@ -85,7 +87,7 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void scatter_rows_k_kernel(
 // Bound by HBM: what counts is how many pieces of a token's rows are on their way.  KT is k where it is 1, 2 or 4 (bf16);
 // with any k in one loop every row is a branch and one piece of each row is out at a time: k = 4, T = 8000, d = 4096 83 -> 62 us
 // (caches swept 125 -> 110), T = 8001, d = 2048 27 -> 25 (71 -> 61).  The scatter gains nothing from more registers: k = 8 97 -> 100.
-template <typename ET, int KT>
+template <typename ET, int KT, bool NT>
 __global__ __launch_bounds__(ROW_WAVES * 64) void combine_kernel(
     const ET* __restrict__ Yp, const int32_t* __restrict__ pos, const float* __restrict__ w,
     ET* __restrict__ out, int T, int d, int k_rt)
@@ -130,13 +132,13 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void combine_kernel(
                     for (int i = 0; i < VN; ++i) acc[i] = fmaf(wj[j], y[i], acc[i]);
                 }
             }
-            dst[v0 + 64 * u] = Vec<ET>::pack(acc);
+            store_piece_of<NT>(dst + v0 + 64 * u, Vec<ET>::pack(acc));
         }
     }
 }
 
 // dYp[pos[a],:] = w[a] * dOut[t,:] ;  dw[t,j] = <dOut[t,:], Yp[pos[a],:]>
-template <typename ET, int KT>
+template <typename ET, int KT, bool NT>
 __global__ __launch_bounds__(ROW_WAVES * 64) void combine_bwd_kernel(
     const ET* __restrict__ dOut, const ET* __restrict__ Yp, const int32_t* __restrict__ pos,
     const float* __restrict__ w, ET* __restrict__ dYp, float* __restrict__ dw, int T, int d, int k_rt)
@@ -168,10 +170,10 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void combine_bwd_kernel(
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (v0 + 64 * u < nv) {
-                graw[u] = gsrc[v0 + 64 * u];
+                graw[u] = load_piece_of<NT>(gsrc + v0 + 64 * u);
 #pragma unroll
                 for (int j = 0; j < KMAX; ++j)
-                    if (j < k) yraw[u][j] = ysrc[j][v0 + 64 * u];
+                    if (j < k) yraw[u][j] = load_piece_of<NT>(ysrc[j] + v0 + 64 * u);
             }
         }
 #pragma unroll
@@ -186,7 +188,7 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void combine_bwd_kernel(
                     Vec<ET>::unpack(yraw[u][j], y);
 #pragma unroll
                     for (int i = 0; i < VN; ++i) { dot[j] = fmaf(g[i], y[i], dot[j]); o[i] = wj[j] * g[i]; }
-                    gdst[j][v0 + 64 * u] = Vec<ET>::pack(o);
+                    store_piece_of<NT>(gdst[j] + v0 + 64 * u, Vec<ET>::pack(o));
                 }
             }
         }
@@ -201,7 +203,7 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void combine_bwd_kernel(
 }
 
 // dX[t,:] = sum_j dXp[pos[t*k+j],:]
-template <typename ET, int KT>
+template <typename ET, int KT, bool NT>
 __global__ __launch_bounds__(ROW_WAVES * 64) void dispatch_bwd_kernel(
     const ET* __restrict__ dXp, const int32_t* __restrict__ pos, ET* __restrict__ dX, int T, int d, int k_rt)
 {
@@ -240,7 +242,7 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void dispatch_bwd_kernel(
                     for (int i = 0; i < VN; ++i) acc[i] += y[i];
                 }
             }
-            dst[v0 + 64 * u] = Vec<ET>::pack(acc);
+            store_piece_of<NT>(dst + v0 + 64 * u, Vec<ET>::pack(acc));
         }
     }
 }
@@ -263,6 +265,8 @@ hipError_t for_token_parts(const moe_shape_t& s, LAUNCH launch)
     return e;
 }
 inline size_t row_bytes(const moe_shape_t& s) { return (size_t)s.d * (s.dtype == MOE_BF16 ? 2 : 4); }
+// bytes: those written
+template <typename F> hipError_t by_size(size_t bytes, F launch) { return streams(bytes) ? launch(std::true_type{}) : launch(std::false_type{}); }
 inline const void* at(const void* p, size_t bytes) { return (const char*)p + bytes; }
 inline void* at(void* p, size_t bytes) { return (char*)p + bytes; }
 
@@ -270,82 +274,94 @@ inline void* at(void* p, size_t bytes) { return (char*)p + bytes; }
 
 hipError_t launch_scatter_rows(const moe_shape_t& all, const void* X0, const int32_t* pos0, void* Xp, hipStream_t st)
 {
+    return by_size((size_t)all.T * all.k * row_bytes(all), [&](auto NT) {
     return for_token_parts(all, [&](size_t t0, const moe_shape_t& s) {
+        constexpr bool nt = decltype(NT)::value;
         const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
         const void* X = at(X0, t0 * row_bytes(s));
         const int32_t* pos = pos0 + t0 * s.k;
         if (s.dtype == MOE_F32)
-            hipLaunchKernelGGL(scatter_rows_kernel<float>, g, b, 0, st, (const float*)X, pos, (float*)Xp, s.T, s.d, s.k);
+            hipLaunchKernelGGL((scatter_rows_kernel<float, nt>), g, b, 0, st, (const float*)X, pos, (float*)Xp, s.T, s.d, s.k);
         else if (s.k == 1)
-            hipLaunchKernelGGL((scatter_rows_k_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d);
+            hipLaunchKernelGGL((scatter_rows_k_kernel<bf16_t, 1, nt>), g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d);
         else if (s.k == 2)
-            hipLaunchKernelGGL((scatter_rows_k_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d);
+            hipLaunchKernelGGL((scatter_rows_k_kernel<bf16_t, 2, nt>), g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d);
         else
-            hipLaunchKernelGGL(scatter_rows_kernel<bf16_t>, g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d, s.k);
+            hipLaunchKernelGGL((scatter_rows_kernel<bf16_t, nt>), g, b, 0, st, (const bf16_t*)X, pos, (bf16_t*)Xp, s.T, s.d, s.k);
+    });
     });
 }
 
 hipError_t launch_combine(const moe_shape_t& all, const void* Yp, const int32_t* pos0, const float* w0, void* out0, hipStream_t st)
 {
+    return by_size((size_t)all.T * row_bytes(all), [&](auto NT) {
     return for_token_parts(all, [&](size_t t0, const moe_shape_t& s) {
+        constexpr bool nt = decltype(NT)::value;
         const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
         const int32_t* pos = pos0 + t0 * s.k;
         const float* w = w0 + t0 * s.k;
         void* out = at(out0, t0 * row_bytes(s));
         if (s.dtype == MOE_F32)
-            hipLaunchKernelGGL((combine_kernel<float, 0>), g, b, 0, st, (const float*)Yp, pos, w, (float*)out, s.T, s.d, s.k);
+            hipLaunchKernelGGL((combine_kernel<float, 0, nt>), g, b, 0, st, (const float*)Yp, pos, w, (float*)out, s.T, s.d, s.k);
         else if (s.k == 1)
-            hipLaunchKernelGGL((combine_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
+            hipLaunchKernelGGL((combine_kernel<bf16_t, 1, nt>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
         else if (s.k == 2)
-            hipLaunchKernelGGL((combine_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
+            hipLaunchKernelGGL((combine_kernel<bf16_t, 2, nt>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
         else if (s.k == 4)
-            hipLaunchKernelGGL((combine_kernel<bf16_t, 4>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
+            hipLaunchKernelGGL((combine_kernel<bf16_t, 4, nt>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
         else
-            hipLaunchKernelGGL((combine_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
+            hipLaunchKernelGGL((combine_kernel<bf16_t, 0, nt>), g, b, 0, st, (const bf16_t*)Yp, pos, w, (bf16_t*)out, s.T, s.d, s.k);
+    });
     });
 }
 
 hipError_t launch_combine_bwd(const moe_shape_t& all, const void* dOut0, const void* Yp, const int32_t* pos0,
                               const float* w0, void* dYp, float* dw0, hipStream_t st)
 {
+    return by_size((size_t)all.T * all.k * row_bytes(all), [&](auto NT) {
     return for_token_parts(all, [&](size_t t0, const moe_shape_t& s) {
+        constexpr bool nt = decltype(NT)::value;
         const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
         const void* dOut = at(dOut0, t0 * row_bytes(s));
         const int32_t* pos = pos0 + t0 * s.k;
         const float* w = w0 + t0 * s.k;
         float* dw = dw0 + t0 * s.k;
         if (s.dtype == MOE_F32)
-            hipLaunchKernelGGL((combine_bwd_kernel<float, 0>), g, b, 0, st, (const float*)dOut, (const float*)Yp, pos, w,
+            hipLaunchKernelGGL((combine_bwd_kernel<float, 0, nt>), g, b, 0, st, (const float*)dOut, (const float*)Yp, pos, w,
                                (float*)dYp, dw, s.T, s.d, s.k);
         else if (s.k == 1)
-            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
+            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 1, nt>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
                                (bf16_t*)dYp, dw, s.T, s.d, s.k);
         else if (s.k == 2)
-            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
+            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 2, nt>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
                                (bf16_t*)dYp, dw, s.T, s.d, s.k);
         else if (s.k == 4)
-            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 4>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
+            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 4, nt>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
                                (bf16_t*)dYp, dw, s.T, s.d, s.k);
         else
-            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
+            hipLaunchKernelGGL((combine_bwd_kernel<bf16_t, 0, nt>), g, b, 0, st, (const bf16_t*)dOut, (const bf16_t*)Yp, pos, w,
                                (bf16_t*)dYp, dw, s.T, s.d, s.k);
+    });
     });
 }
 
 hipError_t launch_dispatch_bwd(const moe_shape_t& all, const void* dXp, const int32_t* pos0, void* dX0, hipStream_t st)
 {
+    return by_size((size_t)all.T * row_bytes(all), [&](auto NT) {
     return for_token_parts(all, [&](size_t t0, const moe_shape_t& s) {
+        constexpr bool nt = decltype(NT)::value;
         const dim3 g = row_grid(s.T), b(ROW_WAVES * 64);
         const int32_t* pos = pos0 + t0 * s.k;
         void* dX = at(dX0, t0 * row_bytes(s));
         if (s.dtype == MOE_F32)
-            hipLaunchKernelGGL((dispatch_bwd_kernel<float, 0>), g, b, 0, st, (const float*)dXp, pos, (float*)dX, s.T, s.d, s.k);
+            hipLaunchKernelGGL((dispatch_bwd_kernel<float, 0, nt>), g, b, 0, st, (const float*)dXp, pos, (float*)dX, s.T, s.d, s.k);
         else if (s.k == 1)
-            hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 1>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
+            hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 1, nt>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
         else if (s.k == 2)
-            hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 2>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
+            hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 2, nt>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
         else
-            hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 0>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
+            hipLaunchKernelGGL((dispatch_bwd_kernel<bf16_t, 0, nt>), g, b, 0, st, (const bf16_t*)dXp, pos, (bf16_t*)dX, s.T, s.d, s.k);
+    });
     });
 }
 
