@@ -285,10 +285,15 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* base, long long bytes)
 // goes through M0); bytes past the end of the buffer arrive as zeros.  Issued as assembly so that
 // the compiler does not serialise later LDS reads of other ring slots behind it; completion is
 // tracked by hand with WAIT_VMCNT before the barrier that publishes the slot.
+template <bool NT = false>
 __device__ __forceinline__ void dma16(rsrc_t r, uint32_t lds_base, uint32_t voff, uint32_t soff)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_base), "v"(voff), "s"(r), "s"(soff) : "memory");
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                     :: "s"(lds_base), "v"(voff), "s"(r), "s"(soff) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     :: "s"(lds_base), "v"(voff), "s"(r), "s"(soff) : "memory");
 }
 
 #define WAIT_VMCNT(n) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(n) : "memory")
@@ -298,7 +303,10 @@ __device__ __forceinline__ void dma16(rsrc_t r, uint32_t lds_base, uint32_t voff
 // ---- the kernel ---------------------------------------------------------------------------------
 // LAST: tiles may be cut unevenly.  Contractions that are too short for it run without that code (d = 256, h = 896, 80 rows: 0.5 and
 // 0.8 us of 14 and 12 more with it).
-template <int KIND, int EPI, bool FIN, class GEO, bool LAST>
+// ONCE: a group has one row tile at most, so a weight is read by one block only and need not stay in the caches: nontemporal
+// requests (64 tokens, d = 4096, h = 14336, SwiGLU, 1.4 GB of weights: the pass 294 -> 281 us, fwd2 86 -> 79; where several row tiles
+// share a weight in L2 these requests take 1.8 times as long).
+template <int KIND, int EPI, bool FIN, class GEO, bool LAST, bool ONCE>
 __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void grouped_gemm_kernel(const GemmParams p)
 {
     constexpr int WGN = GEO::WGN, NWAVES = GEO::NWAVES, WM = GEO::WM, WN = GEO::WN, BM = GEO::BM, BN = GEO::BN, TM = GEO::TM, TN = GEO::TN;
@@ -633,7 +641,7 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     constexpr int SLICE_OPS = PA + PB;                     // of one wave
     auto request_piece = [&](int n, uint32_t st, const rsrc_t ra, const rsrc_t rb0, const rsrc_t rb1, uint32_t oa, uint32_t ob) {
         if (n < PA) dma16(ra, st + ldsA[n], voffA[n], oa);
-        else dma16((DUAL && ((n - PA) & 1)) ? rb1 : rb0, st + A_BYTES + ldsB[n - PA], voffB[n - PA], ob);
+        else dma16<ONCE>((DUAL && ((n - PA) & 1)) ? rb1 : rb0, st + A_BYTES + ldsB[n - PA], voffB[n - PA], ob);
     };
     auto next_stage = [&]() { iss_stage = (iss_stage + 1 == STAGES) ? 0 : iss_stage + 1; };
     auto slice_done = [&]() { next_stage(); ++iss_in_seg; soffA += stepA; soffB += stepB; };
@@ -1367,19 +1375,19 @@ hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, bool finis
     static std::atomic<int> cus_of[64];
     const int dev = current_device();
     int cus = (dev >= 0 && dev < 64) ? cus_of[dev].load(std::memory_order_acquire) : 0;
-    auto kern = grouped_gemm_kernel<KIND, EPI, false, GEO, false>;
-    auto kern_last = grouped_gemm_kernel<KIND, EPI, false, GEO, last_finishes(EPI)>;
-    auto kern_fin = grouped_gemm_kernel<KIND, EPI, true, GEO, false>;
+    auto kern = grouped_gemm_kernel<KIND, EPI, false, GEO, false, false>;
+    auto kern_last = grouped_gemm_kernel<KIND, EPI, false, GEO, last_finishes(EPI), false>;
+    auto kern_once = grouped_gemm_kernel<KIND, EPI, false, GEO, false, KIND == KIND_NN>;
+    auto kern_last_once = grouped_gemm_kernel<KIND, EPI, false, GEO, last_finishes(EPI), KIND == KIND_NN>;
+    auto kern_fin = grouped_gemm_kernel<KIND, EPI, true, GEO, false, false>;
     if (!once.is_done(dev) || cus == 0) {
         int n = 0;
         if (dev < 0 || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
         cus = n / 8 * 8;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern_last), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern_fin), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
-        if (e != hipSuccess) return e;
+        for (auto k : {kern, kern_last, kern_once, kern_last_once, kern_fin}) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
+            if (e != hipSuccess) return e;
+        }
         if (dev >= 0 && dev < 64) cus_of[dev].store(cus, std::memory_order_release);
         once.mark(dev);
     }
@@ -1387,7 +1395,8 @@ hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, bool finis
     p.tn_over = TN_OVER<GEO>;
     p.split_max = SPLIT_MAX<GEO>;
     p.split_cap = SPLIT_CAP<GEO>;
-    hipLaunchKernelGGL(p.uneven_cap > 0 ? kern_last : kern, dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
+    const bool one_tile = KIND == KIND_NN && rows_upper <= BM;        // all rows there can be: the forward pass of a decoding step
+    hipLaunchKernelGGL(one_tile ? (p.uneven_cap > 0 ? kern_last_once : kern_once) : (p.uneven_cap > 0 ? kern_last : kern), dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !finish) return e;
     // the tiles of split contractions: add their parts, run their epilogues
