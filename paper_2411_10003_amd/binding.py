@@ -6,6 +6,7 @@ the library has not been built, `load()` raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Dict, Optional
 
@@ -13,6 +14,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmoehot.so")
+PYCALL_PATH = os.path.join(_HERE, "_pycall.so")
 
 MOE_F32, MOE_BF16 = 0, 1
 MOE_ACT_GELU, MOE_ACT_SWIGLU = 0, 1
@@ -55,7 +57,7 @@ class _PlanOut(ctypes.Structure):
 
 
 _raw_stream, _current_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
-_lib = None
+_lib = _pycall = None
 
 
 def load() -> ctypes.CDLL:
@@ -96,6 +98,18 @@ def load() -> ctypes.CDLL:
         lib.moe_plan.argtypes = [ctypes.POINTER(_Planner), vp, ctypes.POINTER(_PlanOut), vp]
         _lib = lib
     return _lib
+
+
+def _native():
+    """The module of the native calls."""
+    global _pycall
+    if _pycall is None:
+        if not os.path.exists(PYCALL_PATH):
+            raise ImportError(f"{PYCALL_PATH} is not built; run `python -m paper_2411_10003_amd.build`")
+        spec = importlib.util.spec_from_file_location("_pycall", PYCALL_PATH)
+        _pycall = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(_pycall)
+    return _pycall
 
 
 def _ptr(t: Optional[torch.Tensor], dtype: torch.dtype, numel: int, name: str) -> Optional[int]:
@@ -190,6 +204,46 @@ class Layout:
                                                   self.dest_slots, self.pos, self.perm)))
 
 
+# What stands at the arguments of each entry point between the handle and the stream: tensors by dtype, least number of elements and
+# name; "int" an address that is given at the call.  (e: the handle's element type, f and i: fp32 and int32, m: all weights of a kind.)
+# One native call object per handle and entry point.
+def _dispatch_spec(s, e, f, i, m):
+    return (i, s.E, "expert_dest"), (e, s.T * s.d, "X"), (i, s.A, "idx"), (i, s.E, "counts"), "int", (e, s.A * s.d, "Xp"), "int"
+
+
+def _bwd_spec(s, e, f, i, m):
+    rows, hidden = s.A * s.d, s.A * s.h
+    return ((e, rows, "dYp"), (e, rows, "Xp"), (e, hidden, "Z"), (e, hidden, "U"), "int", (e, m, "W1"), (e, m, "W2"), (e, m, "W3"), (e, rows, "dXp"),
+            (f, m, "dW1"), (f, m, "dW2"), (f, m, "dW3"), "int")
+
+
+_SPECS = {
+    "moe_gate_topk": lambda s, e, f, i, m: ((e, s.T * s.d, "X"), (f, s.d * s.E, "Wg"), (f, s.E, "bg"), (f, s.T * s.E, "logits"), (i, s.A, "idx"), (f, s.A, "w")),
+    "moe_expert_counts": lambda s, e, f, i, m: ((i, s.A, "idx"), (i, s.E, "counts"), "int"),
+    "moe_dispatch": _dispatch_spec,
+    "moe_dispatch_after_counts": _dispatch_spec,
+    "moe_expert_ffn_fwd": lambda s, e, f, i, m: ((e, s.A * s.d, "Xp"), "int", (e, m, "W1"), (e, m, "W2"), (e, m, "W3"), (e, s.A * s.d, "Yp"),
+                                                 (e, s.A * s.h, "Z"), (e, s.A * s.h, "U"), "int"),
+    "moe_combine": lambda s, e, f, i, m: ((e, s.A * s.d, "Yp"), (i, s.A, "pos"), (f, s.A, "w"), (e, s.T * s.d, "out")),
+    "moe_combine_bwd": lambda s, e, f, i, m: ((e, s.T * s.d, "dOut"), (e, s.A * s.d, "Yp"), (i, s.A, "pos"), (f, s.A, "w"), (e, s.A * s.d, "dYp"),
+                                              (f, s.A, "dw")),
+    "moe_expert_ffn_bwd": _bwd_spec,
+    "moe_expert_ffn_bwd_acc": _bwd_spec,
+    "moe_dispatch_bwd": lambda s, e, f, i, m: ((e, s.A * s.d, "dXp"), (i, s.A, "pos"), (e, s.T * s.d, "dX")),
+    "moe_gate_bwd": lambda s, e, f, i, m: ((f, s.A, "dw"), (f, s.T * s.E, "logits"), (i, s.A, "idx"), (f, s.T * s.E, "dlogits")),
+    "moe_gate_bwd_params": lambda s, e, f, i, m: ((e, s.T * s.d, "X"), (f, s.T * s.E, "dlogits"), (f, s.d * s.E, "dWg"), (f, s.E, "dbg"), "int"),
+    "moe_input_grad": lambda s, e, f, i, m: ((e, s.A * s.d, "dXp"), (i, s.A, "pos"), (f, s.T * s.E, "dlogits"), (f, s.d * s.E, "Wg"), (e, s.T * s.d, "dX")),
+}
+_entries: Dict[str, int] = {}
+
+
+def _entry(name: str) -> int:
+    """The address of an entry point."""
+    if name not in _entries:
+        _entries[name] = ctypes.cast(getattr(load(), name), ctypes.c_void_p).value
+    return _entries[name]
+
+
 class Handle:
     """A moe_handle_t plus its workspace.  Methods carry the names of the C entry points."""
 
@@ -208,9 +262,11 @@ class Handle:
         self._check(self.lib.moe_workspace_bytes(self._h, ctypes.byref(n)), "moe_workspace_bytes")
         self.workspace_bytes = n.value
         self.ws = torch.empty(n.value, dtype=torch.uint8, device=self.device) if alloc_workspace else None
+        self._calls: Dict[str, object] = {}
 
     def close(self):
         if self._h:
+            self._calls = {}                               # they hold its address
             self.lib.moe_destroy(self._h)
             self._h = ctypes.c_void_p()
 
@@ -241,17 +297,22 @@ class Handle:
         self._check(self.lib.moe_read_status(self._h, self._ws(), _stream(), ctypes.byref(v)), "moe_read_status")
         return v.value
 
+    def _spec(self, name: str):
+        return _SPECS[name](self, self.elt, torch.float32, torch.int32, self.G * self.d * self.h)
+
+    def _call(self, name: str, *args):
+        call = self._calls.get(name)
+        if call is None:
+            call = self._calls[name] = _native().Call(_entry(name), (self._h.value or 0, *self._spec(name), "int"), _ptr)
+        rc = call(*args, _stream())
+        if rc != 0:
+            self._check(rc, name)
+
     def gate_topk(self, X, Wg, bg, logits, idx, w):
-        f32, i32 = torch.float32, torch.int32
-        self._check(self.lib.moe_gate_topk(
-            self._h, _ptr(X, self.elt, self.T * self.d, "X"), _ptr(Wg, f32, self.d * self.E, "Wg"),
-            _ptr(bg, f32, self.E, "bg"), _ptr(logits, f32, self.T * self.E, "logits"),
-            _ptr(idx, i32, self.A, "idx"), _ptr(w, f32, self.A, "w"), _stream()), "moe_gate_topk")
+        self._call("moe_gate_topk", X, Wg, bg, logits, idx, w)
 
     def expert_counts(self, idx, counts):
-        i32 = torch.int32
-        self._check(self.lib.moe_expert_counts(self._h, _ptr(idx, i32, self.A, "idx"), _ptr(counts, i32, self.E, "counts"),
-                                               self._ws(), _stream()), "moe_expert_counts")
+        self._call("moe_expert_counts", idx, counts, self._ws())
 
     def expert_counts_static(self, idx, counts):
         i32 = torch.int32
@@ -259,13 +320,8 @@ class Handle:
                                                       _stream()), "moe_expert_counts_static")
 
     def dispatch(self, expert_dest, X, idx, counts, layout: Layout, Xp, after_counts: bool = False):
-        i32 = torch.int32
-        fn = self.lib.moe_dispatch_after_counts if after_counts else self.lib.moe_dispatch
-        self._check(fn(
-            self._h, _ptr(expert_dest, i32, self.E, "expert_dest"), _ptr(X, self.elt, self.T * self.d, "X"),
-            _ptr(idx, i32, self.A, "idx"), _ptr(counts, i32, self.E, "counts"), ctypes.byref(layout.c),
-            _ptr(Xp, self.elt, self.A * self.d, "Xp"), self._ws(), _stream()),
-            "moe_dispatch_after_counts" if after_counts else "moe_dispatch")
+        self._call("moe_dispatch_after_counts" if after_counts else "moe_dispatch", expert_dest, X, idx, counts,
+                   ctypes.addressof(layout.c), Xp, self._ws())
 
     def dispatch_after_counts(self, expert_dest, X, idx, counts, layout: Layout, Xp):
         self.dispatch(expert_dest, X, idx, counts, layout, Xp, after_counts=True)
@@ -274,47 +330,26 @@ class Handle:
         self._check(self.lib.moe_set_act_saved(self._h, int(bool(saved))), "moe_set_act_saved")
 
     def expert_ffn_fwd(self, Xp, layout: Layout, W1, W2, W3, Yp, Z, U):
-        e, dh = self.elt, self.G * self.d * self.h
-        self._check(self.lib.moe_expert_ffn_fwd(
-            self._h, _ptr(Xp, e, self.A * self.d, "Xp"), ctypes.byref(layout.c), _ptr(W1, e, dh, "W1"), _ptr(W2, e, dh, "W2"),
-            _ptr(W3, e, dh, "W3"), _ptr(Yp, e, self.A * self.d, "Yp"), _ptr(Z, e, self.A * self.h, "Z"),
-            _ptr(U, e, self.A * self.h, "U"), self._ws(), _stream()), "moe_expert_ffn_fwd")
+        self._call("moe_expert_ffn_fwd", Xp, ctypes.addressof(layout.c), W1, W2, W3, Yp, Z, U, self._ws())
 
     def combine(self, Yp, pos, w, out):
-        self._check(self.lib.moe_combine(
-            self._h, _ptr(Yp, self.elt, self.A * self.d, "Yp"), _ptr(pos, torch.int32, self.A, "pos"),
-            _ptr(w, torch.float32, self.A, "w"), _ptr(out, self.elt, self.T * self.d, "out"), _stream()), "moe_combine")
+        self._call("moe_combine", Yp, pos, w, out)
 
     def combine_bwd(self, dOut, Yp, pos, w, dYp, dw):
-        e = self.elt
-        self._check(self.lib.moe_combine_bwd(
-            self._h, _ptr(dOut, e, self.T * self.d, "dOut"), _ptr(Yp, e, self.A * self.d, "Yp"),
-            _ptr(pos, torch.int32, self.A, "pos"), _ptr(w, torch.float32, self.A, "w"),
-            _ptr(dYp, e, self.A * self.d, "dYp"), _ptr(dw, torch.float32, self.A, "dw"), _stream()), "moe_combine_bwd")
+        self._call("moe_combine_bwd", dOut, Yp, pos, w, dYp, dw)
 
     def expert_ffn_bwd(self, dYp, Xp, Z, U, layout: Layout, W1, W2, W3, dXp, dW1, dW2, dW3, accumulate: bool = False):
-        e, f32, dh = self.elt, torch.float32, self.G * self.d * self.h
-        fn = self.lib.moe_expert_ffn_bwd_acc if accumulate else self.lib.moe_expert_ffn_bwd
-        self._check(fn(
-            self._h, _ptr(dYp, e, self.A * self.d, "dYp"), _ptr(Xp, e, self.A * self.d, "Xp"),
-            _ptr(Z, e, self.A * self.h, "Z"), _ptr(U, e, self.A * self.h, "U"), ctypes.byref(layout.c),
-            _ptr(W1, e, dh, "W1"), _ptr(W2, e, dh, "W2"), _ptr(W3, e, dh, "W3"),
-            _ptr(dXp, e, self.A * self.d, "dXp"), _ptr(dW1, f32, dh, "dW1"), _ptr(dW2, f32, dh, "dW2"),
-            _ptr(dW3, f32, dh, "dW3"), self._ws(), _stream()), "moe_expert_ffn_bwd_acc" if accumulate else "moe_expert_ffn_bwd")
+        self._call("moe_expert_ffn_bwd_acc" if accumulate else "moe_expert_ffn_bwd", dYp, Xp, Z, U, ctypes.addressof(layout.c),
+                   W1, W2, W3, dXp, dW1, dW2, dW3, self._ws())
 
     def expert_ffn_bwd_acc(self, *args):
         self.expert_ffn_bwd(*args, accumulate=True)
 
     def dispatch_bwd(self, dXp, pos, dX):
-        self._check(self.lib.moe_dispatch_bwd(
-            self._h, _ptr(dXp, self.elt, self.A * self.d, "dXp"), _ptr(pos, torch.int32, self.A, "pos"),
-            _ptr(dX, self.elt, self.T * self.d, "dX"), _stream()), "moe_dispatch_bwd")
+        self._call("moe_dispatch_bwd", dXp, pos, dX)
 
     def gate_bwd(self, dw, logits, idx, dlogits):
-        f32 = torch.float32
-        self._check(self.lib.moe_gate_bwd(
-            self._h, _ptr(dw, f32, self.A, "dw"), _ptr(logits, f32, self.T * self.E, "logits"),
-            _ptr(idx, torch.int32, self.A, "idx"), _ptr(dlogits, f32, self.T * self.E, "dlogits"), _stream()), "moe_gate_bwd")
+        self._call("moe_gate_bwd", dw, logits, idx, dlogits)
 
     def trans(self, expert_dest, slot_expert, pools, groups, pool_version=None, slot_version=None):
         """moe_trans: gather the hosted experts' tensors from the pools into the group slots."""
@@ -354,18 +389,10 @@ class Handle:
             ctypes.byref(out.c), _stream()), "moe_recv_layout")
 
     def gate_bwd_params(self, X, dlogits, dWg, dbg):
-        f32 = torch.float32
-        self._check(self.lib.moe_gate_bwd_params(
-            self._h, _ptr(X, self.elt, self.T * self.d, "X"), _ptr(dlogits, f32, self.T * self.E, "dlogits"),
-            _ptr(dWg, f32, self.d * self.E, "dWg"), _ptr(dbg, f32, self.E, "dbg"), self._ws(), _stream()),
-            "moe_gate_bwd_params")
+        self._call("moe_gate_bwd_params", X, dlogits, dWg, dbg, self._ws())
 
     def input_grad(self, dXp, pos, dlogits, Wg, dX):
-        f32 = torch.float32
-        self._check(self.lib.moe_input_grad(
-            self._h, _ptr(dXp, self.elt, self.A * self.d, "dXp"), _ptr(pos, torch.int32, self.A, "pos"),
-            _ptr(dlogits, f32, self.T * self.E, "dlogits"), _ptr(Wg, f32, self.d * self.E, "Wg"),
-            _ptr(dX, self.elt, self.T * self.d, "dX"), _stream()), "moe_input_grad")
+        self._call("moe_input_grad", dXp, pos, dlogits, Wg, dX)
 
 
 class LayerBuffers:

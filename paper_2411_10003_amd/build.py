@@ -1,7 +1,7 @@
-"""Builds libmoehot.so (hand-written HIP for gfx950) in-tree with hipcc.
+"""Builds libmoehot.so (hand-written HIP for gfx950) in-tree with hipcc, and the binding's native calls with g++.
 
 `python -m paper_2411_10003_amd.build` compiles every translation unit of csrc/ and links the
-shared library next to this file.  hipcc cross-compiles, so no GPU is needed to build.
+shared libraries next to this file.  hipcc cross-compiles, so no GPU is needed to build.
 """
 from __future__ import annotations
 
@@ -14,6 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmoehot.so")
+PYCALL = os.path.join(HERE, "_pycall.so")
 UNITS = ["api", "gate", "gate_grad", "route", "rows", "plan", "ffn_f32", "ffn_bf16", "noalloc", "calib"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -40,10 +41,27 @@ def _compile(unit: str) -> str:
     return obj
 
 
+def _pycall() -> None:
+    """The native calls: host code only, against the headers and libraries of the torch that will load it."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-isystem{p}" for p in (*cpp_extension.include_paths(), sysconfig.get_paths()["include"])),
+           os.path.join(CSRC, "pycall.cpp"), *(f"-L{p}" for p in cpp_extension.library_paths()), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+           "-o", PYCALL]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for pycall:\n" + r.stderr)
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
+        native = ex.submit(_pycall)
         objs = list(ex.map(_compile, UNITS))
+        native.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

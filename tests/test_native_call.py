@@ -1,0 +1,61 @@
+"""The native calls of the binding: as many arguments as the entry points take, the errors of the Python check, and nothing left of a
+handle that was closed.  No GPU: no call here gets past the library's own argument checks."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2411_10003_amd import binding
+
+ENTRIES = ["moe_gate_topk", "moe_expert_counts", "moe_dispatch", "moe_dispatch_after_counts", "moe_expert_ffn_fwd", "moe_combine",
+           "moe_combine_bwd", "moe_expert_ffn_bwd", "moe_expert_ffn_bwd_acc", "moe_dispatch_bwd", "moe_gate_bwd", "moe_gate_bwd_params",
+           "moe_input_grad"]
+
+
+def _handle():
+    return binding.Handle(T=8, d=64, h=64, E=8, k=1, P=4, self_dest=0, G=2, dtype="bf16", act="swiglu", renorm=0, alloc_workspace=False)
+
+
+def _call(hd, name, handle=0):
+    entry = ctypes.cast(getattr(hd.lib, name), ctypes.c_void_p).value
+    return binding._native().Call(entry, (handle, *hd._spec(name), "int"), binding._ptr)
+
+
+@pytest.mark.parametrize("name", ENTRIES)
+def test_arguments_of_every_entry(name):
+    hd = _handle()
+    spec = hd._spec(name)
+    assert len(spec) + 2 == len(getattr(hd.lib, name).argtypes)
+    # no handle: the library refuses the call (MOE_ERR_NULL)
+    assert _call(hd, name)(*(0 if a == "int" else None for a in spec), 0) == -1
+    # tensors that are not on a device, by name, as the Python check says it
+    first = [a for a in spec if a != "int"][0]
+    with pytest.raises(ValueError, match=f"{first[2]}: need a contiguous device tensor"):
+        _call(hd, name)(*(0 if a == "int" else torch.zeros(4) for a in spec), 0)
+    with pytest.raises(TypeError):
+        _call(hd, name)(0)
+    with pytest.raises(AttributeError):
+        _call(hd, name)(*(0 if a == "int" else "no tensor" for a in spec), 0)
+    with pytest.raises(TypeError):
+        _call(hd, name)(*(None for _ in spec), None)
+
+
+def test_the_check_decides_what_is_not_plain():
+    """What the native check does not know is asked of the Python check, with the entry's own dtype, size and name."""
+    hd, asked = _handle(), []
+    entry = ctypes.cast(hd.lib.moe_gate_bwd, ctypes.c_void_p).value
+
+    def check(t, dtype, numel, name):
+        asked.append((dtype, numel, name))
+        return None
+    call = binding._native().Call(entry, (0, *hd._spec("moe_gate_bwd"), "int"), check)
+    meta = torch.zeros(64, device="meta")
+    assert call(meta, meta.t(), torch.zeros(0), None, 0) == -1
+    assert asked == [(torch.float32, 8, "dw"), (torch.float32, 64, "logits"), (torch.int32, 8, "idx")]
+
+
+def test_a_closed_handle_leaves_no_call():
+    hd = _handle()
+    hd._calls["moe_gate_bwd"] = _call(hd, "moe_gate_bwd", hd._h.value)
+    hd.close()
+    assert hd._calls == {} and not hd._h
