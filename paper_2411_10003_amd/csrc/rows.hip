@@ -416,14 +416,16 @@ __device__ __forceinline__ void move_pieces(long n, long lanes, Load load, Store
     for (int u = 0; u < MOVE_UNROLL - 1; ++u)
         if (v + u * lanes < n) store(u, v + u * lanes);
 }
-// What is read once does not have to stay in the caches, and what is written, and read next by others, does: agg of 134 MB into as
-// much 75.8 -> 61.5 us (6.5 TB/s); trans the same either way.
-typedef unsigned piece_t __attribute__((ext_vector_type(4)));
+// What is read once does not have to stay in the caches; what is written, and read next by others, does unless it is more than
+// they keep (NT).  plan, trans of 67 MB and agg of 134 MB into as much, buffers that change from pass to pass | the same buffers
+// every time: plain 118.5 | 113 us, sources past the caches 113 | 97.5, all of it 104 | 105.
+typedef moe_piece_t piece_t;
 typedef float fpiece_t __attribute__((ext_vector_type(4)));
 
 // commit: the slot's expert, written here where no versions are kept (nobody reads it then); with versions other blocks of the
 // slot still compare it, and a launch of its own writes both afterwards.  (Over 300 drawn moves of up to 67 MB
 // it was a seventh of the call; in a pass that moves 134 MB its 4.8 us of 126 are within the spread.)
+template <bool NT>
 __global__ __launch_bounds__(256) void trans_gather_kernel(
     const int32_t* __restrict__ expert_dest, const int32_t* __restrict__ pool_version,
     const int32_t* slot_expert, const int32_t* __restrict__ slot_version, int32_t* commit, const MoveArgs a, int E, int self)
@@ -438,7 +440,7 @@ __global__ __launch_bounds__(256) void trans_gather_kernel(
     const piece_t* __restrict__ src = reinterpret_cast<const piece_t*>(a.src[blockIdx.z]) + (long)e * vec_per_expert;
     piece_t* __restrict__ dst = reinterpret_cast<piece_t*>(a.dst[blockIdx.z]) + (long)g * vec_per_expert;
     piece_t r[MOVE_UNROLL];
-    move_pieces(vec_per_expert, lanes, [&](int u, long i) { r[u] = __builtin_nontemporal_load(src + i); }, [&](int u, long i) { dst[i] = r[u]; });
+    move_pieces(vec_per_expert, lanes, [&](int u, long i) { r[u] = load_piece_of<true>(src + i); }, [&](int u, long i) { store_piece_of<NT>(dst + i, r[u]); });
 }
 
 // one wave per slot
@@ -456,6 +458,7 @@ __global__ __launch_bounds__(64) void trans_commit_kernel(const int32_t* __restr
 // Agg on one GPU (Section 4.1: the gradients a replica computed are added to the expert's gradient where its
 // parameters live).  The inverse walk of the gather above: the fp32 gradient of hosted group g is added to the
 // pool entry of the expert the plan puts there.  Every element is touched by one thread: same bits every run.
+template <bool NT>
 __global__ __launch_bounds__(256) void agg_add_kernel(const int32_t* __restrict__ expert_dest, const MoveArgs a, int E, int self)
 {
     const int g = blockIdx.y;
@@ -465,7 +468,8 @@ __global__ __launch_bounds__(256) void agg_add_kernel(const int32_t* __restrict_
     const fpiece_t* __restrict__ src = reinterpret_cast<const fpiece_t*>(a.src[blockIdx.z]) + (long)g * vec_per_expert;
     fpiece_t* __restrict__ dst = reinterpret_cast<fpiece_t*>(a.dst[blockIdx.z]) + (long)e * vec_per_expert;
     fpiece_t x[MOVE_UNROLL], y[MOVE_UNROLL];
-    move_pieces(vec_per_expert, lanes, [&](int u, long i) { x[u] = __builtin_nontemporal_load(src + i); y[u] = dst[i]; }, [&](int u, long i) { dst[i] = y[u] + x[u]; });
+    move_pieces(vec_per_expert, lanes, [&](int u, long i) { x[u] = load_piece_of<true>(src + i); y[u] = load_piece_of<NT>(dst + i); },
+                [&](int u, long i) { store_piece_of<NT>(dst + i, y[u] + x[u]); });
 }
 
 // Blocks per slot and tensor: one trip of four pieces per lane up to 512 blocks (8 MB), then a longer walk.
@@ -477,6 +481,14 @@ inline unsigned move_blocks(const MoveArgs& a, int n)
     return (unsigned)(bx > 512 ? 512 : bx);
 }
 
+// Bytes written if every slot moves.
+inline size_t move_bytes(const MoveArgs& a, int n, int G)
+{
+    size_t pieces = 0;
+    for (int i = 0; i < n; ++i) pieces += (size_t)a.vec[i];
+    return pieces * 16 * G;
+}
+
 }  // namespace
 
 hipError_t launch_agg_add(const moe_shape_t& s, const int32_t* expert_dest, int n, const float* const* groups, float* const* pools,
@@ -484,8 +496,10 @@ hipError_t launch_agg_add(const moe_shape_t& s, const int32_t* expert_dest, int 
 {
     MoveArgs a{};
     for (int i = 0; i < n; ++i) { a.src[i] = (const uint4*)groups[i]; a.dst[i] = (uint4*)pools[i]; a.vec[i] = (long)(floats_per_expert[i] / 4); }
-    hipLaunchKernelGGL(agg_add_kernel, dim3(move_blocks(a, n), s.G, n), dim3(256), 0, st, expert_dest, a, s.E, s.self);
-    return hipGetLastError();
+    return by_size(move_bytes(a, n, s.G), [&](auto NT) {
+        hipLaunchKernelGGL(agg_add_kernel<decltype(NT)::value>, dim3(move_blocks(a, n), s.G, n), dim3(256), 0, st, expert_dest, a, s.E, s.self);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_trans_gather(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* pool_version,
@@ -494,9 +508,11 @@ hipError_t launch_trans_gather(const moe_shape_t& s, const int32_t* expert_dest,
 {
     MoveArgs a{};
     for (int i = 0; i < n; ++i) { a.src[i] = (const uint4*)pools[i]; a.dst[i] = (uint4*)groups[i]; a.vec[i] = (long)(bytes_per_expert[i] / 16); }
-    hipLaunchKernelGGL(trans_gather_kernel, dim3(move_blocks(a, n), s.G, n), dim3(256), 0, st, expert_dest, pool_version, slot_expert,
-                       slot_version, pool_version == nullptr ? slot_expert : nullptr, a, s.E, s.self);
-    return hipGetLastError();
+    return by_size(move_bytes(a, n, s.G), [&](auto NT) {
+        hipLaunchKernelGGL(trans_gather_kernel<decltype(NT)::value>, dim3(move_blocks(a, n), s.G, n), dim3(256), 0, st, expert_dest, pool_version, slot_expert,
+                           slot_version, pool_version == nullptr ? slot_expert : nullptr, a, s.E, s.self);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_trans_commit(const moe_shape_t& s, const int32_t* expert_dest, const int32_t* pool_version,

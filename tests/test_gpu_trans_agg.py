@@ -71,3 +71,16 @@ def test_two_tensors_into_one_pool():
     groups = torch.zeros(3, 4096, device=G.DEV)
     hd.trans(dest, torch.full((3,), -1, dtype=torch.int32, device=G.DEV), [pool, other], [groups, groups])
     assert torch.equal(groups, other[hosted])
+
+
+@pytest.mark.parametrize("n", [8388604, 8388608, 8388620])     # two slots: just under 64 MB, at it, and past it with a last short trip
+def test_streamed_moves(n):
+    E, hosted = 4, [1, 3]
+    hd, dest = _handle(E, 2), _dest(E, hosted)
+    pool, groups = torch.randn(E, n, device=G.DEV), torch.zeros(2, n, device=G.DEV)
+    hd.trans(dest, torch.full((2,), -1, dtype=torch.int32, device=G.DEV), [pool], [groups])
+    assert torch.equal(groups, pool[hosted])
+    want = pool.clone()
+    want[hosted] += groups
+    hd.agg(dest, [groups], [pool])
+    assert torch.equal(pool, want)
