@@ -46,7 +46,7 @@ typedef uint16_t bf16_t;  // storage only
 // and the gate that follows 88 -> 52; T = 16384, d = 2048, k = 2, inputs that change from pass to pass: combine, its gradient, the
 // gate's gradients and the input gradient 182 -> 169 us; T = 8001, d = 2048, k = 4: gate to dispatch 95 -> 89.  The line: at 34 MB
 // (dispatch of T = 8192, d = 1024, k = 2, the experts reading the rows at once) 230.5 us a pass with plain stores, 232.4 without;
-// from 64 MB on no pass has been slower.
+// from 64 MB on no pass has been slower (moe_dispatch_bwd, which would be, writes as ever).
 constexpr size_t STREAM_BYTES = (size_t)64 << 20;
 inline bool streams(size_t bytes) { return bytes >= STREAM_BYTES; }
 typedef unsigned moe_piece_t __attribute__((ext_vector_type(4)));
