@@ -1,11 +1,16 @@
 """The native calls of the binding: as many arguments as the entry points take, the errors of the Python check, and nothing left of a
 handle that was closed.  No GPU: no call here gets past the library's own argument checks."""
 import ctypes
+import os
 
 import pytest
 import torch
 
 from paper_2411_10003_amd import binding
+from paper_2411_10003_amd import build as hip_build
+
+if not (os.path.exists(binding.LIB_PATH) and os.path.exists(binding.PYCALL_PATH)):
+    hip_build.build()
 
 ENTRIES = ["moe_gate_topk", "moe_expert_counts", "moe_dispatch", "moe_dispatch_after_counts", "moe_expert_ffn_fwd", "moe_combine",
            "moe_combine_bwd", "moe_expert_ffn_bwd", "moe_expert_ffn_bwd_acc", "moe_dispatch_bwd", "moe_gate_bwd", "moe_gate_bwd_params",
