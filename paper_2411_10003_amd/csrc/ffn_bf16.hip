@@ -297,9 +297,7 @@ __device__ __forceinline__ void dma16(rsrc_t r, uint32_t lds_base, uint32_t voff
 // ---- the kernel ---------------------------------------------------------------------------------
 // LAST: tiles may be cut unevenly.  Contractions that are too short for it run without that code (d = 256, h = 896, 80 rows: 0.5 and
 // 0.8 us of 14 and 12 more with it).
-// ONCE: a group has one row tile at most, so a weight is read by one block only and need not stay in the caches: nontemporal
-// requests (64 tokens, d = 4096, h = 14336, SwiGLU, 1.4 GB of weights: the pass 294 -> 281 us, fwd2 86 -> 79; where several row tiles
-// share a weight in L2 these requests take 1.8 times as long).
+// ONCE: the weights are read by one block and not again while the caches keep them (read_once): nontemporal requests.
 template <int KIND, int EPI, bool FIN, class GEO, bool LAST, bool ONCE>
 __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void grouped_gemm_kernel(const GemmParams p)
 {
@@ -1347,8 +1345,24 @@ WgradPlan wgrad_plan(const moe_shape_t& s, int Mout, int N)
     return cut < whole ? WgradPlan{cut, true} : WgradPlan{whole, false};
 }
 
+// Whether the forward pass requests its weights past the caches.  A group has one row tile at most (a decoding step), so no two blocks
+// share a weight (where several row tiles do, in L2, such requests take 1.8 times as long), and the layer's weights are more than the
+// 256 MB on the memory side keep for its next call.  One layer called again, us with plain | nontemporal requests (8 tokens; 64): GELU of
+// 235 MB 80.2 | 80.8; 88.5 | 91.1, of 268 MB 91.4 | 91.7; 93.8 | 97.9, of 285 MB 88.9 | 86.8; 107.8 | 103.9, of 403 MB 111.7 | 106.5; 127.9 |
+// 117.9; SwiGLU of 252 MB 81.3 | 85.9; 111.9 | 116.2, of 302 MB 98.5 | 97.4; 106.9 | 102.6, of 1.4 GB 131 | 126; 308 | 287.  Layers of less that are
+// more than that together gain as well (four of 101 MB 67.8 | 63.6), but a layer does not know of the others, and those that fit lose (eight
+// of 25 MB 48.5 | 50.2).
+constexpr size_t MEMORY_SIDE_CACHE = (size_t)256 << 20;
+inline bool read_once(const moe_shape_t& s, int BM)
+{
+    return (long)s.T * s.k <= BM && (size_t)s.G * s.d * s.h * (s.act == MOE_ACT_SWIGLU ? 3 : 2) * sizeof(bf16_t) > MEMORY_SIDE_CACHE;
+}
+// Kernels with such requests: Large only for both weight matrices of SwiGLU.  (The cost rule takes it for nothing else of so few rows; it
+// would run with plain requests.)
+template <int KIND, int EPI, class GEO> constexpr bool HAS_ONCE = KIND == KIND_NN && (GEO::BM == Small::BM || EPI == EPI_FWD1_SWIGLU);
+
 template <int KIND, int EPI, class GEO>
-hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, bool finish, hipStream_t st)
+hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, bool once_read, bool finish, hipStream_t st)
 {
     constexpr bool DUAL = (EPI == EPI_FWD1_SWIGLU);
     constexpr int BM = GEO::BM;
@@ -1371,8 +1385,8 @@ hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, bool finis
     int cus = (dev >= 0 && dev < 64) ? cus_of[dev].load(std::memory_order_acquire) : 0;
     auto kern = grouped_gemm_kernel<KIND, EPI, false, GEO, false, false>;
     auto kern_last = grouped_gemm_kernel<KIND, EPI, false, GEO, last_finishes(EPI), false>;
-    auto kern_once = grouped_gemm_kernel<KIND, EPI, false, GEO, false, KIND == KIND_NN>;
-    auto kern_last_once = grouped_gemm_kernel<KIND, EPI, false, GEO, last_finishes(EPI), KIND == KIND_NN>;
+    auto kern_once = grouped_gemm_kernel<KIND, EPI, false, GEO, false, HAS_ONCE<KIND, EPI, GEO>>;
+    auto kern_last_once = grouped_gemm_kernel<KIND, EPI, false, GEO, last_finishes(EPI), HAS_ONCE<KIND, EPI, GEO>>;
     auto kern_fin = grouped_gemm_kernel<KIND, EPI, true, GEO, false, false>;
     if (!once.is_done(dev) || cus == 0) {
         int n = 0;
@@ -1389,8 +1403,7 @@ hipError_t launch_geo(GemmParams p, int rows_upper, int n_groups_cap, bool finis
     p.tn_over = TN_OVER<GEO>;
     p.split_max = SPLIT_MAX<GEO>;
     p.split_cap = SPLIT_CAP<GEO>;
-    const bool one_tile = KIND == KIND_NN && rows_upper <= BM;        // all rows there can be: the forward pass of a decoding step
-    hipLaunchKernelGGL(one_tile ? (p.uneven_cap > 0 ? kern_last_once : kern_once) : (p.uneven_cap > 0 ? kern_last : kern), dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
+    hipLaunchKernelGGL(once_read ? (p.uneven_cap > 0 ? kern_last_once : kern_once) : (p.uneven_cap > 0 ? kern_last : kern), dim3(grid), dim3(GEO::THREADS), LDS_BYTES, st, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !finish) return e;
     // the tiles of split contractions: add their parts, run their epilogues
@@ -1428,7 +1441,8 @@ hipError_t launch(GemmParams p, const moe_shape_t& s, hipStream_t st)
     p.split_slices = t.cut ? t.split_slices : 0x7fffffff;  // none is worth it
     p.uneven_cap = t.uneven ? (t.small ? UNEVEN_CAP<Small> : UNEVEN_CAP<Large>) : 0;
     if (KIND != KIND_TN && t.small) p.band = SMALL_BAND;
-    return t.small ? launch_geo<KIND, EPI, Small>(p, s.T * s.k, s.G, t.cut, st) : launch_geo<KIND, EPI, Large>(p, s.T * s.k, s.G, t.cut, st);
+    return t.small ? launch_geo<KIND, EPI, Small>(p, s.T * s.k, s.G, KIND == KIND_NN && read_once(s, Small::BM), t.cut, st)
+                   : launch_geo<KIND, EPI, Large>(p, s.T * s.k, s.G, KIND == KIND_NN && read_once(s, Large::BM), t.cut, st);
 }
 
 GemmParams base_params(const moe_shape_t& s, const ffn_args& a)
@@ -1526,6 +1540,17 @@ hipError_t launch_ffn_bwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
         if (e != hipSuccess) return e;
     }
     return wgrad(a.Act, h, s.h, a.dYp, d, s.d, a.dW2);
+}
+
+int moe_ffn_reads_once(moe_handle_t hd, int contraction)
+{
+    if (!hd) return MOE_ERR_NULL;
+    const moe_shape_t& s = hd->s;
+    if (s.dtype != MOE_BF16) return MOE_ERR_DTYPE;
+    if (contraction < 0 || contraction > 1) return MOE_ERR_SHAPE;
+    const bool wide = contraction == 0, dual = wide && s.act == MOE_ACT_SWIGLU;
+    const Tiling t = row_tiling(s, wide ? s.h : s.d, (wide ? s.d : s.h) / BK, 1, wide ? (dual ? EPI_FWD1_SWIGLU : EPI_FWD1_GELU) : EPI_BF16);
+    return t.small ? read_once(s, Small::BM) : dual && read_once(s, Large::BM);
 }
 
 int moe_ffn_tiling(moe_handle_t hd, int contraction, int cus, int n_groups, const int32_t* rows, int32_t* out)

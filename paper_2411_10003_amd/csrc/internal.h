@@ -136,6 +136,8 @@ hipError_t launch_ffn_bwd_bf16(const moe_shape_t& s, const ffn_args& a, hipStrea
 //   groups), rows the choice is made for.  4, 5: out[10 .. 10 + G) are the parts of each group.  0 .. 3: out[10] is 0, or the
 //   slices of the first part of each of the other tiles where those are cut unevenly in two.
 extern "C" int moe_ffn_tiling(moe_handle_t h, int contraction, int cus, int n_groups, const int32_t* rows, int32_t* out);
+// Likewise: 1 if a contraction of the forward pass (0 fwd1, 1 fwd2) requests its weights past the caches, else 0.
+extern "C" int moe_ffn_reads_once(moe_handle_t h, int contraction);
 
 // ---- small device helpers ----------------------------------------------------------------
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }

@@ -135,3 +135,20 @@ def test_workspace_for_uneven_cuts_only_where_they_are_made(act, longest):
                 assert 2 * (t["row_tiles"] * t["col_tiles"] - t["n_full"]) * t["side"] ** 2 * 4 <= 512 * tile and h >= longest
                 seen += 1
     assert seen
+
+
+def test_what_is_read_past_the_caches():
+    """Weights of more than 256 MB (2^28 bytes) altogether, of batches of one row tile."""
+    lib = binding.load()
+
+    def once(T, d, h, act, groups=4):
+        hd = binding.Handle(T=T, d=d, h=h, E=16, k=1, P=2, self_dest=0, G=groups, dtype="bf16", act=act, renorm=0, alloc_workspace=False)
+        sides = [G.ffn_tiling(hd, [T], 256)[c]["side"] for c in ("fwd1", "fwd2")]
+        return sides, [lib.moe_ffn_reads_once(hd._h, c) for c in (0, 1)]
+    assert once(64, 2048, 8192, "gelu") == ([128, 128], [0, 0])                     # 2^28 bytes
+    assert once(64, 2048, 8256, "gelu") == ([128, 128], [1, 1])
+    assert once(64, 512, 2048, "swiglu") == ([128, 128], [0, 0])                    # 25 MB
+    assert once(128, 4096, 14336, "swiglu") == ([256, 128], [1, 1]) and once(129, 4096, 14336, "swiglu") == ([256, 128], [1, 0])
+    assert once(256, 4096, 14336, "swiglu")[1] == [1, 0] and once(257, 4096, 14336, "swiglu")[1] == [0, 0]
+    assert once(128, 4096, 14336, "gelu") == ([128, 128], [1, 1]) and once(129, 4096, 14336, "gelu")[1] == [0, 0]
+    assert lib.moe_ffn_reads_once(None, 0) == -1
