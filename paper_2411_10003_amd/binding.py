@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes
 import importlib.util
+import operator
 import os
 from typing import Dict, Optional
 
@@ -57,7 +58,7 @@ class _PlanOut(ctypes.Structure):
 
 
 _raw_stream, _current_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
-_lib = _pycall = None
+_lib = _call_class = None
 
 
 def load() -> ctypes.CDLL:
@@ -100,16 +101,37 @@ def load() -> ctypes.CDLL:
     return _lib
 
 
-def _native():
-    """The module of the native calls."""
-    global _pycall
-    if _pycall is None:
-        if not os.path.exists(PYCALL_PATH):
-            raise ImportError(f"{PYCALL_PATH} is not built; run `python -m paper_2411_10003_amd.build`")
-        spec = importlib.util.spec_from_file_location("_pycall", PYCALL_PATH)
-        _pycall = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(_pycall)
-    return _pycall
+class PythonCall:
+    """What the module of the native calls has as Call, where it is not built: the same arguments, checks and errors, in Python."""
+
+    def __init__(self, entry: int, args: tuple, check):
+        self._f, self._args, self._check = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_void_p] * len(args))(entry), args, check
+        self._n = sum(not isinstance(a, int) for a in args)
+
+    def __call__(self, *given) -> int:
+        if len(given) != self._n:
+            raise TypeError(f"{self._n} positional arguments expected")
+        it = iter(given)
+        return self._f(*(a if isinstance(a, int) else self._pointer(next(it), a) for a in self._args))
+
+    def _pointer(self, given, arg):
+        if arg == "int":
+            return operator.index(given)
+        return None if given is None else self._check(given, *arg)
+
+
+def _call_type():
+    """The type of the calls: native, or in Python where the native ones are not built or were built for another torch."""
+    global _call_class
+    if _call_class is None:
+        try:
+            spec = importlib.util.spec_from_file_location("_pycall", PYCALL_PATH)
+            module = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(module)
+            _call_class = module.Call
+        except ImportError:
+            _call_class = PythonCall
+    return _call_class
 
 
 def _ptr(t: Optional[torch.Tensor], dtype: torch.dtype, numel: int, name: str) -> Optional[int]:
@@ -206,7 +228,7 @@ class Layout:
 
 # What stands at the arguments of each entry point between the handle and the stream: tensors by dtype, least number of elements and
 # name; "int" an address that is given at the call.  (e: the handle's element type, f and i: fp32 and int32, m: all weights of a kind.)
-# One native call object per handle and entry point.
+# One call object per handle and entry point.
 def _dispatch_spec(s, e, f, i, m):
     return (i, s.E, "expert_dest"), (e, s.T * s.d, "X"), (i, s.A, "idx"), (i, s.E, "counts"), "int", (e, s.A * s.d, "Xp"), "int"
 
@@ -303,7 +325,7 @@ class Handle:
     def _call(self, name: str, *args):
         call = self._calls.get(name)
         if call is None:
-            call = self._calls[name] = _native().Call(_entry(name), (self._h.value or 0, *self._spec(name), "int"), _ptr)
+            call = self._calls[name] = _call_type()(_entry(name), (self._h.value or 0, *self._spec(name), "int"), _ptr)
         rc = call(*args, _stream())
         if rc != 0:
             self._check(rc, name)
