@@ -392,7 +392,7 @@ def main():
             "copy_GB/s": round(2.0 * nb / (float(np.median(t_copy)) * 1e-3) / 1e9, 1),
             "copy_what": "1 GiB read + 1 GiB written by a plain 16-byte-per-lane kernel, median of 5",
             "mfma_TFLOP/s": round(mfma_flops / (float(np.median(t_mfma)) * 1e-3) / 1e12, 1),
-            "mfma_what": f"{cus} blocks x 8 waves x {iters} x 8 v_mfma_f32_32x32x16_bf16 on register operands, median of 5",
+            "mfma_what": f"{cus} blocks x 8 waves x {iters} x 16 v_mfma_f32_16x16x32_bf16 on register operands, median of 5",
             "mfma_package_power": cal_power.result(),
         }
         del src, dst, sink

@@ -332,8 +332,8 @@ int moe_plan(const moe_planner_t* cfg, const int32_t* gating, const moe_plan_out
 /* ---- calibration (for the benchmark; nothing of the layer's path calls these) -----------------------------
  * moe_calib_copy: dst[0..bytes) = src[0..bytes) by a plain streaming kernel (device pointers, 16-byte aligned,
  * bytes a multiple of 16): what a copy sustains on this GPU, to set beside the published HBM bandwidth.
- * moe_calib_mfma: one block of 8 wavefronts per compute unit, every wavefront issues iters x 8 bf16 32x32x16
- * matrix instructions (32768 flop each) on operands held in registers: what the matrix cores sustain at this
+ * moe_calib_mfma: one block of 8 wavefronts per compute unit, every wavefront issues iters x 16 bf16 16x16x32
+ * matrix instructions (16384 flop each) on operands held in registers: what the matrix cores sustain at this
  * GPU's power limit, to set beside the published peak.  out: device, out_floats floats of which the first
  * blocks x threads are written (so that the work cannot be optimised away; MOE_ERR_SHAPE if there are fewer:
  * 512 per compute unit are enough); *blocks and *threads (host) receive the launch shape.

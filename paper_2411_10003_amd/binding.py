@@ -200,7 +200,7 @@ def calib_mfma(out: torch.Tensor, iters: int) -> float:
                             ctypes.byref(threads), _stream())
     if rc != 0:
         raise MoeError(rc, "moe_calib_mfma", lib.moe_status_string(rc).decode())
-    return float(blocks.value) * (threads.value // 64) * iters * 8 * 32768.0
+    return float(blocks.value) * (threads.value // 64) * iters * 16 * 16384.0
 
 
 def calib_round_bf16(x: torch.Tensor, out: torch.Tensor) -> None:

@@ -6,7 +6,7 @@
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 cal_bf16x8;
-typedef __attribute__((ext_vector_type(16))) float cal_f32x16;
+typedef __attribute__((ext_vector_type(4))) float cal_f32x4;
 
 // dst[i] = src[i], 16 bytes per lane, four requests in flight per lane, grid-stride.
 __global__ __launch_bounds__(256) void calib_copy_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t n16)
@@ -20,42 +20,45 @@ __global__ __launch_bounds__(256) void calib_copy_kernel(const uint4* __restrict
     for (; i < n16; i += stride) dst[i] = src[i];
 }
 
-// Every wave issues `iters` rounds of eight independent 32x32x16 bf16 matrix instructions (the accumulator
-// layout of the grouped kernel: 4 x 2 fragments) on operands that never leave its registers.  The operands
-// are not all zero, so the multipliers toggle as they do on real data.
+// Every wave issues `iters` rounds of sixteen independent 16x16x32 bf16 matrix instructions, the grouped kernel's instruction in its
+// order (every other row of fragments backwards, so that two in a row share an operand), on operands that never leave its
+// registers.  The operands are not all zero, so the multipliers toggle as they do on real data.
 __global__ __launch_bounds__(512) void calib_mfma_kernel(float* __restrict__ out, int iters)
 {
+    constexpr int F = 4;
     const int lane = threadIdx.x & 63;
-    cal_bf16x8 a[4], b[2];
+    cal_bf16x8 a[F], b[F];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < F; ++i)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) a[i][e] = (__bf16)(0.001f * (float)((lane * 7 + i * 13 + e * 3) % 17 - 8));
+        for (int e = 0; e < 8; ++e) {
+            a[i][e] = (__bf16)(0.001f * (float)((lane * 7 + i * 13 + e * 3) % 17 - 8));
+            b[i][e] = (__bf16)(0.001f * (float)((lane * 5 + i * 11 + e) % 13 - 6));
+        }
+    cal_f32x4 acc[F][F];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < F; ++i)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) b[j][e] = (__bf16)(0.001f * (float)((lane * 5 + j * 11 + e) % 13 - 6));
-    cal_f32x16 acc[4][2];
+        for (int j = 0; j < F; ++j)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+            for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0f;
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < F; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+            for (int jj = 0; jj < F; ++jj) {
+                const int j = (i & 1) ? F - 1 - jj : jj;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);         // in this order
+            }
     }
     float s = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < F; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < F; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) s += acc[i][j][e];
+            for (int e = 0; e < 4; ++e) s += acc[i][j][e];
     out[(size_t)blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 

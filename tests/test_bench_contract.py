@@ -60,6 +60,15 @@ def test_traffic_comes_from_the_counter_summary_and_names_its_workload():
         bench.measured_traffic(3, flops * 1.1)
 
 
+def test_measured_matrix_peak_is_of_the_kernels_instruction():
+    """The loop whose rate roofline.frac_of_measured divides by issues the grouped kernel's matrix instruction."""
+    import re
+    csrc = os.path.join(ROOT, "paper_2411_10003_amd", "csrc")
+    used = {name: set(re.findall(r"mfma_f32_(\d+x\d+x\d+_bf16)", open(path).read())) for name, path in
+            (("kernel", os.path.join(csrc, "ffn_bf16.hip")), ("loop", os.path.join(csrc, "calib.hip")), ("line", os.path.join(ROOT, "bench.py")))}
+    assert len(used["kernel"]) == 1 and used["loop"] == used["kernel"] == used["line"], used
+
+
 def test_group_bounds_follow_the_rooflines():
     """A group of few rows is bound by its weight bytes, a large one by the matrix cores; an empty one still pays
     for writing its gradients."""
