@@ -1,5 +1,5 @@
-"""Rows of 64 MB and more, which go out by nontemporal stores: every token bit for bit as a call of a quarter of the tokens (plain
-stores) leaves it, the scatter against the rows it copies, the gate's parameter gradients against float64."""
+"""Rows of 64 MB and more, which go out by nontemporal stores: every token bit for bit as calls of so few tokens that all their rows are
+under the line (plain stores) leave it, the scatter against the rows it copies, the gate's parameter gradients against float64."""
 import pytest
 import torch
 
@@ -8,6 +8,7 @@ from paper_2411_10003_amd import binding
 
 pytestmark = pytest.mark.gpu
 E = 8
+LINE = 64 << 20
 
 
 def _handle(T, d, k, dtype):
@@ -43,12 +44,16 @@ def test_streamed_rows(T, d, k, dtype):
         hd.input_grad(dXp, pos, dl[t0:t1], Wg, dX[t0:t1])
         hd.dispatch_bwd(dXp, pos, dXs[t0:t1])
 
+    row = k * d * X.element_size()                             # of a token, in the widest of the calls (gradient of the combine)
+    n = next(n for n in range(2, 99) if -(-T // n) * row < LINE)
+    assert T * row >= LINE
     outs = []
-    for parts in (1, 4):
+    for parts in (1, n):
         bufs = [torch.full((T, d), 3.0, dtype=e, **dev), torch.full((A, d), 3.0, dtype=e, **dev), torch.full((T, k), 3.0, **dev),
                 torch.full((T, d), 3.0, dtype=e, **dev), torch.full((T, d), 3.0, dtype=e, **dev)]
         cuts = [T * i // parts for i in range(parts + 1)]
         for t0, t1 in zip(cuts, cuts[1:]):
+            assert parts == 1 or (t1 - t0) * row < LINE
             run(hd if parts == 1 else _handle(t1 - t0, d, k, dtype), t0, t1, *bufs)
         torch.cuda.synchronize()
         outs.append(bufs)
