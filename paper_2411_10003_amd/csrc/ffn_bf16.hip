@@ -32,10 +32,13 @@
 #include <cmath>
 #include <numeric>
 
-// Where the main loop starts relative to a 256-byte boundary of the code, in 4-byte steps.  The loop is one basic
-// block that every wave runs tens of thousands of times; how its two phases fall into the instruction fetch
-// windows changes the time of the weight-gradient contraction by 6 % from the best to the worst placement (period:
-// 32 bytes) and of the others by 1-2 %, so the placement is fixed instead of being left to what precedes the loop.
+// Where the main loop starts relative to a 256-byte boundary of the code, in 4-byte steps (LOOP_OFF: the weight gradients, LOOP_OFF_P: the
+// others).  The loop is one basic block that every wave runs tens of thousands of times, and how its two phases fall into the
+// instruction fetch windows changes its time, so the placement is fixed instead of being left to what precedes the loop.  With
+// 32x32x16 instructions the weight gradients changed by 6 % from the best to the worst placement (period: 32 bytes) and 4 was the best.
+// With the 16x16x32 loop 0 .. 7 change forward and backward together, against 4, by -0.55, -0.50, -0.61, -0.32, 0, -0.41, -0.49, -0.50 %
+// (d = 4096, h = 14336, SwiGLU; d = 2048, h = 8192, GELU: -0.20, -0.02, -0.31, -0.16, 0, -0.20, -0.24, -0.14), a third of which is weight
+// gradients; LOOP_OFF_P by less than 0.25 either way.
 #ifndef LOOP_OFF
 #define LOOP_OFF 4
 #endif
@@ -181,7 +184,7 @@ template <int WGM_, int WGN_, int TM_, int TN_, int STAGES_, int BLOCKS_> struct
     static constexpr uint32_t A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
     static constexpr int PA = A_BYTES / 1024 / NWAVES, PB = B_BYTES / 1024 / NWAVES;   // 1-KB DMA pieces per wave and slice
     static constexpr int EP_PITCH = WN * 4 + 16;           // epilogue patch: bytes per staged row of WN floats (padded against bank conflicts)
-    static constexpr int EP_ROWS = 32;                     // rows a wave stages at a time: one row of fragments
+    static constexpr int EP_ROWS = 32;                     // rows a wave stages at a time: two rows of fragments
     static constexpr int EP_WAVE = EP_ROWS * EP_PITCH;
     static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE_BYTES;
     static constexpr bool TWO_PHASE = BLOCKS == 1;         // the rows of waves of a block alternate; else the blocks of a CU do
@@ -194,7 +197,8 @@ typedef Geometry<2, 2, 2, 2, 5, 2> Small;
 
 // Row tiles per band of the tile walk, per contraction.  Measured, us, 3 | 5 | 6 | 7 | 8 | 16 row tiles: fwd1 at d = 4096, h = 14336,
 // SwiGLU 7990 | 8020 | 7950 | 7920 | 8125 | 8245 (and fwd2 after it 3670 | 3645 | 3640 | 3685 | 3600 | 3590), bwd1 4245 | 4295 | 4315 |
-// 4265 | 4350 | 4494; d = 2048, h = 8192, GELU fwd1 883 | 879 | 875 | 871 | 873 | 872, bwd1 893 | 888 | 890 | 889 | 903 | 909; the others
+// 4265 | 4350 | 4494; forward and backward against 7 there, 8 for both +0.39 %, 16 and 8 +0.58; d = 2048, h = 8192, GELU +0.15 and +0.22, the
+// size of the spread, fwd1 883 | 879 | 875 | 871 | 873 | 872 (GELU as a polynomial), bwd1 893 | 888 | 890 | 889 | 903 | 909; the others
 // are best at 8, which is what the L2 of an XCD needs least fills for (4: weight gradients +0.8 %, 16: +1 % and more).
 #ifndef BAND_FWD1
 #define BAND_FWD1 7
@@ -342,8 +346,8 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     // ---- which tiles.  The kernel is persistent: one block per CU walks its share of the tiles, so a
     // tile's stores drain under the next tile's loads and nothing is relaunched.  Blocks go round-robin
     // over the 8 XCDs (block b runs on XCD b % 8), each with its own L2.  The tiles that actually exist
-    // (the counts are only known here) are cut into rounds of as many tiles as an XCD has blocks, 8 row
-    // tiles by 4 column tiles walked column by column inside a band of 8 row tiles, so that the tiles in
+    // (the counts are only known here) are cut into rounds of as many tiles as an XCD has blocks, walked
+    // column by column inside a band of p.band row tiles (7 or 8 by 4 to 5 column tiles), so that the tiles in
     // flight on an XCD share operand slices in its L2; consecutive rounds go to the 8 XCDs in turn, so
     // that at any time the XCDs work on neighbouring rounds and what one of them has fetched from HBM
     // the others find in the memory-side cache.
@@ -468,7 +472,7 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     }
     const int q_first = FIN ? (int)blockIdx.x : q0;
     const int q_step = FIN ? nblk : q_stride;
-    const int q_end = FIN ? (KIND == KIND_TN ? __popcll(tn_split_mask) * tiles_g : rem) * TM       // FIN: a row of fragments of a tile is an item
+    const int q_end = FIN ? (KIND == KIND_TN ? __popcll(tn_split_mask) * tiles_g : rem) * TM       // FIN: two rows of fragments (32 rows) of a tile's upper and lower waves are an item
                           : (KIND == KIND_TN ? 0x7fffffff : ((n_rounds + 7) >> 3) * q_stride);
 
   int turn = 0, next = q_step;
@@ -979,7 +983,7 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     }
     // ---- epilogue.  A lane holds, per fragment, row l%16 and columns (l/16)*4 + 0..3: storing
     // from there would touch 8-byte pieces of 16 different rows per instruction.  Instead every wave
-    // passes its 128 x 64 accumulators through its own LDS patch (one row of fragments, 32 rows, at a time,
+    // passes its 128 x 64 accumulators through its own LDS patch (two rows of fragments, 32 rows, at a time,
     // fp32) and reads them back row-major, 8 consecutive columns per lane, so that global loads and stores
     // move whole 128/256-byte row segments.  The patches lie at the top of LDS, above ring slots 0 and 1.
     unsigned char* patch = smem + (LDS_BYTES - (size_t)NWAVES * EP_WAVE) + wave * EP_WAVE;
@@ -989,7 +993,7 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
     const int erow = lane / CG, ecg = lane % CG;
     constexpr int ROWS_PER_PASS = 64 / CG;
     constexpr bool BWD1 = (EPI == EPI_BWD1_GELU || EPI == EPI_BWD1_SWIGLU);
-    constexpr int N_PASS = EP_ROWS / ROWS_PER_PASS;        // passes per staged row of fragments
+    constexpr int N_PASS = EP_ROWS / ROWS_PER_PASS;        // passes per 32 staged rows
     // NN/NT: every store of the epilogue is issued whatever the tile looks like, as a buffer store whose resource
     // ends with the tile's last valid row (or has no length at all, for an output that is not written): no predicate
     // per row.  TN keeps ordinary predicated stores.
@@ -1014,8 +1018,8 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
 #define BWD1_BATCH 2
 #endif
     constexpr int BATCH = BWD1 ? BWD1_BATCH : N_PASS;
-    constexpr int NB = N_PASS / BATCH;                     // batches per staged row of fragments
-    static_assert(N_PASS % BATCH == 0, "batches tile the passes of a staged row of fragments");
+    constexpr int NB = N_PASS / BATCH;                     // batches per 32 staged rows
+    static_assert(N_PASS % BATCH == 0, "batches tile the passes of 32 staged rows");
     uint4 zin[BWD1 ? 2 : 1][BWD1 ? BATCH : 1], uin[EPI == EPI_BWD1_SWIGLU ? 2 : 1][EPI == EPI_BWD1_SWIGLU ? BATCH : 1];
     auto request = [&](int fr, int pb, uint4* zi, uint4* ui) {
 #pragma unroll
@@ -1030,14 +1034,14 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
         }
     };
     // WHOLE: the tile's results.  Of a tile cut unevenly (LAST): KEEP leaves what this part holds in the workspace as it comes
-    // out of the patches, [unit][wave][row of fragments][pass][half][lane] as float4; SUM adds the other part from there to this
+    // out of the patches, [unit][wave][32 rows][pass][half][lane] as float4; SUM adds the other part from there to this
     // one's and goes on with the sum (of two terms: the same whichever part comes last).
     // Both go past the L2 of the XCD (sc1: coherent on the device, where every XCD has an L2 of its own), so that no L2 has to be
     // written back or invalidated for them: with plain accesses between agent-scope fences d = 1024, h = 4096, 152 tiles of 128
     // slices took 114 us where this takes 90 and whole tiles 108.
     constexpr int WHOLE = 0, SUM = 1, KEEP = 2, AT_DEVICE = 16;
     static_assert(!LAST || GEO::UNIT_BYTES == NWAVES * TM * N_PASS * 2 * 1024, "a part fills its unit");
-    const long rows_left = row_limit - m0 - wm * WM;           // rows of fragments past the last row are not kept
+    const long rows_left = row_limit - m0 - wm * WM;           // 32 rows past the last one are not kept
     auto part_rsrc = [&](int u) {
         return __builtin_amdgcn_make_buffer_rsrc((void*)((char*)p.split_ws + (size_t)u * GEO::UNIT_BYTES), 0, GEO::UNIT_BYTES, 0x00020000);
     };
@@ -1079,7 +1083,7 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
                 for (int k = 0; k < 2; ++k)
                     other[i][k] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(from, part_ofs + (i * 2 + k) * 1024, 0, AT_DEVICE));
         }
-        if (FIN && fr != q % TM) continue;                     // the tile's other rows of fragments are items of other blocks
+        if (FIN && fr != q % TM) continue;                     // the tile's other rows are items of other blocks
         if (BWD1 && FIN) request(fr, 0, zin[(fr * NB) & 1], uin[EPI == EPI_BWD1_SWIGLU ? (fr * NB) & 1 : 0]);
         float4 fsum[FIN ? 2 * FN : 1];
         if (FIN) {                                             // the parts of a split tile, added in ascending order
@@ -1271,7 +1275,9 @@ __global__ __launch_bounds__(GEO::THREADS, GEO::BLOCKS * GEO::NWAVES / 4) void g
 // The host knows T k and how many of the experts are hosted here, not how many rows they got: it estimates 0.8 T k
 // sqrt(G / E) (more than the share of an even load, G / E, while that is below 0.64: hosted experts are the popular ones; a
 // fifth less than all rows where all experts are hosted, which chose no worse than all of them) and compares the two by the
-// times above, which are those of 256 CUs and know nothing of uneven cuts.  Over 250 drawn shapes (200 to 40000 rows, d 256 to
+// times above, which are those of 256 CUs, of 32x32x16 matrix instructions, and know nothing of uneven cuts.  With those of
+// now, over 160 drawn shapes, a contraction takes 3.0 % more than in the better geometry in the mean and up
+// to 1.5 times (d = 768, h = 3072, 16 experts of which 5 are hosted, 1999 tokens: fwd1 42 in Large, 34 in Small).  With those of then, over 250 drawn shapes (200 to 40000 rows, d 256 to
 // 3072, h 1792 to 12800, 1 to 16 groups of any evenness) the forward pass is within 2.1 % of the best of the four choices for
 // its two contractions in the mean, at worst 1.32 times as long (2333 tokens, k = 2, d = 1536, h = 3136, GELU, 8 groups: Large twice 156,
 // Small 118); the weight gradients, over 660 shapes (to 60000 rows, 32 groups), within 0.6 % of the better one.

@@ -42,11 +42,21 @@ typedef uint16_t bf16_t;  // storage only
 
 // Rows that are written once and are many more than the caches between here and HBM can keep until they are read (256 MB on the
 // memory side, shared with everything else that passes) go out by nontemporal stores, and with them what is read for the last time:
-// left dirty in those caches they are written back under the next kernel's reads.  T = 32768, d = 4096, k = 2: dispatch 126 -> 119 us
-// and the gate that follows 88 -> 52; T = 16384, d = 2048, k = 2, inputs that change from pass to pass: combine, its gradient, the
-// gate's gradients and the input gradient 182 -> 169 us; T = 8001, d = 2048, k = 4: gate to dispatch 95 -> 89.  The line: at 34 MB
-// (dispatch of T = 8192, d = 1024, k = 2, the experts reading the rows at once) 230.5 us a pass with plain stores, 232.4 without;
-// from 64 MB on no pass has been slower (moe_dispatch_bwd, which would be, writes as ever).
+// left dirty in those caches they are written back under the next kernels' reads, so what counts is the step and not the call.
+// Forward and backward of two layers, one after the other (bf16, h = 512), us with plain accesses in one kernel against all of them as
+// they are; rows of T x d elements:
+//                           34 MB    67 MB   98 MB  134 MB  268 MB | 67 MB, d = 2048 | one expert per token, d = 2048: 134 MB  268 MB
+//   scatter                 +10.7    +13.9   +33.8   +43.4   +66.3 | +20.2           |                                  +4.6   +25.2
+//   combine                  +2.3     +6.5   +11.0   +11.1    +7.0 |  +1.0           |                                  +1.0   +11.9
+//   combine's gradient      +14.0     +9.5   +19.4   +34.9   +46.5 | +10.1           |                                  +6.3   +16.1
+//   input gradient           +3.7     +3.7    -1.4    +1.8   +10.9 |  -0.3           |                                  +0.6    +2.2
+//   gate's gradients         +1.9     +4.3    +4.5    +6.3   +18.2 |  -1.2           |                                  -3.3    -6.0
+//   all plain               +31      +31     +86     +96    +148   | +35             |                                 +28     +61
+//   of a step of            668     1098    1436    1733    3022   | 930             |                                1128    2044
+// In its own time combine loses (T = 32768, d = 4096, k = 2: 141 -> 150 us) and the step gains all the same; moe_dispatch_bwd in the input
+// gradient's place loses in the step as well (+5.6, +15.5, +12.0, -2.8 | +0.4 | +13.2, +18.0 from 67 MB on if streamed): it writes as
+// ever.  The line: at 17 MB no kernel gains or loses; at 34 MB this step gains, and a prefill whose experts read their rows at once
+// lost 0.8 % (T = 8192, d = 1024, k = 2: 230.5 us a pass, 232.4); from 64 MB on no step measured has been slower.
 constexpr size_t STREAM_BYTES = (size_t)64 << 20;
 inline bool streams(size_t bytes) { return bytes >= STREAM_BYTES; }
 typedef unsigned moe_piece_t __attribute__((ext_vector_type(4)));

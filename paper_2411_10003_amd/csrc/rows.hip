@@ -202,7 +202,8 @@ __global__ __launch_bounds__(ROW_WAVES * 64) void combine_bwd_kernel(
     }
 }
 
-// dX[t,:] = sum_j dXp[pos[t*k+j],:].  Its rows stay in the caches at any size (T = 32768, d = 4096, k = 2: 155 us, past them 175).
+// dX[t,:] = sum_j dXp[pos[t*k+j],:].  Its rows stay in the caches at any size (T = 32768, d = 4096, k = 2: 155 us, past them
+// 175, and the step that goes on with them takes as long or longer: STREAM_BYTES).
 template <typename ET, int KT>
 __global__ __launch_bounds__(ROW_WAVES * 64) void dispatch_bwd_kernel(
     const ET* __restrict__ dXp, const int32_t* __restrict__ pos, ET* __restrict__ dX, int T, int d, int k_rt)
